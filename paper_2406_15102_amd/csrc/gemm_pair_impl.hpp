@@ -52,6 +52,9 @@ __global__ __launch_bounds__(256) void k_gemm_pair(GemmDev ga, GemmDev gb, GemmD
     const bool in_first = b < n0_pad;
     if (in_first && b >= n0) return;                    // padding
     const int idx = in_first ? b : b - n0_pad;
+    // the product that goes first has the longer tiles: where two tiles share a compute unit its wavefronts
+    // issue first (12608 x 768 x 3072, the whole pass: 108.5 -> 107.3 us; elsewhere no difference)
+    if (in_first) __builtin_amdgcn_s_setprio(2);
     if (in_first != (b_first != 0)) {
         pair_tile<CA>(ga, idx);
         return;
