@@ -127,6 +127,8 @@ __device__ __forceinline__ void hla_body(const Tin *__restrict__ T, int64_t N, i
     hla_body_src<B, BASIS, DenseRows<Tin>, LM>(DenseRows<Tin>{T, D}, N, D, r, ThatT, coeffT, bx, by);
 }
 
+template <int NW> struct Words { static constexpr int value = NW; };
+
 // ---- integer g_w list: pass 1 (column maxima of the kept coefficients) and pass 2 (int8 codes) ----
 template <int B, int BASIS, typename Src>
 __device__ __forceinline__ void hla_absmax_body_src(const Src &src, int64_t N, int D, int r,
@@ -200,38 +202,35 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
         const int64_t o = static_cast<int64_t>(col0 + c) * Kc + blk * r;          // r % 4 == 0
         const uint32_t cnt = static_cast<uint32_t>(col0 + c) * static_cast<uint32_t>(Kc >> 2) +
                              static_cast<uint32_t>((blk * r) >> 2);
-        if constexpr (P4) {
+        // the kept coefficients in order, a group of random words at a time
+        auto codes = [&](auto nw, int k) {
+            constexpr int NW = decltype(nw)::value;
+            float x[4 * NW];
 #pragma unroll
-            for (int k = 0; k < B; k += 8) {
-                if (k < r) {
-                    const uint32_t lo =
-                        quant_pack4r<MANT>(v[kept_row<B, BASIS>(k + 0) * CPL + c], v[kept_row<B, BASIS>(k + 1) * CPL + c],
-                                           v[kept_row<B, BASIS>(k + 2) * CPL + c], v[kept_row<B, BASIS>(k + 3) * CPL + c], inv,
-                                           cnt + (k >> 2), k0, k1);
-                    const uint32_t hi =
-                        quant_pack4r<MANT>(v[kept_row<B, BASIS>(k + 4) * CPL + c], v[kept_row<B, BASIS>(k + 5) * CPL + c],
-                                           v[kept_row<B, BASIS>(k + 6) * CPL + c], v[kept_row<B, BASIS>(k + 7) * CPL + c], inv,
-                                           cnt + (k >> 2) + 1u, k0, k1);
-                    *reinterpret_cast<uint32_t *>(TqT + ((o + k) >> 1)) = nibble_pack8(lo, hi);
-                    if (coeffT) {
+            for (int e = 0; e < 4 * NW; ++e) x[e] = v[kept_row<B, BASIS>(k + e) * CPL + c];
+            int q[4 * NW];
+            quant_codes<MANT, NW>(x, 1, inv, cnt + (k >> 2), k0, k1, q);
+            if constexpr (P4) {
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) coeffT[o + k + e] = v[kept_row<B, BASIS>(k + e) * CPL + c];
-                    }
-                }
+                for (int d = 0; d < NW / 2; ++d) *reinterpret_cast<uint32_t *>(TqT + ((o + k) >> 1) + 4 * d) = pack_nibbles8(q + 8 * d);
+            } else {
+#pragma unroll
+                for (int d = 0; d < NW; ++d) *reinterpret_cast<uint32_t *>(TqT + o + k + 4 * d) = pack_bytes4(q + 4 * d);
             }
-            continue;
-        }
+            if (coeffT) {
 #pragma unroll
-        for (int k = 0; k < B; k += 4) {
-            if (k < r) {
-                *reinterpret_cast<uint32_t *>(TqT + o + k) =
-                    quant_pack4r<MANT>(v[kept_row<B, BASIS>(k + 0) * CPL + c], v[kept_row<B, BASIS>(k + 1) * CPL + c],
-                                       v[kept_row<B, BASIS>(k + 2) * CPL + c], v[kept_row<B, BASIS>(k + 3) * CPL + c], inv,
-                                       cnt + (k >> 2), k0, k1);
-                if (coeffT)
-                    *reinterpret_cast<float4 *>(coeffT + o + k) =
-                        make_float4(v[kept_row<B, BASIS>(k + 0) * CPL + c], v[kept_row<B, BASIS>(k + 1) * CPL + c], v[kept_row<B, BASIS>(k + 2) * CPL + c], v[kept_row<B, BASIS>(k + 3) * CPL + c]);
+                for (int e = 0; e < 4 * NW; e += 4)
+                    *reinterpret_cast<float4 *>(coeffT + o + k + e) = make_float4(x[e], x[e + 1], x[e + 2], x[e + 3]);
             }
+        };
+        if (r >= 16) {
+#pragma unroll
+            for (int k = 0; k < B; k += 16)
+                if (k < r) codes(Words<4>{}, k);
+        } else if (r == 8) {
+            codes(Words<2>{}, 0);
+        } else if constexpr (!P4) {
+            codes(Words<1>{}, 0);      // r == 4
         }
     }
 }

@@ -117,23 +117,35 @@ __device__ __forceinline__ void fwht_regs(float *v)
 // x_upper - x_lower = -(a - b).  Callers carry that sign per lane (it is the same for both lanes of
 // every later exchange, because they differ in a higher lane bit only) and fold it into whatever
 // consumes the value.  The s_nop covers the VALU-write -> DPP-read hazard, which the compiler
-// cannot see inside an asm statement.
+// cannot see inside an asm statement; the eight values of a chunk go together so that one covers them all.
+#define HLQ_DPP8(PERM)                                                                                        \
+    asm("s_nop 1\n\t"                                                                                         \
+        "v_fmac_f32_dpp %0, %0, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
+        "v_fmac_f32_dpp %1, %1, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
+        "v_fmac_f32_dpp %2, %2, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
+        "v_fmac_f32_dpp %3, %3, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
+        "v_fmac_f32_dpp %4, %4, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
+        "v_fmac_f32_dpp %5, %5, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
+        "v_fmac_f32_dpp %6, %6, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
+        "v_fmac_f32_dpp %7, %7, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1"                \
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])      \
+        : "v"(sigma))
 template <int MASK>
-__device__ __forceinline__ float butterfly_lanes_signed(float x, float sigma)
+__device__ __forceinline__ void butterfly_lanes_signed8(float *x, float sigma)
 {
-    if (MASK == 1) {
-        asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "+v"(x) : "v"(x), "v"(sigma));
-        return x;
-    } else if (MASK == 2) {
-        asm("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "+v"(x) : "v"(x), "v"(sigma));
-        return x;
+    if constexpr (MASK == 1) {
+        HLQ_DPP8("[1,0,3,2]");
+    } else if constexpr (MASK == 2) {
+        HLQ_DPP8("[2,3,0,1]");
     } else {
-        const float p = __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), 0x101F));  // lane ^ 4
-        return __builtin_fmaf(p, sigma, x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float p = __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x[e]), 0x101F));  // lane ^ 4
+            x[e] = __builtin_fmaf(p, sigma, x[e]);
+        }
     }
 }
+#undef HLQ_DPP8
 
 // Row of the natural-order Hadamard matrix kept as coefficient k of the low-rank projection.
 // BASIS 0: row k.  BASIS 1: the row with k sign changes (sequency order), which is the
@@ -151,17 +163,41 @@ __host__ __device__ constexpr int kept_row(int k)
 
 // ---- random stream ---------------------------------------------------------------------------
 // Word `counter` of the stream keyed by (k0, k1): a keyed xorshift-multiply bijection of the
-// counter (multipliers of the public-domain "lowbias32" integer hash).
-__device__ __forceinline__ uint32_t rand_word(uint32_t counter, uint32_t k0, uint32_t k1)
+// counter (multipliers of the public-domain "lowbias32" integer hash):
+//   x = counter ^ k0;  x ^= x >> 16;  x *= M1;  x ^= x >> 15;  x ^= k1;  x *= M2;  x ^= x >> 16
+constexpr uint32_t kMix1 = 0x7FEB352Du, kMix2 = 0x846CA68Bu;
+__device__ __forceinline__ uint32_t rand_finish(uint32_t x, uint32_t k1)
 {
-    uint32_t x = counter ^ k0;
-    x ^= x >> 16;
-    x *= 0x7FEB352Du;
     x ^= x >> 15;
     x ^= k1;
-    x *= 0x846CA68Bu;
+    x *= kMix2;
+    return x ^ (x >> 16);
+}
+
+// Words counter .. counter + NW - 1 (counter a multiple of NW = 1, 2 or 4).  The words of an aligned group differ
+// only in the low bits of the counter, which reach the first multiplication unmixed: with x the first word's
+// factor, word i's is x ^ i = x + (+-1 for bit 0 of i) + (+-2 for bit 1), the signs set by those bits of x.  So one
+// product serves the group, the others are one addition of +-M1, +-2 M1 each: a 32-bit multiplication issues
+// at a quarter of the rate of anything else here, and there are two of them to four codes otherwise.
+template <int NW>
+__device__ __forceinline__ void rand_words(uint32_t counter, uint32_t k0, uint32_t k1, uint32_t *w)
+{
+    static_assert(NW == 1 || NW == 2 || NW == 4, "aligned groups of one, two or four words");
+    uint32_t x = counter ^ k0;
     x ^= x >> 16;
-    return x;
+    const uint32_t p = x * kMix1;
+    w[0] = rand_finish(p, k1);
+    if constexpr (NW >= 2) {
+        const uint32_t s0 = 0u - (x & 1u);
+        const uint32_t d0 = (s0 & (0u - kMix1)) | (~s0 & kMix1);
+        w[1] = rand_finish(p + d0, k1);
+        if constexpr (NW == 4) {
+            const uint32_t s1 = 0u - ((x >> 1) & 1u);
+            const uint32_t p2 = p + ((s1 & (0u - 2u * kMix1)) | (~s1 & (2u * kMix1)));
+            w[2] = rand_finish(p2, k1);
+            w[3] = rand_finish(p2 + d0, k1);
+        }
+    }
 }
 
 // floor(t) as an integer in one instruction (v_cvt_flr_i32_f32).
@@ -172,34 +208,36 @@ __device__ __forceinline__ int floor_to_int(float t)
     return r;
 }
 
-// One code: floor(fma(x, inv, u)), u = (byte + 0.5) / 256 (exact in fp32, built with one fma).
+// Four codes floor(fma(x, inv, u)), u = (byte + 0.5) / 256 for the four bytes of a random word.
+// u has nine significant bits, so it is exact in fp16 and the four are built two to an instruction: a byte
+// permutation puts each byte b under the exponent of 1024 (0x6400 + b = 1024 + b), and one packed fp16 fma
+// makes (1024 + b) / 256 - (4 - 1/512).  The fma that adds u reads it as fp16 (v_fma_mix_f32: exact
+// operands, one fp32 rounding), the same value as with u in fp32 -- two instructions a code fewer than
+// converting each byte and scaling it were four of every fourteen.
 // No clamp is needed: |x| <= absmax and inv = RN(qmax / absmax) give |x*inv| <= qmax (1 + 2^-24),
 // and u lies in [2^-9, 1 - 2^-9], so the rounded sum stays inside (-qmax, qmax + 1) and its floor
 // inside [-qmax, qmax] (a zero row has inv = 0 and floor(u) = 0).  Inf/NaN inputs are outside the
 // contract.
-__device__ __forceinline__ int quant_code(float x, float inv, float byte_as_float)
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ v2h round_bits_pair(uint32_t w, uint32_t sel)
 {
-    const float u = __builtin_fmaf(byte_as_float, 0.00390625f, 0.001953125f);
-    return floor_to_int(__builtin_fmaf(x, inv, u));
+    const v2h b = __builtin_bit_cast(v2h, __builtin_amdgcn_perm(0x64646464u, w, sel));
+    const v2h scale = {static_cast<_Float16>(0.00390625f), static_cast<_Float16>(0.00390625f)};
+    const v2h shift = {static_cast<_Float16>(-3.998046875f), static_cast<_Float16>(-3.998046875f)};
+    return __builtin_elementwise_fma(b, scale, shift);
 }
-
-// Four codes from four values and one random word, packed little-endian into a dword
-// (two's-complement bytes, as the int8 MFMA reads them).
-__device__ __forceinline__ uint32_t quant_pack4(float x0, float x1, float x2, float x3, float inv, uint32_t w)
+__device__ __forceinline__ void quant_codes4(const float *x, int es, float inv, uint32_t w, int *q)
 {
-    const uint32_t q0 = static_cast<uint32_t>(quant_code(x0, inv, static_cast<float>(w & 0xFFu)));
-    const uint32_t q1 = static_cast<uint32_t>(quant_code(x1, inv, static_cast<float>((w >> 8) & 0xFFu)));
-    const uint32_t q2 = static_cast<uint32_t>(quant_code(x2, inv, static_cast<float>((w >> 16) & 0xFFu)));
-    const uint32_t q3 = static_cast<uint32_t>(quant_code(x3, inv, static_cast<float>(w >> 24)));
-    // v_perm_b32: selector bytes 0-3 pick bytes of the second operand, 4-7 of the first, 0x0c = zero
-    const uint32_t lo = __builtin_amdgcn_perm(q1, q0, 0x0c0c0400u);
-    const uint32_t hi = __builtin_amdgcn_perm(q3, q2, 0x04000c0cu);
-    return lo | hi;
+    const v2h u01 = round_bits_pair(w, 0x04010400u), u23 = round_bits_pair(w, 0x04030402u);
+    q[0] = floor_to_int(__builtin_fmaf(x[0], inv, static_cast<float>(u01[0])));
+    q[1] = floor_to_int(__builtin_fmaf(x[es], inv, static_cast<float>(u01[1])));
+    q[2] = floor_to_int(__builtin_fmaf(x[2 * es], inv, static_cast<float>(u23[0])));
+    q[3] = floor_to_int(__builtin_fmaf(x[3 * es], inv, static_cast<float>(u23[1])));
 }
 
 // The paper's pseudo-stochastic rounding (Sec. 6.1): the low 11 bits of the value's own binary32
 // pattern replace the random number, u = (m + 0.5) / 2048 (exact, one fma).  A sign flip of the
-// value (see butterfly_lanes_signed) leaves those bits alone.
+// value (see butterfly_lanes_signed8) leaves those bits alone.
 __device__ __forceinline__ int quant_code_mantissa(float x, float inv)
 {
     const float m = static_cast<float>(__float_as_uint(x) & 0x7FFu);
@@ -207,28 +245,40 @@ __device__ __forceinline__ int quant_code_mantissa(float x, float inv)
     return floor_to_int(__builtin_fmaf(x, inv, u));
 }
 
-// Four codes packed into a dword, rounding by the seeded stream (word `counter` of the stream keyed
-// by k0, k1) or, with MANT, by the values' own low mantissa bits.
-template <bool MANT>
-__device__ __forceinline__ uint32_t quant_pack4r(float x0, float x1, float x2, float x3, float inv, uint32_t counter,
-                                                 uint32_t k0, uint32_t k1)
+// Codes of NW * 4 values x[0], x[es], x[2 es], ...: rounding by words counter .. of the stream keyed by k0, k1
+// (counter a multiple of NW), or, with MANT, by the values' own low mantissa bits.
+template <bool MANT, int NW>
+__device__ __forceinline__ void quant_codes(const float *x, int es, float inv, uint32_t counter, uint32_t k0, uint32_t k1, int *q)
 {
-    if (!MANT) return quant_pack4(x0, x1, x2, x3, inv, rand_word(counter, k0, k1));
-    const uint32_t q0 = static_cast<uint32_t>(quant_code_mantissa(x0, inv));
-    const uint32_t q1 = static_cast<uint32_t>(quant_code_mantissa(x1, inv));
-    const uint32_t q2 = static_cast<uint32_t>(quant_code_mantissa(x2, inv));
-    const uint32_t q3 = static_cast<uint32_t>(quant_code_mantissa(x3, inv));
-    return __builtin_amdgcn_perm(q1, q0, 0x0c0c0400u) | __builtin_amdgcn_perm(q3, q2, 0x04000c0cu);
+    if constexpr (MANT) {
+#pragma unroll
+        for (int e = 0; e < 4 * NW; ++e) q[e] = quant_code_mantissa(x[e * es], inv);
+    } else {
+        uint32_t w[NW];
+        rand_words<NW>(counter, k0, k1, w);
+#pragma unroll
+        for (int d = 0; d < NW; ++d) quant_codes4(x + 4 * d * es, es, inv, w[d], q + 4 * d);
+    }
 }
 
-// Eight 4-bit codes from two dwords of int8 codes (as quant_pack4 makes them), two to a byte:
-// code 2b in the low nibble of byte b, code 2b+1 in the high nibble, two's complement.
-__device__ __forceinline__ uint32_t nibble_pack8(uint32_t lo, uint32_t hi)
+// Four codes as the bytes of a dword, little-endian two's complement (as the int8 MFMA reads them).
+__device__ __forceinline__ uint32_t pack_bytes4(const int *q)
 {
-    // bytes (c0, c1, c2, c3) -> bits 0..7 = c0 | c1 << 4, bits 16..23 = c2 | c3 << 4
-    const uint32_t a = ((lo >> 4) & 0x00F000F0u) | (lo & 0x000F000Fu);
-    const uint32_t b = ((hi >> 4) & 0x00F000F0u) | (hi & 0x000F000Fu);
-    return __builtin_amdgcn_perm(b, a, 0x06040200u);   // bytes 0, 2 of a, then bytes 0, 2 of b
+    // v_perm_b32: selector bytes 0-3 pick bytes of the second operand, 4-7 of the first, 0x0c = zero
+    const uint32_t lo = __builtin_amdgcn_perm(static_cast<uint32_t>(q[1]), static_cast<uint32_t>(q[0]), 0x0c0c0400u);
+    const uint32_t hi = __builtin_amdgcn_perm(static_cast<uint32_t>(q[3]), static_cast<uint32_t>(q[2]), 0x04000c0cu);
+    return lo | hi;
+}
+
+// Eight codes in [-7, 7] as the nibbles of a dword, two's complement, code 2b in the low nibble of byte b and
+// code 2b+1 in the high one: the sum of q_i 16^i by shift-and-add (one instruction a code), with 8 added to every
+// digit at once (each is then in [1, 15], nothing carries) and the bias taken out again by flipping bit 3.
+__device__ __forceinline__ uint32_t pack_nibbles8(const int *q)
+{
+    int r = q[7];
+#pragma unroll
+    for (int e = 6; e >= 0; --e) asm("v_lshl_add_u32 %0, %0, 4, %1" : "+v"(r) : "v"(q[e]));   // left alone, two each
+    return (static_cast<uint32_t>(r) + 0x88888888u) ^ 0x88888888u;
 }
 
 // qmax = 7 for 4-bit codes, 127 for 8-bit codes (int8 warm-up phase, integer g_w path).

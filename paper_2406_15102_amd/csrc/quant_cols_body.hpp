@@ -69,18 +69,13 @@ __device__ __forceinline__ void cols_quantize_block(const Tin *__restrict__ W, i
                              static_cast<uint32_t>(o0 >> 2);
 #pragma unroll
         for (int d4 = 0; d4 < B / 16; ++d4) {
-            uint32_t out[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int j = (d4 * 4 + d) * 4;
-                out[d] = quant_pack4r<MANT>(v[(j + 0) * CPL + c], v[(j + 1) * CPL + c], v[(j + 2) * CPL + c],
-                                            v[(j + 3) * CPL + c], inv[c], cnt + d4 * 4 + d, k0, k1);
-            }
+            int q[16];
+            quant_codes<MANT, 4>(v + d4 * 16 * CPL + c, CPL, inv[c], cnt + d4 * 4, k0, k1, q);
             if (PACKED)
-                *reinterpret_cast<uint2 *>(WqT + orow / 2 + d4 * 8) =
-                    make_uint2(nibble_pack8(out[0], out[1]), nibble_pack8(out[2], out[3]));
+                *reinterpret_cast<uint2 *>(WqT + orow / 2 + d4 * 8) = make_uint2(pack_nibbles8(q), pack_nibbles8(q + 8));
             else
-                *reinterpret_cast<uint4 *>(WqT + orow + d4 * 16) = make_uint4(out[0], out[1], out[2], out[3]);
+                *reinterpret_cast<uint4 *>(WqT + orow + d4 * 16) =
+                    make_uint4(pack_bytes4(q), pack_bytes4(q + 4), pack_bytes4(q + 8), pack_bytes4(q + 12));
         }
         if (coeffT) {
 #pragma unroll

@@ -30,7 +30,7 @@ __device__ __forceinline__ void quant_rows_body(const Tin *__restrict__ G, int64
         if (ci < nch) Loader<Tin, 8>::load(grow + static_cast<int64_t>(ci) * 8, v[m]);
     }
 
-    // Cross-lane stages leave the lane with value sign * (coefficient): see butterfly_lanes_signed.
+    // Cross-lane stages leave the lane with value sign * (coefficient): see butterfly_lanes_signed8.
     const float sg1 = (tid & 1) ? -1.0f : 1.0f;
     const float sg2 = (tid & 2) ? -1.0f : 1.0f;
     const float sg4 = (tid & 4) ? -1.0f : 1.0f;
@@ -44,15 +44,11 @@ __device__ __forceinline__ void quant_rows_body(const Tin *__restrict__ G, int64
         // (aligned groups of B/8 lanes) take this branch together
         if (ci < nch) {
             fwht_regs<8, 1>(v[m]);
+            butterfly_lanes_signed8<1>(v[m], sg1);
+            if (B >= 32) butterfly_lanes_signed8<2>(v[m], sg2);
+            if (B >= 64) butterfly_lanes_signed8<4>(v[m], sg4);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float x = v[m][e];
-                x = butterfly_lanes_signed<1>(x, sg1);
-                if (B >= 32) x = butterfly_lanes_signed<2>(x, sg2);
-                if (B >= 64) x = butterfly_lanes_signed<4>(x, sg4);
-                v[m][e] = x;
-                amax = fmaxf(amax, fabsf(x));
-            }
+            for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(v[m][e]));
         }
     }
 
@@ -78,11 +74,10 @@ __device__ __forceinline__ void quant_rows_body(const Tin *__restrict__ G, int64
     for (int m = 0; m < K1_MAXC; ++m) {
         const int ci = g + m * T;
         if (ci < nch) {
-            uint2 out;
-            out.x = quant_pack4r<MANT>(v[m][0], v[m][1], v[m][2], v[m][3], inv, cbase + 2u * ci, k0, k1);
-            out.y = quant_pack4r<MANT>(v[m][4], v[m][5], v[m][6], v[m][7], inv, cbase + 2u * ci + 1u, k0, k1);
-            if (PACKED) *reinterpret_cast<uint32_t *>(qrow + static_cast<int64_t>(ci) * 4) = nibble_pack8(out.x, out.y);
-            else *reinterpret_cast<uint2 *>(qrow + static_cast<int64_t>(ci) * 8) = out;
+            int q[8];
+            quant_codes<MANT, 2>(v[m], 1, inv, cbase + 2u * ci, k0, k1, q);
+            if (PACKED) *reinterpret_cast<uint32_t *>(qrow + static_cast<int64_t>(ci) * 4) = pack_nibbles8(q);
+            else *reinterpret_cast<uint2 *>(qrow + static_cast<int64_t>(ci) * 8) = make_uint2(pack_bytes4(q), pack_bytes4(q + 4));
             if (coeff) {
                 float4 *c = reinterpret_cast<float4 *>(coeff + row * static_cast<int64_t>(O) + static_cast<int64_t>(ci) * 8);
                 c[0] = make_float4(sign * v[m][0], sign * v[m][1], sign * v[m][2], sign * v[m][3]);

@@ -1,0 +1,67 @@
+"""The quantisers draw their random words in aligned groups (two or four share a multiplication) and add the
+rounding value as fp16: codes and scales bit-exact against the oracle, which mixes every word by itself, at
+every group length and at values down to the subnormal range of binary32."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2406_15102_amd as hlq
+from paper_2406_15102_amd import workloads as wl
+from test_gpu_packed import unpack_nibbles
+from test_gpu_parity import dev, rand_tensor
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _tiny(T, axis):
+    """Every third row (axis 0) or column (axis 1) of T brought down to 1e-35 at its largest, where 127 / absmax is still
+    finite, and nine tenths of its values to the subnormal range."""
+    T = T.clone()
+    sub = T[::3] if axis == 0 else T[:, ::3]
+    keep = torch.rand(sub.shape, generator=torch.Generator().manual_seed(1)) < 0.1
+    sub.div_(sub.abs().amax(dim=1 - axis, keepdim=True)).mul_(torch.where(keep, 1e-35, 3e-39))
+    (sub[:, 0] if axis == 0 else sub[0]).fill_(1e-35)
+    return T
+
+
+@pytest.mark.parametrize("N,D,B,r", [(272, 40, 16, 4), (256, 72, 16, 8), (528, 24, 16, 16), (96, 136, 32, 16), (320, 40, 64, 64)])
+@pytest.mark.parametrize("seed", [0, 3, 0x7FFFFFFFFFFFFFFF])
+def test_projection_codes(N, D, B, r, seed):
+    if (N // B * r) % 16:
+        N += B * (16 // r - (N // B) % (16 // r))     # whole 16-byte rows of codes
+    X = _tiny(rand_tensor((N, D), torch.float32, seed=N + D, scale=1.0, spread=0.5), 1)
+    Kc = N // B * r
+    q = torch.full((D, Kc), 0x5A, dtype=torch.int8, device=DEV)
+    s = torch.empty(D, dtype=torch.float32, device=DEV)
+    ws = torch.empty(hlq.hlq_hla_quantize_workspace_bytes(D), dtype=torch.uint8, device=DEV)
+    hlq.hlq_hla_quantize(dev(X), B, r, seed, 3, q, s, ws)
+    ref_q, ref_s = oracle.quantize_rows(oracle.hla_f32(wl.as_f32_numpy(X), B, r), seed, 3, qmax=127)
+    assert np.array_equal(s.cpu().numpy().view(np.uint32), ref_s.view(np.uint32))
+    assert int(np.count_nonzero(q.cpu().numpy() != ref_q)) == 0
+
+
+@pytest.mark.parametrize("rows,K,B", [(37, 256, 16), (6, 4128, 32), (9, 1088, 64)])
+@pytest.mark.parametrize("bits", [4, 8, 0x104])
+@pytest.mark.parametrize("seed", [0, 5, 0x7FFFFFFFFFFFFFFF])
+def test_row_and_column_codes(rows, K, B, bits, seed):
+    packed, qmax = bits == 0x104, 127 if bits == 8 else 7
+    G = _tiny(rand_tensor((rows, K), torch.float32, seed=rows + K, scale=1e-3, spread=1.0), 0)
+    q = torch.empty((rows, K // 2 if packed else K), dtype=torch.uint8 if packed else torch.int8, device=DEV)
+    s = torch.empty(rows, dtype=torch.float32, device=DEV)
+    hlq.hlq_quantize_g(dev(G), B, seed, q, s, None, bits=bits)
+    ref_q, ref_s = oracle.quantize_rows(oracle.transform_rows(wl.as_f32_numpy(G), B), seed, 0, qmax=qmax)
+    got = unpack_nibbles(q.cpu().numpy()) if packed else q.cpu().numpy()
+    assert np.array_equal(s.cpu().numpy().view(np.uint32), ref_s.view(np.uint32))
+    assert int(np.count_nonzero(got != ref_q)) == 0
+    I = rows + (-rows) % 8
+    W = _tiny(rand_tensor((K, I), torch.float32, seed=K + rows, scale=0.02), 1)
+    q = torch.empty((I, K // 2 if packed else K), dtype=torch.uint8 if packed else torch.int8, device=DEV)
+    s = torch.empty(I, dtype=torch.float32, device=DEV)
+    ws = torch.empty(hlq.hlq_quantize_w_workspace_bytes(K, I), dtype=torch.uint8, device=DEV)
+    hlq.hlq_quantize_w(dev(W), B, seed, q, s, ws, None, bits=bits)
+    ref_q, ref_s = oracle.quantize_rows(oracle.transform_cols(wl.as_f32_numpy(W), B), seed, 1, qmax=qmax)
+    got = unpack_nibbles(q.cpu().numpy()) if packed else q.cpu().numpy()
+    assert np.array_equal(s.cpu().numpy().view(np.uint32), ref_s.view(np.uint32))
+    assert int(np.count_nonzero(got != ref_q)) == 0
