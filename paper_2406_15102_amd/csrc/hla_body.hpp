@@ -132,7 +132,7 @@ template <int NW> struct Words { static constexpr int value = NW; };
 // ---- integer g_w list: pass 1 (column maxima of the kept coefficients) and pass 2 (int8 codes) ----
 template <int B, int BASIS, typename Src>
 __device__ __forceinline__ void hla_absmax_body_src(const Src &src, int64_t N, int D, int r,
-                                                    uint32_t *__restrict__ amax_bits, int bx, int by)
+                                                    uint32_t *__restrict__ amax_bits, int bx, int by, bool table = false)
 {
     constexpr int CPL = 128 / B, L = hla_lanes(B), NB = hla_blocks(B);
     __shared__ float s_max[NB][L * CPL];
@@ -162,15 +162,19 @@ __device__ __forceinline__ void hla_absmax_body_src(const Src &src, int64_t N, i
 #pragma unroll
         for (int g = 1; g < NB; ++g) m = fmaxf(m, s_max[g][idx]);
         const int col = bx * L * CPL + idx;
-        if (col < D && m > 0.0f) atomicMax(amax_bits + col, __float_as_uint(m));
+        if (table) {   // a row of the table per `by`
+            if (col < D) amax_bits[static_cast<int64_t>(by) * D + col] = __float_as_uint(m);
+        } else if (col < D && m > 0.0f) {
+            atomicMax(amax_bits + col, __float_as_uint(m));
+        }
     }
 }
 
 template <typename Tin, int B, int BASIS>
 __device__ __forceinline__ void hla_absmax_body(const Tin *__restrict__ T, int64_t N, int D, int r,
-                                                uint32_t *__restrict__ amax_bits, int bx, int by)
+                                                uint32_t *__restrict__ amax_bits, int bx, int by, bool table = false)
 {
-    hla_absmax_body_src<B, BASIS>(DenseRows<Tin>{T, D}, N, D, r, amax_bits, bx, by);
+    hla_absmax_body_src<B, BASIS>(DenseRows<Tin>{T, D}, N, D, r, amax_bits, bx, by, table);
 }
 
 // P4: codes in [-7, 7] stored two to a byte (TqT then has Kc/2 bytes per feature; needs r % 8 == 0) -- the
@@ -180,7 +184,7 @@ template <int B, int BASIS, bool MANT, typename Src, bool P4 = false>
 __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N, int D, int r,
                                                       const uint32_t *__restrict__ amax_bits, uint32_t k0, uint32_t k1,
                                                       int8_t *__restrict__ TqT, float *__restrict__ sT,
-                                                      float *__restrict__ coeffT, int bx, int by)
+                                                      float *__restrict__ coeffT, int bx, int by, int table = 0)
 {
     constexpr int CPL = 128 / B, L = hla_lanes(B), NB = hla_blocks(B);
     const int tid = threadIdx.x;
@@ -188,6 +192,8 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
     const int64_t nblk = N / B;
     const int64_t Kc = nblk * r;
     const int64_t blk = static_cast<int64_t>(by) * NB + tid / L;
+    float amax[CPL];
+    fold_column_maxima<CPL>(amax_bits, D, table, bx, tid % L, amax);
     if (col0 >= D || blk >= nblk) return;
 
     float v[B * CPL];
@@ -196,7 +202,7 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
     for (int c = 0; c < CPL; ++c) {
         fwht_regs<B, CPL>(v + c);
         constexpr float QMAX = P4 ? 7.0f : 127.0f;
-        const float a = __uint_as_float(amax_bits[col0 + c]);
+        const float a = amax[c];
         const float inv = absmax_to_inv(a, QMAX);
         if (blk == 0) sT[col0 + c] = absmax_to_scale(a, QMAX);
         const int64_t o = static_cast<int64_t>(col0 + c) * Kc + blk * r;          // r % 4 == 0
@@ -239,10 +245,10 @@ template <typename Tin, int B, int BASIS, bool MANT = false, bool P4 = false>
 __device__ __forceinline__ void hla_quantize_body(const Tin *__restrict__ T, int64_t N, int D, int r,
                                                   const uint32_t *__restrict__ amax_bits, uint32_t k0, uint32_t k1,
                                                   int8_t *__restrict__ TqT, float *__restrict__ sT,
-                                                  float *__restrict__ coeffT, int bx, int by)
+                                                  float *__restrict__ coeffT, int bx, int by, int table = 0)
 {
     hla_quantize_body_src<B, BASIS, MANT, DenseRows<Tin>, P4>(DenseRows<Tin>{T, D}, N, D, r, amax_bits, k0, k1, TqT, sT, coeffT,
-                                                             bx, by);
+                                                             bx, by, table);
 }
 
 }  // namespace hlq

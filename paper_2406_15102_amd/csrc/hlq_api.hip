@@ -77,7 +77,7 @@ int check_backward_shape(int64_t N, int64_t d_in, int64_t d_out, int B, int r)
 // Carving of the backward workspace.  With HLQ_FLAG_GW_INT8 the compressed operands are int8
 // codes with one scale per feature plus one word of column maximum per feature.
 struct Layout {
-    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, gws, gws_bytes, total;
+    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, total;
 };
 
 Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags)
@@ -91,10 +91,13 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
     L.sG = off;    off += up256(static_cast<size_t>(N) * 4);
     L.Wq = off;    off += up256(static_cast<size_t>(d_in) * d_out);
     L.sW = off;    off += up256(static_cast<size_t>(d_in) * 4);
-    L.wws = off;   off += up256(hlq::quant_cols_ws_bytes(d_out, d_in));
-    // integer g_w list: column maxima of projected G (d_out words), then of projected X (d_in words),
-    // right behind those of the weight so that one fill zeroes all three
-    L.hws = off;   off += gwi ? up256(hlq::hla_quant_ws_bytes(d_out)) + up256(hlq::hla_quant_ws_bytes(d_in)) : 0;
+    const size_t wws1 = hlq::quant_cols_ws_bytes(d_out, d_in), wwst = gwi ? hlq::amax_table_bytes(d_out, d_in) : 0;
+    L.wws = off;   off += up256(wws1 > wwst ? wws1 : wwst);
+    // integer g_w list: column maxima of projected G (d_out columns), then of projected X (d_in columns),
+    // right behind those of the weight so that one fill zeroes all that are merged by atomics
+    L.hws = off;   off += gwi ? up256(hlq::amax_table_bytes(N, d_out)) : 0;
+    L.hwsx = off;  off += gwi ? up256(hlq::amax_table_bytes(N, d_in)) : 0;
+    L.amax_end = off;
     L.GhatT = off; off += up256(static_cast<size_t>(d_out) * Kc * esz);
     L.sGhat = off; off += gwi ? up256(static_cast<size_t>(d_out) * 4) : 0;
     // X projected here, or the int8 codes unpacked from a 4-bit store that was handed over
@@ -623,12 +626,6 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     float *sGh = reinterpret_cast<float *>(ws + L.sGhat);
     const void *Xh = Xc;
     const float *sXh = sXc;
-    if (dW && Xc && (flags & HLQ_FLAG_XC_INT4)) {
-        // the activation was kept as 4-bit codes (Sec. 6.1): widen them to the int8 operand of the product
-        int8_t *xu = reinterpret_cast<int8_t *>(ws + L.XhatT);
-        if ((rc = launch_rc(hlq::launch_unpack_nibbles(Xc, xu, static_cast<int64_t>(d_in) * Kc / 2, st))) != HLQ_OK) return rc;
-        Xh = xu;
-    }
     // The transforms that depend on nothing share launches when the shapes allow (k_front.hip): two
     // and pass 2 over the weight for the default path (one in all when the weight has few rows or
     // is not transformed here), three for the integer g_w list.  Very long rows of G and the mantissa-bit rounding keep one
@@ -637,41 +634,48 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     const bool fused = !gwi && fusable;
     const bool fused_q = gwi && fusable;
     const uint64_t kg = stream_key(seed, 0);
+    hlq::FrontUnpack ju = hlq::front_unpack(nullptr, nullptr, 0);
+    if (dW && Xc && (flags & HLQ_FLAG_XC_INT4)) {
+        // the activation was kept as 4-bit codes (Sec. 6.1): widened to the int8 operand of the product, beside the
+        // passes that take the maxima where there is such a launch
+        int8_t *xu = reinterpret_cast<int8_t *>(ws + L.XhatT);
+        const int64_t bytes = static_cast<int64_t>(d_in) * Kc / 2;
+        if (fused_q) ju = hlq::front_unpack(Xc, xu, bytes);
+        else if ((rc = launch_rc(hlq::launch_unpack_nibbles(Xc, xu, bytes, st))) != HLQ_OK) return rc;
+        Xh = xu;
+    }
     if (fused_q) {
         uint32_t *amax_w = reinterpret_cast<uint32_t *>(ws + L.wws);
         uint32_t *amax_g = reinterpret_cast<uint32_t *>(ws + L.hws);
-        uint32_t *amax_x = reinterpret_cast<uint32_t *>(ws + L.hws + up256(hlq::hla_quant_ws_bytes(O)));
-        const size_t zero_bytes = (L.hws - L.wws) + up256(hlq::hla_quant_ws_bytes(O)) + up256(hlq::hla_quant_ws_bytes(I));
+        uint32_t *amax_x = reinterpret_cast<uint32_t *>(ws + L.hwsx);
         const uint64_t k3 = stream_key(seed, 3), k2 = stream_key(seed, 2), kw = stream_key(seed, 1);
         const hlq::FrontRows jr = hlq::front_rows(dX ? G : nullptr, N, O, B, static_cast<uint32_t>(kg),
                                                   static_cast<uint32_t>(kg >> 32), qmax, Gq, sG);
-        const hlq::FrontFill jf{amax_w, static_cast<int>(zero_bytes / 4)};
+        int8_t *xq = xc ? nullptr : reinterpret_cast<int8_t *>(ws + L.XhatT);
+        float *sx = xc ? nullptr : reinterpret_cast<float *>(ws + L.sXhat);
+        const hlq::FrontHlaQ jg = hlq::front_hlaq(dW ? G : nullptr, N, O, B, r, amax_g, static_cast<uint32_t>(k3),
+                                                  static_cast<uint32_t>(k3 >> 32), static_cast<int8_t *>(Gh), sGh);
+        const hlq::FrontHlaQ jx = hlq::front_hlaq(dW && !xc ? X : nullptr, N, I, B, r, amax_x, static_cast<uint32_t>(k2),
+                                                  static_cast<uint32_t>(k2 >> 32), xq, sx);
+        const bool wq = dX && !wc;
+        const hlq::FrontColsQ jq = hlq::front_colsq(wq ? W : nullptr, O, I, B, amax_w, static_cast<uint32_t>(kw),
+                                                    static_cast<uint32_t>(kw >> 32), qmax, reinterpret_cast<int8_t *>(ws + L.Wq),
+                                                    reinterpret_cast<float *>(ws + L.sW));
+        hlq::FrontAbsmax jw = hlq::front_absmax(wq ? W : nullptr, O, I, B, amax_w);
+        jw.table = jq.table;
+        // The maxima that are merged by atomics are zeroed first: from the first of them to the last.  The row
+        // quantiser goes with that launch, or -- in turns -- beside the three passes that only read.
+        const size_t zero_from = (wq && !jq.table) ? L.wws : ((jg.T && !jg.table) ? L.hws : L.hwsx);
+        const size_t zero_to = (jx.T && !jx.table) ? L.amax_end : ((jg.T && !jg.table) ? L.hwsx : ((wq && !jq.table) ? L.hws : zero_from));
+        const hlq::FrontFill jf{reinterpret_cast<uint32_t *>(ws + zero_from), static_cast<int>((zero_to > zero_from ? zero_to - zero_from : 0) / 4)};
         const hlq::FrontHla none = hlq::front_hla(nullptr, N, O, B, r, nullptr);
         const hlq::FrontAbsmax none_w = hlq::front_absmax(nullptr, O, I, B, nullptr);
-        // the zeroing first; the row quantiser with it, or -- in turns -- beside the three passes that only read
         const bool k1_later = hlq::front_mix_enabled();
         const hlq::FrontRows no_rows = hlq::front_rows(nullptr, N, O, B, 0, 0, qmax, nullptr, nullptr);
         if ((rc = launch_rc(hlq::launch_front(k1_later ? no_rows : jr, none, jf, none, none_w, nullptr, B, basis, f32, packed, st))) != HLQ_OK)
             return rc;
-        int8_t *xq = xc ? nullptr : reinterpret_cast<int8_t *>(ws + L.XhatT);
-        float *sx = xc ? nullptr : reinterpret_cast<float *>(ws + L.sXhat);
-        if (conv && dW && !xc) {
-            // the image's projection keeps its own launches (it zeroes its maxima itself)
-            if ((rc = launch_rc(hlq::launch_hla_quant_conv(X, *conv, B, r, basis, f32, static_cast<uint32_t>(k2),
-                                                           static_cast<uint32_t>(k2 >> 32), mant, xq, sx, nullptr, amax_x,
-                                                           st))) != HLQ_OK)
-                return rc;
-        }
-        const hlq::FrontHlaQ jg = hlq::front_hlaq(dW ? G : nullptr, N, O, B, r, amax_g, static_cast<uint32_t>(k3),
-                                                  static_cast<uint32_t>(k3 >> 32), static_cast<int8_t *>(Gh), sGh);
-        const hlq::FrontHlaQ jx = hlq::front_hlaq(dW && !xc && !conv ? X : nullptr, N, I, B, r, amax_x, static_cast<uint32_t>(k2),
-                                                  static_cast<uint32_t>(k2 >> 32), xq, sx);
-        const bool wq = dX && !wc;
-        const hlq::FrontAbsmax jw = hlq::front_absmax(wq ? W : nullptr, O, I, B, amax_w);
-        const hlq::FrontColsQ jq = hlq::front_colsq(wq ? W : nullptr, O, I, B, amax_w, static_cast<uint32_t>(kw),
-                                                    static_cast<uint32_t>(kw >> 32), qmax, reinterpret_cast<int8_t *>(ws + L.Wq),
-                                                    reinterpret_cast<float *>(ws + L.sW));
-        if ((rc = launch_rc(hlq::launch_front_q(jg, jx, jw, jq, k1_later ? jr : no_rows, B, basis, f32, packed, st))) != HLQ_OK) return rc;
+        if ((rc = launch_rc(hlq::launch_front_q(jg, jx, jw, jq, k1_later ? jr : no_rows, ju, conv, B, basis, f32, packed, st))) != HLQ_OK)
+            return rc;
         if (dW && !xc) {
             Xh = xq;
             sXh = sx;

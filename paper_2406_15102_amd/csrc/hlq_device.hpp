@@ -281,6 +281,50 @@ __device__ __forceinline__ uint32_t pack_nibbles8(const int *q)
     return (static_cast<uint32_t>(r) + 0x88888888u) ^ 0x88888888u;
 }
 
+// Maxima of a lane's CPL columns (bit patterns of non-negative floats): one row of D of them, or `table` rows to be
+// folded, which the 256 threads of the workgroup do together for its 128 columns.  Every thread calls it; `sub` is the
+// lane's place among those that cover the 128 columns.
+template <int CPL>
+__device__ __forceinline__ void fold_column_maxima(const uint32_t *__restrict__ bits, int D, int table, int bx, int sub, float *a)
+{
+    const float *m = reinterpret_cast<const float *>(bits);
+    if (table <= 1) {
+        if (bx * 128 + sub * CPL < D) Loader<float, CPL>::load(m + bx * 128 + sub * CPL, a);
+        return;
+    }
+    __shared__ float s_fold[2][128];
+    const int c = threadIdx.x & 127, half = threadIdx.x >> 7, col = bx * 128 + c;
+    float f = 0.0f;
+    if (col < D)
+        for (int t = half; t < table; t += 2) f = fmaxf(f, m[static_cast<int64_t>(t) * D + col]);
+    s_fold[half][c] = f;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) a[k] = fmaxf(s_fold[0][sub * CPL + k], s_fold[1][sub * CPL + k]);
+}
+
+// 4-bit codes two to a byte -> one int8 each: a lane turns 16 bytes into 32 (see k_unpack_nibbles)
+__device__ __forceinline__ void unpack_nibbles16(const uint4 *__restrict__ in, uint4 *__restrict__ out, int64_t i)
+{
+    const uint4 x = in[i];
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+    uint32_t o[8];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t lo = w[d] & 0x0F0F0F0Fu, hi = (w[d] >> 4) & 0x0F0F0F0Fu;
+        // bytes (lo0, hi0, lo1, hi1) and (lo2, hi2, lo3, hi3): v_perm selectors 0-3 = second operand, 4-7 = first
+        uint32_t a = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
+        uint32_t b = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
+        // sign-extend every byte's nibble: a set bit 3 fills the upper half of its byte
+        a |= ((a >> 3) & 0x01010101u) * 0xF0u;
+        b |= ((b >> 3) & 0x01010101u) * 0xF0u;
+        o[2 * d] = a;
+        o[2 * d + 1] = b;
+    }
+    out[2 * i] = make_uint4(o[0], o[1], o[2], o[3]);
+    out[2 * i + 1] = make_uint4(o[4], o[5], o[6], o[7]);
+}
+
 // qmax = 7 for 4-bit codes, 127 for 8-bit codes (int8 warm-up phase, integer g_w path).
 __device__ __forceinline__ float absmax_to_inv(float a, float qmax) { return a > 0.0f ? qmax / a : 0.0f; }
 __device__ __forceinline__ float absmax_to_scale(float a, float qmax) { return a / qmax; }

@@ -129,6 +129,7 @@ struct FrontAbsmax { // pass 1 of K1T
     int O, I;
     uint32_t *amax;
     int gx, gy;
+    int table;       // see kAmaxTableRows; 0: one maximum per column, merged by atomics
 };
 struct FrontHlaQ {   // K3 + int8 quantisation of one tensor: pass 1 (amax) and pass 2 (codes) read the same fields
     const void *T;
@@ -139,6 +140,13 @@ struct FrontHlaQ {   // K3 + int8 quantisation of one tensor: pass 1 (amax) and 
     int8_t *TqT;
     float *sT;
     int gx, gy;
+    int table;       // see kAmaxTableRows; 0: one maximum per column, merged by atomics
+};
+struct FrontUnpack { // 4-bit codes two to a byte -> one int8 each; n16 pieces of 16 bytes in
+    const void *in;
+    void *out;
+    int64_t n16;
+    int blocks;
 };
 struct FrontColsQ {  // pass 2 of K1T
     const void *W;
@@ -149,16 +157,34 @@ struct FrontColsQ {  // pass 2 of K1T
     int8_t *WqT;
     float *sW;
     int gx, gy;
+    int table;       // of the strips that run both passes by themselves: unused
 };
+// Column maxima of the integer g_w list.  A workgroup of a pass 1 covers 256 rows.  Where a tensor has at most
+// kAmaxTableRows of them, each leaves its maxima in a row of its own of a table, [groups of 256 rows][columns],
+// and pass 2 folds the rows: nothing has to be zeroed, and when every tensor of the call is of that kind the
+// launch that zeroes is not there.  Beyond, one row merged by atomics: pass 2 would read more maxima than codes
+// it writes.  Integer g_w list, whole pass, two launches less in all with the store widened beside the passes 1:
+// 4096 x 4096 x 11008 from the 4-bit store with cached weight codes 288 -> 271 us, 320 x 120 x 384 21.0 -> 18.6,
+// 512 x 8320 x 1920 from the store 52.5 -> 46.0.
+constexpr int kAmaxTableRows = 16;
+inline int amax_table_rows(int64_t rows) { return rows <= 256 * kAmaxTableRows ? static_cast<int>((rows + 255) / 256) : 0; }
+inline size_t amax_table_bytes(int64_t rows, int64_t cols)
+{
+    const int t = amax_table_rows(rows);
+    return static_cast<size_t>(t ? t : 1) * static_cast<size_t>(cols) * 4;
+}
 FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, uint32_t k0, uint32_t k1, int8_t *TqT,
                      float *sT);
 FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, uint32_t k0, uint32_t k1, float qmax,
                        int8_t *WqT, float *sW);
-// The integer g_w list in three launches: (K1(G) | zeroing) through launch_front with empty K3 jobs,
-// then every pass 1 (maxima of projected G, projected X, transformed W), then every pass 2.  `jr`, if it is
-// not empty, is K1(G) riding in the second launch instead, its workgroups in turns with the passes 1.
+FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in);
+// The integer g_w list in two launches: every pass 1 (maxima of projected G, projected X, transformed W),
+// then every pass 2; where maxima are merged by atomics, a launch of launch_front zeroes them first.  `jr`, if it
+// is not empty, is K1(G) riding in the first of them, its workgroups in turns with the passes 1; `ju`, if it is not
+// empty, widens a 4-bit store beside them.  conv: NULL, or the geometry whose column matrix jx.T (an image) stands for.
 hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
-                          const FrontRows &jr, int B, int basis, bool is_f32, bool packed, hipStream_t st);
+                          const FrontRows &jr, const FrontUnpack &ju, const ConvShape *conv, int B, int basis, bool is_f32,
+                          bool packed, hipStream_t st);
 bool front_fusable(int O, int B);
 FrontRows front_rows(const void *G, int64_t N, int O, int B, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG);
 FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, uint16_t *out);

@@ -10,8 +10,8 @@
 // convolution has K3 of the image, read as its column matrix, in front A and K3(G) in front B)
 // or ONE, when the weight has few row blocks (k_front_one below): the maxima stay per row block.
 // and three launches carry the integer g_w list, whose projections are quantised in two passes too:
-//   front A   K1(G)  |  zeroing of all three sets of maxima
-//   front Q1  maxima of projected G  |  of projected X  |  of H^T W
+//   front A   zeroing of the maxima that are merged by atomics (none where every tensor has few rows)
+//   front Q1  K1(G)  |  maxima of projected G  |  of projected X  |  of H^T W  |  widening of a 4-bit store
 //   front Q2  int8 codes of projected G  |  of projected X  |  codes of the weight
 // A workgroup looks up its job from its index (jobs occupy consecutive index ranges, a job may be
 // empty) and runs the same device body as the stand-alone kernel of that stage.
@@ -183,44 +183,56 @@ __global__ __launch_bounds__(256) void k_front_b(FrontHla jg, FrontAbsmax jw)
 // integer g_w list, pass 1 of everything: maxima of the kept coefficients of G and of X, of H^T W
 // With jr (the row quantiser of G, which waits for nothing) riding along, in turns: its arithmetic beside three
 // passes that only read.
-template <typename Tin, int B, int BASIS, bool PACKED>
-__global__ __launch_bounds__(256) void k_front_q1(FrontHlaQ jg, FrontHlaQ jx, FrontAbsmax jw, FrontRows jr, FrontMix jm)
+template <typename Tin, int B, int BASIS, bool PACKED, bool CONV>
+__global__ __launch_bounds__(256) void k_front_q1(FrontHlaQ jg, FrontHlaQ jx, FrontAbsmax jw, FrontRows jr, FrontMix jm,
+                                                  FrontUnpack ju, FrontConv jc)
 {
     int b = blockIdx.x;
     if (jr.blocks > 0) {
         int k1 = -1, k3 = -1;
-        const int n3 = jg.gx * jg.gy + jx.gx * jx.gy + jw.gx * jw.gy;
         if (jm.gran) {
+            // (the widening of a 4-bit store stays behind the turns: counted among the readers it would thin out the
+            // quantiser's share of them -- fp32 57728 x 1192 x 2688, this launch: 236 us so, 210 as two launches)
+            const int n3 = jg.gx * jg.gy + jx.gx * jx.gy + jw.gx * jw.gy;
             front_turns(jm, b, jr.blocks, n3, k1, k3);
+            if (k1 < 0) b = k3 >= 0 ? k3 : n3 + b;
         } else if (b < jr.blocks) {
             k1 = b;
         } else {
-            k3 = b - jr.blocks;
+            b -= jr.blocks;
         }
         if (k1 >= 0) {
             quant_rows_body<Tin, B, 256, PACKED>(static_cast<const Tin *>(jr.G), jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax, jr.Gq,
                                                  jr.sG, nullptr, k1);
             return;
         }
-        if (k3 < 0) return;
-        b = k3;
     }
     if (b < jg.gx * jg.gy) {
-        hla_absmax_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, b % jg.gx, b / jg.gx);
+        hla_absmax_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, b % jg.gx, b / jg.gx, jg.table != 0);
         return;
     }
     b -= jg.gx * jg.gy;
     if (b < jx.gx * jx.gy) {
-        hla_absmax_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, b % jx.gx, b / jx.gx);
+        if (CONV)
+            hla_absmax_body_src<B, BASIS>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.amax, b % jx.gx,
+                                          b / jx.gx, jx.table != 0);
+        else
+            hla_absmax_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, b % jx.gx, b / jx.gx, jx.table != 0);
         return;
     }
     b -= jx.gx * jx.gy;
-    cols_absmax_body<Tin, B>(static_cast<const Tin *>(jw.W), jw.O, jw.I, jw.amax, b % jw.gx, b / jw.gx);
+    if (b < jw.gx * jw.gy) {
+        cols_absmax_body<Tin, B>(static_cast<const Tin *>(jw.W), jw.O, jw.I, jw.amax, b % jw.gx, b / jw.gx, jw.table != 0);
+        return;
+    }
+    b -= jw.gx * jw.gy;
+    const int64_t i = static_cast<int64_t>(b) * 256 + threadIdx.x;
+    if (i < ju.n16) unpack_nibbles16(static_cast<const uint4 *>(ju.in), static_cast<uint4 *>(ju.out), i);
 }
 
 // pass 2 of everything: int8 codes of projected G and X, codes of the weight
-template <typename Tin, int B, int BASIS, bool PACKED>
-__global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, FrontColsQ jq)
+template <typename Tin, int B, int BASIS, bool PACKED, bool CONV>
+__global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, FrontColsQ jq, FrontConv jc)
 {
     // backwards through the jobs and through each of them (reverse_same_xcd): what the passes that took the maxima
     // read last is what the last-level cache still holds
@@ -228,25 +240,37 @@ __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, Fr
     int b = reverse_same_xcd(blockIdx.x, gridDim.x, bytes * static_cast<int64_t>(sizeof(Tin)));
     if (b < jg.gx * jg.gy) {
         hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, jg.k0, jg.k1, jg.TqT,
-                                         jg.sT, nullptr, b % jg.gx, b / jg.gx);
+                                         jg.sT, nullptr, b % jg.gx, b / jg.gx, jg.table);
         return;
     }
     b -= jg.gx * jg.gy;
     if (b < jx.gx * jx.gy) {
-        hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, jx.k0, jx.k1, jx.TqT,
-                                         jx.sT, nullptr, b % jx.gx, b / jx.gx);
+        if (CONV)
+            hla_quantize_body_src<B, BASIS, false>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.amax,
+                                                   jx.k0, jx.k1, jx.TqT, jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
+        else
+            hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, jx.k0, jx.k1, jx.TqT,
+                                             jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
         return;
     }
     b -= jx.gx * jx.gy;
     cols_quantize_body<Tin, B, PACKED>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.amax, jq.k0, jq.k1, jq.qmax, jq.WqT,
-                                       jq.sW, nullptr, b % jq.gx, b / jq.gx);
+                                       jq.sW, nullptr, b % jq.gx, b / jq.gx, jq.table);
+}
+
+FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in)
+{
+    FrontUnpack j{in, out, in ? bytes_in / 16 : 0, 0};
+    j.blocks = static_cast<int>((j.n16 + 255) / 256);
+    return j;
 }
 
 FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, uint32_t k0, uint32_t k1, int8_t *TqT,
                      float *sT)
 {
-    FrontHlaQ j{T, N, D, r, amax, k0, k1, TqT, sT, 0, 0};
+    FrontHlaQ j{T, N, D, r, amax, k0, k1, TqT, sT, 0, 0, 0};
     if (!T) return j;
+    j.table = amax_table_rows(N);
     j.gx = hla_grid_x(D, B);
     j.gy = hla_grid_y(N, B);
     return j;
@@ -255,42 +279,55 @@ FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *am
 FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, uint32_t k0, uint32_t k1, float qmax,
                        int8_t *WqT, float *sW)
 {
-    FrontColsQ j{W, O, I, amax, k0, k1, qmax, WqT, sW, 0, 0};
+    FrontColsQ j{W, O, I, amax, k0, k1, qmax, WqT, sW, 0, 0, 0};
     if (!W) return j;
+    j.table = amax_table_rows(O);
     j.gx = cols_grid_x(I, B);
     j.gy = cols_grid_y(O, B);
     return j;
 }
 
-template <typename Tin, int B, int BASIS>
+template <typename Tin, int B, int BASIS, bool PACKED, bool CONV>
 static hipError_t launch_front_q_t(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
-                                   const FrontRows &jr, bool packed, hipStream_t st)
+                                   const FrontRows &jr, const FrontUnpack &ju, const FrontConv &jc, hipStream_t st)
 {
     const int n3 = jg.gx * jg.gy + jx.gx * jx.gy + jw.gx * jw.gy;
-    const int n1 = n3 + jr.blocks;
+    const int n1 = n3 + jr.blocks + ju.blocks;
     const FrontMix jm = jr.blocks > 0 ? front_mix_of(jr.blocks, n3) : FrontMix{0, 0, 0};
-    if (n1 > 0) {
-        if (packed) hipLaunchKernelGGL((k_front_q1<Tin, B, BASIS, true>), dim3(n1), dim3(256), 0, st, jg, jx, jw, jr, jm);
-        else hipLaunchKernelGGL((k_front_q1<Tin, B, BASIS, false>), dim3(n1), dim3(256), 0, st, jg, jx, jw, jr, jm);
-    }
+    if (n1 > 0) hipLaunchKernelGGL((k_front_q1<Tin, B, BASIS, PACKED, CONV>), dim3(n1), dim3(256), 0, st, jg, jx, jw, jr, jm, ju, jc);
     const int n2 = jg.gx * jg.gy + jx.gx * jx.gy + jq.gx * jq.gy;
-    if (n2 > 0) {
-        if (packed) hipLaunchKernelGGL((k_front_q2<Tin, B, BASIS, true>), dim3(n2), dim3(256), 0, st, jg, jx, jq);
-        else hipLaunchKernelGGL((k_front_q2<Tin, B, BASIS, false>), dim3(n2), dim3(256), 0, st, jg, jx, jq);
-    }
+    if (n2 > 0) hipLaunchKernelGGL((k_front_q2<Tin, B, BASIS, PACKED, CONV>), dim3(n2), dim3(256), 0, st, jg, jx, jq, jc);
     return hipGetLastError();
 }
 
-hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
-                          const FrontRows &jr, int B, int basis, bool is_f32, bool packed, hipStream_t st)
+template <typename Tin, int B, int BASIS>
+static hipError_t launch_front_q_p(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
+                                   const FrontRows &jr, const FrontUnpack &ju, const FrontConv &jc, bool packed, hipStream_t st)
 {
-#define HLQ_FRONTQ_CASE(BB)                                                                     \
-    case BB:                                                                                    \
-        if (basis)                                                                              \
-            return is_f32 ? launch_front_q_t<float, BB, 1>(jg, jx, jw, jq, jr, packed, st)          \
-                          : launch_front_q_t<bf16_t, BB, 1>(jg, jx, jw, jq, jr, packed, st);        \
-        return is_f32 ? launch_front_q_t<float, BB, 0>(jg, jx, jw, jq, jr, packed, st)              \
-                      : launch_front_q_t<bf16_t, BB, 0>(jg, jx, jw, jq, jr, packed, st);
+    if (jc.on)
+        return packed ? launch_front_q_t<Tin, B, BASIS, true, true>(jg, jx, jw, jq, jr, ju, jc, st)
+                      : launch_front_q_t<Tin, B, BASIS, false, true>(jg, jx, jw, jq, jr, ju, jc, st);
+    return packed ? launch_front_q_t<Tin, B, BASIS, true, false>(jg, jx, jw, jq, jr, ju, jc, st)
+                  : launch_front_q_t<Tin, B, BASIS, false, false>(jg, jx, jw, jq, jr, ju, jc, st);
+}
+
+hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
+                          const FrontRows &jr, const FrontUnpack &ju, const ConvShape *conv, int B, int basis, bool is_f32,
+                          bool packed, hipStream_t st)
+{
+    FrontConv jc{};
+    if (conv && jx.T) {
+        if (!hla_conv_ok(*conv, B)) return hipErrorInvalidValue;
+        jc.g = *conv;
+        jc.on = 1;
+    }
+#define HLQ_FRONTQ_CASE(BB)                                                                         \
+    case BB:                                                                                        \
+        if (basis)                                                                                  \
+            return is_f32 ? launch_front_q_p<float, BB, 1>(jg, jx, jw, jq, jr, ju, jc, packed, st)  \
+                          : launch_front_q_p<bf16_t, BB, 1>(jg, jx, jw, jq, jr, ju, jc, packed, st); \
+        return is_f32 ? launch_front_q_p<float, BB, 0>(jg, jx, jw, jq, jr, ju, jc, packed, st)      \
+                      : launch_front_q_p<bf16_t, BB, 0>(jg, jx, jw, jq, jr, ju, jc, packed, st);
     switch (B) {
         HLQ_FRONTQ_CASE(16)
         HLQ_FRONTQ_CASE(32)
@@ -329,7 +366,7 @@ FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, uint16_t *out)
 
 FrontAbsmax front_absmax(const void *W, int O, int I, int B, uint32_t *amax)
 {
-    FrontAbsmax j{W, O, I, amax, 0, 0};
+    FrontAbsmax j{W, O, I, amax, 0, 0, 0};
     if (!W) return j;
     j.gx = cols_grid_x(I, B);
     j.gy = cols_grid_y(O, B);
@@ -343,7 +380,7 @@ bool cols_full_ok(int O, int I, int B, bool is_f32)
 
 FrontColsQ front_cols_full(const void *W, int O, int I, int B, uint32_t k0, uint32_t k1, float qmax, int8_t *WqT, float *sW)
 {
-    FrontColsQ j{W, O, I, nullptr, k0, k1, qmax, WqT, sW, 0, 0};
+    FrontColsQ j{W, O, I, nullptr, k0, k1, qmax, WqT, sW, 0, 0, 0};
     if (!W) return j;
     // as many groups of lanes as there are row blocks, so that a pass is one round where it can be: 16, 32 or
     // 64; beyond 64 row blocks there are several rounds anyway and the longer runs of 32 groups measure better

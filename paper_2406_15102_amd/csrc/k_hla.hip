@@ -96,23 +96,7 @@ __global__ __launch_bounds__(256) void k_unpack_nibbles(const uint4 *__restrict_
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (i >= n16) return;
-    const uint4 x = in[i];
-    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-    uint32_t o[8];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t lo = w[d] & 0x0F0F0F0Fu, hi = (w[d] >> 4) & 0x0F0F0F0Fu;
-        // bytes (lo0, hi0, lo1, hi1) and (lo2, hi2, lo3, hi3): v_perm selectors 0-3 = second operand, 4-7 = first
-        uint32_t a = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
-        uint32_t b = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
-        // sign-extend every byte's nibble: a set bit 3 fills the upper half of its byte
-        a |= ((a >> 3) & 0x01010101u) * 0xF0u;
-        b |= ((b >> 3) & 0x01010101u) * 0xF0u;
-        o[2 * d] = a;
-        o[2 * d + 1] = b;
-    }
-    out[2 * i] = make_uint4(o[0], o[1], o[2], o[3]);
-    out[2 * i + 1] = make_uint4(o[4], o[5], o[6], o[7]);
+    unpack_nibbles16(in, out, i);
 }
 
 hipError_t launch_unpack_nibbles(const void *in, int8_t *out, int64_t bytes_in, hipStream_t st)

@@ -15,10 +15,11 @@ __device__ __forceinline__ void load_row_block(const Tin *base, int64_t pitch, f
 
 // pass 1: a row block per group of B lanes (256 / B groups); the groups' maxima meet in LDS and are merged
 // into one maximum per column with an atomic on the bit patterns (non-negative floats order like
-// their bit patterns), so the maxima must have been zeroed by an earlier launch.
+// their bit patterns), so the maxima must have been zeroed by an earlier launch -- or, with `table`,
+// each row of workgroups leaves its own and pass 2 folds them (kAmaxTableRows).
 template <typename Tin, int B>
 __device__ __forceinline__ void cols_absmax_body(const Tin *__restrict__ W, int O, int I, uint32_t *__restrict__ amax_bits,
-                                                 int bx, int by)
+                                                 int bx, int by, bool table = false)
 {
     constexpr int CPL = 128 / B, L = B, NB = 256 / B;     // lanes side by side, row blocks
     __shared__ float s_max[NB][L * CPL];
@@ -47,7 +48,11 @@ __device__ __forceinline__ void cols_absmax_body(const Tin *__restrict__ W, int 
 #pragma unroll
         for (int g = 1; g < NB; ++g) m = fmaxf(m, s_max[g][idx]);
         const int col = bx * L * CPL + idx;
-        if (col < I && m > 0.0f) atomicMax(amax_bits + col, __float_as_uint(m));
+        if (table) {   // a row of the table per `by`
+            if (col < I) amax_bits[static_cast<int64_t>(by) * I + col] = __float_as_uint(m);
+        } else if (col < I && m > 0.0f) {
+            atomicMax(amax_bits + col, __float_as_uint(m));
+        }
     }
 }
 
@@ -91,20 +96,20 @@ template <typename Tin, int B, bool PACKED, bool MANT = false>
 __device__ __forceinline__ void cols_quantize_body(const Tin *__restrict__ W, int O, int I,
                                                    const uint32_t *__restrict__ amax_bits, uint32_t k0, uint32_t k1,
                                                    float qmax, int8_t *__restrict__ WqT, float *__restrict__ sW,
-                                                   float *__restrict__ coeffT, int bx, int by)
+                                                   float *__restrict__ coeffT, int bx, int by, int table = 0)
 {
     constexpr int CPL = 128 / B;
     constexpr int L = B, NB = 256 / B;
     const int tid = threadIdx.x;
     const int col0 = (bx * L + tid % L) * CPL;
     const int o0 = (by * NB + tid / L) * B;
+    float inv[CPL], a[CPL];
+    fold_column_maxima<CPL>(amax_bits, I, table, bx, tid % L, a);
     if (col0 >= I || o0 >= O) return;
-    float inv[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
-        const float a = __uint_as_float(amax_bits[col0 + c]);
-        inv[c] = absmax_to_inv(a, qmax);
-        if (o0 == 0) sW[col0 + c] = absmax_to_scale(a, qmax);
+        inv[c] = absmax_to_inv(a[c], qmax);
+        if (o0 == 0) sW[col0 + c] = absmax_to_scale(a[c], qmax);
     }
     cols_quantize_block<Tin, B, PACKED, MANT>(W, O, I, inv, k0, k1, WqT, coeffT, col0, o0);
 }
