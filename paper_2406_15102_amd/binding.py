@@ -145,7 +145,7 @@ def _ptr(t, dtype=None):
         raise ValueError("tensor must be contiguous (dense row-major)")
     if dtype is not None and t.dtype != dtype:
         raise TypeError("expected %s, got %s" % (dtype, t.dtype))
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()      # a plain int: the argument types make a pointer of it
 
 
 def _expect(name, t, shape, dtype):
@@ -164,11 +164,10 @@ def _expect(name, t, shape, dtype):
 
 def _expect_backward(G, X, W, dX, dW, N, d_in, d_out):
     dt = G.dtype
-    _expect("G", G, (N, d_out), dt)
-    _expect("X", X, (N, d_in), dt)
-    _expect("W", W, (d_out, d_in), dt)
-    _expect("dX", dX, (N, d_in), dt)
-    _expect("dW", dW, (d_out, d_in), dt)
+    for name, t, rows, cols in (("G", G, N, d_out), ("X", X, N, d_in), ("W", W, d_out, d_in), ("dX", dX, N, d_in),
+                                ("dW", dW, d_out, d_in)):
+        if t is not None and (t.dtype != dt or t.numel() != rows * cols):
+            _expect(name, t, (rows, cols), dt)
 
 
 def _expect_store(Xc, sXc, d_in, Kc, flags):
@@ -185,7 +184,8 @@ def _expect_store(Xc, sXc, d_in, Kc, flags):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current device's current stream, without the stream object around it."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(status: int, where: str):

@@ -264,3 +264,22 @@ def test_binding_refuses_mismatched_tensors():
     with pytest.raises(TypeError):
         binding._expect_store(torch.empty((16, 16), dtype=torch.bfloat16), None, 16, 16, binding.HLQ_FLAG_GW_INT8)
     binding._expect_backward(g, x, torch.empty((64, 16), dtype=torch.bfloat16), None, None, 32, 16, 64)
+
+
+@pytest.mark.parametrize("which", range(5))
+def test_binding_checks_every_tensor_of_a_pass(which):
+    import torch
+    shapes = [(32, 64), (32, 16), (64, 16), (32, 16), (64, 16)]     # G, X, W, dX, dW
+    args = [torch.empty(s, dtype=torch.bfloat16) for s in shapes]
+    binding._expect_backward(*args, 32, 16, 64)
+    short = list(args)
+    short[which] = short[which][:-1]
+    with pytest.raises(ValueError):
+        binding._expect_backward(*short, 32, 16, 64)
+    if which:                                                        # the others must have G's element type
+        other = list(args)
+        other[which] = other[which].float()
+        with pytest.raises(TypeError):
+            binding._expect_backward(*other, 32, 16, 64)
+        other[which] = None
+        binding._expect_backward(*other, 32, 16, 64)
