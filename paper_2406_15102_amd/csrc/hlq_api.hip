@@ -628,7 +628,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     const float *sXh = sXc;
     // The transforms that depend on nothing share launches when the shapes allow (k_front.hip): two
     // and pass 2 over the weight for the default path (one in all when the weight has few rows or
-    // is not transformed here), three for the integer g_w list.  Very long rows of G and the mantissa-bit rounding keep one
+    // is not transformed here), two or three for the integer g_w list.  Very long rows of G and the mantissa-bit rounding keep one
     // launch per stage.
     const bool fusable = hlq::front_fusable(O, B) && !mant;   // the fused launches carry the seeded rounding only
     const bool fused = !gwi && fusable;

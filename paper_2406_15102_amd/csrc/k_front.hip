@@ -9,7 +9,7 @@
 // (with HLQ_OPT_FRONT_INTERLEAVE off, each job keeps its own index range and K3(X) rides in front B; a
 // convolution has K3 of the image, read as its column matrix, in front A and K3(G) in front B)
 // or ONE, when the weight has few row blocks (k_front_one below): the maxima stay per row block.
-// and three launches carry the integer g_w list, whose projections are quantised in two passes too:
+// and two or three launches carry the integer g_w list, whose projections are quantised in two passes too:
 //   front A   zeroing of the maxima that are merged by atomics (none where every tensor has few rows)
 //   front Q1  K1(G)  |  maxima of projected G  |  of projected X  |  of H^T W  |  widening of a 4-bit store
 //   front Q2  int8 codes of projected G  |  of projected X  |  codes of the weight
