@@ -20,7 +20,7 @@ OBJDIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
-    # packed-fp32 instructions are not to be generated on the test machines
+    # no packed-fp32 instructions: some of their forms have given wrong results
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-command-line-argument",
     # the k loops of the matrix products are written to be unrolled in full (a step of 256 MFMAs with
