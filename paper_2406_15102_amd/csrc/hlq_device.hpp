@@ -270,15 +270,17 @@ __device__ __forceinline__ uint32_t pack_bytes4(const int *q)
     return lo | hi;
 }
 
-// Eight codes in [-7, 7] as the nibbles of a dword, two's complement, code 2b in the low nibble of byte b and
-// code 2b+1 in the high one: the sum of q_i 16^i by shift-and-add (one instruction a code), with 8 added to every
-// digit at once (each is then in [1, 15], nothing carries) and the bias taken out again by flipping bit 3.
+// Eight codes as the nibbles of a dword, two's complement, code 2b in the low nibble of byte b and code 2b+1 in the
+// high one: each code's low four bits enter at the top of the word and push the earlier ones down, one instruction a
+// code (v_alignbit_b32: the low word of {code, word} >> 4).  Bits above the low four never reach a neighbour, so it holds
+// for codes outside [-7, 7] too: a row or column whose largest value is below 7 / FLT_MAX (2.06e-38) has an infinite
+// reciprocal and saturated codes.
 __device__ __forceinline__ uint32_t pack_nibbles8(const int *q)
 {
-    int r = q[7];
+    uint32_t r = static_cast<uint32_t>(q[0]) << 28;
 #pragma unroll
-    for (int e = 6; e >= 0; --e) asm("v_lshl_add_u32 %0, %0, 4, %1" : "+v"(r) : "v"(q[e]));   // left alone, two each
-    return (static_cast<uint32_t>(r) + 0x88888888u) ^ 0x88888888u;
+    for (int e = 1; e < 8; ++e) r = __builtin_amdgcn_alignbit(static_cast<uint32_t>(q[e]), r, 4);
+    return r;
 }
 
 // Maxima of a lane's CPL columns (bit patterns of non-negative floats): one row of D of them, or `table` rows to be

@@ -65,3 +65,51 @@ def test_row_and_column_codes(rows, K, B, bits, seed):
     got = unpack_nibbles(q.cpu().numpy()) if packed else q.cpu().numpy()
     assert np.array_equal(s.cpu().numpy().view(np.uint32), ref_s.view(np.uint32))
     assert int(np.count_nonzero(got != ref_q)) == 0
+
+
+# Rows or columns whose largest value is below 7 / FLT_MAX have an infinite reciprocal: a value other than zero saturates to
+# the largest or smallest int32, zero (0 * inf) gives 0.  Packed, every code still is its own low four bits and leaves
+# its neighbours alone.
+def _below_reciprocal(shape, axis, seed):
+    T = rand_tensor(shape, torch.float32, seed=seed, scale=1.0, spread=0.0)
+    sub = T[::2] if axis == 0 else T[:, ::2]
+    sub.copy_(torch.where(torch.rand(sub.shape, generator=torch.Generator().manual_seed(seed)) < 0.5, sub.sign() * 2e-40, 0.0))
+    return T
+
+
+@pytest.mark.parametrize("rows,K,B", [(37, 256, 16), (6, 4128, 32), (9, 1088, 64)])
+@pytest.mark.parametrize("mant", [0, hlq.HLQ_BITS_ROUND_MANTISSA])
+def test_packed_codes_are_the_low_nibbles(rows, K, B, mant):
+    G = dev(_below_reciprocal((rows, K), 0, rows + K))
+    q, s = torch.empty((rows, K), dtype=torch.int8, device=DEV), torch.empty(rows, dtype=torch.float32, device=DEV)
+    p = torch.empty((rows, K // 2), dtype=torch.uint8, device=DEV)
+    hlq.hlq_quantize_g(G, B, 5, q, s, None, bits=hlq.HLQ_BITS_4 | mant)
+    hlq.hlq_quantize_g(G, B, 5, p, s, None, bits=hlq.HLQ_BITS_4_PACKED | mant)
+    assert torch.equal(p, (q[:, ::2] & 15).to(torch.uint8) | ((q[:, 1::2] & 15) << 4).to(torch.uint8))
+    assert int((p[::2] & 15).max()) == 15 and int(torch.isfinite(s).sum()) == rows
+    I = rows + (-rows) % 8
+    W = dev(_below_reciprocal((K, I), 1, K + rows))
+    q, s = torch.empty((I, K), dtype=torch.int8, device=DEV), torch.empty(I, dtype=torch.float32, device=DEV)
+    p = torch.empty((I, K // 2), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(hlq.hlq_quantize_w_workspace_bytes(K, I), dtype=torch.uint8, device=DEV)
+    hlq.hlq_quantize_w(W, B, 5, q, s, ws, None, bits=hlq.HLQ_BITS_4 | mant)
+    hlq.hlq_quantize_w(W, B, 5, p, s, ws, None, bits=hlq.HLQ_BITS_4_PACKED | mant)
+    assert torch.equal(p, (q[:, ::2] & 15).to(torch.uint8) | ((q[:, 1::2] & 15) << 4).to(torch.uint8))
+
+
+@pytest.mark.parametrize("N,D,B,r", [(256, 40, 16, 8), (320, 24, 32, 32), (256, 136, 64, 32)])
+def test_store_codes_are_the_low_nibbles(N, D, B, r):
+    X = _below_reciprocal((N, D), 1, N + D)
+    Kc = N // B * r
+    q = torch.empty((D, Kc // 2), dtype=torch.uint8, device=DEV)
+    s = torch.empty(D, dtype=torch.float32, device=DEV)
+    ws = torch.empty(hlq.hlq_hla_quantize_workspace_bytes(D), dtype=torch.uint8, device=DEV)
+    hlq.hlq_compress_act_int4(dev(X), B, r, 5, q, s, ws)
+    c = oracle.hla_f32(wl.as_f32_numpy(X), B, r)
+    ref, _ = oracle.quantize_rows(c, 5, 2, qmax=7)
+    got = unpack_nibbles(q.cpu().numpy())
+    tiny = np.arange(D) % 2 == 0
+    assert np.abs(c[tiny]).max() < 2.0e-38
+    # all ones for the largest int32, all zeros for the smallest and for zero
+    assert np.array_equal(got[tiny], np.where(c[tiny] > 0, -1, 0))
+    assert np.array_equal(got[~tiny], ref[~tiny])
