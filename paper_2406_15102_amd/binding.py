@@ -25,6 +25,8 @@ HLQ_FLAG_SEPARATE_PRODUCTS = 32
 HLQ_FLAG_XC_INT4 = 64
 HLQ_BITS_4, HLQ_BITS_8, HLQ_BITS_4_PACKED = 4, 8, 0x104
 
+# not part of torch's public interface: absent from some builds (torch without a GPU among them)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 class hlq_conv_geom(C.Structure):
@@ -184,8 +186,10 @@ def _expect_store(Xc, sXc, d_in, Kc, flags):
 
 
 def _stream():
-    """Handle of the current device's current stream, without the stream object around it."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """Handle of the current device's current stream, without the stream object around it where torch has that."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(status: int, where: str):

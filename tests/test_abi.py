@@ -283,3 +283,15 @@ def test_binding_checks_every_tensor_of_a_pass(which):
             binding._expect_backward(*other, 32, 16, 64)
         other[which] = None
         binding._expect_backward(*other, 32, 16, 64)
+
+
+def test_binding_stream_without_the_raw_handle(monkeypatch):
+    # torch's raw stream handle is not a public name: without it the public stream object gives the same handle
+    import types
+    import torch
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    assert binding._stream() == 0x1230
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 0x4560 + device)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    assert binding._stream() == 0x4563
