@@ -97,16 +97,18 @@ __device__ __forceinline__ void gemm_tile(const GemmDev &g, const int bid)
 
     // Step KT of k into registers (A rows, then Bm rows) with raw buffer loads: the address is
     // (tile base in the resource) + (per-thread row offset, a loop-invariant VGPR) + (k offset, an
-    // SGPR).  Chunks past the end of the row (TAIL, a ragged last step) and steps past the last one
-    // get bit 31 of their offset set: out of the resource's range (row offsets stay below 2^31), so
-    // the load returns zeros and fetches nothing.  One instruction a load; the zeroing it replaces,
-    // four selects per LDS write, cost a ragged product 0.09 us a step (99 steps of 128-tiles, 144
-    // tiles: 54.5 us against 46.5 for the same k in whole steps).
+    // SGPR), so no vector arithmetic is spent on addresses inside the loop.  Steps past the last one are
+    // clamped to it.  With a ragged last step (TAIL) chunks past the end of the row and steps past the
+    // last one get bit 31 of their offset set instead, at one instruction a load: out of the resource's
+    // range (row offsets stay below 2^31), so the load returns zeros and fetches nothing.  Whole pass of
+    // 12608 x 768 x 3072 with selects before every LDS write in its place 116.1 us, so 113.7; 9200 x 1160 x
+    // 3120 145.2 and 141.9.  In products of whole steps the instruction is only cost: 50176 x 432 x 96
+    // 53.1 us with it, 52.9 without (runs of one side within 0.1).
     const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(baseA), 0, 0x7FFFFFFF, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(baseB), 0, 0x7FFFFFFF, 0x00020000);
 #define HLQ_KOFS(KT)                                                                                          \
         const int kuni = (kbeg + (KT)) * (KCH * 16);      /* wave-uniform: lives in an SGPR */                \
-        const uint32_t none = ((KT) < nk && (!TAIL || kuni + lc * 16 < g.Kb)) ? 0u : 0x80000000u;
+        const uint32_t none = (TAIL && !((KT) < nk && kuni + lc * 16 < g.Kb)) ? 0x80000000u : 0u;
 #define HLQ_LOAD_GLOBAL_A(KT)                                                                                 \
     {                                                                                                         \
         HLQ_KOFS(KT)                                                                                          \
@@ -181,8 +183,8 @@ __device__ __forceinline__ void gemm_tile(const GemmDev &g, const int bid)
         _Pragma("unroll") for (int ks = 0; ks < NS; ++ks) { rdA[ks] ^= STAGE_BYTES; rdB[ks] ^= STAGE_BYTES; } \
     }
 
-    // The loop body is branch-free: past the end, steps of zeros are loaded and published but never
-    // multiplied.
+    // The loop body is branch-free: past the end, the last step (TAIL: zeros) is loaded and published again but
+    // never multiplied.
     //
     // Step kt, sub-step ks:
     //   every ks     read the fragments of the next sub-step (the next step's first one for the
@@ -250,7 +252,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev &g, const int bid)
     static_assert(NS == 4, "the staging schedule below is written for four sub-steps per step");
 
     for (int kt = 0; kt < (one_step ? 0 : nk); ++kt) {
-        const int kt2 = kt + 2;
+        const int kt2 = (TAIL || kt + 2 < nk) ? kt + 2 : nk - 1;
 #pragma unroll
         for (int ks = 0; ks < NS; ++ks) {
             const int cur = ks & 1;
