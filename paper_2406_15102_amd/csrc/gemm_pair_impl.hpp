@@ -52,10 +52,6 @@ __global__ __launch_bounds__(256) void k_gemm_pair(GemmDev ga, GemmDev gb, GemmD
     const bool in_first = b < n0_pad;
     if (in_first && b >= n0) return;                    // padding
     const int idx = in_first ? b : b - n0_pad;
-    // the product that goes first has the longer tiles: where two tiles share a compute unit its wavefronts
-    // issue first (whole pass without and with: fp32 4096 x 2048 x 5632 167.3 -> 166.4 us, runs of one side within
-    // 0.4 %; 50176 x 432 x 96 54.55 -> 54.47; no difference at 12608 x 768 x 3072, 9200 x 1160 x 3120)
-    if (in_first) __builtin_amdgcn_s_setprio(2);
     if (in_first != (b_first != 0)) {
         pair_tile<CA>(ga, idx);
         return;
