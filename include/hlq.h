@@ -124,7 +124,9 @@ int hlq_set_option(int option, int value);
  *   dev_ptr  256-byte aligned device memory that stays valid until it is replaced or withdrawn;
  *            NULL (bytes ignored) withdraws the registration and returns to the library-owned scratch.
  *   bytes    its size; size it with hlq_workspace_bytes / hlq_workspace_bytes_mode /
- *            hlq_conv_workspace_bytes for the largest problem that will be run.
+ *            hlq_conv_workspace_bytes for the largest problem that will be run.  (The integer g_w list takes
+ *            a little more, for a launch less, where N or d_out is at most 4096: a problem of that kind whose
+ *            size comes out above what a longer one needed runs in the longer one's scratch, without that.)
  * HLQ_ERR_WORKSPACE for a misaligned pointer or bytes == 0 with a non-NULL pointer (the previous
  * registration stays).  The memory is not touched by this call.  Host-side only: no GPU work.
  */

@@ -75,9 +75,12 @@ int check_backward_shape(int64_t N, int64_t d_in, int64_t d_out, int B, int r)
 }
 
 // Carving of the backward workspace.  With HLQ_FLAG_GW_INT8 the compressed operands are int8
-// codes with one scale per feature plus one word of column maximum per feature.
+// codes with one scale per feature plus one word of column maximum per feature, and the tables of column
+// maxima (kAmaxTableRows) come last: `least` is the size without them.  A call that is given that much and not `total`
+// merges by atomics instead (same bits), so that scratch sized for a longer problem, whose maxima have no table,
+// holds a shorter one: 4096 x 4096 x 4096 with its tables takes 67.96 MB, 4112 x 4096 x 4096 has none and takes 67.67.
 struct Layout {
-    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, total;
+    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, least, tabw, tabg, tabx, total;
 };
 
 Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags)
@@ -91,12 +94,11 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
     L.sG = off;    off += up256(static_cast<size_t>(N) * 4);
     L.Wq = off;    off += up256(static_cast<size_t>(d_in) * d_out);
     L.sW = off;    off += up256(static_cast<size_t>(d_in) * 4);
-    const size_t wws1 = hlq::quant_cols_ws_bytes(d_out, d_in), wwst = gwi ? hlq::amax_table_bytes(d_out, d_in) : 0;
-    L.wws = off;   off += up256(wws1 > wwst ? wws1 : wwst);
-    // integer g_w list: column maxima of projected G (d_out columns), then of projected X (d_in columns),
+    L.wws = off;   off += up256(hlq::quant_cols_ws_bytes(d_out, d_in));
+    // integer g_w list: column maxima of projected G (d_out words), then of projected X (d_in words),
     // right behind those of the weight so that one fill zeroes all that are merged by atomics
-    L.hws = off;   off += gwi ? up256(hlq::amax_table_bytes(N, d_out)) : 0;
-    L.hwsx = off;  off += gwi ? up256(hlq::amax_table_bytes(N, d_in)) : 0;
+    L.hws = off;   off += gwi ? up256(hlq::hla_quant_ws_bytes(d_out)) : 0;
+    L.hwsx = off;  off += gwi ? up256(hlq::hla_quant_ws_bytes(d_in)) : 0;
     L.amax_end = off;
     L.GhatT = off; off += up256(static_cast<size_t>(d_out) * Kc * esz);
     L.sGhat = off; off += gwi ? up256(static_cast<size_t>(d_out) * 4) : 0;
@@ -118,6 +120,12 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
         if (gp > L.gws_bytes) L.gws_bytes = gp;
     }
     L.gws = off;   off += up256(L.gws_bytes);
+    L.least = off;
+    // the passes that fold a table are those of the fused launches
+    const bool tables = gwi && !(flags & HLQ_FLAG_ROUND_MANTISSA) && hlq::front_fusable(static_cast<int>(d_out), B);
+    L.tabw = off;  off += tables ? up256(hlq::amax_table_bytes(d_out, d_in)) : 0;
+    L.tabg = off;  off += tables ? up256(hlq::amax_table_bytes(N, d_out)) : 0;
+    L.tabx = off;  off += tables && !x_is_compressed ? up256(hlq::amax_table_bytes(N, d_in)) : 0;
     L.total = off;
     return L;
 }
@@ -171,18 +179,20 @@ int current_device()
     return dev;
 }
 
-int own_workspace(size_t bytes, void **out)
+// Scratch of a call that was given none: at least `least` bytes, `wanted` where it is allocated here.
+int own_workspace(size_t least, size_t wanted, void **out, size_t *bytes)
 {
     const int dev = current_device();
     if (dev < 0 || dev >= kMaxDevices) return HLQ_ERR_WORKSPACE;
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     if (g_user_ws_ptr[dev]) {
         // registered by the caller: use it or refuse; nothing is allocated, freed or waited for
-        if (g_user_ws_bytes[dev] < bytes) return HLQ_ERR_WORKSPACE;
+        if (g_user_ws_bytes[dev] < least) return HLQ_ERR_WORKSPACE;
         *out = g_user_ws_ptr[dev];
+        *bytes = g_user_ws_bytes[dev];
         return HLQ_OK;
     }
-    if (g_ws_bytes[dev] < bytes) {
+    if (g_ws_bytes[dev] < least) {
         if (g_ws_ptr[dev]) {
             // earlier calls may still be running on the old buffer
             if (hipDeviceSynchronize() != hipSuccess) return HLQ_ERR_WORKSPACE;
@@ -191,14 +201,15 @@ int own_workspace(size_t bytes, void **out)
             g_ws_bytes[dev] = 0;
         }
         void *p = nullptr;
-        if (hipMalloc(&p, bytes) != hipSuccess) {
+        if (hipMalloc(&p, wanted) != hipSuccess) {
             (void)hipGetLastError();
             return HLQ_ERR_WORKSPACE;
         }
         g_ws_ptr[dev] = p;
-        g_ws_bytes[dev] = bytes;
+        g_ws_bytes[dev] = wanted;
     }
     *out = g_ws_ptr[dev];
+    *bytes = g_ws_bytes[dev];
     return HLQ_OK;
 }
 
@@ -603,10 +614,10 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     const Layout L = make_layout(N, d_in, d_out, B, r, xc, flags);
     char *ws = static_cast<char *>(workspace);
     if (ws) {
-        if (!aligned(ws, 256) || workspace_bytes < L.total) return HLQ_ERR_WORKSPACE;
+        if (!aligned(ws, 256) || workspace_bytes < L.least) return HLQ_ERR_WORKSPACE;
     } else {
         void *p = nullptr;
-        if ((rc = own_workspace(L.total, &p)) != HLQ_OK) return rc;
+        if ((rc = own_workspace(L.least, L.total, &p, &workspace_bytes)) != HLQ_OK) return rc;
         ws = static_cast<char *>(p);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -645,29 +656,33 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         Xh = xu;
     }
     if (fused_q) {
-        uint32_t *amax_w = reinterpret_cast<uint32_t *>(ws + L.wws);
-        uint32_t *amax_g = reinterpret_cast<uint32_t *>(ws + L.hws);
-        uint32_t *amax_x = reinterpret_cast<uint32_t *>(ws + L.hwsx);
+        // a table of one row is where the maxima merged by atomics would be
+        const bool room = workspace_bytes >= L.total;
+        const int rows_w = hlq::amax_table_rows(O), rows_t = hlq::amax_table_rows(N);
+        const int tw = room || rows_w == 1 ? rows_w : 0, tt = room || rows_t == 1 ? rows_t : 0;
+        uint32_t *amax_w = reinterpret_cast<uint32_t *>(ws + (tw > 1 ? L.tabw : L.wws));
+        uint32_t *amax_g = reinterpret_cast<uint32_t *>(ws + (tt > 1 ? L.tabg : L.hws));
+        uint32_t *amax_x = reinterpret_cast<uint32_t *>(ws + (tt > 1 ? L.tabx : L.hwsx));
         const uint64_t k3 = stream_key(seed, 3), k2 = stream_key(seed, 2), kw = stream_key(seed, 1);
         const hlq::FrontRows jr = hlq::front_rows(dX ? G : nullptr, N, O, B, static_cast<uint32_t>(kg),
                                                   static_cast<uint32_t>(kg >> 32), qmax, Gq, sG);
         int8_t *xq = xc ? nullptr : reinterpret_cast<int8_t *>(ws + L.XhatT);
         float *sx = xc ? nullptr : reinterpret_cast<float *>(ws + L.sXhat);
-        const hlq::FrontHlaQ jg = hlq::front_hlaq(dW ? G : nullptr, N, O, B, r, amax_g, static_cast<uint32_t>(k3),
+        const hlq::FrontHlaQ jg = hlq::front_hlaq(dW ? G : nullptr, N, O, B, r, amax_g, tt, static_cast<uint32_t>(k3),
                                                   static_cast<uint32_t>(k3 >> 32), static_cast<int8_t *>(Gh), sGh);
-        const hlq::FrontHlaQ jx = hlq::front_hlaq(dW && !xc ? X : nullptr, N, I, B, r, amax_x, static_cast<uint32_t>(k2),
+        const hlq::FrontHlaQ jx = hlq::front_hlaq(dW && !xc ? X : nullptr, N, I, B, r, amax_x, tt, static_cast<uint32_t>(k2),
                                                   static_cast<uint32_t>(k2 >> 32), xq, sx);
         const bool wq = dX && !wc;
-        const hlq::FrontColsQ jq = hlq::front_colsq(wq ? W : nullptr, O, I, B, amax_w, static_cast<uint32_t>(kw),
+        const hlq::FrontColsQ jq = hlq::front_colsq(wq ? W : nullptr, O, I, B, amax_w, tw, static_cast<uint32_t>(kw),
                                                     static_cast<uint32_t>(kw >> 32), qmax, reinterpret_cast<int8_t *>(ws + L.Wq),
                                                     reinterpret_cast<float *>(ws + L.sW));
-        hlq::FrontAbsmax jw = hlq::front_absmax(wq ? W : nullptr, O, I, B, amax_w);
-        jw.table = jq.table;
+        const hlq::FrontAbsmax jw = hlq::front_absmax(wq ? W : nullptr, O, I, B, amax_w, tw);
         // The maxima that are merged by atomics are zeroed first: from the first of them to the last.  The row
         // quantiser goes with that launch, or -- in turns -- beside the three passes that only read.
-        const size_t zero_from = (wq && !jq.table) ? L.wws : ((jg.T && !jg.table) ? L.hws : L.hwsx);
-        const size_t zero_to = (jx.T && !jx.table) ? L.amax_end : ((jg.T && !jg.table) ? L.hwsx : ((wq && !jq.table) ? L.hws : zero_from));
-        const hlq::FrontFill jf{reinterpret_cast<uint32_t *>(ws + zero_from), static_cast<int>((zero_to > zero_from ? zero_to - zero_from : 0) / 4)};
+        const bool zw = wq && !tw, zg = jg.T && !tt, zx = jx.T && !tt;
+        const size_t zero_from = zw ? L.wws : (zg ? L.hws : L.hwsx);
+        const size_t zero_to = zx ? L.amax_end : (zg ? L.hwsx : (zw ? L.hws : zero_from));
+        const hlq::FrontFill jf{reinterpret_cast<uint32_t *>(ws + zero_from), static_cast<int>((zero_to - zero_from) / 4)};
         const hlq::FrontHla none = hlq::front_hla(nullptr, N, O, B, r, nullptr);
         const hlq::FrontAbsmax none_w = hlq::front_absmax(nullptr, O, I, B, nullptr);
         const bool k1_later = hlq::front_mix_enabled();
@@ -940,7 +955,7 @@ int hlq_conv_compress_act_int8(const void *X, const hlq_conv_geom *g, int B, int
 // The column matrix is stored only when the g_w list cannot read it through the image.
 struct ConvLayout {
     bool pointwise, implicit;
-    size_t cols, dcols, inner, inner_bytes, total;
+    size_t cols, dcols, inner, least, total;   // least: see Layout
 };
 
 static ConvLayout conv_layout(const hlq::ConvShape &c, const hlq_conv_geom *g, int B, int r, int dtype, int flags)
@@ -953,8 +968,12 @@ static ConvLayout conv_layout(const hlq::ConvShape &c, const hlq_conv_geom *g, i
     L.cols = 0;
     L.dcols = L.implicit ? 0 : mat;
     L.inner = L.dcols + mat;
-    L.inner_bytes = hlq_workspace_bytes_mode(c.N, I, g->O, B, r, 0, flags);
-    L.total = L.inner + L.inner_bytes;
+    L.least = L.total = 0;
+    if (check_backward_shape(c.N, I, g->O, B, r) == HLQ_OK && check_flags(flags, r, c.N, B) == HLQ_OK) {
+        const Layout in = make_layout(c.N, I, g->O, B, r, false, flags);
+        L.least = L.inner + in.least;
+        L.total = L.inner + in.total;
+    }
     return L;
 }
 
@@ -962,8 +981,7 @@ size_t hlq_conv_workspace_bytes(const hlq_conv_geom *g, int B, int r, int dtype,
 {
     hlq::ConvShape c;
     if (conv_shape(g, &c) != HLQ_OK || check_dtype(dtype) != HLQ_OK || check_block(B) != HLQ_OK) return 0;
-    const ConvLayout L = conv_layout(c, g, B, r, dtype, flags);
-    return L.inner_bytes == 0 ? 0 : L.total;
+    return conv_layout(c, g, B, r, dtype, flags).total;
 }
 
 int hlq_conv2d_backward(const void *G, const void *X, const void *Wt, const hlq_conv_geom *g, int B, int r,
@@ -983,10 +1001,10 @@ int hlq_conv2d_backward(const void *G, const void *X, const void *Wt, const hlq_
     const ConvLayout L = conv_layout(c, g, B, r, dtype, flags);
     char *ws = static_cast<char *>(workspace);
     if (ws) {
-        if (!aligned(ws, 256) || workspace_bytes < L.total) return HLQ_ERR_WORKSPACE;
+        if (!aligned(ws, 256) || workspace_bytes < L.least) return HLQ_ERR_WORKSPACE;
     } else {
         void *p = nullptr;
-        if ((rc = own_workspace(L.total, &p)) != HLQ_OK) return rc;
+        if ((rc = own_workspace(L.least, L.total, &p, &workspace_bytes)) != HLQ_OK) return rc;
         ws = static_cast<char *>(p);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1003,7 +1021,7 @@ int hlq_conv2d_backward(const void *G, const void *X, const void *Wt, const hlq_
     const bool fold = !L.pointwise && dX;
     hlq::SplitReduce red{};
     rc = backward_impl(G, dW ? xmat : nullptr, nullptr, nullptr, dX ? Wt : nullptr, nullptr, nullptr, c.N, I, g->O, B, r,
-                       seed, dtype, flags, dxmat, dW, ws + L.inner, L.inner_bytes, stream, L.implicit ? &c : nullptr,
+                       seed, dtype, flags, dxmat, dW, ws + L.inner, workspace_bytes - L.inner, stream, L.implicit ? &c : nullptr,
                        fold ? &red : nullptr);
     if (rc != HLQ_OK) return rc;
     // the fold, and in the same launch the reduction that the weight gradient's product left to do, if any

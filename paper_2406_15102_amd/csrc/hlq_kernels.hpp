@@ -157,7 +157,7 @@ struct FrontColsQ {  // pass 2 of K1T
     int8_t *WqT;
     float *sW;
     int gx, gy;
-    int table;       // of the strips that run both passes by themselves: unused
+    int table;       // see kAmaxTableRows; 0: one maximum per column, merged by atomics.  front_cols_full: unused
 };
 // Column maxima of the integer g_w list.  A workgroup of a pass 1 covers 256 rows.  Where a tensor has at most
 // kAmaxTableRows of them, each leaves its maxima in a row of its own of a table, [groups of 256 rows][columns],
@@ -171,12 +171,12 @@ inline int amax_table_rows(int64_t rows) { return rows <= 256 * kAmaxTableRows ?
 inline size_t amax_table_bytes(int64_t rows, int64_t cols)
 {
     const int t = amax_table_rows(rows);
-    return static_cast<size_t>(t ? t : 1) * static_cast<size_t>(cols) * 4;
+    return t > 1 ? static_cast<size_t>(t) * static_cast<size_t>(cols) * 4 : 0;   // a single row has a place anyway
 }
-FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, uint32_t k0, uint32_t k1, int8_t *TqT,
-                     float *sT);
-FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, uint32_t k0, uint32_t k1, float qmax,
-                       int8_t *WqT, float *sW);
+FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, int table, uint32_t k0, uint32_t k1,
+                     int8_t *TqT, float *sT);
+FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, int table, uint32_t k0, uint32_t k1,
+                       float qmax, int8_t *WqT, float *sW);
 FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in);
 // The integer g_w list in two launches: every pass 1 (maxima of projected G, projected X, transformed W),
 // then every pass 2; where maxima are merged by atomics, a launch of launch_front zeroes them first.  `jr`, if it
@@ -188,7 +188,7 @@ hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontA
 bool front_fusable(int O, int B);
 FrontRows front_rows(const void *G, int64_t N, int O, int B, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG);
 FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, uint16_t *out);
-FrontAbsmax front_absmax(const void *W, int O, int I, int B, uint32_t *amax);
+FrontAbsmax front_absmax(const void *W, int O, int I, int B, uint32_t *amax, int table = 0);
 // all of K1T for a weight that passes cols_full_ok: one workgroup per strip of columns (gy carries the
 // strip's width as a shift)
 FrontColsQ front_cols_full(const void *W, int O, int I, int B, uint32_t k0, uint32_t k1, float qmax, int8_t *WqT, float *sW);

@@ -265,23 +265,21 @@ FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in)
     return j;
 }
 
-FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, uint32_t k0, uint32_t k1, int8_t *TqT,
-                     float *sT)
+FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, int table, uint32_t k0, uint32_t k1,
+                     int8_t *TqT, float *sT)
 {
-    FrontHlaQ j{T, N, D, r, amax, k0, k1, TqT, sT, 0, 0, 0};
+    FrontHlaQ j{T, N, D, r, amax, k0, k1, TqT, sT, 0, 0, table};
     if (!T) return j;
-    j.table = amax_table_rows(N);
     j.gx = hla_grid_x(D, B);
     j.gy = hla_grid_y(N, B);
     return j;
 }
 
-FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, uint32_t k0, uint32_t k1, float qmax,
-                       int8_t *WqT, float *sW)
+FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, int table, uint32_t k0, uint32_t k1,
+                       float qmax, int8_t *WqT, float *sW)
 {
-    FrontColsQ j{W, O, I, amax, k0, k1, qmax, WqT, sW, 0, 0, 0};
+    FrontColsQ j{W, O, I, amax, k0, k1, qmax, WqT, sW, 0, 0, table};
     if (!W) return j;
-    j.table = amax_table_rows(O);
     j.gx = cols_grid_x(I, B);
     j.gy = cols_grid_y(O, B);
     return j;
@@ -364,9 +362,9 @@ FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, uint16_t *out)
     return j;
 }
 
-FrontAbsmax front_absmax(const void *W, int O, int I, int B, uint32_t *amax)
+FrontAbsmax front_absmax(const void *W, int O, int I, int B, uint32_t *amax, int table)
 {
-    FrontAbsmax j{W, O, I, amax, 0, 0, 0};
+    FrontAbsmax j{W, O, I, amax, 0, 0, table};
     if (!W) return j;
     j.gx = cols_grid_x(I, B);
     j.gy = cols_grid_y(O, B);
