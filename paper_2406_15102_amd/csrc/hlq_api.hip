@@ -78,7 +78,7 @@ int check_backward_shape(int64_t N, int64_t d_in, int64_t d_out, int B, int r)
 // codes with one scale per feature plus one word of column maximum per feature, and the tables of column
 // maxima (kAmaxTableRows) come last: `least` is the size without them.  A call that is given that much and not `total`
 // merges by atomics instead (same bits), so that scratch sized for a longer problem, whose maxima have no table,
-// holds a shorter one: 4096 x 4096 x 4096 with its tables takes 67.96 MB, 4112 x 4096 x 4096 has none and takes 67.67.
+// holds a shorter one: 4096 x 96 x 768 at r = 16 with its tables takes 10.08 MB, 4112 x 96 x 768 10.05.
 struct Layout {
     size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, least, tabw, tabg, tabx, total;
 };
@@ -656,13 +656,15 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         Xh = xu;
     }
     if (fused_q) {
-        // Tables where every tensor of the call has one (and the scratch room for those of more than one row), atomics for
-        // all of them otherwise: the zeroing is then launched anyway, and a table only adds its folding to pass 2.  Whole
-        // pass with tables for some against atomics for all, one binary: 4096 x 768 x 6144 88.3 and 85.2 us, 4096 x 4096 x
-        // 11008 326.1 and 322.1, fp32 8192 x 2048 x 3840 193.8 and 190.4.
+        // Tables where every tensor of the call has one, folding them is cheap (kAmaxTableReads) and the scratch has room for
+        // those of more than one row; atomics for all of them otherwise: the zeroing is then launched anyway, and a table
+        // only adds its folding to pass 2.  Whole pass with tables for some against atomics for all, one binary: 4096 x 768 x
+        // 6144 88.3 and 85.2 us, 4096 x 4096 x 11008 326.1 and 322.1, fp32 8192 x 2048 x 3840 193.8 and 190.4.
         const bool wq = dX && !wc;
         const int rows_w = wq ? hlq::amax_table_rows(O) : 1, rows_t = dW ? hlq::amax_table_rows(N) : 1;
-        const bool tables = rows_w && rows_t && ((rows_w == 1 && rows_t == 1) || workspace_bytes >= L.total);
+        const int64_t reads = (wq ? hlq::amax_table_reads(O, I) : 0) + (dW ? hlq::amax_table_reads(N, xc ? O : O + I) : 0);
+        const bool tables = rows_w && rows_t && reads <= hlq::kAmaxTableReads &&
+                            ((rows_w == 1 && rows_t == 1) || workspace_bytes >= L.total);
         const int tw = tables ? rows_w : 0, tt = tables ? rows_t : 0;
         uint32_t *amax_w = reinterpret_cast<uint32_t *>(ws + (tw > 1 ? L.tabw : L.wws));
         uint32_t *amax_g = reinterpret_cast<uint32_t *>(ws + (tt > 1 ? L.tabg : L.hws));

@@ -162,16 +162,27 @@ struct FrontColsQ {  // pass 2 of K1T
 // Column maxima of the integer g_w list.  A workgroup of a pass 1 covers 256 rows.  Where a tensor has at most
 // kAmaxTableRows of them, each leaves its maxima in a row of its own of a table, [groups of 256 rows][columns],
 // and pass 2 folds the rows: nothing has to be zeroed, and when every tensor of the call is of that kind the
-// launch that zeroes is not there.  Beyond, one row merged by atomics: pass 2 would read more maxima than codes
-// it writes.  Integer g_w list, whole pass, two launches less in all with the store widened beside the passes 1:
-// 4096 x 4096 x 11008 from the 4-bit store with cached weight codes 288 -> 271 us, 320 x 120 x 384 21.0 -> 18.6,
-// 512 x 8320 x 1920 from the store 52.5 -> 46.0.
+// launch that zeroes, about 2 us, is not there.  Otherwise one row merged by atomics.
+// Every workgroup of a pass 2 folds the whole table of its columns, rows * rows * columns reads over a tensor.  Their sum
+// over the call decides (whole pass, atomics -> tables, one binary, us): up to 1.4 M reads tables are ahead or
+// even (512 x 1024 x 1024 22.9 -> 20.8, 4096 x 1024 x 1024 37.2 -> 34.3, 2048 x 4096 x 11008 with weight codes 162.6 -> 162.0),
+// to 2.25 M it goes either way by 1 % (3072 x 4096 x 4096 120.0 -> 118.6, fp32 4096 x 3072 x 3072 127.5 -> 129.2), beyond tables
+// are behind (4096 x 8192 x 1024 with codes, 2.4 M, 99.7 -> 101.1; 4096 x 4096 x 4096, 3.1 M, 136.1 -> 137.5; 4096 x 11008 x 3072,
+// 5.2 M, 264.0 -> 271.1).  With tables of more than 16 rows, 4096: 8192 x 768 x 3072 82.1 -> 87.6, 16384 x 4096 x 4096 with codes
+// 438 -> 471.
 constexpr int kAmaxTableRows = 16;
+constexpr int64_t kAmaxTableReads = 2250000;
 inline int amax_table_rows(int64_t rows) { return rows <= 256 * kAmaxTableRows ? static_cast<int>((rows + 255) / 256) : 0; }
+inline int64_t amax_table_reads(int64_t rows, int64_t cols)
+{
+    const int64_t t = amax_table_rows(rows);
+    return t * t * cols;
+}
 inline size_t amax_table_bytes(int64_t rows, int64_t cols)
 {
     const int t = amax_table_rows(rows);
-    return t > 1 ? static_cast<size_t>(t) * static_cast<size_t>(cols) * 4 : 0;   // a single row has a place anyway
+    // (a single row has a place anyway)
+    return t > 1 && amax_table_reads(rows, cols) <= kAmaxTableReads ? static_cast<size_t>(t) * static_cast<size_t>(cols) * 4 : 0;
 }
 FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, int table, uint32_t k0, uint32_t k1,
                      int8_t *TqT, float *sT);

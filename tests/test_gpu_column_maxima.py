@@ -1,5 +1,5 @@
-"""Integer g_w list: up to 4096 rows the column maxima are left as a table that the second pass folds, beyond they
-are merged by atomics, tensor by tensor; a 4-bit store is widened beside the first passes; an image is projected
+"""Integer g_w list: where every tensor of the call has at most 4096 rows, and the scratch room, the column maxima are
+left as tables that the second pass folds, otherwise they are merged by atomics; a 4-bit store is widened beside the first passes; an image is projected
 there too.  Each way, the pass gives the bits that the stage entry points give (which merge by atomics)."""
 import pytest
 import torch
@@ -44,9 +44,9 @@ def _by_stages(G, X, W, B, r, seed, store):
 @pytest.mark.parametrize("N,d_in,d_out,B,r", [
     (64, 64, 16, 16, 8),                # one row of workgroups
     (4096, 136, 48, 16, 8),             # the largest table of tokens
-    (4096 + 64, 136, 4096, 64, 32),     # tokens by atomics, the weight's out-features at the largest table
-    (512, 72, 4096 + 32, 32, 16),       # the other way round
-    (4096 + 32, 40, 4096 + 32, 32, 32), # all by atomics
+    (4096 + 64, 136, 4096, 64, 32),     # by atomics: too many tokens
+    (512, 72, 4096 + 32, 32, 16),       # too many out-features
+    (4096 + 32, 40, 4096 + 32, 32, 32), # both
 ])
 @pytest.mark.parametrize("store", [None, "int8", "int4"])
 def test_pass_equals_its_stages(N, d_in, d_out, B, r, store):
@@ -82,9 +82,11 @@ def test_image_equals_its_column_matrix(H, C, stride, dtype):
 CODES8, UNPACKED, SEQ = hlq.HLQ_FLAG_GX_8BIT, hlq.HLQ_FLAG_GX_UNPACKED, hlq.HLQ_FLAG_GW_SEQUENCY
 SHAPES = [
     (1024, 72, 1056, 32, 16),           # every tensor with a table, the last row of the weight's partly filled
-    (4096 + 64, 136, 4096, 64, 32),     # tokens by atomics, the weight with a table
-    (512, 72, 4096 + 32, 32, 16),       # the other way round
+    (4096 + 64, 136, 4096, 64, 32),     # too many tokens for a table: one for the weight only where it is alone
+    (512, 72, 4096 + 32, 32, 16),       # too many out-features: a table for the tokens only without a pass over the weight
     (4096 + 32, 40, 4096 + 32, 32, 32), # all by atomics
+    (4096, 8192, 320, 16, 8),           # few enough reads of the tables (2.21 M)
+    (4096, 8192, 640, 16, 8),           # too many (2.33 M): all by atomics
 ]
 
 
