@@ -10,7 +10,7 @@
 // convolution has K3 of the image, read as its column matrix, in front A and K3(G) in front B)
 // or ONE, when the weight has few row blocks (k_front_one below): the maxima stay per row block.
 // and two or three launches carry the integer g_w list, whose projections are quantised in two passes too:
-//   front A   zeroing of the maxima that are merged by atomics (none where every tensor has few rows)
+//   front A   zeroing of the maxima where they are merged by atomics (kAmaxTableRows, kAmaxTableReads)
 //   front Q1  K1(G)  |  maxima of projected G  |  of projected X  |  of H^T W  |  widening of a 4-bit store
 //   front Q2  int8 codes of projected G  |  of projected X  |  codes of the weight
 // A workgroup looks up its job from its index (jobs occupy consecutive index ranges, a job may be
@@ -192,7 +192,9 @@ __global__ __launch_bounds__(256) void k_front_q1(FrontHlaQ jg, FrontHlaQ jx, Fr
         int k1 = -1, k3 = -1;
         if (jm.gran) {
             // (the widening of a 4-bit store stays behind the turns: counted among the readers it would thin out the
-            // quantiser's share of them -- fp32 57728 x 1192 x 2688, this launch: 236 us so, 210 as two launches)
+            // quantiser's share of them.  Whole pass from the store with it counted / as a launch of its own / behind, us:
+            // fp32 57728 x 1192 x 2688 711.7 / 688.9 / 685.7, 4096 x 768 x 3072 48.9 / 50.9 / 47.9, 512 x 8320 x 1920
+            // 48.6 / 51.7 / 48.5)
             const int n3 = jg.gx * jg.gy + jx.gx * jx.gy + jw.gx * jw.gy;
             front_turns(jm, b, jr.blocks, n3, k1, k3);
             if (k1 < 0) b = k3 >= 0 ? k3 : n3 + b;
