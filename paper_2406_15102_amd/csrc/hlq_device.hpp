@@ -118,6 +118,7 @@ __device__ __forceinline__ void fwht_regs(float *v)
 // every later exchange, because they differ in a higher lane bit only) and fold it into whatever
 // consumes the value.  The s_nop covers the VALU-write -> DPP-read hazard, which the compiler
 // cannot see inside an asm statement; the eight values of a chunk go together so that one covers them all.
+// Every one of them is written before sigma is read for the last time, hence early-clobber operands.
 #define HLQ_DPP8(PERM)                                                                                        \
     asm("s_nop 1\n\t"                                                                                         \
         "v_fmac_f32_dpp %0, %0, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
@@ -128,7 +129,7 @@ __device__ __forceinline__ void fwht_regs(float *v)
         "v_fmac_f32_dpp %5, %5, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
         "v_fmac_f32_dpp %6, %6, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"            \
         "v_fmac_f32_dpp %7, %7, %8 quad_perm:" PERM " row_mask:0xf bank_mask:0xf bound_ctrl:1"                \
-        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])      \
+        : "+&v"(x[0]), "+&v"(x[1]), "+&v"(x[2]), "+&v"(x[3]), "+&v"(x[4]), "+&v"(x[5]), "+&v"(x[6]), "+&v"(x[7]) \
         : "v"(sigma))
 template <int MASK>
 __device__ __forceinline__ void butterfly_lanes_signed8(float *x, float sigma)
