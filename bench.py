@@ -26,7 +26,7 @@ PEAK_BF16_TFLOPS = 2500.0
 
 WARM_MS = 60.0        # load that precedes every timed region, whatever --warmup says
 DENSE_WARM_MS = 400.0  # the dense comparator (hipBLASLt) keeps getting faster for some 0.3 s of calls: 712 us after 60 ms
-                       # of them, 684 after 400 ms on one box; the speed-up is quoted against the settled figure
+                       # of them, 684 after 400 ms on one card; the speed-up is quoted against the settled figure
 
 
 def _warm(fn, torch, calls=0, warm_ms=WARM_MS):
@@ -123,7 +123,7 @@ def main():
                     help="skip the extra whole-path timings of the method's options (keeps a profile to the default path)")
     args = ap.parse_args()
     if args.gpus != 1:
-        sys.exit("bench.py: this build runs on one GPU only (no collectives, no sharding); use --gpus 1")
+        sys.exit("bench.py: this program runs on one GPU only (no collectives, no sharding); use --gpus 1")
 
     import torch
 
@@ -406,7 +406,7 @@ def main():
                                 "(784,96,384)": [179, 91], "ResNet-34 (1024,64,576)": [194, 95],
                                 "(256,128,1152; printed 152)": [156, 76], "(256,128,64)": [111, 50],
                                 "(64,256,1152)": [171, 86], "(64,256,128)": [113, 50], "(16,512,2304)": [252, 101]},
-        "note": "layer shapes (L, O, I) at an unstated batch; this build's figures for the same twelve shapes at "
+        "note": "layer shapes (L, O, I) at an unstated batch; this library's figures for the same twelve shapes at "
                 "batch 64 come from `bench.py --workload p01` ... `p12` (against a bf16 hipBLASLt backward, not fp32)",
     }
 

@@ -165,7 +165,7 @@ int hlqo_transform_cols(const float *W, long O, long I, int B, float *WhatT /* [
 
 /* ------------------------------------------------------------------------- */
 /* Seeded counter-based random bits for stochastic rounding (Sec. 6.1 asks    */
-/* for an unbiased stochastic quantiser; the generator is this build's).      */
+/* for an unbiased stochastic quantiser; the generator is this library's).    */
 /* ------------------------------------------------------------------------- */
 
 /* Stream key for (seed, tensor id): output number (tensor+1) of the SplitMix64 */

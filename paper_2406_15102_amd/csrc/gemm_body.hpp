@@ -103,7 +103,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDev &g, const int bid)
     // range (row offsets stay below 2^31), so the load returns zeros and fetches nothing.  Whole pass of
     // 12608 x 768 x 3072 with selects before every LDS write in its place 116.1 us, so 113.7; 9200 x 1160 x
     // 3120 145.2 and 141.9.  Products of whole steps have no use for the instruction: 50176 x 432 x 96
-    // 53.1 us with it and 52.9 without on one box, 54.44 and 54.40 on another.
+    // 53.1 us with it and 52.9 without on one card, 54.44 and 54.40 on another.
     const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(baseA), 0, 0x7FFFFFFF, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(baseB), 0, 0x7FFFFFFF, 0x00020000);
 #define HLQ_KOFS(KT)                                                                                          \

@@ -404,7 +404,7 @@ std::atomic<int> g_share_enabled{0};
 void front_share_enable(bool on) { g_share_enabled.store(on ? 1 : 0); }
 
 namespace {
-// On by default.  Whole pass at 4096 x 4096 x 11008, alternating runs on one box: 371.9 us with each job in its
+// On by default.  Whole pass at 4096 x 4096 x 11008, alternating runs on one card: 371.9 us with each job in its
 // own range, 364-367 with turns of 8 to 128 workgroups of the projection (32 the best by a microsecond);
 // 8192 x 28672 x 8192 and the small layers do not move.
 std::atomic<int> g_mix_enabled{1};

@@ -1,6 +1,6 @@
 """Integer g_w list: where every tensor of the call has at most 4096 rows, and the scratch room, the column maxima are
-left as tables that the second pass folds, otherwise they are merged by atomics; a 4-bit store is widened beside the first passes; an image is projected
-there too.  Each way, the pass gives the bits that the stage entry points give (which merge by atomics)."""
+left as tables that the second pass folds, otherwise they are merged by atomics; a 4-bit store is widened beside the
+first passes; an image is projected there too.  Each way, the pass gives the bits that the stage entry points give (which merge by atomics)."""
 import pytest
 import torch
 
