@@ -863,7 +863,8 @@ static int conv_shape(const hlq_conv_geom *g, hlq::ConvShape *out)
         static_cast<int64_t>(g->W) + 2 * static_cast<int64_t>(g->pad_w) + static_cast<int64_t>(g->kw) * g->dil_w >= limit)
         return HLQ_ERR_SHAPE;
     hlq::ConvShape c{g->Nb, g->H, g->W, g->C, g->kh, g->kw, g->stride_h, g->stride_w, g->pad_h, g->pad_w,
-                     g->dil_h, g->dil_w, static_cast<int>(Ho), static_cast<int>(Wo), N};
+                     g->dil_h, g->dil_w, static_cast<int>(Ho), static_cast<int>(Wo), N, 0};
+    c.far = hlq::conv_far(c);
     if (out) *out = c;
     return HLQ_OK;
 }

@@ -46,10 +46,22 @@ constexpr int64_t kColsFullMaxBytes = 8 << 20;
 bool cols_full_ok(int O, int I, int B, bool is_f32);
 
 // Geometry of a convolution over channels-last tensors.  N = Nb * Ho * Wo rows of the column matrix.
+// far: the images that the positions of a wavefront (at most 64 in a row, and the block they begin in) fall into
+// take 2^31 bytes of fp32 or more, and are not addressed in 32 bits from the first of them.
 struct ConvShape {
     int Nb, H, W, C, kh, kw, sh, sw, ph, pw, dh, dw, Ho, Wo;
     int64_t N;
+    int far;
 };
+inline bool conv_far(const ConvShape &s)
+{
+    const int64_t image = static_cast<int64_t>(s.H) * s.W;           // below 2^62
+    const int64_t images = 128 / (static_cast<int64_t>(s.Ho) * s.Wo) + 2;
+    return image >= (int64_t(1) << 31) || image * s.C >= (int64_t(1) << 31) / 4 / images ||
+           // the taps next to an image, too: offsets are stepped through them
+           (static_cast<int64_t>(s.H) + 2 * static_cast<int64_t>(s.ph) + static_cast<int64_t>(s.kh) * s.dh) *
+                   (static_cast<int64_t>(s.W) + 2 * static_cast<int64_t>(s.pw) + static_cast<int64_t>(s.kw) * s.dw) >= (int64_t(1) << 31);
+}
 
 // The independent transforms of one backward pass in two launches (k_front.hip).  A job with a
 // null tensor is empty.
