@@ -477,8 +477,10 @@ int hlq_conv_compress_act_int8(const void *X, const hlq_conv_geom *g, int B, int
  * hlq_col2im of the column gradient.  dX [Nb, H, W, C] and dW [O, kh, kw, C] of `dtype`; either may
  * be NULL.  A 1x1 kernel with unit stride and no padding is its own column matrix: no copy is made;
  * with C % (128 / B) == 0 the g_w list projects straight from the image (hlq_conv_compress_act) and
- * no column matrix is stored either -- same result bit for bit.  The column gradient is held in
- * `dtype` before it is folded.
+ * no column matrix is stored either -- same result bit for bit.  The column gradient's entries are
+ * rounded to `dtype` before they are folded, whether it is stored or, where that is faster, its entries are
+ * added to the image gradient as they come: dX is that of the three calls bit for bit.  The k split of
+ * the g_w product is planned for this call: dW agrees with theirs up to the order of its partial sums.
  *   workspace >= hlq_conv_workspace_bytes(...) bytes, 256-aligned; or NULL for the library-owned one.
  */
 size_t hlq_conv_workspace_bytes(const hlq_conv_geom *g, int B, int r, int dtype, int flags);

@@ -1,0 +1,89 @@
+// Host-side planning of the image gradient of a convolution (conv_dx_body.hpp), shared by its launchers.
+#pragma once
+#include "conv_dx_body.hpp"
+#include "gemm_plan.hpp"
+
+namespace hlq {
+
+struct ConvDxPlan {
+    ConvDx g;
+    int blocks;
+    size_t lds;
+};
+
+static inline int conv_gcd(int a, int b)
+{
+    while (b) {
+        const int t = a % b;
+        a = b;
+        b = t;
+    }
+    return a;
+}
+
+// Tile of a layer: 128 pixels x 128 channels where the channels fill it, else 256 x 64; 128 x 64 where fewer than a
+// workgroup a compute unit would come of that, 64 x 64 where 128 x 64 fills little more than half of the chip
+// (image gradient and weight gradient together, us, 256 or 128 x 128 / 128 x 64 / 64 x 64 pixels x channels: 12544 pixels x 256
+// channels over 256 codes 33.2 / 30.5 / -, 200704 x 64 over 64 52.1 / 52.8 / -, 3136 x 512 over 512 39.4 / 33.0 / 36.3,
+// 12544 x 48 over 448 36.1 / 28.1 / 25.2, 4096 x 128 over 128 - / 15.1 / 11.8).
+static inline void conv_dx_shape(const ConvShape &s, int &form, int &tiles_px, int &tiles_c, int &blocks)
+{
+    const int64_t most = static_cast<int64_t>(s.Nb) * ((s.H + s.sh - 1) / s.sh) * ((s.W + s.sw - 1) / s.sw);   // pixels of a class
+    const int classes = s.sh * s.sw, c64 = (s.C + 63) / 64;
+    form = c64 % 2 == 0 ? 0 : 1;
+    if ((most + 255) / 256 * c64 * classes < 256) form = (most + 127) / 128 * c64 * classes < 160 ? 3 : 2;
+    const int bm = conv_dx_bm(form);
+    tiles_c = form == 0 ? c64 / 2 : c64;
+    tiles_px = static_cast<int>((most + bm - 1) / bm);
+    blocks = tiles_px * tiles_c * classes;
+}
+
+// Time of a tile, us, two to a compute unit: an item (RB codes of every row, of one tap) by shape and RB, from the
+// measurements of conv_dx_wanted.
+static inline double conv_dx_tile_us(int form, const ConvShape &s, int O)
+{
+    static const double item[4][3] = {{0.6, 0.75, 1.1}, {0.55, 0.6, 0.6}, {0.4, 0.5, 0.75}, {0.25, 0.3, 0.5}};
+    const int rb = conv_dx_rb(form, O);
+    return static_cast<double>(s.kh) * s.kw / (s.sh * s.sw) * ((O + rb - 1) / rb) * item[form][rb / 64];
+}
+
+// Whether the image gradient is taken straight from the codes: not where the column gradient is small beside the
+// chain of taps and codes that one tile goes through.  The alternative writes the column gradient at about 2.3 TB/s and
+// reads it at about 5 (65536 x 1224: 70 and 32 us), in a launch of its own more.  Kernel times of a pass, us, column
+// gradient -> straight (pixels x channels x taps, over codes): 65536 x 136 x 9 over 32 144.3 -> 87.7, 65536 x 192 x 9
+// over 128 218.7 -> 124.7, 200704 x 64 x 9 over 64 245.5 -> 110.0, 50176 x 512 x 9 over 512 601 -> 416, fp32 50176 x 96 x
+// 9 over 256 with stride 2 220 -> 127, 12544 x 256 x 9 over 256 58.1 -> 51.8, 1024 x 128 x 9 over 256 with stride 2 23.3 -> 15.8;
+// taken the old way by this rule: 65536 x 16 x 9 over 512 73.4 -> 103.8, 16384 x 16 x 9 over 512 33.1 -> 47.2, 3136 x 64 x 9
+// over 512 27.0 -> 33.4, fp32 12544 x 48 x 9 over 448 42.5 -> 46.6, 4096 x 32 x 9 over 32 19.3 -> 19.9.
+// A 1 x 1 kernel with a stride has fewer taps than classes of pixels: most workgroups would write zeros only
+// (50176 x 128 over 256, stride 2, 25.9 -> 28.6).
+static inline bool conv_dx_wanted(const ConvShape &s, int O, bool is_f32)
+{
+    if (s.kh * s.kw < s.sh * s.sw) return false;
+    int form, tiles_px, tiles_c, blocks;
+    conv_dx_shape(s, form, tiles_px, tiles_c, blocks);
+    const double mb = static_cast<double>(s.N) * s.kh * s.kw * s.C * (is_f32 ? 4e-6 : 2e-6);
+    const double columns = 10.0 + (s.sh * s.sw > 1 ? 1.0 : 0.0) + mb / 2.3 + mb / 5.0;
+    const double rounds = __builtin_ceil(blocks / 512.0) * (blocks <= 256 && form != 3 ? 0.75 : 1.0);
+    return 9.3 + rounds * conv_dx_tile_us(form, s, O) < columns;
+}
+
+static inline ConvDxPlan conv_dx_plan(const GemmArgs &a, const ConvShape &s)
+{
+    ConvDxPlan p;
+    p.g.Gq = static_cast<const char *>(a.A);
+    p.g.sG = a.sA;
+    p.g.Wq = static_cast<const char *>(a.Bm);
+    p.g.sW = a.sB;
+    p.g.dX = a.C;
+    p.g.alpha = a.alpha;
+    p.g.s = s;
+    p.g.Kb = a.K;
+    p.g.stepy = s.sh / conv_gcd(s.sh, s.dh);
+    p.g.stepx = s.sw / conv_gcd(s.sw, s.dw);
+    conv_dx_shape(s, p.g.form, p.g.tiles_px, p.g.tiles_c, p.blocks);
+    p.lds = conv_dx_lds(p.g.form, p.g.Kb, s.kh * s.kw);
+    return p;
+}
+
+}  // namespace hlq

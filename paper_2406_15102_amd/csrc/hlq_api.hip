@@ -595,10 +595,13 @@ static int backward_check(const void *G, const void *X, const void *Xc, const fl
 
 // conv: NULL, or the geometry of a convolution; X is then its channels-last image and stands for
 // the column matrix [N, d_in], which the g_w list reads through the image (hla_conv_ok required).
+// image: NULL, or the geometry of a convolution whose image gradient dX is (conv_dx_ok required), instead of the
+// column gradient.
 static int backward_impl(const void *G, const void *X, const void *Xc, const float *sXc, const void *W, const void *Wc,
                          const float *sWc, int64_t N, int64_t d_in, int64_t d_out, int B, int r, uint64_t seed, int dtype,
                          int flags, void *dX, void *dW, void *workspace, size_t workspace_bytes, void *stream,
-                         const hlq::ConvShape *conv = nullptr, hlq::SplitReduce *defer = nullptr)
+                         const hlq::ConvShape *conv = nullptr, const hlq::ConvShape *image = nullptr,
+                         hlq::SplitReduce *defer = nullptr)
 {
     if (defer) defer->blocks = 0;
     int rc;
@@ -606,7 +609,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0;
     const float qmax = (flags & HLQ_FLAG_GX_8BIT) ? 127.0f : 7.0f;
     // 4-bit codes travel two to a byte whenever their rows stay 16-byte aligned that way
-    const bool packed = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && d_out % 32 == 0;
+    const bool packed = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && d_out % 32 == 0 && !image;
     const int basis = (flags & HLQ_FLAG_GW_SEQUENCY) ? HLQ_BASIS_SEQUENCY : HLQ_BASIS_NATURAL;
     const bool mant = (flags & HLQ_FLAG_ROUND_MANTISSA) != 0;
 
@@ -793,6 +796,12 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     hlq::GemmArgs aw{Gh, Xh, O, I, Kc, gwi ? sGh : nullptr, gwi ? sXh : nullptr, invB, dW, f32, nullptr, ws + L.gws,
                      L.gws_bytes};
     const int kind_x = packed ? 2 : 0, kind_w = gwi ? 0 : 1;
+    if (dX && image) {
+        if (dW && !(flags & HLQ_FLAG_SEPARATE_PRODUCTS) && hlq::conv_pair_available())
+            return launch_rc(hlq::launch_conv_pair(ax, *image, kind_w, aw, st));
+        if ((rc = launch_rc(hlq::launch_conv_dx(ax, *image, st))) != HLQ_OK || !dW) return rc;
+        return launch_rc(hlq::launch_gemm_nt(kind_w, aw, st));
+    }
     if (dX && dW && !(flags & HLQ_FLAG_SEPARATE_PRODUCTS) && hlq::gemm_pair_available(kind_x, ax, kind_w, aw))
         return launch_rc(hlq::launch_gemm_pair(kind_x, ax, kind_w, aw, st, defer));
     if (dX && (rc = launch_rc(hlq::launch_gemm_nt(kind_x, ax, st))) != HLQ_OK) return rc;
@@ -1021,13 +1030,15 @@ int hlq_conv2d_backward(const void *G, const void *X, const void *Wt, const hlq_
             if ((rc = launch_rc(hlq::launch_im2col(X, c, f32, ws + L.cols, st))) != HLQ_OK) return rc;
             xmat = ws + L.cols;
         }
-        if (dX) dxmat = ws + L.dcols;
     }
-    const bool fold = !L.pointwise && dX;
+    // the image gradient straight from the codes; where that kernel does not take the shape, the column gradient and its fold
+    const bool image = !L.pointwise && dX && hlq::conv_dx_ok(g->O, c, f32);
+    const bool fold = !L.pointwise && dX && !image;
+    if (fold) dxmat = ws + L.dcols;
     hlq::SplitReduce red{};
     rc = backward_impl(G, dW ? xmat : nullptr, nullptr, nullptr, dX ? Wt : nullptr, nullptr, nullptr, c.N, I, g->O, B, r,
                        seed, dtype, flags, dxmat, dW, ws + L.inner, workspace_bytes - L.inner, stream, L.implicit ? &c : nullptr,
-                       fold ? &red : nullptr);
+                       image ? &c : nullptr, fold ? &red : nullptr);
     if (rc != HLQ_OK) return rc;
     // the fold, and in the same launch the reduction that the weight gradient's product left to do, if any
     if (fold) return launch_rc(hlq::launch_col2im(dxmat, c, f32, dX, st, &red));

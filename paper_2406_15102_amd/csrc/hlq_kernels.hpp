@@ -312,6 +312,16 @@ hipError_t launch_im2col(const void *X, const ConvShape &g, bool is_f32, void *c
 hipError_t launch_col2im(const void *cols, const ConvShape &g, bool is_f32, void *dx, hipStream_t st,
                          const SplitReduce *red = nullptr);
 
+// Image gradient of a convolution, product and fold in one (conv_dx_body.hpp), the bits of the two passes it replaces:
+// `a` is the g_x product of the column matrix as launch_gemm_nt takes it for kind 0 (A = codes of G, Bm = codes of the
+// weight, K = out-features), a.C the image gradient [Nb, H, W, C].  launch_conv_pair: with the weight gradient's
+// product `b` in the same launch on 128 x 128 tiles (conv_pair_available: no other tile is asked for), its k split by
+// the plan (b.ws) and reduced behind it.
+bool conv_dx_ok(int O, const ConvShape &s, bool is_f32);   // the shape is taken that way
+hipError_t launch_conv_dx(const GemmArgs &a, const ConvShape &s, hipStream_t st);
+bool conv_pair_available();
+hipError_t launch_conv_pair(const GemmArgs &a, const ConvShape &s, int kindB, const GemmArgs &b, hipStream_t st);
+
 // K3 / K3q on the column matrix of X [Nb, H, W, C] without storing it: same outputs as launch_hla /
 // launch_hla_quant on launch_im2col's result, D = kh*kw*C.  Needs hla_conv_ok (C a multiple of the
 // 128 / B features a lane owns).

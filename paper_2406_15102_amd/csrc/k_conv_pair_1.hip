@@ -1,0 +1,10 @@
+#include "conv_pair_impl.hpp"
+
+namespace hlq {
+
+hipError_t launch_conv_pair_1(const ConvDxPlan &p, bool f32, const GemmDev &gb, bool partial, bool b_first, hipStream_t st)
+{
+    return f32 ? launch_conv_pair_k<true, 1>(p, gb, partial, b_first, st) : launch_conv_pair_k<false, 1>(p, gb, partial, b_first, st);
+}
+
+}  // namespace hlq

@@ -30,49 +30,6 @@ struct PairPlan {
     bool b_first;    // the g_w product's tiles are dispatched first
 };
 
-namespace {
-constexpr double kStepBig = 1.3, kPackedScale = 1.8, kStepSmallAlone = 0.6, kStepSmallShared = 0.9;
-constexpr double kFixedBig = 16.0, kFixedSmall = 6.5;
-constexpr double kOneStepSaves = 2.0;    // a tile of one step skips the pipeline (gemm_body.hpp)
-constexpr int kSplitChoices[] = {1, 2, 3, 4, 6, 8, 12, 16};
-
-struct TileClass {
-    double step, fixed;
-    int slots;   // tiles in flight on the chip
-};
-TileClass tile_class(bool big, bool mixed, double n)
-{
-    if (big) return {kStepBig, kFixedBig, 256};
-    if (mixed || n <= 256.0) return {kStepSmallAlone, kFixedSmall, 256};
-    return {kStepSmallShared, kFixedSmall, 512};
-}
-
-// nA tiles of tA on mA slots, then nB tiles of tB on mB slots (the same silicon, possibly cut finer)
-double pair_makespan(double nA, double tA, int mA, double nB, double tB, int mB)
-{
-    const double qA = __builtin_floor(nA / mA), rA = nA - qA * mA;
-    const double T1 = qA * tA, T2 = rA > 0 ? T1 + tA : T1;
-    const double g2 = __builtin_round(rA / mA * mB), g1 = mB - g2;      // slots free at T2 / at T1
-    // candidate finishing times: T1 + k tB and T2 + k tB; the first with enough capacity
-    double best = 1e30;
-    for (int grp = 0; grp < 2; ++grp) {
-        const double base = grp ? T2 : T1;
-        const double gs = grp ? g2 : g1;
-        if (gs <= 0) continue;
-        // smallest k with g1 floor((T - T1)/tB) + g2 floor((T - T2)/tB) >= nB at T = base + k tB
-        double lo = grp ? 0 : 1, hi = __builtin_ceil(nB / gs) + 1;
-        while (lo < hi) {
-            const double k = __builtin_floor((lo + hi) / 2), T = base + k * tB;
-            const double c1 = g1 * __builtin_fmax(0.0, __builtin_floor((T - T1) / tB + 1e-9));
-            const double c2 = g2 * __builtin_fmax(0.0, __builtin_floor((T - T2) / tB + 1e-9));
-            if (c1 + c2 >= nB) hi = k; else lo = k + 1;
-        }
-        const double T = base + lo * tB;
-        if (T < best) best = T;
-    }
-    return best > T2 ? best : T2;
-}
-}  // namespace
 
 static PairPlan plan_pair(const GemmArgs &a, int kindA, const GemmArgs &b, int kindB, size_t ws_bytes)
 {

@@ -1,0 +1,69 @@
+"""The image gradient taken straight from the codes (product and fold in one) against the calls it stands for: the
+quantisers, the product that writes the column gradient, and its fold.  Same bits, for every shape of the kernel's
+tile and every number of bytes a step takes of a row of codes, at sizes that end inside a tile or a step."""
+import pytest
+import torch
+
+import paper_2406_15102_amd as hlq
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# Nb, H, W, C, O, k, stride, pad, dilation
+CASES = [
+    (32, 32, 33, 128, 32, 3, 1, 1, 1),     # 128 x 128 tiles, ragged pixels, 32 bytes a step
+    (32, 32, 32, 124, 48, 4, 1, 1, 1),     # 64 bytes a step, 16 of them past the end; channels past the end
+    (32, 32, 32, 256, 144, 3, 1, 0, 1),    # 128 bytes a step, a ragged second one; no padding
+    (48, 37, 40, 56, 16, 3, 1, 1, 1),      # 256 x 64, rows of codes half a step long
+    (48, 37, 40, 44, 80, 4, 1, 1, 1),      # 256 x 64, two steps of 64 bytes, the second ragged
+    (32, 28, 28, 72, 272, 3, 1, 2, 1),     # 128 x 64, padding past the image, three steps of 128 bytes
+    (16, 16, 16, 40, 32, 3, 1, 1, 1),      # 64 x 64
+    (16, 24, 20, 104, 64, 3, 1, 2, 2),     # dilated
+    (32, 33, 31, 64, 64, 3, 2, 1, 1),      # classes of pixels of different sizes
+    (32, 30, 30, 72, 48, 5, 3, 2, 2),      # stride and dilation without a common factor
+    (32, 30, 30, 64, 96, 4, 2, 1, 2),      # ... and with one: half of the classes have no tap
+    (16, 40, 36, 64, 128, 3, 1, 1, 1),
+]
+
+
+def _geom(c):
+    Nb, H, W, C, O, k, s, p, d = c
+    return hlq.hlq_conv_geom(Nb=Nb, H=H, W=W, C=C, O=O, kh=k, kw=k, stride_h=s, stride_w=s, pad_h=p, pad_w=p, dil_h=d, dil_w=d)
+
+
+@pytest.mark.parametrize("c", CASES)
+@pytest.mark.parametrize("dtype,flags", [(torch.bfloat16, 0), (torch.float32, 0), (torch.bfloat16, hlq.HLQ_FLAG_GX_8BIT),
+                                         (torch.float32, hlq.HLQ_FLAG_GX_UNPACKED | hlq.HLQ_FLAG_SEPARATE_PRODUCTS)])
+def test_image_gradient_is_the_fold_of_the_column_gradient(c, dtype, flags):
+    Nb, H, W, C, O, k, s, p, d = c
+    B, r, seed = 16, 8, 3
+    geom = _geom(c)
+    Ho, Wo, N, I = hlq.hlq_conv_sizes(geom)
+    while N % B or N // B * r % 8 or I % 8:
+        Nb *= 2
+        assert Nb <= 1024
+        geom = _geom((Nb,) + c[1:])
+        Ho, Wo, N, I = hlq.hlq_conv_sizes(geom)
+    print("conv", c, dtype, flags, "N", N, "I", I, flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    X, Wt, G = (torch.randn(shape, generator=gen, device=DEV).mul_(scale).to(dtype)
+                for shape, scale in (((Nb, H, W, C), 1.0), ((O, k, k, C), 0.02), ((Nb, Ho, Wo, O), 1e-3)))
+    bits = hlq.HLQ_BITS_8 if flags & hlq.HLQ_FLAG_GX_8BIT else hlq.HLQ_BITS_4
+    Gq, Wq = torch.empty((N, O), dtype=torch.int8, device=DEV), torch.empty((I, O), dtype=torch.int8, device=DEV)
+    sG, sW = torch.empty(N, dtype=torch.float32, device=DEV), torch.empty(I, dtype=torch.float32, device=DEV)
+    ws = torch.empty(hlq.hlq_quantize_w_workspace_bytes(O, I), dtype=torch.uint8, device=DEV)
+    hlq.hlq_quantize_g(G.reshape(N, O), B, seed, Gq, sG, None, bits)
+    hlq.hlq_quantize_w(Wt.reshape(O, I), B, seed, Wq, sW, ws, None, bits)
+    cols = torch.empty((N, I), dtype=dtype, device=DEV)
+    hlq.hlq_int8_gemm_nt(Gq, Wq, sG, sW, 1.0 / B, cols)
+    want = torch.full_like(X, 7.0)
+    hlq.hlq_col2im(cols, geom, want)
+    memory = torch.full((hlq.hlq_conv_workspace_bytes(geom, B, r, hlq.binding._dt(G), flags),), 0xFF, dtype=torch.uint8, device=DEV)
+    dX, dW, only = torch.full_like(X, 3.0), torch.empty_like(Wt), torch.full_like(X, 5.0)
+    hlq.hlq_conv2d_backward(G, X, Wt, geom, B, r, seed, flags, dX, dW, memory)
+    hlq.hlq_conv2d_backward(G, None, Wt, geom, B, r, seed, flags, only, None, memory)
+    assert torch.equal(dX, want) and torch.equal(only, want)
+    # the column gradient's place in the scratch (the first thing in it where the image is projected straight) is untouched
+    if C % 8 == 0:
+        assert bool((memory[:cols.numel() * cols.element_size()] == 0xFF).all())
+    assert torch.isfinite(dW.float()).all()
