@@ -87,7 +87,8 @@ size_t hlq_workspace_bytes(int64_t N, int64_t d_in, int64_t d_out, int B, int r,
  *       0 (default): each stage's workgroups keep their own index range.
  *   HLQ_OPT_DIRECT_TO_LDS  1 (default): 256 x 256 tiles of the matrix products whose operand rows are
  *       whole 128-byte steps (at least four per workgroup) load their operands from global memory
- *       straight into LDS;  0: every tile stages them through registers.
+ *       straight into LDS, and so do the 128 x 128 tiles of two products in one launch that has more of
+ *       them than compute units;  0: every tile stages them through registers.
  *   HLQ_OPT_TAIL_TILES  1 (default): a product on 256 x 256 tiles that loads straight into LDS and would
  *       leave most compute units idle in its last round hands its last rows to tiles of 192 x 256, which
  *       shortens that round by a quarter (the g_w product when it closes the launch of both products, or a

@@ -1,4 +1,5 @@
-// Device body of K2 / K4 for 256 x 256 (or 192 x 256) tiles and rows of whole 128-byte steps, with the operands
+// Device body of K2 / K4 for 256 x 256 (or 192 x 256) tiles and rows of whole 128-byte steps, and for 128 x 128
+// tiles and any rows, with the operands
 // streamed from global memory straight into LDS and multiplied by 16 x 16 MFMAs (arXiv 2406.15102,
 // Sec. 6.1: stages 5-6 of the g_x list, stage 5 of the g_w list; the same products, tile, LDS layout
 // and bits as gemm_body.hpp).
@@ -33,6 +34,15 @@
 // work), serves the last rows of a product whose 256-row tiles would leave most compute units idle in
 // their last round: 11008 x 4096 is 688 tiles of 256 x 256, 2.69 rounds on 256 compute units; with the
 // last 2816 rows in 192-row tiles it is 512 + 240 tiles, two rounds and one of three-quarter tiles.
+//
+// A third, 128 x 128 (4 x 4 accumulators per wavefront, ring units of 16 KB: 80 KB, two workgroups to a compute unit),
+// serves the pairs of products whose 256-tiles would not fill the chip.  A step reads 64 KB of fragments for 16 x 16 x 2
+// MFMAs a tile, so LDS bounds it, and what it saves over the register-staged body is the 32 KB that the ds_writes
+// put there a second time: 32 MFMAs a step and wavefront hide fewer cycles than 128, hence the second workgroup.  Both
+// products of a pass alone, register-staged -> this: 4096 x 2048 x 5632 91.0 -> 83.8 us, 8192 x 2048 x 2048 72.4 -> 69.1,
+// 4096 x 1024 x 4096 29.4 -> 26.6, 2048 x 2048 x 2048 21.3 -> 20.0; gemm_dl128_ok says where it is taken.
+// RAGGED (128 x 128 only): the last step of a row need not be whole.  It is multiplied behind the loop, chunks past
+// the end of a row cleared in registers, so the loop of whole steps carries one subtraction a load for it.
 #pragma once
 #include "gemm_common.hpp"
 
@@ -42,6 +52,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 
 constexpr size_t kGemmDlLdsBytes = 5u * 256u * 128u;   // the ring; the epilogue's slabs reuse its start
+constexpr size_t kGemmDl128LdsBytes = 5u * 128u * 128u;   // of a 128 x 128 tile: two to a compute unit
 
 // 16 x 16 MFMAs.  The MFMA's A operand is fed from Bm and its B operand from A, which leaves a lane with
 // C[m][n .. n + 3], m = 16 i + lane % 16, n = 16 j + 4 (lane / 16), of accumulator (i, j).
@@ -49,8 +60,8 @@ constexpr size_t kGemmDlLdsBytes = 5u * 256u * 128u;   // the ring; the epilogue
 // compiler is free to give an MFMA of this size a destination other than its addend, and with all 256
 // accumulator registers in use it then moves dozens of accumulators around at the top of every k step.
 // What the compiler's hazard handling no longer sees is kept apart by construction: an accumulator is
-// touched by one MFMA in 64, operands written by vector instructions (the widened codes) are written a
-// sub-step before they are multiplied, and the epilogue waits out the last MFMAs before it reads.
+// touched by one MFMA in 16 or more, operands written by vector instructions (the widened codes) are written a
+// sub-step before they are multiplied (behind s_nops where no sub-step lies between), and the epilogue waits out the last MFMAs before it reads.
 template <int KIND> struct Mma16;
 template <> struct Mma16<0> {
     typedef v4i acc_t;
@@ -85,8 +96,8 @@ template <> struct Mma16<2> : Mma16<0> {
 };
 
 // raw 32-bit accumulators of the 16 x 16 layout (parity export, split-k partials): direct 16-byte stores
-template <int KIND, int NBM, bool GUARD>
-__device__ __forceinline__ void store_raw16(typename Mma16<KIND>::acc_t (&acc)[NBM][8], int32_t *out, int M, int N, int wm0,
+template <int KIND, int NBM, int NB, bool GUARD>
+__device__ __forceinline__ void store_raw16(typename Mma16<KIND>::acc_t (&acc)[NBM][NB], int32_t *out, int M, int N, int wm0,
                                             int wn0, int lane)
 {
     const int fr = lane & 15, fq = lane >> 4;
@@ -95,7 +106,7 @@ __device__ __forceinline__ void store_raw16(typename Mma16<KIND>::acc_t (&acc)[N
         const int m = wm0 + i * 16 + fr;
         int32_t *row = out + static_cast<int64_t>(m) * N + wn0 + fq * 4;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NB; ++j) {
             if (!GUARD || (m < M && wn0 + j * 16 + fq * 4 < N)) {
                 const auto e0 = acc[i][j][0], e1 = acc[i][j][1], e2 = acc[i][j][2], e3 = acc[i][j][3];
                 v4i raw = {Mma<KIND>::raw(e0), Mma<KIND>::raw(e1), Mma<KIND>::raw(e2), Mma<KIND>::raw(e3)};
@@ -107,29 +118,29 @@ __device__ __forceinline__ void store_raw16(typename Mma16<KIND>::acc_t (&acc)[N
 
 // C = alpha * sA[m] * sB[n] * acc for the 16 x 16 layout, the arithmetic of store_scaled value for value;
 // staged per 16-row group through LDS so that global stores are 16-byte, row-contiguous pieces.
-template <int KIND, int NBM, bool F32, bool GUARD>
-__device__ __forceinline__ void store_scaled16(typename Mma16<KIND>::acc_t (&acc)[NBM][8], void *Cout, int M, int N,
+template <int KIND, int NBM, int NB, bool F32, bool GUARD>
+__device__ __forceinline__ void store_scaled16(typename Mma16<KIND>::acc_t (&acc)[NBM][NB], void *Cout, int M, int N,
                                                const float *sA, const float *sB, float alpha, int wm0, int wn0, int lane,
                                                char *slab)
 {
-    constexpr int PITCH = 128 * (F32 ? 4 : 2) + 16;
+    constexpr int PITCH = 16 * NB * (F32 ? 4 : 2) + 16;
     constexpr int EPL = F32 ? 4 : 8;       // elements per 16-byte piece
-    constexpr int LPR = 128 / EPL;         // lanes per row
+    constexpr int LPR = 16 * NB / EPL;         // lanes per row
     constexpr int RPI = 64 / LPR;          // rows per store instruction
     const int fr = lane & 15, fq = lane >> 4;
-    f32x4 cs[8];
+    f32x4 cs[NB];
     if (KIND == 1) {
         // unused
     } else if (sB) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NB; ++j) {
             int n = wn0 + j * 16 + fq * 4;
             if (GUARD) n = n < N ? n : 0;
             cs[j] = *reinterpret_cast<const f32x4 *>(sB + n) * alpha;
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) cs[j] = f32x4{alpha, alpha, alpha, alpha};
+        for (int j = 0; j < NB; ++j) cs[j] = f32x4{alpha, alpha, alpha, alpha};
     }
     float sa[NBM];
 #pragma unroll
@@ -144,7 +155,7 @@ __device__ __forceinline__ void store_scaled16(typename Mma16<KIND>::acc_t (&acc
 #pragma unroll
     for (int i = 0; i < NBM; ++i) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NB; ++j) {
             f32x4 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -187,18 +198,20 @@ __device__ __forceinline__ void store_scaled16(typename Mma16<KIND>::acc_t (&acc
 }
 
 // OUT as in gemm_tile; `bid`: index of the workgroup among those of this product.
-// Requires g.Kb % 128 == 0 and tiles of 32 NBM rows x 256 columns, NBM = 8 or 6 (g.tiles_m, g.tiles_n counted
-// in such tiles; the 192-row tile is not written for packed codes).
-template <int KIND, int NBM, int OUT>
+// Requires tiles of 32 NBM rows x 32 NB columns, NBM = 8 or 6 with NB = 8, or both 4 (g.tiles_m, g.tiles_n counted
+// in such tiles; the 192-row tile is not written for packed codes), at least two whole steps a workgroup, and
+// g.Kb % 128 == 0 unless RAGGED (then g.Kb % 16 == 0).
+template <int KIND, int NBM, int OUT, int NB = 8, bool RAGGED = false>
 __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 {
-    constexpr int BT = 256, BTM = 32 * NBM, GROUP = 4, NB = 8;
+    constexpr int BT = 32 * NB, BTM = 32 * NBM, GROUP = 4;
     constexpr bool PACKED = KIND == 2;
-    static_assert(NBM == 8 || (NBM == 6 && !PACKED), "tiles of 256 x 256, or 192 x 256 for byte and bf16 operands");
+    static_assert((NB == 8 && (NBM == 8 || (NBM == 6 && !PACKED)) && !RAGGED) || (NB == 4 && NBM == 4),
+                  "tiles of 256 x 256, of 192 x 256 for byte and bf16 operands, or of 128 x 128");
     constexpr int NS = PACKED ? 4 : 2;            // sub-steps per step: 32 B of packed codes, 64 B otherwise
     constexpr int SLOTS = NBM * NB;               // MFMAs of a sub-step, one per accumulator
     constexpr int NR = NBM + NB;                  // fragments of a sub-step
-    constexpr uint32_t UNIT = BT * 128u;          // one operand's rows of one step: 32 KB
+    constexpr uint32_t UNIT = BT * 128u;          // one operand's rows of one step: 32 or 16 KB
     constexpr uint32_t RING = 5u * UNIT;
     extern __shared__ u32x4 lds[];
     char *const ldsb = reinterpret_cast<char *>(lds);
@@ -234,31 +247,41 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     const char *baseB = g.Bm + static_cast<int64_t>(n0) * g.Kb;
     const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(baseA), 0, 0x7FFFFFFF, 0x00020000);
     const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(baseB), 0, 0x7FFFFFFF, 0x00020000);
-    uint32_t offa[NBM], offb[8];
+    uint32_t offa[NBM], offb[NB];
     {
         const int rb = lane >> 3, slot = lane & 7;
         const uint32_t c16 = static_cast<uint32_t>(slot ^ rb ^ (wave & 1)) * 16u;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NB; ++j) {
             const int row = 8 * (4 * j + wave) + rb;
             if (j < NBM) offa[j < NBM ? j : 0] = static_cast<uint32_t>(m0 + row < g.M ? row : 0) * static_cast<uint32_t>(g.Kb) + c16;
             offb[j] = static_cast<uint32_t>(n0 + row < g.N ? row : 0) * static_cast<uint32_t>(g.Kb) + c16;
         }
     }
-    const int nk_all = g.Kb / 128;
+    const int nk_all = RAGGED ? (g.Kb + 127) / 128 : g.Kb / 128;
     const int split = bid / (g.tiles_m * g.tiles_n);
     const int kbeg = static_cast<int>(static_cast<int64_t>(nk_all) * split / g.splits);
-    const int nk = static_cast<int>(static_cast<int64_t>(nk_all) * (split + 1) / g.splits) - kbeg;
+    // RAGGED: bytes of a last step that is not whole, where this workgroup multiplies it (0: it does not).  The lanes
+    // whose chunk lies beyond them load the row's chunk 0 of that step instead; its products are masked out.
+    const int rag = RAGGED && split + 1 == g.splits ? g.Kb % 128 : 0;
+    const int nk = static_cast<int>(static_cast<int64_t>(nk_all) * (split + 1) / g.splits) - kbeg - (rag ? 1 : 0);   // whole steps
+    const int last = nk - (rag ? 0 : 1);
+    uint32_t back = 0;
+    if (RAGGED) {
+        const uint32_t c16 = static_cast<uint32_t>((lane & 7) ^ (lane >> 3) ^ (wave & 1)) * 16u;
+        back = rag && c16 >= static_cast<uint32_t>(rag) ? c16 : 0u;
+    }
 
     // instruction J of operand OP (0 = A, 1 = Bm) of step KT into ring unit UNIT_.  Past the end, steps are
     // clamped to the last one: loaded again into a free unit, never multiplied.
 #define HLQD_LOAD_ONE(KT, OP, J, UNIT_)                                                                       \
     {                                                                                                         \
-        const int kt_ = (KT) < nk ? (KT) : nk - 1;                                                            \
+        const int kt_ = (KT) < last ? (KT) : last;                                                           \
         const int kuni = (kbeg + kt_) * 128;      /* wave-uniform: lives in an SGPR */                        \
         const uint32_t dst = static_cast<uint32_t>(UNIT_) * UNIT + static_cast<uint32_t>(wave) * 1024u + (J) * 4096u; \
-        if ((OP) == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void_t *)(ldsb + dst), 16, offa[J], kuni, 0, 0); \
-        else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_void_t *)(ldsb + dst), 16, offb[J], kuni, 0, 0); \
+        const uint32_t back_ = RAGGED && kt_ == nk ? back : 0u;                                               \
+        if ((OP) == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, (lds_void_t *)(ldsb + dst), 16, offa[J] - back_, kuni, 0, 0); \
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, (lds_void_t *)(ldsb + dst), 16, offb[J] - back_, kuni, 0, 0); \
     }
 
     // ---- fragment reads: one per-lane register per (operand, sub-step), holding the ring position ----
@@ -271,7 +294,7 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
         const int chunk = PACKED ? 2 * s + (fq >> 1) : 4 * s + fq;
         const uint32_t half = PACKED ? static_cast<uint32_t>(fq & 1) * 8u : 0u;
         rdA[s] = lds_chunk<8>(wave_m * (16 * NBM) + fr, chunk) * 16u + half;
-        rdB[s] = UNIT + lds_chunk<8>(wave_n * 128 + fr, chunk) * 16u + half;
+        rdB[s] = UNIT + lds_chunk<8>(wave_n * (16 * NB) + fr, chunk) * 16u + half;
     }
     // the reads of a step are done: the read position of sub-step S2 (A or Bm) moves on two units, mod the ring
 #define HLQD_NEXT_UNIT(S2, OP)                                                                                \
@@ -312,11 +335,11 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 #pragma unroll
     for (int j = 0; j < NBM; ++j) HLQD_LOAD_ONE(0, 0, j, 0)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) HLQD_LOAD_ONE(0, 1, j, 1)
+    for (int j = 0; j < NB; ++j) HLQD_LOAD_ONE(0, 1, j, 1)
 #pragma unroll
     for (int j = 0; j < NBM; ++j) HLQD_LOAD_ONE(1, 0, j, 2)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) HLQD_LOAD_ONE(1, 1, j, 3)
+    for (int j = 0; j < NB; ++j) HLQD_LOAD_ONE(1, 1, j, 3)
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0070 | (NR & 15) | ((NR >> 4) << 14));   // vmcnt(NR): step 0 has landed
     __builtin_amdgcn_s_barrier();
@@ -363,7 +386,34 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
                     if (q < 2 * NR && !(q & 1)) HLQD_READ_ONE(cur ^ 1, ns, q >> 1)
                     if (s < NS - 1 && (s * SLOTS + q) % APER == APER - 3) HLQD_LOAD_ONE(kt + 2, 0, (s * SLOTS + q) / APER, ua)
                     if (s == NS - 1 && q < 4 * NB && (q & 3) == 1) HLQD_LOAD_ONE(kt + 2, 1, q >> 2, u)
-                    if (s == NS - 2 && q >= 4 * NB && q < 4 * NB + 2 * NS) HLQD_NEXT_UNIT((q - 4 * NB) >> 1, q & 1)
+                    if constexpr (NB == 8) {
+                        if (s == NS - 2 && q >= 4 * NB && q < 4 * NB + 2 * NS) HLQD_NEXT_UNIT((q - 4 * NB) >> 1, q & 1)
+                    } else {
+                        // 16 slots: each position in the sub-step behind the one that read from it
+                        if (q == 3 || q == 7) HLQD_NEXT_UNIT(s, q == 7)
+                    }
+                    Mma16<KIND>::mma(fb[cur][q % NB], fa[cur][q / NB], acc[q / NB][q % NB]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else if constexpr (NB == 4) {
+                // packed codes, 16 slots: the 8 fragments in slots 0-3, the 24 parts of their widening in slots 6-15
+                // (three instructions a MFMA; the wavefront of the other workgroup on the SIMD issues beside them)
+#pragma unroll
+                for (int q = 0; q < SLOTS; ++q) {
+                    if (q < 4) {
+                        HLQD_READ_ONE(cur ^ 1, ns, 2 * q)
+                        HLQD_READ_ONE(cur ^ 1, ns, 2 * q + 1)
+                    }
+                    if (s == 0 && (q == 4 || q == 11)) HLQD_LOAD_ONE(kt + 2, 0, q == 11, ua)
+                    if ((s == 1 || s == 2) && q == 4) HLQD_LOAD_ONE(kt + 2, 0, s + 1, ua)
+                    if (s == 3 && (q & 3) == 1) HLQD_LOAD_ONE(kt + 2, 1, q >> 2, u)
+                    if (s < 3 && (q == 5 || q == 12)) HLQD_NEXT_UNIT(ns, q == 12)
+                    if (s == 0 && (q == 13 || q == 14)) HLQD_NEXT_UNIT(0, q == 14)
+                    if (q >= 6) {
+                        const int e0 = q < 10 ? 3 * (q - 6) : 12 + 2 * (q - 10), ne = q < 10 ? 3 : 2;
+#pragma unroll
+                        for (int e = e0; e < e0 + ne; ++e) HLQD_EXPAND(cur ^ 1, e / 3, e % 3)
+                    }
                     Mma16<KIND>::mma(fb[cur][q % NB], fa[cur][q / NB], acc[q / NB][q % NB]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -407,6 +457,41 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
         }
         u = u + 2 >= 5 ? u - 3 : u + 2;
     }
+    if constexpr (RAGGED) {
+        // the sub-steps of the ragged step, with what lies past the end of a row cleared in either operand (not in one
+        // alone: infinities).  It landed before the last barrier, and its first fragments have been read.
+        constexpr int SUB = 128 / NS;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (s * SUB < rag) {
+                if (s > 0) {
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) HLQD_READ_ONE(0, s, q)
+                    if constexpr (PACKED) {
+#pragma unroll
+                        for (int q = 0; q < NR; ++q)
+#pragma unroll
+                            for (int p = 0; p < 3; ++p) HLQD_EXPAND(0, q, p)
+                    }
+                }
+                const bool in = s * SUB + fq * (SUB / 4) < rag;
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    u32x4 &x = q < NB ? fb[0][q < NB ? q : 0] : fa[0][q < NB ? 0 : q - NB];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = in ? x[e] : 0u;
+                }
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    u32x4 &x = q < NB ? fb[0][q < NB ? q : 0] : fa[0][q < NB ? 0 : q - NB];
+                    asm volatile("s_nop 1" : "+v"(x));      // computed two instructions ahead of the MFMAs
+                }
+#pragma unroll
+                for (int q = 0; q < SLOTS; ++q) Mma16<KIND>::mma(fb[0][q % NB], fa[0][q / NB], acc[q / NB][q % NB]);
+                asm volatile("s_nop 15");                   // and read by them before they are written again
+            }
+        }
+    }
 #undef HLQD_LOAD_ONE
 #undef HLQD_READ_ONE
 #undef HLQD_NEXT_UNIT
@@ -419,19 +504,19 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0070);   // every load has landed: LDS is free for staging C
     __syncthreads();
-    const int wm0 = m0 + wave_m * (16 * NBM), wn0 = n0 + wave_n * 128;
+    const int wm0 = m0 + wave_m * (16 * NBM), wn0 = n0 + wave_n * (16 * NB);
     char *slab = ldsb + wave * (16 * (128 * 4 + 16));   // wavefront-private, one 16-row group
     const bool interior = (m0 + BTM <= g.M) && (n0 + BT <= g.N) && ((g.N & 7) == 0);
     if (OUT == 2) {
-        if (interior) store_raw16<KIND, NBM, false>(acc, g.acc, g.M, g.N, wm0, wn0, lane);
-        else store_raw16<KIND, NBM, true>(acc, g.acc, g.M, g.N, wm0, wn0, lane);
+        if (interior) store_raw16<KIND, NBM, NB, false>(acc, g.acc, g.M, g.N, wm0, wn0, lane);
+        else store_raw16<KIND, NBM, NB, true>(acc, g.acc, g.M, g.N, wm0, wn0, lane);
     } else if (OUT == 3) {
         int32_t *part = g.partial + static_cast<int64_t>(split) * g.M * g.N;
-        if (interior) store_raw16<KIND, NBM, false>(acc, part, g.M, g.N, wm0, wn0, lane);
-        else store_raw16<KIND, NBM, true>(acc, part, g.M, g.N, wm0, wn0, lane);
+        if (interior) store_raw16<KIND, NBM, NB, false>(acc, part, g.M, g.N, wm0, wn0, lane);
+        else store_raw16<KIND, NBM, NB, true>(acc, part, g.M, g.N, wm0, wn0, lane);
     } else {
-        if (interior) store_scaled16<KIND, NBM, OUT == 1, false>(acc, g.C, g.M, g.N, g.sA, g.sB, g.alpha, wm0, wn0, lane, slab);
-        else store_scaled16<KIND, NBM, OUT == 1, true>(acc, g.C, g.M, g.N, g.sA, g.sB, g.alpha, wm0, wn0, lane, slab);
+        if (interior) store_scaled16<KIND, NBM, NB, OUT == 1, false>(acc, g.C, g.M, g.N, g.sA, g.sB, g.alpha, wm0, wn0, lane, slab);
+        else store_scaled16<KIND, NBM, NB, OUT == 1, true>(acc, g.C, g.M, g.N, g.sA, g.sB, g.alpha, wm0, wn0, lane, slab);
     }
 }
 

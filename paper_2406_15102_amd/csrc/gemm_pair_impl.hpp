@@ -9,8 +9,8 @@
 // the k split of the g_w product are planned for the pair, not for each product alone.
 //
 // One translation unit per pair of operand kinds (k_gemm_pair_*.hip instantiate launch_pair_kinds
-// below: 100 kernels each -- two tile sizes and whole or ragged k steps per product, the 256-tile also with
-// its operands loaded straight into LDS, bf16 or fp32
+// below: 116 kernels each -- two tile sizes and whole or ragged k steps per product, the 256-tile of whole steps and
+// two 128-tiles also with their operands loaded straight into LDS, bf16 or fp32
 // output, direct output or split-k partials for the g_w product); k_gemm_pair.hip plans and dispatches.
 #pragma once
 #include "gemm_body.hpp"
@@ -20,21 +20,21 @@
 namespace hlq {
 
 // MODE: 0 = rows of whole 128-byte steps, 1 = a ragged last step, 2 = whole steps loaded straight into
-// LDS (gemm_dl_body.hpp; 256-tiles only)
+// LDS (gemm_dl_body.hpp), 3 = the same with a ragged last step (128-tiles only)
 template <int KIND_, int W_, int MODE_, int OUT_> struct TileCfg {
     static constexpr int KIND = KIND_, W = W_, OUT = OUT_, MODE = MODE_;
-    static constexpr size_t LDS = MODE_ == 2 ? kGemmDlLdsBytes : gemm_lds_bytes(W_, W_, 8);
-    static_assert(MODE_ != 2 || W_ == 4, "the direct-to-LDS body is written for 256 x 256 tiles");
+    static constexpr size_t LDS = MODE_ >= 2 ? (W_ == 4 ? kGemmDlLdsBytes : kGemmDl128LdsBytes) : gemm_lds_bytes(W_, W_, 8);
+    static_assert(MODE_ < 3 || W_ == 2, "a ragged last step straight into LDS: 128 x 128 tiles");
 };
 
 template <class C>
 __device__ __forceinline__ void pair_tile(const GemmDev &g, int idx)
 {
-    if constexpr (C::MODE == 2) gemm_tile_dl<C::KIND, 8, C::OUT>(g, idx);
+    if constexpr (C::MODE >= 2) gemm_tile_dl<C::KIND, 2 * C::W, C::OUT, 2 * C::W, C::MODE == 3>(g, idx);
     else gemm_tile<C::KIND, C::W, C::W, 8, C::MODE == 1, C::OUT>(g, idx);
 }
 // whether a product of this configuration may hand its last rows to 192-row tiles (gemm_dl_body.hpp)
-template <class C> constexpr bool pair_has_tail() { return C::MODE == 2 && C::KIND != 2 && (C::OUT == 0 || C::OUT == 1); }
+template <class C> constexpr bool pair_has_tail() { return C::MODE == 2 && C::W == 4 && C::KIND != 2 && (C::OUT == 0 || C::OUT == 1); }
 template <class C>
 __device__ __forceinline__ void pair_tail_tile(const GemmDev &g, int idx)
 {
@@ -98,11 +98,15 @@ template <class CA, int KB>
 static hipError_t launch_pair_a(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigB, int modeB, int outB,
                                 bool b_first, hipStream_t st)
 {
-    if (bigB) {
-        if (modeB == 2) return launch_pair_b<CA, KB, 4, 2>(ga, gb, gbt, outB, b_first, st);
-        return modeB ? launch_pair_b<CA, KB, 4, 1>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 4, 0>(ga, gb, gbt, outB, b_first, st);
+    if constexpr (CA::W == 2 && CA::MODE >= 2) {      // 128-tiles straight into LDS: both products or neither
+        return modeB == 3 ? launch_pair_b<CA, KB, 2, 3>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 2, 2>(ga, gb, gbt, outB, b_first, st);
+    } else {
+        if (bigB) {
+            if (modeB == 2) return launch_pair_b<CA, KB, 4, 2>(ga, gb, gbt, outB, b_first, st);
+            return modeB ? launch_pair_b<CA, KB, 4, 1>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 4, 0>(ga, gb, gbt, outB, b_first, st);
+        }
+        return modeB ? launch_pair_b<CA, KB, 2, 1>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 2, 0>(ga, gb, gbt, outB, b_first, st);
     }
-    return modeB ? launch_pair_b<CA, KB, 2, 1>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 2, 0>(ga, gb, gbt, outB, b_first, st);
 }
 
 template <int KA, int KB, int WA, int MODEA>
@@ -118,13 +122,21 @@ template <int KA, int KB>
 static hipError_t launch_pair_kinds(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB,
                                     int outB, bool b_first, hipStream_t st)
 {
-    const int modeA = ga.Kb % 128 != 0 ? 1 : (bigA && gemm_dl_ok(ga.Kb, ga.splits) ? 2 : 0);
-    const int modeB = gb.Kb % 128 != 0 ? 1 : (bigB && gemm_dl_ok(gb.Kb, gb.splits) ? 2 : 0);
+    const bool dl128 = !bigA && !bigB && gemm_dl128_ok(ga, KA == 2 ? kPackedScale : 1.0, gb);
+    const auto mode = [dl128](const GemmDev &g, bool big) {
+        const bool whole = g.Kb % 128 == 0;
+        if (dl128) return whole ? 2 : 3;
+        return whole ? (big && gemm_dl_ok(g.Kb, g.splits) ? 2 : 0) : 1;
+    };
+    const int modeA = mode(ga, bigA), modeB = mode(gb, bigB);
     if (bigA) {
         if (modeA == 2) return launch_pair_o<KA, KB, 4, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
         return modeA ? launch_pair_o<KA, KB, 4, 1>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st)
                      : launch_pair_o<KA, KB, 4, 0>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
     }
+    if (modeA >= 2)
+        return modeA == 3 ? launch_pair_o<KA, KB, 2, 3>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st)
+                          : launch_pair_o<KA, KB, 2, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
     return modeA ? launch_pair_o<KA, KB, 2, 1>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st)
                  : launch_pair_o<KA, KB, 2, 0>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
 }

@@ -33,6 +33,8 @@ int gemm_plan_forced_splits(int nk, double mn, size_t ws_bytes, bool allow_split
 // loads its operands straight into LDS (gemm_dl_body.hpp)
 bool gemm_dl_ok(int Kb, int splits);
 void gemm_dl_enable(bool on);
+// the same for two products on 128-tiles in one launch; scale_a: cost of a step of `a` in steps of `b`
+bool gemm_dl128_ok(const GemmDev &a, double scale_a, const GemmDev &b);
 
 // Rows at the end of a product of M x N in 256 x 256 tiles that are better served by 192-row tiles
 // (gemm_dl_body.hpp), 0 = none: when `before` tiles of the same launch are dispatched ahead of it and its

@@ -19,6 +19,22 @@ bool gemm_dl_ok(int Kb, int splits)
     return g_dl_enabled.load() != 0 && Kb % 128 == 0 && (Kb / 128) / splits >= 4;
 }
 
+// Where the work of the launch, spread over two tiles a compute unit, is about as long as its longest tile or longer:
+// most of the time two tiles then share a unit, and these step faster than the register-staged ones.  A tile that is
+// alone, or that the whole launch waits for, steps slower: its loads are 0.5-1.5 steps ahead instead of two, and its
+// one wavefront a SIMD waits out LDS.  Whole pass on changing inputs, register-staged -> this: 4096 x 2048 x 5632 in
+// fp32 (work 2.1 x the longest tile) 167.9 -> 158.3 us, 12608 x 768 x 3072 (0.53 x) 120.3 -> 125.6; products alone, 4 tiles
+// of 392 steps beside short ones (50176 x 432 x 96) 157 -> 180.
+bool gemm_dl128_ok(const GemmDev &a, double scale_a, const GemmDev &b)
+{
+    constexpr int kMinSteps = 2;
+    constexpr double kSlots = 512.0, kLeastRounds = 0.9;
+    const double steps_a = scale_a * (a.Kb / 128 / a.splits), steps_b = b.Kb / 128 / b.splits;
+    const double work = steps_a * a.tiles_m * a.tiles_n * a.splits + steps_b * b.tiles_m * b.tiles_n * b.splits;
+    return g_dl_enabled.load() != 0 && a.Kb / 128 / a.splits >= kMinSteps && b.Kb / 128 / b.splits >= kMinSteps &&
+           work >= kLeastRounds * kSlots * (steps_a > steps_b ? steps_a : steps_b);
+}
+
 // `gt`: the product's last rows in 192-row tiles (gt.tiles_m = 0: none), dispatched behind the n_main
 // workgroups of the 256-row tiles
 template <int KIND, int OUT>
