@@ -67,3 +67,39 @@ def test_image_gradient_is_the_fold_of_the_column_gradient(c, dtype, flags):
     if C % 8 == 0:
         assert bool((memory[:cols.numel() * cols.element_size()] == 0xFF).all())
     assert torch.isfinite(dW.float()).all()
+
+
+@pytest.mark.parametrize("c", [CASES[i] for i in (0, 2, 3, 5, 6, 7, 8, 11)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_weights_that_are_not_finite_stay_in_the_pixels_that_meet_them(c, dtype):
+    """An infinite weight makes its column's scale infinite.  A pixel that does not have that column's tap gets nothing
+    from it, not 0 * inf; one that has it gets what the fold of the column gradient gives, whatever the codes are."""
+    Nb, H, W, C, O, k, s, p, d = c
+    B, r, seed = 16, 8, 3
+    geom = _geom(c)
+    Ho, Wo, N, I = hlq.hlq_conv_sizes(geom)
+    while N % B:
+        Nb *= 2
+        geom = _geom((Nb,) + c[1:])
+        Ho, Wo, N, I = hlq.hlq_conv_sizes(geom)
+    print("conv", c, dtype, "N", N, "I", I, flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(12)
+    Wt, G = (torch.randn(shape, generator=gen, device=DEV).mul_(scale).to(dtype) for shape, scale in (((O, k, k, C), 0.02), ((Nb, Ho, Wo, O), 1e-3)))
+    Wt[1, 0, 0, 5] = float("inf")
+    Wt[2, k - 1, k - 1, C - 1] = -float("inf")
+    Wt[0, k // 2, 0, C // 2] = float("nan")
+    G[0, 0] = 0.0                                  # rows of codes whose scale is 0: 0 * inf where they are met
+    G[1, Ho - 1, Wo - 1, 3] = float("inf")
+    Gq, Wq = torch.empty((N, O), dtype=torch.int8, device=DEV), torch.empty((I, O), dtype=torch.int8, device=DEV)
+    sG, sW = torch.empty(N, dtype=torch.float32, device=DEV), torch.empty(I, dtype=torch.float32, device=DEV)
+    ws = torch.empty(hlq.hlq_quantize_w_workspace_bytes(O, I), dtype=torch.uint8, device=DEV)
+    hlq.hlq_quantize_g(G.reshape(N, O), B, seed, Gq, sG, None, hlq.HLQ_BITS_4)
+    hlq.hlq_quantize_w(Wt.reshape(O, I), B, seed, Wq, sW, ws, None, hlq.HLQ_BITS_4)
+    assert not torch.isfinite(sW).all() and float(sG[0]) == 0.0
+    cols = torch.empty((N, I), dtype=dtype, device=DEV)
+    hlq.hlq_int8_gemm_nt(Gq, Wq, sG, sW, 1.0 / B, cols)
+    want, dX = (torch.full((Nb, H, W, C), v, dtype=dtype, device=DEV) for v in (7.0, 3.0))
+    hlq.hlq_col2im(cols, geom, want)
+    hlq.hlq_conv2d_backward(G, None, Wt, geom, B, r, seed, 0, dX, None)
+    assert not torch.isfinite(want).all() and torch.isfinite(want).any()
+    assert torch.equal(dX.isnan(), want.isnan()) and torch.equal(dX.nan_to_num(nan=0.5), want.nan_to_num(nan=0.5))
