@@ -76,11 +76,13 @@ constexpr size_t conv_dx_lds(int form, int Kb, int taps)
            static_cast<size_t>(taps) * conv_dx_bn(form) * 4;
 }
 
-// One value of the image gradient, by the definition.
+// One value of the image gradient, by the definition.  `g`: the kernel's first argument, read from where the launch put it,
+// so that what only this needs is not in registers through the kernel's loop.
+typedef const __attribute__((address_space(4))) ConvDx ConvDxArg;
 template <bool F32>
-__device__ __forceinline__ float conv_dx_value(const ConvDx &g, int n, int h, int w, int c)
+__device__ __forceinline__ float conv_dx_value(const ConvDxArg &g, int n, int h, int w, int c)
 {
-    const ConvShape &s = g.s;
+    const auto &s = g.s;
     float sum = 0.0f;
     for (int ky = 0; ky < s.kh; ++ky) {
         const int hn = h + s.ph - ky * s.dh, ho = hn / s.sh;        // the output row that read this pixel
@@ -347,6 +349,8 @@ __device__ __forceinline__ void conv_dx_tile(const ConvDx &g, int bid)
         }
     }
     if (nans == nans) return;
+    ConvDxArg *arg = (ConvDxArg *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(arg));
     uint64_t again = 0;
 #pragma unroll
     for (int f = 0; f < FM; ++f)
@@ -361,7 +365,7 @@ __device__ __forceinline__ void conv_dx_tile(const ConvDx &g, int bid)
         const Pixel p = pixel(q);
         const int h = p.h * s.sh + hs, w = p.w * s.sw + ws;
         const int64_t at = (static_cast<int64_t>(p.n * s.H + h) * s.W + w) * s.C + c;
-        const float v = conv_dx_value<F32>(g, p.n, h, w, c);
+        const float v = conv_dx_value<F32>(*arg, p.n, h, w, c);
         if (F32) static_cast<float *>(g.dX)[at] = v;
         else static_cast<bf16_t *>(g.dX)[at] = static_cast<bf16_t>(pack_bf16(v, 0.0f) & 0xFFFFu);
     }
