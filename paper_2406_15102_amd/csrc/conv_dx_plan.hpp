@@ -86,4 +86,23 @@ static inline ConvDxPlan conv_dx_plan(const GemmArgs &a, const ConvShape &s)
     return p;
 }
 
+// Time of the launch that carries both products, us: the image gradient's blocks and nb tiles of the weight gradient of
+// `steps` k steps each.  Fitted to whole passes of 470 layers at every split in either order, on changing inputs: a
+// tile of the image gradient takes 3.95, `item` for RB codes of a tap, and `tap` for the sums of a tap; one of the
+// weight gradient 2.45 and 0.45 a step; where they have a compute unit to themselves, 0.86 and 0.68 of that.
+static inline double conv_pair_time(const ConvDxPlan &p, double nb, double steps, bool b_first)
+{
+    static const double item[4][3] = {{0.60, 0.65, 0.68}, {0.82, 0.40, 0.40}, {0.28, 0.40, 0.36}, {0.28, 0.12, 0.19}};
+    static const double tap[4] = {0.48, 0.48, 0.24, 0.12};
+    constexpr double kFixedA = 3.95, kFixedB = 2.45, kStepB = 0.45, kAloneA = 0.86, kAloneB = 0.68;
+    const ConvShape &s = p.g.s;
+    const int form = p.g.form, rb = conv_dx_rb(form, p.g.Kb);
+    const double taps = static_cast<double>(s.kh) * s.kw / (s.sh * s.sw);
+    const double a = taps * (((p.g.Kb + rb - 1) / rb) * item[form][rb / 64] + tap[form]), b = steps * kStepB;
+    const double ta = kFixedA + a, tb = kFixedB + b, all = p.blocks + nb;
+    if (all <= 256) return __builtin_fmax(kFixedA + a * kAloneA, kFixedB + b * kAloneB);
+    if (all <= 512) return ta < tb ? ta + (tb - ta) * kAloneB : tb + (ta - tb) * kAloneA;    // all resident
+    return b_first ? pair_makespan(nb, tb, 512, p.blocks, ta, 512) : pair_makespan(p.blocks, ta, 512, nb, tb, 512);
+}
+
 }  // namespace hlq

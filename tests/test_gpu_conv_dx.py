@@ -103,3 +103,37 @@ def test_weights_that_are_not_finite_stay_in_the_pixels_that_meet_them(c, dtype)
     hlq.hlq_conv2d_backward(G, None, Wt, geom, B, r, seed, 0, dX, None)
     assert not torch.isfinite(want).all() and torch.isfinite(want).any()
     assert torch.equal(dX.isnan(), want.isnan()) and torch.equal(dX.nan_to_num(nan=0.5), want.nan_to_num(nan=0.5))
+
+
+def _time(run):
+    for _ in range(3):
+        run()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(4):
+            run()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return sorted(times)[2]
+
+
+def test_long_reduction_beside_a_full_chip_is_split():
+    """490 tiles of the image gradient beside 15 of the weight gradient whose reduction takes 980 steps: left whole, for
+    want of room beside the 490, they take 2.3 times as long as in 16 parts.  The plan's choice is held to 1.5 times."""
+    geom = hlq.hlq_conv_geom(Nb=40, H=56, W=56, C=24, O=384, kh=5, kw=5, stride_h=1, stride_w=1, pad_h=2, pad_w=2, dil_h=1, dil_w=1)
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    X, Wt, G = (torch.randn(shape, generator=gen, device=DEV) for shape in ((40, 56, 56, 24), (384, 5, 5, 24), (40, 56, 56, 384)))
+    dX, dW = torch.empty_like(X), torch.empty_like(Wt)
+    took = []
+    try:
+        for splits in (0, 16):
+            hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, splits)
+            ws = torch.empty(hlq.hlq_conv_workspace_bytes(geom, 16, 8, hlq.HLQ_F32, 0), dtype=torch.uint8, device=DEV)
+            took.append(_time(lambda: hlq.hlq_conv2d_backward(G, X, Wt, geom, 16, 8, 3, 0, dX, dW, ws)))
+    finally:
+        hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, 0)
+    print("us a pass: the plan's choice %.0f, 16 splits %.0f" % (took[0] * 250, took[1] * 250), flush=True)
+    assert took[0] < 1.5 * took[1]
