@@ -11,6 +11,9 @@ struct ConvDxPlan {
     size_t lds;
 };
 
+// whether a compute unit's LDS holds one tile only (128 x 128 with more than 30 taps over more than 64 codes, or more than 61)
+static inline bool conv_dx_alone(int form, int O, int taps) { return conv_dx_lds(form, O, taps) > kConvDxMaxLds / 2; }
+
 static inline int conv_gcd(int a, int b)
 {
     while (b) {
@@ -55,6 +58,9 @@ static inline double conv_dx_tile_us(int form, const ConvShape &s, int O)
 // 9 over 256 with stride 2 220 -> 127, 12544 x 256 x 9 over 256 58.1 -> 51.8, 1024 x 128 x 9 over 256 with stride 2 23.3 -> 15.8;
 // taken the old way by this rule: 65536 x 16 x 9 over 512 73.4 -> 103.8, 16384 x 16 x 9 over 512 33.1 -> 47.2, 3136 x 64 x 9
 // over 512 27.0 -> 33.4, fp32 12544 x 48 x 9 over 448 42.5 -> 46.6, 4096 x 32 x 9 over 32 19.3 -> 19.9.
+// Tiles that fill a compute unit's LDS go one to a unit, each in 0.82 of the time (64 x 14 x 14 x 384, 8 x 8, over 96: 294 of them,
+// 1.7 times the column gradient's time; 120 layers of 6 x 6 to 8 x 8 taps come to 0.3 % from the faster of the two in the
+// mean, 2.7 % counted as two; the plan of launch_conv_pair counts two there as well, 0.5 % behind one in the mean and up to 8 % ahead).
 // A 1 x 1 kernel with a stride has fewer taps than classes of pixels: most workgroups would write zeros only
 // (50176 x 128 over 256, stride 2, 25.9 -> 28.6).
 static inline bool conv_dx_wanted(const ConvShape &s, int O, bool is_f32)
@@ -64,7 +70,9 @@ static inline bool conv_dx_wanted(const ConvShape &s, int O, bool is_f32)
     conv_dx_shape(s, form, tiles_px, tiles_c, blocks);
     const double mb = static_cast<double>(s.N) * s.kh * s.kw * s.C * (is_f32 ? 4e-6 : 2e-6);
     const double columns = 10.0 + (s.sh * s.sw > 1 ? 1.0 : 0.0) + mb / 2.3 + mb / 5.0;
-    const double rounds = __builtin_ceil(blocks / 512.0) * (blocks <= 256 && form != 3 ? 0.75 : 1.0);
+    const bool alone = conv_dx_alone(form, O, s.kh * s.kw);
+    const double rounds = alone ? __builtin_ceil(blocks / 256.0) * (blocks <= 256 ? 0.62 : 0.82)
+                                : __builtin_ceil(blocks / 512.0) * (blocks <= 256 && form != 3 ? 0.75 : 1.0);
     return 9.3 + rounds * conv_dx_tile_us(form, s, O) < columns;
 }
 

@@ -137,3 +137,19 @@ def test_long_reduction_beside_a_full_chip_is_split():
         hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, 0)
     print("us a pass: the plan's choice %.0f, 16 splits %.0f" % (took[0] * 250, took[1] * 250), flush=True)
     assert took[0] < 1.5 * took[1]
+
+
+@pytest.mark.parametrize("c,stored", [((64, 14, 14, 384, 96, 8, 1, 0, 1), True), ((64, 14, 14, 384, 96, 5, 1, 0, 1), False)])
+def test_tiles_that_fill_a_compute_unit_are_counted_one_to_a_unit(c, stored):
+    """294 tiles of 64 taps over 96 codes, 97 KB of LDS each: two rounds of the chip, not one, and 1.7 times as long as the
+    column gradient, which is stored then (the first thing in the scratch).  With 25 taps two fit a compute unit."""
+    geom = _geom(c)
+    _, _, N, I = hlq.hlq_conv_sizes(geom)
+    Nb, H, W, C, O, k, *_ = c
+    gen = torch.Generator(device=DEV).manual_seed(2)
+    X, Wt, G = (torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16) for shape in ((Nb, H, W, C), (O, k, k, C), (N, O)))
+    memory = torch.full((hlq.hlq_conv_workspace_bytes(geom, 16, 8, hlq.HLQ_BF16, 0),), 0xFF, dtype=torch.uint8, device=DEV)
+    dX, dW = torch.empty_like(X), torch.empty_like(Wt)
+    hlq.hlq_conv2d_backward(G, X, Wt, geom, 16, 8, 3, 0, dX, dW, memory)
+    untouched = bool((memory[:N * I * 2] == 0xFF).all())
+    assert untouched != stored
