@@ -1,6 +1,7 @@
 """The image gradient taken straight from the codes (product and fold in one) against the calls it stands for: the
-quantisers, the product that writes the column gradient, and its fold.  Same bits, for every shape of the kernel's
-tile and every number of bytes a step takes of a row of codes, at sizes that end inside a tile or a step."""
+quantisers, the product that writes the column gradient, and its fold.  Same bits, for every form of the kernel (the tile's
+shape and the bytes of a row of codes that an item takes), at sizes that end inside a tile or an item; and the weight
+gradient that shares its launch, under several plans of the two."""
 import pytest
 import torch
 
@@ -153,3 +154,77 @@ def test_tiles_that_fill_a_compute_unit_are_counted_one_to_a_unit(c, stored):
     hlq.hlq_conv2d_backward(G, X, Wt, geom, 16, 8, 3, 0, dX, dW, memory)
     untouched = bool((memory[:N * I * 2] == 0xFF).all())
     assert untouched != stored
+
+
+# Nb, H, W, C, O, k, stride, pad, dilation, B: the forms of the kernel that the cases above leave out, blocks of 32 and 64
+# rows, and plans of the launch on either side of the 512 workgroups that are resident at once
+PAIRS = [
+    (16, 16, 16, 128, 256, 3, 2, 1, 1, 16),    # 64 x 64, two items of 128 bytes a tap; dW not split
+    (16, 16, 16, 128, 144, 3, 2, 1, 1, 16),    # ... the second one ragged
+    (16, 40, 36, 64, 32, 3, 1, 1, 1, 16),      # 128 x 64, items of 32 bytes; dW in 16 parts
+    (16, 32, 32, 40, 32, 3, 1, 1, 1, 32),      # 64 x 64, items of 32 bytes, channels past the end
+    (24, 20, 20, 40, 64, 5, 2, 2, 1, 32),      # 64 x 64, items of 64 bytes, stride
+    (72, 16, 16, 128, 320, 3, 1, 1, 1, 64),    # 128 x 64, three items of 128 bytes, the last one half
+    (64, 14, 14, 256, 256, 3, 1, 1, 1, 16),    # 500 workgroups in three parts
+    (32, 32, 32, 256, 144, 3, 1, 0, 1, 16),    # more than 512, dW's first (bf16 projections)
+    (156, 20, 20, 32, 32, 5, 1, 2, 1, 32),     # dW's reduction longer than the image gradient: more than there is room for
+    (32, 32, 32, 124, 48, 4, 1, 1, 1, 16),     # the column matrix is stored
+    (48, 37, 40, 44, 80, 4, 1, 1, 1, 16),
+]
+
+
+@pytest.mark.parametrize("c", PAIRS)
+@pytest.mark.parametrize("dtype,flags,splits", [(torch.bfloat16, 0, 0), (torch.float32, 0, 3), (torch.bfloat16, hlq.HLQ_FLAG_GW_INT8, 0),
+                                                (torch.float32, hlq.HLQ_FLAG_GW_INT8, 3), (torch.bfloat16, hlq.HLQ_FLAG_GW_INT8, 2)])
+def test_both_gradients_of_one_launch(c, dtype, flags, splits):
+    """dX against the three calls, and dW: integer projections bit for bit against the call for dW alone, bf16 ones against
+    their product in 64 bits.  splits: parts of dW's reduction, 0 = the plan's choice."""
+    Nb, H, W, C, O, k, s, p, d, B = c
+    r, seed = B // 2, 4
+    geom = _geom((Nb,) + c[1:9])
+    Ho, Wo, N, I = hlq.hlq_conv_sizes(geom)
+    while N % B or N // B * r % 16:
+        Nb *= 2
+        geom = _geom((Nb,) + c[1:9])
+        Ho, Wo, N, I = hlq.hlq_conv_sizes(geom)
+    print("conv", c, dtype, flags, splits, "N", N, "I", I, flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(13)
+    X, Wt, G = (torch.randn(shape, generator=gen, device=DEV).mul_(scale).to(dtype)
+                for shape, scale in (((Nb, H, W, C), 1.0), ((O, k, k, C), 0.02), ((Nb, Ho, Wo, O), 1e-3)))
+    Gq, Wq = torch.empty((N, O), dtype=torch.int8, device=DEV), torch.empty((I, O), dtype=torch.int8, device=DEV)
+    sG, sW = torch.empty(N, dtype=torch.float32, device=DEV), torch.empty(I, dtype=torch.float32, device=DEV)
+    ws = torch.empty(hlq.hlq_quantize_w_workspace_bytes(O, I), dtype=torch.uint8, device=DEV)
+    hlq.hlq_quantize_g(G.reshape(N, O), B, seed, Gq, sG, None, hlq.HLQ_BITS_4)
+    hlq.hlq_quantize_w(Wt.reshape(O, I), B, seed, Wq, sW, ws, None, hlq.HLQ_BITS_4)
+    cols = torch.empty((N, I), dtype=dtype, device=DEV)
+    hlq.hlq_int8_gemm_nt(Gq, Wq, sG, sW, 1.0 / B, cols)
+    want = torch.full_like(X, 7.0)
+    hlq.hlq_col2im(cols, geom, want)
+    dX, dW = torch.full_like(X, 3.0), torch.full_like(Wt, float("nan"))
+    try:
+        hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, splits)
+        memory = torch.full((hlq.hlq_conv_workspace_bytes(geom, B, r, hlq.binding._dt(G), flags),), 0xFF, dtype=torch.uint8, device=DEV)
+        hlq.hlq_conv2d_backward(G, X, Wt, geom, B, r, seed, flags, dX, dW, memory)
+        torch.cuda.synchronize()
+    finally:
+        hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, 0)
+    assert torch.equal(dX, want)
+    # the column gradient's place, behind that of a column matrix that is stored, is untouched
+    size = cols.numel() * cols.element_size()
+    at = (size + 255) // 256 * 256 if C % (128 // B) else 0
+    untouched = bool((memory[at:at + size] == 0xFF).all())
+    assert untouched
+    if flags & hlq.HLQ_FLAG_GW_INT8:
+        alone = torch.full_like(Wt, 5.0)
+        hlq.hlq_conv2d_backward(G, X, None, geom, B, r, seed, flags, None, alone)
+        assert torch.equal(dW, alone)
+        return
+    hlq.hlq_im2col(X, geom, cols)
+    Gh, Xh = (torch.empty((n, N // B * r), dtype=torch.bfloat16, device=DEV) for n in (O, I))
+    hlq.hlq_hla_project_basis(G.reshape(N, O), B, r, hlq.HLQ_BASIS_NATURAL, Gh)
+    hlq.hlq_hla_project_basis(cols, B, r, hlq.HLQ_BASIS_NATURAL, Xh)
+    ref, size = Gh.double() @ Xh.double().T / B, Gh.double().abs() @ Xh.double().abs().T / B
+    # products of bf16 are exact in fp32, Kc of them are summed in fp32, scaled, and rounded to the type (half a unit in
+    # the last place of bf16 is up to 2^-8 of the value)
+    eps = 2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8
+    assert torch.all((dW.reshape(O, I).double() - ref).abs() <= ref.abs() * (eps + 2.0 ** -22) + size * (N // B * r) * 2.0 ** -24)
