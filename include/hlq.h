@@ -87,8 +87,11 @@ size_t hlq_workspace_bytes(int64_t N, int64_t d_in, int64_t d_out, int B, int r,
  *       0 (default): each stage's workgroups keep their own index range.
  *   HLQ_OPT_DIRECT_TO_LDS  1 (default): 256 x 256 tiles of the matrix products whose operand rows are
  *       whole 128-byte steps (at least four per workgroup) load their operands from global memory
- *       straight into LDS, and so do the 128 x 128 tiles of two products in one launch that has more of
- *       them than compute units;  0: every tile stages them through registers.
+ *       straight into LDS, and so do the 128 x 128 tiles of two products in one launch where each has at
+ *       least two whole steps a workgroup and their work, spread over two tiles a compute unit, takes at
+ *       least 0.9 of the time of the longest tile;  0: every tile of these stages them through registers.
+ *       (The image gradient that hlq_conv2d_backward takes from the codes is no matrix product of this
+ *       kind: it always loads straight into LDS.)
  *   HLQ_OPT_TAIL_TILES  1 (default): a product on 256 x 256 tiles that loads straight into LDS and would
  *       leave most compute units idle in its last round hands its last rows to tiles of 192 x 256, which
  *       shortens that round by a quarter (the g_w product when it closes the launch of both products, or a
@@ -482,6 +485,9 @@ int hlq_conv_compress_act_int8(const void *X, const hlq_conv_geom *g, int B, int
  * rounded to `dtype` before they are folded, whether it is stored or, where that is faster, its entries are
  * added to the image gradient as they come: dX is that of the three calls bit for bit.  The k split of
  * the g_w product is planned for this call: dW agrees with theirs up to the order of its partial sums.
+ * The workspace is sized as if the column gradient were stored and as the linear pass sizes its split
+ * partials, whichever way the call goes: where it is not stored its place is left untouched, and the
+ * split is cut to those partials' place.
  *   workspace >= hlq_conv_workspace_bytes(...) bytes, 256-aligned; or NULL for the library-owned one.
  */
 size_t hlq_conv_workspace_bytes(const hlq_conv_geom *g, int B, int r, int dtype, int flags);

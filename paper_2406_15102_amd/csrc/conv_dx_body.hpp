@@ -9,7 +9,7 @@
 //
 // What it replaces, the product with its column gradient and then the fold, was bound by that tensor: 160 MB written
 // and read for an image of 18 MB at 65536 x 1224 over 32 out-features, 70 + 32 us of a pass of 144 (87 now); 12544 x
-// 2304 over 256 32 + 11 us of 58 (51 now).
+// 2304 over 256, both products and the fold 33.4 + 11.5 us of a pass of 63.8, now 26.9 of 45.1.
 //
 // Tile: WM x WN wavefronts of 16 FM pixels x 16 FN channels, 16 x 16 MFMAs.  Rows of codes go straight into LDS, RB bytes
 // of each at a time (an item: one tap, or RB bytes of its reduction), two items ahead of the one that is
@@ -17,9 +17,11 @@
 // over 256 33 us against 23, the sum without the rounding in both): four adjacent lanes of an MFMA operand are
 // four different rows, so that each load is 64 requests of 16 bytes.
 // Codes are one int8 each here: 4-bit codes two to a byte would be widened by twelve vector instructions per 128 codes of
-// a row, and what bounds the kernel is vector arithmetic -- conversion, the two scales, the rounding and the sum are
-// five and a half instructions per value and tap in bf16, four in fp32 -- and, where a tile has many taps and codes and
-// the layer few tiles, the chain of barriers and LDS reads of its items (about 0.5 us an item at one workgroup a unit).
+// a row, on top of the five and a half per value and tap in bf16 (four in fp32) that conversion, the two scales, the
+// rounding and the sum are.  What bounds the kernel is the chain of a tile's items, each a barrier, LDS reads, MFMAs and, at the
+// end of a tap, those sums one after the other, with two workgroups a compute unit at most to fill the gaps: at 12544 pixels x 256 channels over
+// 256 codes (392 tiles of 18 items, about 0.7 us each where two share a unit) vector instructions issue for 34 % of the launch,
+// LDS is active for 20 %, the MFMAs for 12 %, and a wavefront waits 38 % of its time.
 // A stride splits the pixels into sh * sw classes (their coordinates mod the stride) that are met by different
 // taps; a tile belongs to one class, so no MFMA is spent on a tap that its pixels do not have.
 #pragma once

@@ -52,15 +52,20 @@ static inline double conv_dx_tile_us(int form, const ConvShape &s, int O)
 
 // Whether the image gradient is taken straight from the codes: not where the column gradient is small beside the
 // chain of taps and codes that one tile goes through.  The alternative writes the column gradient at about 2.3 TB/s and
-// reads it at about 5 (65536 x 1224: 70 and 32 us), in a launch of its own more.  Kernel times of a pass, us, column
-// gradient -> straight (pixels x channels x taps, over codes): 65536 x 136 x 9 over 32 144.3 -> 87.7, 65536 x 192 x 9
-// over 128 218.7 -> 124.7, 200704 x 64 x 9 over 64 245.5 -> 110.0, 50176 x 512 x 9 over 512 601 -> 416, fp32 50176 x 96 x
-// 9 over 256 with stride 2 220 -> 127, 12544 x 256 x 9 over 256 58.1 -> 51.8, 1024 x 128 x 9 over 256 with stride 2 23.3 -> 15.8;
-// taken the old way by this rule: 65536 x 16 x 9 over 512 73.4 -> 103.8, 16384 x 16 x 9 over 512 33.1 -> 47.2, 3136 x 64 x 9
-// over 512 27.0 -> 33.4, fp32 12544 x 48 x 9 over 448 42.5 -> 46.6, 4096 x 32 x 9 over 32 19.3 -> 19.9.
+// reads it at about 5 (65536 x 1224: 70 and 32 us), in a launch of its own more.  Whole passes of both gradients, us, column
+// gradient -> straight (images x height x width x channels, kernel, over codes): 64 x 56 x 56 x 64, 3 x 3, over 64 247 -> 119;
+// 64 x 28 x 28 x 128, 3 x 3, over 128 97 -> 69; 64 x 14 x 14 x 256, 3 x 3, over 256 57.1 -> 46.3; 128 x 16 x 16 x 512, 3 x 3, over 512
+// 395 -> 272; 32 x 28 x 28 x 128, 5 x 5, over 128 127 -> 72; 32 x 56 x 56 x 32, 7 x 7, over 32 335 -> 118; fp32 64 x 28 x 28 x
+// 128, 7 x 7, over 128 755 -> 383; 64 x 32 x 32 x 256, 8 x 8 with stride 2, over 128 508 -> 332; kept on the column gradient by this rule:
+// 8 x 20 x 20 x 64, 7 x 7, over 512 48 -> 115; 4 x 32 x 32 x 128, 7 x 7, over 704 100 -> 185; 80 x 64 x 64 x 16, 7 x 7 with stride 2, over
+// 736 290 -> 653.
 // Tiles that fill a compute unit's LDS go one to a unit, each in 0.82 of the time (64 x 14 x 14 x 384, 8 x 8, over 96: 294 of them,
 // 1.7 times the column gradient's time; 120 layers of 6 x 6 to 8 x 8 taps come to 0.3 % from the faster of the two in the
 // mean, 2.7 % counted as two; the plan of launch_conv_pair counts two there as well, 0.5 % behind one in the mean and up to 8 % ahead).
+// Of 233 layers that it takes (2 x 2 to 8 x 8 taps, whole passes of both gradients; 0.72 of the column gradient's time in the
+// geometric mean) three are more than a tenth slower: 32 x 14 x 14 x 512 over 512 68 -> 77 us, whose weight gradient finds no room beside
+// 392 tiles (the image gradient alone 54 -> 47); 112 x 16 x 16 x 56, 4 x 4, over 160 46 -> 56; 128 x 20 x 20 x 112, 7 x 7 with stride 2, over
+// 512 183 -> 209.  No constants of this form were found that leave those out and lose none of the others.
 // A 1 x 1 kernel with a stride has fewer taps than classes of pixels: most workgroups would write zeros only
 // (50176 x 128 over 256, stride 2, 25.9 -> 28.6).
 static inline bool conv_dx_wanted(const ConvShape &s, int O, bool is_f32)

@@ -14,7 +14,7 @@
 //     steps every line is asked for twice and a load takes 1.7 x as long to land;
 //   * loads go out singly between the MFMAs, never in a burst from all four wavefronts (the address
 //     queues of the memory pipeline fill up and the wavefront stalls at issue);
-//   * LDS is a ring of five 32 KB units -- all 160 KB.  Step kt keeps its A rows in unit 2 kt mod 5 and
+//   * LDS is a ring of five units, 32 KB each for a 256-tile -- all 160 KB.  Step kt keeps its A rows in unit 2 kt mod 5 and
 //     its Bm rows in the next one, so while step kt is multiplied step kt + 1 is complete or landing
 //     in two more units and the fifth takes the A rows of step kt + 2 already: a load has between
 //     0.75 and 1.5 steps to land, about what the register-staged pipeline gives it.
@@ -36,11 +36,12 @@
 // last 2816 rows in 192-row tiles it is 512 + 240 tiles, two rounds and one of three-quarter tiles.
 //
 // A third, 128 x 128 (4 x 4 accumulators per wavefront, ring units of 16 KB: 80 KB, two workgroups to a compute unit),
-// serves the pairs of products whose 256-tiles would not fill the chip.  A step reads 64 KB of fragments for 16 x 16 x 2
-// MFMAs a tile, so LDS bounds it, and what it saves over the register-staged body is the 32 KB that the ds_writes
-// put there a second time: 32 MFMAs a step and wavefront hide fewer cycles than 128, hence the second workgroup.  Both
-// products of a pass alone, register-staged -> this: 4096 x 2048 x 5632 91.0 -> 83.8 us, 8192 x 2048 x 2048 72.4 -> 69.1,
-// 4096 x 1024 x 4096 29.4 -> 26.6, 2048 x 2048 x 2048 21.3 -> 20.0; gemm_dl128_ok says where it is taken.
+// serves the pairs of products whose 256-tiles would not fill the chip.  A step reads 64 KB of fragments, 512 cycles of
+// LDS, for 8 x 8 x 2 MFMAs a tile, 512 cycles of every SIMD, and takes 32 KB in, so LDS bounds it, and what it saves over
+// the register-staged body is that 32 KB passing through registers: 32 MFMAs a step and wavefront hide fewer cycles
+// than 128, hence the second workgroup.  The launch of both products, register-staged -> this, whole passes on changing
+// inputs: 4096 x 2048 x 5632 in fp32 92.1 -> 84.1 us; products called alone: 8192 x 2048 x 2048 72.4 -> 69.1, 4096 x 1024 x
+// 4096 29.4 -> 26.6, 2048 x 2048 x 2048 21.3 -> 20.0; gemm_dl128_ok says where it is taken.
 // RAGGED (128 x 128 only): the last step of a row need not be whole.  It is multiplied behind the loop, chunks past
 // the end of a row cleared in registers, so the loop of whole steps carries one subtraction a load for it.
 #pragma once
@@ -239,7 +240,7 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     const int m0 = tm * BTM, n0 = tn * BT;
 
     // ---- loads: instruction j of this wavefront fills rows 8 (4 j + wave) .. + 7 of an operand ----
-    // (NBM instructions for the A rows, 8 for the Bm rows)
+    // (NBM instructions for the A rows, NB for the Bm rows)
     // 1 KB of LDS in lane order: lane -> row lane / 8 of the block, position lane % 8 of the row, which
     // in the swizzled layout (lds_chunk<8>) holds chunk position ^ (row & 7) ^ (row >> 3 & 1) of that
     // row.  Rows past the end of an operand are redirected to the tile's first row (never stored).
@@ -362,16 +363,16 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     }
 
     // Step kt reads units u = 2 kt mod 5 (A) and u + 1 (Bm); step kt + 1 sits in the next two units.
-    // Every sub-step is 64 MFMAs -- accumulator (q / 8, q % 8) in slot q -- and reads the 16 fragments of
-    // the next sub-step in the even slots of its first half (packed codes: see below).  The loop is written
+    // Every sub-step is SLOTS = NBM NB MFMAs -- accumulator (q / NB, q % NB) in slot q -- and reads the NR = NBM + NB
+    // fragments of the next sub-step in its even slots, from the first on (packed codes: see below).  The loop is written
     // slot by slot, what is to issue around one MFMA, with a scheduling fence after each slot, so the issue
     // order is the source order.
     //   all but the last sub-step   the A rows of step kt + 2 go into the one free unit, u + 4, evenly spread
-    //   last but one                the read positions move on; its barrier: every wavefront's loads of
-    //                               step kt + 1 have landed (all but the 8 youngest have) and nobody reads
-    //                               step kt from LDS any more
+    //   last but one                the read positions move on (128 x 128: each in the sub-step that has read from
+    //                               it last); its barrier: every wavefront's loads of step kt + 1 have landed (all
+    //                               but the NBM youngest have) and nobody reads step kt from LDS any more
     //   last                        fragments of step kt + 1's first sub-step; the Bm rows of step kt + 2
-    //                               go into unit u, one load every fourth slot of its first half
+    //                               go into unit u, one load every fourth slot from the first on
     int u = 0;
     for (int kt = 0; kt < nk; ++kt) {
         const int ua = u == 0 ? 4 : u - 1;   // (2 kt + 4) mod 5
