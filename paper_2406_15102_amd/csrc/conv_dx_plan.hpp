@@ -26,9 +26,9 @@ static inline int conv_gcd(int a, int b)
 
 // Tile of a layer: 128 pixels x 128 channels where the channels fill it, else 256 x 64; 128 x 64 where fewer than a
 // workgroup a compute unit would come of that, 64 x 64 where 128 x 64 fills little more than half of the chip
-// (image gradient and weight gradient together, us, 256 or 128 x 128 / 128 x 64 / 64 x 64 pixels x channels: 12544 pixels x 256
-// channels over 256 codes 33.2 / 30.5 / -, 200704 x 64 over 64 52.1 / 52.8 / -, 3136 x 512 over 512 39.4 / 33.0 / 36.3,
-// 12544 x 48 over 448 36.1 / 28.1 / 25.2, 4096 x 128 over 128 - / 15.1 / 11.8).
+// (whole passes of 3 x 3 layers, us, 256 x 64 or 128 x 128 / 128 x 64 / 64 x 64 pixels x channels: 12544 pixels x 256 channels over
+// 256 codes 53.2 / 46.9 / 55.2, 200704 x 64 over 64 118.8 / 120.5 / 135.3, 3136 x 512 over 512 51.8 / 45.2 / 52.6, 12544 x 48
+// over 448 61.1 / 43.0 / 42.6, 4096 x 128 over 128 28.7 / 27.3 / 23.0).
 static inline void conv_dx_shape(const ConvShape &s, int &form, int &tiles_px, int &tiles_c, int &blocks)
 {
     const int64_t most = static_cast<int64_t>(s.Nb) * ((s.H + s.sh - 1) / s.sh) * ((s.W + s.sw - 1) / s.sw);   // pixels of a class

@@ -50,13 +50,14 @@ bool conv_pair_available() { return gemm_plan_forced_tile() != 256; }
 
 // Plan of the launch: the k split of the weight gradient's product and which of the two goes first.  Where the image
 // gradient leaves room for the other's tiles beside it -- two workgroups a compute unit, 512 -- all of them are resident
-// at once: as many splits as fit, of eight steps or more, behind it (12544 pixels x 256 channels, 36 tiles: 500
-// workgroups at 3 splits 30.5 us, 536 at 4 37.7; 1024 x 128 with a stride, eight steps: not split 9.0 and no reduction,
-// 2 splits 9.6 + 2.9).  Larger layers by the model of gemm_plan.hpp, with the image gradient's tiles as the first product.
+// at once: as many splits as fit, of eight steps or more, behind it (whole passes: 12544 pixels x 256
+// channels, 36 tiles, 500 workgroups at 3 splits 47.2 us, 536 at 4 56.0; 16 x 14 x 14 x 64, 4 x 4 with stride 2, over 64, eight
+// steps: not split and no reduction 14.3, 2 splits 16.7).  Larger layers by the model of gemm_plan.hpp, with the image
+// gradient's tiles as the first product.
 // Neither looks at how long the weight gradient's tiles are beside a small image gradient that fills the chip (whole pass of
 // 40 x 56 x 56 x 24, 5 x 5, over 384, fp32: 490 blocks leave its 15 tiles of 980 steps whole, 754 us; 16 splits 332): a choice
 // that conv_pair_time prices a sixth lower takes their place.  Over 470 layers, every split in either order measured, that
-// takes the mean distance to the best one from 3.7 to 2.2 %, 53 layers by more than 2 % faster, none slower; the lowest price
+// takes the mean distance to the best one from 3.7 to 2.2 %, 54 layers by more than 2 % faster, none slower; the lowest price
 // throughout 1.0 %, with 18 layers slower, by up to 16 %.
 hipError_t launch_conv_pair(const GemmArgs &a, const ConvShape &s, int kindB, const GemmArgs &b, hipStream_t st)
 {
