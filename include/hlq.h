@@ -20,8 +20,9 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  All work is
  *     enqueued on it; no call synchronises the device.  Except where noted, no call allocates.
  *   - `dtype` selects the element type of G, X, W and of dX, dW: HLQ_BF16 or HLQ_F32.
- *     Arithmetic is fp32 (transforms, scales), int8 x int8 -> int32 (dX product) and
- *     bf16 x bf16 -> fp32 (dW product) whatever the dtype.
+ *     Arithmetic is fp32 (transforms, scales), whole numbers (dX product: int8 x int8 -> int32, or
+ *     4-bit codes as 6-bit floats -> fp32, exact below 2^24) and bf16 x bf16 -> fp32 (dW product) whatever
+ *     the dtype.
  *   - Every function returns an hlq_status.  On any status other than HLQ_OK nothing has been
  *     enqueued and no output byte is written (HLQ_ERR_LAUNCH excepted: an earlier kernel of the
  *     same call may already be queued).
@@ -91,7 +92,8 @@ size_t hlq_workspace_bytes(int64_t N, int64_t d_in, int64_t d_out, int B, int r,
  *       least two whole steps a workgroup and their work, spread over two tiles a compute unit, takes at
  *       least 0.9 of the time of the longest tile;  0: every tile of these stages them through registers.
  *       (The image gradient that hlq_conv2d_backward takes from the codes is no matrix product of this
- *       kind: it always loads straight into LDS.)
+ *       kind, and the whole path's product of 4-bit codes is kept in a layout of its own: both always load
+ *       straight into LDS.)
  *   HLQ_OPT_TAIL_TILES  1 (default): a product on 256 x 256 tiles that loads straight into LDS and would
  *       leave most compute units idle in its last round hands its last rows to tiles of 192 x 256, which
  *       shortens that round by a quarter (the g_w product when it closes the launch of both products, or a
@@ -305,7 +307,7 @@ int hlq_bf16_gemm_nt(const void *A, const void *Bm, int64_t M, int64_t Nn, int64
                                         the chip for most layers); dX is the same bit for bit either way, dW
                                         up to the summation order of its k splits. */
 #define HLQ_FLAG_GX_UNPACKED 4 /* keep the 4-bit g_x codes one per int8 between the stages.  By default
-                                  they are stored two to a byte whenever d_out % 32 == 0 (same codes, same
+                                  they are stored two to a byte (same codes, same
                                   dX bit for bit; half the traffic). */
 
 /*

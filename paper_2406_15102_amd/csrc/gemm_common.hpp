@@ -10,6 +10,7 @@ namespace hlq {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));  // one 16-B chunk (first-class vector: stays in registers)
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x6 __attribute__((ext_vector_type(6)));  // 32 codes as 6-bit floats: one MFMA operand of a lane
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -57,6 +58,13 @@ template <> struct Mma<2> {
     }
     static __device__ __forceinline__ float to_float(int v) { return static_cast<float>(v >> 8); }
     static __device__ __forceinline__ int raw(int v) { return v >> 8; }
+};
+// 4-bit codes in the layout that widens to 6-bit floats (f6_pack32, hlq_device.hpp), multiplied by gemm_dl_body.hpp only.
+// An operand is the code divided by 8, so the accumulators are the integer dot product divided by 64: exact, and so is
+// the factor, as long as the product stays below 2^24 (49 K, K <= 131072).
+template <> struct Mma<3> {
+    static __device__ __forceinline__ float to_float(float v) { return v * 64.0f; }
+    static __device__ __forceinline__ int raw(float v) { return static_cast<int>(v * 64.0f); }
 };
 
 struct GemmDev {

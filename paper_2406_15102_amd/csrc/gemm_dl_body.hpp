@@ -42,6 +42,13 @@
 // than 128, hence the second workgroup.  The launch of both products, register-staged -> this, whole passes on changing
 // inputs: 4096 x 2048 x 5632 in fp32 92.1 -> 84.1 us; products called alone: 8192 x 2048 x 2048 72.4 -> 69.1, 4096 x 1024 x
 // 4096 29.4 -> 26.6, 2048 x 2048 x 2048 21.3 -> 20.0; gemm_dl128_ok says where it is taken.
+// 4-bit codes in the f6 layout (KIND 3; hlq_device.hpp says how it widens) are 6-bit floats to the matrix cores, 128 of k
+// to an MFMA of the cycles that 64 bytes take.  Registers alone sustain 6.9 POP/s that way, 4.1 on the bytes that
+// nibbles widen to (Mma16<2>): 1.65 and 1.97 GHz, the power limit in either case.  A step is that of bytes: 16 rows x 64 B
+// and one ds_read_b128 a fragment, where nibbles are read 8 bytes a lane with two-way conflicts.  The product alone,
+// nibbles -> f6: 4096 x 4096 x 11008 112.5 -> 80.8 us (4.6 POP/s), 8192 x 28672 x 8192 1168 -> 828: MFMAs busy 61 % of its
+// cycles at 1.82 GHz, vector instructions issued for 12 %, so it is power here too, and an MFMA's share of the
+// widening (1.5 instructions) and of LDS reads weighs double beside half the MFMAs.
 // RAGGED (128 x 128 only): the last step of a row need not be whole.  It is multiplied behind the loop, chunks past
 // the end of a row cleared in registers, so the loop of whole steps carries one subtraction a load for it.
 #pragma once
@@ -93,6 +100,24 @@ template <> struct Mma16<2> : Mma16<0> {
         } else {
             o[part - 1] = (x[part - 1] << 4) & 0xF0F0F0F0u;
         }
+    }
+};
+
+// 4-bit codes in the f6 layout (hlq_device.hpp): 16 bytes (32 codes) widen to one operand of six registers
+template <> struct Mma16<3> {
+    typedef v4f_t acc_t;
+    static __device__ __forceinline__ acc_t zero() { return acc_t{0.0f, 0.0f, 0.0f, 0.0f}; }
+    static __device__ __forceinline__ void mma(const u32x6 &x, const u32x6 &y, acc_t &c)
+    {
+        asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:2 blgp:2" : "+a"(c) : "v"(x), "v"(y));
+    }
+    // dword `part` (0-5) of the operand, one instruction
+    static __device__ __forceinline__ void expand_part(const u32x4 &x, u32x6 &o, int part)
+    {
+        const uint32_t a = x[part < 3 ? 0 : 2], b = x[part < 3 ? 1 : 3];
+        if (part % 3 == 0) o[part] = a & F6M0;
+        else if (part % 3 == 1) o[part] = b & F6M1;
+        else o[part] = (a ^ b) & F6M2;
     }
 };
 
@@ -206,7 +231,8 @@ template <int KIND, int NBM, int OUT, int NB = 8, bool RAGGED = false>
 __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 {
     constexpr int BT = 32 * NB, BTM = 32 * NBM, GROUP = 4;
-    constexpr bool PACKED = KIND == 2;
+    constexpr bool PACKED = KIND == 2, F6 = KIND == 3;
+    static_assert(!F6 || (!RAGGED && NBM == NB), "f6 rows are whole steps, in square tiles");
     static_assert((NB == 8 && (NBM == 8 || (NBM == 6 && !PACKED)) && !RAGGED) || (NB == 4 && NBM == 4),
                   "tiles of 256 x 256, of 192 x 256 for byte and bf16 operands, or of 128 x 128");
     constexpr int NS = PACKED ? 4 : 2;            // sub-steps per step: 32 B of packed codes, 64 B otherwise
@@ -308,10 +334,18 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     // codes they hold the widened operands, and pk the 8-byte pieces between their read and their widening.
     u32x4 fa[2][NBM], fb[2][NB];
     u32x2 pk[NR];
+    // f6: the widened operands, and the 16-byte pieces before.  At 8 x 8 accumulators a row of A is widened over itself,
+    // behind its eight MFMAs: registers for the Bm blocks twice and the A blocks once.
+    constexpr int FA = NB == 8 ? 1 : 2;
+    u32x6 wa[FA][NBM], wb[2][NB];
+    u32x4 pw[NR];
     // fragment Q of sub-step S (0-7: Bm blocks -- the first row of MFMAs takes them all --, 8-15: A blocks)
 #define HLQD_READ_ONE(BUF, S, Q)                                                                              \
     {                                                                                                         \
-        if constexpr (PACKED) {                                                                               \
+        if constexpr (F6) {                                                                                   \
+            if ((Q) < NB) pw[Q] = *reinterpret_cast<const u32x4 *>(ldsb + rdB[S] + (Q) * 2048u);              \
+            else pw[Q] = *reinterpret_cast<const u32x4 *>(ldsb + rdA[S] + ((Q) - NB) * 2048u);                \
+        } else if constexpr (PACKED) {                                                                        \
             if ((Q) < NB) pk[Q] = *reinterpret_cast<const u32x2 *>(ldsb + rdB[S] + (Q) * 2048u);              \
             else pk[Q] = *reinterpret_cast<const u32x2 *>(ldsb + rdA[S] + ((Q) - NB) * 2048u);                \
         } else {                                                                                              \
@@ -324,6 +358,13 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     {                                                                                                         \
         if ((Q) < NB) Mma16<2>::expand_part(pk[Q], fb[BUF][Q], P);                                            \
         else Mma16<2>::expand_part(pk[Q], fa[BUF][(Q) - NB], P);                                              \
+    }
+
+    // f6: dword P (0-5) of fragment Q widened into buffer BUF
+#define HLQD_WIDEN(BUF, Q, P)                                                                                 \
+    {                                                                                                         \
+        if ((Q) < NB) Mma16<3>::expand_part(pw[Q], wb[BUF][(Q) < NB ? (Q) : 0], P);                           \
+        else Mma16<3>::expand_part(pw[Q], wa[FA == 2 ? (BUF) : 0][(Q) < NB ? 0 : (Q) - NB], P);               \
     }
 
     typename Mma16<KIND>::acc_t acc[NBM][NB];
@@ -347,6 +388,18 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int q = 0; q < NR; ++q) HLQD_READ_ONE(0, 0, q)
+    if constexpr (F6) {
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+#pragma unroll
+            for (int p = 0; p < 6; ++p) HLQD_WIDEN(0, q, p)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            asm volatile("" ::"v"(wb[0][q]));       // as below
+            asm volatile("" ::"v"(wa[0][q]));
+        }
+        asm volatile("s_nop 1");
+    }
     if constexpr (PACKED) {
 #pragma unroll
         for (int q = 0; q < NR; ++q)
@@ -380,7 +433,43 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
         for (int s = 0; s < NS; ++s) {
             const int cur = s & 1;
             const int ns = s < NS - 1 ? s + 1 : 0;       // the sub-step whose fragments are read now
-            if constexpr (!PACKED) {
+            if constexpr (F6 && NB == 8) {
+                // 64 slots, a slot's share beside its MFMA one and a half of the 96 widening instructions and a quarter of a
+                // read.  Bm block j: read in slot 6 j, widened one dword a slot from 6 j + 10 on.  A block j: read in slot
+                // 5 j + 3, widened over the block it replaces in the six slots 8 j + 10 .. 8 j + 15, two behind that
+                // block's last MFMA -- for j = 7 in the next sub-step's slots 2-7, ahead of its own MFMAs in 56-63.
+#pragma unroll
+                for (int q = 0; q < SLOTS; ++q) {
+                    if (q % 6 == 0 && q < 48) HLQD_READ_ONE(cur ^ 1, ns, q / 6)
+                    if (q % 5 == 3 && q < 40) HLQD_READ_ONE(cur ^ 1, ns, NB + q / 5)
+                    if (q >= 2 && q < 8) HLQD_WIDEN(0, NB + 7, q - 2)
+                    if (q >= 8 && (q & 7) >= 2) HLQD_WIDEN(0, NB + (q >> 3) - 1, (q & 7) - 2)
+                    if (q >= 10 && q < 58) HLQD_WIDEN(cur ^ 1, (q - 10) / 6, (q - 10) % 6)
+                    if (s == 0 && (q & 7) == 1) HLQD_LOAD_ONE(kt + 2, 0, q >> 3, ua)
+                    if (s == 1 && q < 32 && (q & 3) == 1) HLQD_LOAD_ONE(kt + 2, 1, q >> 2, u)
+                    if (s == 0 && q >= 58 && q < 62) HLQD_NEXT_UNIT((q - 58) >> 1, q & 1)
+                    Mma16<KIND>::mma(wb[cur][q & 7], wa[0][q >> 3], acc[q >> 3][q & 7]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else if constexpr (F6) {
+                // 16 slots: the 8 fragments in slots 0-3, the 48 dwords of their widening four a slot from slot 4 on (the
+                // wavefront of the other workgroup on the SIMD issues beside them)
+#pragma unroll
+                for (int q = 0; q < SLOTS; ++q) {
+                    if (q < 4) {
+                        HLQD_READ_ONE(cur ^ 1, ns, 2 * q)
+                        HLQD_READ_ONE(cur ^ 1, ns, 2 * q + 1)
+                    }
+                    if ((q & 3) == 1) HLQD_LOAD_ONE(kt + 2, s, q >> 2, s == 0 ? ua : u)
+                    if (q == 3 || q == 7) HLQD_NEXT_UNIT(s, q == 7)
+                    if (q >= 4) {
+#pragma unroll
+                        for (int e = 4 * (q - 4); e < 4 * (q - 4) + 4; ++e) HLQD_WIDEN(cur ^ 1, e / 6, e % 6)
+                    }
+                    Mma16<KIND>::mma(wb[cur][q & 3], wa[FA == 2 ? cur : 0][q >> 2], acc[q >> 2][q & 3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else if constexpr (!PACKED) {
                 constexpr int APER = SLOTS * (NS - 1) / NBM;   // slots between two loads of A rows
 #pragma unroll
                 for (int q = 0; q < SLOTS; ++q) {
@@ -497,6 +586,7 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 #undef HLQD_READ_ONE
 #undef HLQD_NEXT_UNIT
 #undef HLQD_EXPAND
+#undef HLQD_WIDEN
 
     // ---- epilogue ----
     // the last MFMAs have written their accumulators (the compiler does not know that the statements

@@ -98,12 +98,16 @@ template <class CA, int KB>
 static hipError_t launch_pair_a(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigB, int modeB, int outB,
                                 bool b_first, hipStream_t st)
 {
-    if constexpr (CA::W == 2 && CA::MODE >= 2) {      // 128-tiles straight into LDS: both products or neither
+    if constexpr (CA::W == 2 && CA::MODE >= 2 && CA::KIND != 3) {      // 128-tiles straight into LDS: both products or neither
         return modeB == 3 ? launch_pair_b<CA, KB, 2, 3>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 2, 2>(ga, gb, gbt, outB, b_first, st);
     } else {
         if (bigB) {
             if (modeB == 2) return launch_pair_b<CA, KB, 4, 2>(ga, gb, gbt, outB, b_first, st);
             return modeB ? launch_pair_b<CA, KB, 4, 1>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 4, 0>(ga, gb, gbt, outB, b_first, st);
+        }
+        if constexpr (CA::KIND == 3 && CA::W == 2) {
+            if (modeB == 2) return launch_pair_b<CA, KB, 2, 2>(ga, gb, gbt, outB, b_first, st);
+            if (modeB == 3) return launch_pair_b<CA, KB, 2, 3>(ga, gb, gbt, outB, b_first, st);
         }
         return modeB ? launch_pair_b<CA, KB, 2, 1>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 2, 0>(ga, gb, gbt, outB, b_first, st);
     }
@@ -117,18 +121,11 @@ static hipError_t launch_pair_o(const GemmDev &ga, const GemmDev &gb, const Gemm
                : launch_pair_a<TileCfg<KA, WA, MODEA, 0>, KB>(ga, gb, gbt, bigB, modeB, outB, b_first, st);
 }
 
-// every kernel of one pair of kinds; the plan comes from the caller
+// the g_x product through registers or, where modeA says so, straight into LDS
 template <int KA, int KB>
-static hipError_t launch_pair_kinds(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB,
-                                    int outB, bool b_first, hipStream_t st)
+static hipError_t launch_pair_modes(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB,
+                                    int modeA, int modeB, int outB, bool b_first, hipStream_t st)
 {
-    const bool dl128 = !bigA && !bigB && gemm_dl128_ok(ga, KA == 2 ? kPackedScale : 1.0, gb);
-    const auto mode = [dl128](const GemmDev &g, bool big) {
-        const bool whole = g.Kb % 128 == 0;
-        if (dl128) return whole ? 2 : 3;
-        return whole ? (big && gemm_dl_ok(g.Kb, g.splits) ? 2 : 0) : 1;
-    };
-    const int modeA = mode(ga, bigA), modeB = mode(gb, bigB);
     if (bigA) {
         if (modeA == 2) return launch_pair_o<KA, KB, 4, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
         return modeA ? launch_pair_o<KA, KB, 4, 1>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st)
@@ -139,6 +136,24 @@ static hipError_t launch_pair_kinds(const GemmDev &ga, const GemmDev &gb, const 
                           : launch_pair_o<KA, KB, 2, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
     return modeA ? launch_pair_o<KA, KB, 2, 1>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st)
                  : launch_pair_o<KA, KB, 2, 0>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
+}
+
+// every kernel of one pair of kinds; the plan comes from the caller
+template <int KA, int KB>
+static hipError_t launch_pair_kinds(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB,
+                                    int outB, bool b_first, hipStream_t st)
+{
+    const bool dl128 = !bigA && !bigB && gemm_dl128_ok(ga, step_scale(KA), gb);
+    const auto mode = [dl128](const GemmDev &g, bool big) {
+        const bool whole = g.Kb % 128 == 0;
+        if (dl128) return whole ? 2 : 3;
+        return whole ? (big && gemm_dl_ok(g.Kb, g.splits) ? 2 : 0) : 1;
+    };
+    const int modeB = mode(gb, bigB);
+    if constexpr (KA == 3)      // f6 codes: always straight into LDS
+        return bigA ? launch_pair_o<KA, KB, 4, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st)
+                    : launch_pair_o<KA, KB, 2, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
+    else return launch_pair_modes<KA, KB>(ga, gb, gbt, bigA, f32, bigB, mode(ga, bigA), modeB, outB, b_first, st);
 }
 
 }  // namespace hlq

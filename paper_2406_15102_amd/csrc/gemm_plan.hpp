@@ -4,8 +4,11 @@
 
 namespace hlq {
 
-// bytes per operand row: int8 codes, bf16 values, nibble-packed codes
-static inline int row_bytes(int kind, int K) { return kind == 0 ? K : (kind == 1 ? 2 * K : K / 2); }
+// bytes per operand row: int8 codes, bf16 values, nibble-packed codes, codes in the f6 layout (whole 128-byte steps)
+static inline int row_bytes(int kind, int K)
+{
+    return kind == 0 ? K : (kind == 1 ? 2 * K : (kind == 2 ? K / 2 : f6_row_bytes(K)));
+}
 
 // Plan: tile size and number of k splits, from a small cost model (microseconds) fitted to
 // measurements on MI355X: a 256-tile step (128 B of k) costs ~1.6 us and a tile ~12 us of fixed
@@ -13,6 +16,9 @@ static inline int row_bytes(int kind, int K) { return kind == 0 ? K : (kind == 1
 // unit and ~0.95 us when two share it, ~6 us fixed; the split-K partials cost their HBM round trip
 // plus a launch.  A step of the packed product carries twice the MFMAs of a byte-operand step.
 constexpr double P4_STEP_SCALE = 1.8;
+constexpr double F6_STEP_SCALE = 1.0;    // a step of f6 codes: as many MFMA cycles as one of bytes
+// cost of a step of operand kind `kind` in steps of bytes
+static inline double step_scale(int kind) { return kind == 2 ? P4_STEP_SCALE : (kind == 3 ? F6_STEP_SCALE : 1.0); }
 struct GemmPlan {
     bool big;
     int splits;
@@ -101,7 +107,7 @@ static inline GemmDev gemm_dev_cut_tail(GemmDev &g, int tail_rows)
 }
 
 // ---- model of a launch that carries two products (k_gemm_pair.hip says how it is fitted), microseconds ----
-constexpr double kStepBig = 1.3, kPackedScale = 1.8, kStepSmallAlone = 0.6, kStepSmallShared = 0.9;
+constexpr double kStepBig = 1.3, kStepSmallAlone = 0.6, kStepSmallShared = 0.9;
 constexpr double kFixedBig = 16.0, kFixedSmall = 6.5;
 constexpr double kOneStepSaves = 2.0;    // a tile of one step skips the pipeline (gemm_body.hpp)
 constexpr int kSplitChoices[] = {1, 2, 3, 4, 6, 8, 12, 16};

@@ -155,6 +155,7 @@ inline bool bits_ok(int bits)
     return b == HLQ_BITS_4 || b == HLQ_BITS_8 || b == HLQ_BITS_4_PACKED;
 }
 inline float bits_qmax(int bits) { return bits_base(bits) == HLQ_BITS_8 ? 127.0f : 7.0f; }
+inline int bits_codes(int bits) { return bits_base(bits) == HLQ_BITS_4_PACKED ? hlq::kCodesNibbles : hlq::kCodesBytes; }
 inline bool bits_packed(int bits) { return bits_base(bits) == HLQ_BITS_4_PACKED; }
 
 // Workspace of the calls that pass none: per device, either the memory the caller registered with
@@ -286,7 +287,7 @@ int hlq_quantize_g(const void *G, int64_t N, int64_t d_out, int B, uint64_t seed
     const uint64_t key = stream_key(seed, 0);
     return launch_rc(hlq::launch_quant_rows(G, N, static_cast<int>(d_out), B, dtype == HLQ_F32,
                                             static_cast<uint32_t>(key), static_cast<uint32_t>(key >> 32),
-                                            bits_qmax(bits), bits_packed(bits), bits_mant(bits), Gq, sG, coeff,
+                                            bits_qmax(bits), bits_codes(bits), bits_mant(bits), Gq, sG, coeff,
                                             static_cast<hipStream_t>(stream)));
 }
 
@@ -312,7 +313,7 @@ int hlq_quantize_w(const void *W, int64_t d_out, int64_t d_in, int B, uint64_t s
     const uint64_t key = stream_key(seed, 1);
     return launch_rc(hlq::launch_quant_cols(W, static_cast<int>(d_out), static_cast<int>(d_in), B, dtype == HLQ_F32,
                                             static_cast<uint32_t>(key), static_cast<uint32_t>(key >> 32),
-                                            bits_qmax(bits), bits_packed(bits), bits_mant(bits), WqT, sW, coeffT, workspace,
+                                            bits_qmax(bits), bits_codes(bits), bits_mant(bits), WqT, sW, coeffT, workspace,
                                             static_cast<hipStream_t>(stream)));
 }
 
@@ -337,7 +338,7 @@ int hlq_quantize_w_static(const void *W, int64_t d_out, int64_t d_in, int B, uin
     const uint64_t key = stream_key(seed, 1);
     return launch_rc(hlq::launch_quant_cols(W, static_cast<int>(d_out), static_cast<int>(d_in), B, dtype == HLQ_F32,
                                             static_cast<uint32_t>(key), static_cast<uint32_t>(key >> 32),
-                                            bits_qmax(bits), bits_packed(bits), bits_mant(bits), WqT, sW, nullptr, ws,
+                                            bits_qmax(bits), bits_codes(bits), bits_mant(bits), WqT, sW, nullptr, ws,
                                             static_cast<hipStream_t>(stream)));
 }
 
@@ -608,8 +609,11 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     if ((rc = backward_check(G, X, Xc, sXc, W, Wc, sWc, N, d_in, d_out, B, r, dtype, flags, dX, dW)) != HLQ_OK) return rc;
     const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0;
     const float qmax = (flags & HLQ_FLAG_GX_8BIT) ? 127.0f : 7.0f;
-    // 4-bit codes travel two to a byte whenever their rows stay 16-byte aligned that way
-    const bool packed = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && d_out % 32 == 0 && !image;
+    // 4-bit codes travel two to a byte: in the f6 layout unless more than a quarter of its rows would be padding (f6_rows_ok),
+    // else, or where the persistent form of the products is asked for, which multiplies bytes, as nibbles where the rows stay
+    // 16-byte aligned that way
+    const bool four = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && !image;
+    const int codes = four && hlq::f6_rows_ok(static_cast<int>(d_out)) && !hlq::gemm_stream_enabled() ? hlq::kCodesF6 : (four && d_out % 32 == 0 ? hlq::kCodesNibbles : hlq::kCodesBytes);
     const int basis = (flags & HLQ_FLAG_GW_SEQUENCY) ? HLQ_BASIS_SEQUENCY : HLQ_BASIS_NATURAL;
     const bool mant = (flags & HLQ_FLAG_ROUND_MANTISSA) != 0;
 
@@ -634,7 +638,9 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     int8_t *Gq = reinterpret_cast<int8_t *>(ws + L.Gq);
     float *sG = reinterpret_cast<float *>(ws + L.sG);
     const bool wc = (Wc != nullptr);
-    const int8_t *Wq = wc ? static_cast<const int8_t *>(Wc) : reinterpret_cast<const int8_t *>(ws + L.Wq);
+    // codes that were handed over are nibbles or bytes: they are brought into the f6 layout first
+    const bool recode = wc && dX && codes == hlq::kCodesF6;
+    const int8_t *Wq = wc && !recode ? static_cast<const int8_t *>(Wc) : reinterpret_cast<const int8_t *>(ws + L.Wq);
     const float *sW = wc ? sWc : reinterpret_cast<const float *>(ws + L.sW);
     void *Gh = ws + L.GhatT;
     float *sGh = reinterpret_cast<float *>(ws + L.sGhat);
@@ -648,6 +654,13 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     const bool fused = !gwi && fusable;
     const bool fused_q = gwi && fusable;
     const uint64_t kg = stream_key(seed, 0);
+    hlq::FrontRecode jk = hlq::front_recode(recode ? Wc : nullptr, I, O, d_out % 32 == 0, ws + L.Wq);
+    const hlq::FrontRecode no_recode = hlq::front_recode(nullptr, 0, O, false, nullptr);
+    const bool front_mix = hlq::front_mix_enabled();
+    if (recode && !fused_q && !(fused && front_mix)) {      // no launch for it to ride in
+        if ((rc = launch_rc(hlq::launch_f6_recode(jk, st))) != HLQ_OK) return rc;
+        jk = no_recode;
+    }
     hlq::FrontUnpack ju = hlq::front_unpack(nullptr, nullptr, 0);
     if (dW && Xc && (flags & HLQ_FLAG_XC_INT4)) {
         // the activation was kept as 4-bit codes (Sec. 6.1): widened to the int8 operand of the product, beside the
@@ -673,7 +686,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         uint32_t *amax_g = reinterpret_cast<uint32_t *>(ws + (tt > 1 ? L.tabg : L.hws));
         uint32_t *amax_x = reinterpret_cast<uint32_t *>(ws + (tt > 1 ? L.tabx : L.hwsx));
         const uint64_t k3 = stream_key(seed, 3), k2 = stream_key(seed, 2), kw = stream_key(seed, 1);
-        const hlq::FrontRows jr = hlq::front_rows(dX ? G : nullptr, N, O, B, static_cast<uint32_t>(kg),
+        const hlq::FrontRows jr = hlq::front_rows(dX ? G : nullptr, N, O, B, codes, static_cast<uint32_t>(kg),
                                                   static_cast<uint32_t>(kg >> 32), qmax, Gq, sG);
         int8_t *xq = xc ? nullptr : reinterpret_cast<int8_t *>(ws + L.XhatT);
         float *sx = xc ? nullptr : reinterpret_cast<float *>(ws + L.sXhat);
@@ -692,11 +705,11 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         const hlq::FrontFill jf{reinterpret_cast<uint32_t *>(ws + zero_from), tables ? 0 : static_cast<int>((zero_to - zero_from) / 4)};
         const hlq::FrontHla none = hlq::front_hla(nullptr, N, O, B, r, nullptr);
         const hlq::FrontAbsmax none_w = hlq::front_absmax(nullptr, O, I, B, nullptr);
-        const bool k1_later = hlq::front_mix_enabled();
-        const hlq::FrontRows no_rows = hlq::front_rows(nullptr, N, O, B, 0, 0, qmax, nullptr, nullptr);
-        if ((rc = launch_rc(hlq::launch_front(k1_later ? no_rows : jr, none, jf, none, none_w, nullptr, B, basis, f32, packed, st))) != HLQ_OK)
+        const bool k1_later = front_mix;
+        const hlq::FrontRows no_rows = hlq::front_rows(nullptr, N, O, B, codes, 0, 0, qmax, nullptr, nullptr);
+        if ((rc = launch_rc(hlq::launch_front(k1_later ? no_rows : jr, none, jf, none, none_w, no_recode, nullptr, B, basis, f32, codes, st))) != HLQ_OK)
             return rc;
-        if ((rc = launch_rc(hlq::launch_front_q(jg, jx, jw, jq, k1_later ? jr : no_rows, ju, conv, B, basis, f32, packed, st))) != HLQ_OK)
+        if ((rc = launch_rc(hlq::launch_front_q(jg, jx, jw, jq, k1_later ? jr : no_rows, ju, jk, conv, B, basis, f32, codes, st))) != HLQ_OK)
             return rc;
         if (dW && !xc) {
             Xh = xq;
@@ -710,22 +723,22 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     bool w_done = wc || fused_q || !dX;   // handed over by the caller, made by the fused launches above, or not needed
     if (fused) {
         uint16_t *xh = xc ? nullptr : reinterpret_cast<uint16_t *>(ws + L.XhatT);
-        const hlq::FrontRows jr = hlq::front_rows(dX ? G : nullptr, N, O, B, static_cast<uint32_t>(kg),
+        const hlq::FrontRows jr = hlq::front_rows(dX ? G : nullptr, N, O, B, codes, static_cast<uint32_t>(kg),
                                                   static_cast<uint32_t>(kg >> 32), qmax, Gq, sG);
         const hlq::FrontHla jx = hlq::front_hla(dW && !xc ? X : nullptr, N, I, B, r, xh);
         const hlq::FrontHla jg = hlq::front_hla(dW ? G : nullptr, N, O, B, r, static_cast<uint16_t *>(Gh));
-        if (w_done && !conv && hlq::front_mix_enabled()) {
+        if (w_done && !conv && front_mix) {
             // no pass over W here: the front launch alone (its second launch has nothing to do), with the
             // quantiser's and the projections' workgroups in turns
             const hlq::FrontAbsmax none_w = hlq::front_absmax(nullptr, O, I, B, nullptr);
             const hlq::FrontFill no_fill{nullptr, 0};
-            rc = launch_rc(hlq::launch_front(jr, jg, no_fill, jx, none_w, nullptr, B, basis, f32, packed, st));
+            rc = launch_rc(hlq::launch_front(jr, jg, no_fill, jx, none_w, jk, nullptr, B, basis, f32, codes, st));
         } else if (w_done || hlq::cols_full_ok(O, I, B, f32)) {
             // no pass over W here (a convolution, or the turns switched off), or a weight of few rows, which one
             // workgroup per strip of columns quantises completely: everything independent in one launch
             const hlq::FrontColsQ jq = hlq::front_cols_full(w_done ? nullptr : W, O, I, B, static_cast<uint32_t>(kw),
                                                             static_cast<uint32_t>(kw >> 32), qmax, wq, sw);
-            rc = launch_rc(hlq::launch_front_one(jr, jx, jg, jq, conv, B, basis, f32, packed, st));
+            rc = launch_rc(hlq::launch_front_one(jr, jx, jg, jq, conv, B, basis, f32, codes, st));
             w_done = true;
         } else {
             // pass 1 over W rides in the second launch, behind the zeroing of its maxima in the first
@@ -734,8 +747,8 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
             // The first launch takes K1(G) and K3(G) -- and, unless HLQ_OPT_FRONT_INTERLEAVE is off, K3(X) too,
             // see launch_front_t --, the second what is left and pass 1.  The projection straight from an
             // image exists for the first launch only, so a convolution has K3(X) there and K3(G) in the second.
-            if (conv) rc = launch_rc(hlq::launch_front(jr, jx, jf, jg, jw, conv, B, basis, f32, packed, st));
-            else rc = launch_rc(hlq::launch_front(jr, jg, jf, jx, jw, nullptr, B, basis, f32, packed, st));
+            if (conv) rc = launch_rc(hlq::launch_front(jr, jx, jf, jg, jw, no_recode, conv, B, basis, f32, codes, st));
+            else rc = launch_rc(hlq::launch_front(jr, jg, jf, jx, jw, no_recode, nullptr, B, basis, f32, codes, st));
         }
         if (rc != HLQ_OK) return rc;
         if (dW && !xc) Xh = xh;
@@ -743,7 +756,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     if (dX && !fused && !fused_q) {
         // g_x stages 1-2: Q(G H)
         if ((rc = launch_rc(hlq::launch_quant_rows(G, N, O, B, f32, static_cast<uint32_t>(kg),
-                                                   static_cast<uint32_t>(kg >> 32), qmax, packed, mant, Gq, sG, nullptr, st))) != HLQ_OK)
+                                                   static_cast<uint32_t>(kg >> 32), qmax, codes, mant, Gq, sG, nullptr, st))) != HLQ_OK)
             return rc;
     }
     if (dW && !gwi && !fused) {
@@ -781,11 +794,11 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     if (!w_done) {
         if (fused)   // pass 1 ran in the second front launch
             rc = launch_rc(hlq::launch_quant_cols_pass2(W, O, I, B, f32, static_cast<uint32_t>(kw),
-                                                        static_cast<uint32_t>(kw >> 32), qmax, packed, false, wq, sw,
+                                                        static_cast<uint32_t>(kw >> 32), qmax, codes, false, wq, sw,
                                                         nullptr, ws + L.wws, st));
         else
             rc = launch_rc(hlq::launch_quant_cols(W, O, I, B, f32, static_cast<uint32_t>(kw),
-                                                  static_cast<uint32_t>(kw >> 32), qmax, packed, mant, wq, sw, nullptr,
+                                                  static_cast<uint32_t>(kw >> 32), qmax, codes, mant, wq, sw, nullptr,
                                                   ws + L.wws, st));
         if (rc != HLQ_OK) return rc;
     }
@@ -795,7 +808,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     hlq::GemmArgs ax{Gq, Wq, static_cast<int>(N), I, O, sG, sW, invB, dX, f32, nullptr, ws + L.gws, L.gws_bytes};
     hlq::GemmArgs aw{Gh, Xh, O, I, Kc, gwi ? sGh : nullptr, gwi ? sXh : nullptr, invB, dW, f32, nullptr, ws + L.gws,
                      L.gws_bytes};
-    const int kind_x = packed ? 2 : 0, kind_w = gwi ? 0 : 1;
+    const int kind_x = codes == hlq::kCodesF6 ? 3 : (codes == hlq::kCodesNibbles ? 2 : 0), kind_w = gwi ? 0 : 1;
     if (dX && image) {
         if (dW && !(flags & HLQ_FLAG_SEPARATE_PRODUCTS) && hlq::conv_pair_available())
             return launch_rc(hlq::launch_conv_pair(ax, *image, kind_w, aw, st));

@@ -262,6 +262,32 @@ __device__ __forceinline__ void quant_codes(const float *x, int es, float inv, u
     }
 }
 
+// The same codes as floats (whole numbers), for the conversion to 6-bit floats.
+__device__ __forceinline__ void quant_floats4(const float *x, int es, float inv, uint32_t w, float *f)
+{
+    const v2h u01 = round_bits_pair(w, 0x04010400u), u23 = round_bits_pair(w, 0x04030402u);
+    f[0] = __builtin_floorf(__builtin_fmaf(x[0], inv, static_cast<float>(u01[0])));
+    f[1] = __builtin_floorf(__builtin_fmaf(x[es], inv, static_cast<float>(u01[1])));
+    f[2] = __builtin_floorf(__builtin_fmaf(x[2 * es], inv, static_cast<float>(u23[0])));
+    f[3] = __builtin_floorf(__builtin_fmaf(x[3 * es], inv, static_cast<float>(u23[1])));
+}
+template <bool MANT, int NW>
+__device__ __forceinline__ void quant_floats(const float *x, int es, float inv, uint32_t counter, uint32_t k0, uint32_t k1, float *f)
+{
+    if constexpr (MANT) {
+#pragma unroll
+        for (int e = 0; e < 4 * NW; ++e) {
+            const float m = static_cast<float>(__float_as_uint(x[e * es]) & 0x7FFu);
+            f[e] = __builtin_floorf(__builtin_fmaf(x[e * es], inv, __builtin_fmaf(m, 0.00048828125f, 0.000244140625f)));
+        }
+    } else {
+        uint32_t w[NW];
+        rand_words<NW>(counter, k0, k1, w);
+#pragma unroll
+        for (int d = 0; d < NW; ++d) quant_floats4(x + 4 * d * es, es, inv, w[d], f + 4 * d);
+    }
+}
+
 // Four codes as the bytes of a dword, little-endian two's complement (as the int8 MFMA reads them).
 __device__ __forceinline__ uint32_t pack_bytes4(const int *q)
 {
@@ -282,6 +308,60 @@ __device__ __forceinline__ uint32_t pack_nibbles8(const int *q)
 #pragma unroll
     for (int e = 1; e < 8; ++e) r = __builtin_amdgcn_alignbit(static_cast<uint32_t>(q[e]), r, 4);
     return r;
+}
+
+// ---- codes for the 6-bit matrix instructions ("f6") -------------------------------------------
+// The matrix cores multiply 6-bit floats (e2m3) at twice the rate of bytes.  A code in [-7, 7] divided by 8 is a
+// subnormal one: sign in bit 5, |code| in bits 0-2, bits 3 and 4 clear.  So four bits of every six carry anything, and 16
+// codes, three dwords of fields, travel in two: the dwords' fields cover the bits F0, F1 and F2 (bit 3 and 4 of a
+// field never set), the complements of F0 and F1 are disjoint and fill F2, so the third dword hides in the bits that the
+// first two do not use.  It goes in xored with what they have there, which makes getting it out one instruction of three
+// operands (v_bitop3_b32): d0 = a & F0, d1 = b & F1, d2 = (a ^ b) & F2 -- three instructions for 16 codes, half of what
+// two's complement nibbles take to become bytes (Mma16<2>: 6 for 16).
+constexpr uint32_t f6_field_bits(int dword)
+{
+    uint32_t m = 0;
+    for (int b = 0; b < 32; ++b) {
+        const int f = (32 * dword + b) % 6;
+        if (f != 3 && f != 4) m |= 1u << b;
+    }
+    return m;
+}
+constexpr uint32_t F6M0 = f6_field_bits(0), F6M1 = f6_field_bits(1), F6M2 = f6_field_bits(2);
+static_assert((~F6M0 & ~F6M1) == 0 && (~F6M0 | ~F6M1) == F6M2, "the third dword fits where the first two have no field bits");
+
+// 32 codes as floats (integers in [-7, 7]) -> 16 bytes.  The conversion takes its two halves in turns, so a row's codes
+// lie in the order 0, 16, 1, 17, ...: every row of both operands of a product is packed by this function.
+// Codes that are none (a reciprocal scale that is infinite, sums that are not numbers) set one of the bits 3 and 4; they
+// are then taken as the low four bits, two's complement, of what the conversion to an integer gives, as pack_nibbles8
+// and pack_bytes4 take them (0 and -1 where the scale's reciprocal is infinite).
+typedef float v16f_t __attribute__((ext_vector_type(16)));
+typedef unsigned int v6u_t __attribute__((ext_vector_type(6)));
+__device__ __forceinline__ v6u_t f6_convert(const float *f)
+{
+    v16f_t lo, hi;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        lo[e] = f[e];
+        hi[e] = f[16 + e];
+    }
+    return __builtin_bit_cast(v6u_t, __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(lo, hi, 8.0f));
+}
+__device__ __forceinline__ uint4 f6_pack32(float *f)
+{
+    v6u_t d = f6_convert(f);
+    const uint32_t stray = (d[0] & ~F6M0) | (d[1] & ~F6M1) | (d[2] & ~F6M2) | (d[3] & ~F6M0) | (d[4] & ~F6M1) | (d[5] & ~F6M2);
+    if (stray != 0) {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) {
+            const int q = floor_to_int(f[e]);
+            f[e] = static_cast<float>(static_cast<int>(static_cast<uint32_t>(q) << 28) >> 28);
+        }
+        d = f6_convert(f);
+    }
+    const uint32_t x0 = d[1] ^ d[2], x1 = d[0] ^ d[2], x2 = d[4] ^ d[5], x3 = d[3] ^ d[5];
+    return make_uint4((d[0] & F6M0) | (x0 & ~F6M0), (d[1] & F6M1) | (x1 & ~F6M1), (d[3] & F6M0) | (x2 & ~F6M0),
+                      (d[4] & F6M1) | (x3 & ~F6M1));
 }
 
 // Maxima of a lane's CPL columns (bit patterns of non-negative floats): one row of D of them, or `table` rows to be

@@ -7,17 +7,26 @@
 
 namespace hlq {
 
-// K1: rows of G -> codes + per-row scales (and optionally the fp32 coefficients).  `packed`
-// (4-bit codes only): two codes to a byte, O/2 bytes per row, instead of one int8 each.
+// How the codes of the g_x list are stored: one int8 each; 4-bit codes two to a byte, two's complement (O/2 bytes a
+// row); or 4-bit codes in the f6 layout (hlq_device.hpp), f6_row_bytes(O) a row.
+constexpr int kCodesBytes = 0, kCodesNibbles = 1, kCodesF6 = 2;
+// bytes of a row of K codes in the f6 layout: two to a byte, zeros up to whole steps of 128 bytes
+__host__ __device__ constexpr int f6_row_bytes(int K) { return (K + 255) / 256 * 128; }
+// Rows of G are written and read with their padding, and layers of few out-features wait for memory: with half of each
+// row padding (44416 x 176 over 128) a pass took 31.2 us against 30.5 with nibbles.  (Rows that pass fit the scratch of one
+// int8 a code.)
+inline bool f6_rows_ok(int K) { return 2 * K >= 3 * f6_row_bytes(K); }
+
+// K1: rows of G -> codes + per-row scales (and optionally, not with kCodesF6, the fp32 coefficients).
 // `mant`: round by the low 11 mantissa bits of each value instead of the seeded stream (k0, k1 unused).
 hipError_t launch_quant_rows(const void *G, int64_t N, int O, int B, bool is_f32, uint32_t k0, uint32_t k1,
-                             float qmax, bool packed, bool mant, int8_t *Gq, float *sG, float *coeff, hipStream_t st);
+                             float qmax, int codes, bool mant, int8_t *Gq, float *sG, float *coeff, hipStream_t st);
 
 // K1T: W [O, I] -> WqT [I, O] codes + per-in-feature scales.  `ws` holds the partial column
 // maxima and the reciprocal scales: quant_cols_ws_bytes(O, I) bytes.
 size_t quant_cols_ws_bytes(int64_t O, int64_t I);
 hipError_t launch_quant_cols(const void *W, int O, int I, int B, bool is_f32, uint32_t k0, uint32_t k1,
-                             float qmax, bool packed, bool mant, int8_t *WqT, float *sW, float *coeffT, void *ws,
+                             float qmax, int codes, bool mant, int8_t *WqT, float *sW, float *coeffT, void *ws,
                              hipStream_t st);
 
 // The same scratch as a file-scope device array inside the library (k_quant_cols.hip), for callers that
@@ -35,7 +44,7 @@ inline int cols_grid_y(int O, int B) { return (O + 255) / 256; }       // 256/B 
 // K1T split in its two passes, for callers that run pass 1 elsewhere (the fused front launches):
 // pass 2 alone, reading the column maxima pass 1 left in `ws`.
 hipError_t launch_quant_cols_pass2(const void *W, int O, int I, int B, bool is_f32, uint32_t k0, uint32_t k1,
-                                   float qmax, bool packed, bool mant, int8_t *WqT, float *sW, float *coeffT,
+                                   float qmax, int codes, bool mant, int8_t *WqT, float *sW, float *coeffT,
                                    const void *ws, hipStream_t st);
 // The weights that one workgroup per strip of columns quantises completely, both passes, inside the
 // one-launch front (launch_front_one below): at most 256 row blocks (O / B; 64 groups of four lanes
@@ -160,6 +169,11 @@ struct FrontUnpack { // 4-bit codes two to a byte -> one int8 each; n16 pieces o
     int64_t n16;
     int blocks;
 };
+struct FrontRecode { // weight codes [rows][O], one int8 each or two to a byte -> the f6 layout; 256 groups of 32 codes a workgroup
+    const void *in;
+    uint8_t *out;
+    int rows, O, nibbles, blocks;
+};
 struct FrontColsQ {  // pass 2 of K1T
     const void *W;
     int O, I;
@@ -201,15 +215,17 @@ FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *am
 FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, int table, uint32_t k0, uint32_t k1,
                        float qmax, int8_t *WqT, float *sW);
 FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in);
+FrontRecode front_recode(const void *in, int rows, int O, bool nibbles, void *out);   // in == NULL: empty
+hipError_t launch_f6_recode(const FrontRecode &jk, hipStream_t st);
 // The integer g_w list in two launches: every pass 1 (maxima of projected G, projected X, transformed W),
 // then every pass 2; where maxima are merged by atomics, a launch of launch_front zeroes them first.  `jr`, if it
 // is not empty, is K1(G) riding in the first of them, its workgroups in turns with the passes 1; `ju`, if it is not
-// empty, widens a 4-bit store beside them.  conv: NULL, or the geometry whose column matrix jx.T (an image) stands for.
+// empty, widens a 4-bit store beside them, and `jk` brings weight codes into the f6 layout (codes == kCodesF6).  conv: NULL, or the geometry whose column matrix jx.T (an image) stands for.
 hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
-                          const FrontRows &jr, const FrontUnpack &ju, const ConvShape *conv, int B, int basis, bool is_f32,
-                          bool packed, hipStream_t st);
+                          const FrontRows &jr, const FrontUnpack &ju, const FrontRecode &jk, const ConvShape *conv, int B, int basis, bool is_f32,
+                          int codes, hipStream_t st);
 bool front_fusable(int O, int B);
-FrontRows front_rows(const void *G, int64_t N, int O, int B, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG);
+FrontRows front_rows(const void *G, int64_t N, int O, int B, int codes, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG);
 FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, uint16_t *out);
 FrontAbsmax front_absmax(const void *W, int O, int I, int B, uint32_t *amax, int table = 0);
 // all of K1T for a weight that passes cols_full_ok: one workgroup per strip of columns (gy carries the
@@ -218,10 +234,10 @@ FrontColsQ front_cols_full(const void *W, int O, int I, int B, uint32_t k0, uint
 // K1(G) | K3(X) | K3(G) | all of K1T in ONE launch (jq from front_cols_full, or without a weight):
 // nothing has to be zeroed beforehand and no launch for pass 2 follows.
 hipError_t launch_front_one(const FrontRows &jr, const FrontHla &jx, const FrontHla &jg, const FrontColsQ &jq,
-                            const ConvShape *conv, int B, int basis, bool is_f32, bool packed, hipStream_t st);
+                            const ConvShape *conv, int B, int basis, bool is_f32, int codes, hipStream_t st);
 // conv: NULL, or the geometry whose column matrix jx.T (an image) stands for; needs hla_conv_ok.
 hipError_t launch_front(const FrontRows &jr, const FrontHla &jx, const FrontFill &jf, const FrontHla &jg,
-                        const FrontAbsmax &jw, const ConvShape *conv, int B, int basis, bool is_f32, bool packed,
+                        const FrontAbsmax &jw, const FrontRecode &jk, const ConvShape *conv, int B, int basis, bool is_f32, int codes,
                         hipStream_t st);
 // whether launch_front lets K1 (jr) and its first K3 job (jx) share the read of their tensor; switch for A/B
 FrontShare front_share(const FrontRows &jr, const FrontHla &jx, int B, bool is_f32);
@@ -246,7 +262,8 @@ hipError_t launch_hla_quant(const void *T, int64_t N, int D, int B, int r, int b
 hipError_t launch_unpack_nibbles(const void *in, int8_t *out, int64_t bytes_in, hipStream_t st);
 
 // K2 / K4: C = alpha * sA (x) sB * (A . Bm^T).  kind 0: int8 operands, int32 accumulate;
-// kind 1: bf16 operands, fp32 accumulate.  K in elements.
+// kind 1: bf16 operands, fp32 accumulate; kind 2: 4-bit codes two to a byte; kind 3: 4-bit codes in the f6
+// layout.  K in elements.
 struct GemmArgs {
     const void *A;
     const void *Bm;
@@ -290,6 +307,7 @@ hipError_t launch_gemm_pair(int kindA, const GemmArgs &a, int kindB, const GemmA
 bool gemm_stream_wanted(int kindA, const GemmArgs &a, int kindB, const GemmArgs *b);
 hipError_t launch_gemm_stream(int kindA, const GemmArgs &a, int kindB, const GemmArgs *b, hipStream_t st);
 void gemm_stream_enable(bool on);
+bool gemm_stream_enabled();
 void gemm_dl_enable(bool on);   // operands of 256-tiles straight into LDS where the shape allows (default on)
 void gemm_tail_enable(bool on);   // 192-row tiles for the last rows of a product whose last round would be partly empty (default on)
 void gemm_plan_force(int tile, int splits);   // measurement overrides of the plans, see gemm_plan.hpp

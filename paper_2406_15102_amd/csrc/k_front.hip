@@ -26,6 +26,17 @@ namespace hlq {
 
 FrontMix front_mix_of(int n1, int n3);
 
+// workgroup `blk` of K1
+template <typename Tin, int B, int CODES>
+__device__ __forceinline__ void front_rows_body(const FrontRows &jr, int blk)
+{
+    const Tin *G = static_cast<const Tin *>(jr.G);
+    if constexpr (CODES == kCodesF6)
+        quant_rows_f6_body<Tin, B, 256>(G, jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax, reinterpret_cast<uint8_t *>(jr.Gq), jr.sG, blk);
+    else
+        quant_rows_body<Tin, B, 256, CODES == kCodesNibbles>(G, jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax, jr.Gq, jr.sG, nullptr, blk);
+}
+
 // Workgroup b of the n1 + n3 that two kinds of job share, handed out in turns (FrontMix): k1 >= 0, the index
 // among the first kind, or k3 >= 0, among the second; both < 0 past the end, with b counted from there.
 __device__ __forceinline__ void front_turns(const FrontMix &jm, int &b, int n1, int n3, int &k1, int &k3)
@@ -45,12 +56,26 @@ __device__ __forceinline__ void front_turns(const FrontMix &jm, int &b, int n1, 
     else b -= k1_left + k3_left;
 }
 
+// what comes behind the jobs of the first launch: the zeroing, then the weight codes that were handed over, brought into
+// the f6 layout
+template <int CODES>
+__device__ __forceinline__ void front_fill_or_recode(const FrontFill &jf, const FrontRecode &jk, int b)
+{
+    const int fill = (jf.n + 255) >> 8;
+    if (b < fill) {
+        const int i = b * 256 + threadIdx.x;
+        if (i < jf.n) jf.p[i] = 0u;
+    } else if constexpr (CODES == kCodesF6) {
+        f6_recode_body(jk, b - fill);
+    }
+}
+
 // CONV: X is a channels-last image and K3 reads its column matrix through ConvRows.  A kernel of
 // its own: the extra address arithmetic would cost the matrix variant registers, and with them a
 // wavefront of occupancy at B = 32.
-template <typename Tin, int B, bool PACKED, int BASIS, bool CONV>
+template <typename Tin, int B, int CODES, int BASIS, bool CONV>
 __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, FrontFill jf, FrontConv jc, FrontShare js,
-                                                 FrontMix jm, FrontHla jy)
+                                                 FrontMix jm, FrontHla jy, FrontRecode jk)
 {
     int b = blockIdx.x;
     if (!CONV && js.on) {
@@ -65,24 +90,20 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
             if (v < js.nk1) {
                 const int blk = grp * js.nk1 + v;
                 if (blk < jr.blocks)
-                    quant_rows_body<Tin, B, 256, PACKED>(static_cast<const Tin *>(jr.G), jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax,
-                                                         jr.Gq, jr.sG, nullptr, blk);
+                    front_rows_body<Tin, B, CODES>(jr, blk);
             } else {
                 hla_body<Tin, B, BASIS, 2>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.out, nullptr, v - js.nk1, grp);
             }
             return;
         }
-        b -= js.blocks;
-        const int i = b * 256 + threadIdx.x;
-        if (i < jf.n) jf.p[i] = 0u;
+        front_fill_or_recode<CODES>(jf, jk, b - js.blocks);
         return;
     }
     if (!CONV && jm.gran) {
         int k1, k3;
         front_turns(jm, b, jr.blocks, jx.nb + jy.nb, k1, k3);
         if (k1 >= 0) {
-            quant_rows_body<Tin, B, 256, PACKED>(static_cast<const Tin *>(jr.G), jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax, jr.Gq,
-                                                 jr.sG, nullptr, k1);
+            front_rows_body<Tin, B, CODES>(jr, k1);
         } else if (k3 >= 0 && k3 < jx.nb) {
             int bx, by;
             hla_job_map(k3, jx.gx, jx.grp, bx, by);
@@ -92,14 +113,12 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
             hla_job_map(k3 - jx.nb, jy.gx, jy.grp, bx, by);
             hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.out, nullptr, bx, by);
         } else {
-            const int i = b * 256 + threadIdx.x;
-            if (i < jf.n) jf.p[i] = 0u;
+            front_fill_or_recode<CODES>(jf, jk, b);
         }
         return;
     }
     if (b < jr.blocks) {
-        quant_rows_body<Tin, B, 256, PACKED>(static_cast<const Tin *>(jr.G), jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax, jr.Gq,
-                                             jr.sG, nullptr, b);
+        front_rows_body<Tin, B, CODES>(jr, b);
         return;
     }
     b -= jr.blocks;
@@ -119,22 +138,20 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
         hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.out, nullptr, bx, by);
         return;
     }
-    b -= jy.nb;
-    const int i = b * 256 + threadIdx.x;
-    if (i < jf.n) jf.p[i] = 0u;
+    front_fill_or_recode<CODES>(jf, jk, b - jy.nb);
 }
 
 // The whole front in one launch, for weights of few rows: a workgroup per strip of columns runs both
 // passes of K1T (cols_full_body), so neither a zeroing launch before it nor a launch for pass 2 is needed.
 // (three wavefronts per SIMD asked for below B = 64, which the other jobs had before the strip quantiser
 // joined them: left alone, the register allocator spends all 256 registers on it)
-template <typename Tin, int B, bool PACKED, int BASIS, bool CONV>
+template <typename Tin, int B, int CODES, int BASIS, bool CONV>
 __global__ __launch_bounds__(256, B == 64 ? 2 : 3) void k_front_one(FrontRows jr, FrontHla jx, FrontHla jg, FrontColsQ jq, FrontConv jc,
                                                                     FrontMix jm)
 {
     int b = blockIdx.x;
     if (b < jq.gx) {       // first: these workgroups pass over their strip twice
-        cols_full_body<Tin, B, PACKED>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.k0, jq.k1, jq.qmax, jq.WqT, jq.sW, b, jq.gy);
+        cols_full_body<Tin, B, CODES>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.k0, jq.k1, jq.qmax, jq.WqT, jq.sW, b, jq.gy);
         return;
     }
     b -= jq.gx;
@@ -146,8 +163,7 @@ __global__ __launch_bounds__(256, B == 64 ? 2 : 3) void k_front_one(FrontRows jr
         b = k1 >= 0 ? k1 : jr.blocks + k3;
     }
     if (b < jr.blocks) {
-        quant_rows_body<Tin, B, 256, PACKED>(static_cast<const Tin *>(jr.G), jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax, jr.Gq,
-                                             jr.sG, nullptr, b);
+        front_rows_body<Tin, B, CODES>(jr, b);
         return;
     }
     b -= jr.blocks;
@@ -183,9 +199,9 @@ __global__ __launch_bounds__(256) void k_front_b(FrontHla jg, FrontAbsmax jw)
 // integer g_w list, pass 1 of everything: maxima of the kept coefficients of G and of X, of H^T W
 // With jr (the row quantiser of G, which waits for nothing) riding along, in turns: its arithmetic beside three
 // passes that only read.
-template <typename Tin, int B, int BASIS, bool PACKED, bool CONV>
+template <typename Tin, int B, int BASIS, int CODES, bool CONV>
 __global__ __launch_bounds__(256) void k_front_q1(FrontHlaQ jg, FrontHlaQ jx, FrontAbsmax jw, FrontRows jr, FrontMix jm,
-                                                  FrontUnpack ju, FrontConv jc)
+                                                  FrontUnpack ju, FrontConv jc, FrontRecode jk)
 {
     int b = blockIdx.x;
     if (jr.blocks > 0) {
@@ -204,8 +220,7 @@ __global__ __launch_bounds__(256) void k_front_q1(FrontHlaQ jg, FrontHlaQ jx, Fr
             b -= jr.blocks;
         }
         if (k1 >= 0) {
-            quant_rows_body<Tin, B, 256, PACKED>(static_cast<const Tin *>(jr.G), jr.N, jr.O, jr.T, jr.k0, jr.k1, jr.qmax, jr.Gq,
-                                                 jr.sG, nullptr, k1);
+            front_rows_body<Tin, B, CODES>(jr, k1);
             return;
         }
     }
@@ -228,12 +243,18 @@ __global__ __launch_bounds__(256) void k_front_q1(FrontHlaQ jg, FrontHlaQ jx, Fr
         return;
     }
     b -= jw.gx * jw.gy;
+    if constexpr (CODES == kCodesF6) {
+        if (b >= ju.blocks) {
+            f6_recode_body(jk, b - ju.blocks);
+            return;
+        }
+    }
     const int64_t i = static_cast<int64_t>(b) * 256 + threadIdx.x;
     if (i < ju.n16) unpack_nibbles16(static_cast<const uint4 *>(ju.in), static_cast<uint4 *>(ju.out), i);
 }
 
 // pass 2 of everything: int8 codes of projected G and X, codes of the weight
-template <typename Tin, int B, int BASIS, bool PACKED, bool CONV>
+template <typename Tin, int B, int BASIS, int CODES, bool CONV>
 __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, FrontColsQ jq, FrontConv jc)
 {
     // backwards through the jobs and through each of them (reverse_same_xcd): what the passes that took the maxima
@@ -256,8 +277,12 @@ __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, Fr
         return;
     }
     b -= jx.gx * jx.gy;
-    cols_quantize_body<Tin, B, PACKED>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.amax, jq.k0, jq.k1, jq.qmax, jq.WqT,
-                                       jq.sW, nullptr, b % jq.gx, b / jq.gx, jq.table);
+    if constexpr (CODES == kCodesF6)
+        cols_quantize_f6_body<Tin, B>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.amax, jq.k0, jq.k1, jq.qmax,
+                                      reinterpret_cast<uint8_t *>(jq.WqT), jq.sW, b % jq.gx, b / jq.gx, jq.table);
+    else
+        cols_quantize_body<Tin, B, CODES == kCodesNibbles>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.amax, jq.k0, jq.k1, jq.qmax,
+                                                           jq.WqT, jq.sW, nullptr, b % jq.gx, b / jq.gx, jq.table);
 }
 
 FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in)
@@ -265,6 +290,22 @@ FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in)
     FrontUnpack j{in, out, in ? bytes_in / 16 : 0, 0};
     j.blocks = static_cast<int>((j.n16 + 255) / 256);
     return j;
+}
+
+FrontRecode front_recode(const void *in, int rows, int O, bool nibbles, void *out)
+{
+    FrontRecode j{in, static_cast<uint8_t *>(out), in ? rows : 0, O, nibbles ? 1 : 0, 0};
+    j.blocks = static_cast<int>((static_cast<int64_t>(j.rows) * (f6_row_bytes(O) / 16) + 255) / 256);
+    return j;
+}
+
+__global__ __launch_bounds__(256) void k_f6_recode(FrontRecode jk) { f6_recode_body(jk, blockIdx.x); }
+
+hipError_t launch_f6_recode(const FrontRecode &jk, hipStream_t st)
+{
+    if (jk.blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_f6_recode, dim3(jk.blocks), dim3(256), 0, st, jk);
+    return hipGetLastError();
 }
 
 FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, int table, uint32_t k0, uint32_t k1,
@@ -287,33 +328,35 @@ FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax,
     return j;
 }
 
-template <typename Tin, int B, int BASIS, bool PACKED, bool CONV>
+template <typename Tin, int B, int BASIS, int CODES, bool CONV>
 static hipError_t launch_front_q_t(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
-                                   const FrontRows &jr, const FrontUnpack &ju, const FrontConv &jc, hipStream_t st)
+                                   const FrontRows &jr, const FrontUnpack &ju, const FrontRecode &jk, const FrontConv &jc, hipStream_t st)
 {
     const int n3 = jg.gx * jg.gy + jx.gx * jx.gy + jw.gx * jw.gy;
-    const int n1 = n3 + jr.blocks + ju.blocks;
+    const int n1 = n3 + jr.blocks + ju.blocks + jk.blocks;
     const FrontMix jm = jr.blocks > 0 ? front_mix_of(jr.blocks, n3) : FrontMix{0, 0, 0};
-    if (n1 > 0) hipLaunchKernelGGL((k_front_q1<Tin, B, BASIS, PACKED, CONV>), dim3(n1), dim3(256), 0, st, jg, jx, jw, jr, jm, ju, jc);
+    if (n1 > 0) hipLaunchKernelGGL((k_front_q1<Tin, B, BASIS, CODES, CONV>), dim3(n1), dim3(256), 0, st, jg, jx, jw, jr, jm, ju, jc, jk);
     const int n2 = jg.gx * jg.gy + jx.gx * jx.gy + jq.gx * jq.gy;
-    if (n2 > 0) hipLaunchKernelGGL((k_front_q2<Tin, B, BASIS, PACKED, CONV>), dim3(n2), dim3(256), 0, st, jg, jx, jq, jc);
+    if (n2 > 0) hipLaunchKernelGGL((k_front_q2<Tin, B, BASIS, CODES, CONV>), dim3(n2), dim3(256), 0, st, jg, jx, jq, jc);
     return hipGetLastError();
 }
 
 template <typename Tin, int B, int BASIS>
 static hipError_t launch_front_q_p(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
-                                   const FrontRows &jr, const FrontUnpack &ju, const FrontConv &jc, bool packed, hipStream_t st)
+                                   const FrontRows &jr, const FrontUnpack &ju, const FrontRecode &jk, const FrontConv &jc, int codes, hipStream_t st)
 {
-    if (jc.on)
-        return packed ? launch_front_q_t<Tin, B, BASIS, true, true>(jg, jx, jw, jq, jr, ju, jc, st)
-                      : launch_front_q_t<Tin, B, BASIS, false, true>(jg, jx, jw, jq, jr, ju, jc, st);
-    return packed ? launch_front_q_t<Tin, B, BASIS, true, false>(jg, jx, jw, jq, jr, ju, jc, st)
-                  : launch_front_q_t<Tin, B, BASIS, false, false>(jg, jx, jw, jq, jr, ju, jc, st);
+#define HLQ_FRONT_Q(CV)                                                                                                    \
+    return codes == kCodesF6 ? launch_front_q_t<Tin, B, BASIS, kCodesF6, CV>(jg, jx, jw, jq, jr, ju, jk, jc, st)               \
+                             : (codes == kCodesNibbles ? launch_front_q_t<Tin, B, BASIS, kCodesNibbles, CV>(jg, jx, jw, jq, jr, ju, jk, jc, st) \
+                                                       : launch_front_q_t<Tin, B, BASIS, kCodesBytes, CV>(jg, jx, jw, jq, jr, ju, jk, jc, st))
+    if (jc.on) HLQ_FRONT_Q(true);
+    HLQ_FRONT_Q(false);
+#undef HLQ_FRONT_Q
 }
 
 hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontAbsmax &jw, const FrontColsQ &jq,
-                          const FrontRows &jr, const FrontUnpack &ju, const ConvShape *conv, int B, int basis, bool is_f32,
-                          bool packed, hipStream_t st)
+                          const FrontRows &jr, const FrontUnpack &ju, const FrontRecode &jk, const ConvShape *conv, int B, int basis, bool is_f32,
+                          int codes, hipStream_t st)
 {
     FrontConv jc{};
     if (conv && jx.T) {
@@ -324,10 +367,10 @@ hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontA
 #define HLQ_FRONTQ_CASE(BB)                                                                         \
     case BB:                                                                                        \
         if (basis)                                                                                  \
-            return is_f32 ? launch_front_q_p<float, BB, 1>(jg, jx, jw, jq, jr, ju, jc, packed, st)  \
-                          : launch_front_q_p<bf16_t, BB, 1>(jg, jx, jw, jq, jr, ju, jc, packed, st); \
-        return is_f32 ? launch_front_q_p<float, BB, 0>(jg, jx, jw, jq, jr, ju, jc, packed, st)      \
-                      : launch_front_q_p<bf16_t, BB, 0>(jg, jx, jw, jq, jr, ju, jc, packed, st);
+            return is_f32 ? launch_front_q_p<float, BB, 1>(jg, jx, jw, jq, jr, ju, jk, jc, codes, st)  \
+                          : launch_front_q_p<bf16_t, BB, 1>(jg, jx, jw, jq, jr, ju, jk, jc, codes, st); \
+        return is_f32 ? launch_front_q_p<float, BB, 0>(jg, jx, jw, jq, jr, ju, jk, jc, codes, st)      \
+                      : launch_front_q_p<bf16_t, BB, 0>(jg, jx, jw, jq, jr, ju, jk, jc, codes, st);
     switch (B) {
         HLQ_FRONTQ_CASE(16)
         HLQ_FRONTQ_CASE(32)
@@ -343,11 +386,11 @@ bool front_fusable(int O, int B)
     return T > 0;   // rows that need the 1024-thread K1 keep their own launch
 }
 
-FrontRows front_rows(const void *G, int64_t N, int O, int B, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG)
+FrontRows front_rows(const void *G, int64_t N, int O, int B, int codes, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG)
 {
     FrontRows j{G, N, O, 0, k0, k1, qmax, Gq, sG, 0};
     if (!G) return j;
-    j.T = quant_rows_lanes(O, B);
+    j.T = codes == kCodesF6 ? quant_rows_f6_lanes(O) : quant_rows_lanes(O, B);
     const int rows_per_block = 256 / j.T;     // T == 256: one row per workgroup
     j.blocks = static_cast<int>((N + rows_per_block - 1) / rows_per_block);
     return j;
@@ -460,9 +503,15 @@ FrontShare front_share(const FrontRows &jr, const FrontHla &jx, int B, bool is_f
     return s;
 }
 
+// launch LAUNCH(codes, CONV) for the codes asked for
+#define HLQ_FRONT_CODES(LAUNCH, CONV)                         \
+    if (codes == kCodesF6) LAUNCH(kCodesF6, CONV);            \
+    else if (codes == kCodesNibbles) LAUNCH(kCodesNibbles, CONV); \
+    else LAUNCH(kCodesBytes, CONV);
+
 template <typename Tin, int B, int BASIS>
 static hipError_t launch_front_t(const FrontRows &jr, const FrontHla &jx, const FrontFill &jf, const FrontHla &jg,
-                                 const FrontAbsmax &jw, const FrontConv &jc, bool packed, hipStream_t st)
+                                 const FrontAbsmax &jw, const FrontRecode &jk, const FrontConv &jc, int codes, hipStream_t st)
 {
     const FrontShare js = jc.on ? FrontShare{} : front_share(jr, jx, B, sizeof(Tin) == 4);
     // Unless that is switched off, the first launch takes both projections (the second is left with the pass
@@ -473,13 +522,13 @@ static hipError_t launch_front_t(const FrontRows &jr, const FrontHla &jx, const 
     const FrontMix jm = (jc.on || js.on) ? FrontMix{0, 0, 0} : front_mix(jr, jx, both ? jg.nb : 0);
     const FrontHla &jy = both ? jg : none;        // second projection of the first launch
     const FrontHla &jb = both ? none : jg;        // projection of the second launch
-    const int na = (js.on ? js.blocks : jr.blocks + jx.nb + jy.nb) + (jf.n + 255) / 256;
+    const int na = (js.on ? js.blocks : jr.blocks + jx.nb + jy.nb) + (jf.n + 255) / 256 + jk.blocks;
     if (na > 0) {
-#define HLQ_FRONT_A(P, CV) hipLaunchKernelGGL((k_front_a<Tin, B, P, BASIS, CV>), dim3(na), dim3(256), 0, st, jr, jx, jf, jc, js, jm, jy)
+#define HLQ_FRONT_A(P, CV) hipLaunchKernelGGL((k_front_a<Tin, B, P, BASIS, CV>), dim3(na), dim3(256), 0, st, jr, jx, jf, jc, js, jm, jy, jk)
         if (jc.on) {
-            if (packed) HLQ_FRONT_A(true, true); else HLQ_FRONT_A(false, true);
+            HLQ_FRONT_CODES(HLQ_FRONT_A, true)
         } else {
-            if (packed) HLQ_FRONT_A(true, false); else HLQ_FRONT_A(false, false);
+            HLQ_FRONT_CODES(HLQ_FRONT_A, false)
         }
 #undef HLQ_FRONT_A
     }
@@ -490,7 +539,7 @@ static hipError_t launch_front_t(const FrontRows &jr, const FrontHla &jx, const 
 
 template <typename Tin, int B, int BASIS>
 static hipError_t launch_front_one_t(const FrontRows &jr, const FrontHla &jx, const FrontHla &jg, const FrontColsQ &jq,
-                                     const FrontConv &jc, bool packed, hipStream_t st)
+                                     const FrontConv &jc, int codes, hipStream_t st)
 {
     const int n = jq.gx + jr.blocks + jx.nb + jg.nb;
     if (n == 0) return hipSuccess;
@@ -498,16 +547,16 @@ static hipError_t launch_front_one_t(const FrontRows &jr, const FrontHla &jx, co
     const FrontMix jm = (jr.G && jr.blocks >= 1024) ? front_mix_of(jr.blocks, jx.nb + jg.nb) : FrontMix{0, 0, 0};
 #define HLQ_FRONT_ONE(P, CV) hipLaunchKernelGGL((k_front_one<Tin, B, P, BASIS, CV>), dim3(n), dim3(256), 0, st, jr, jx, jg, jq, jc, jm)
     if (jc.on) {
-        if (packed) HLQ_FRONT_ONE(true, true); else HLQ_FRONT_ONE(false, true);
+        HLQ_FRONT_CODES(HLQ_FRONT_ONE, true)
     } else {
-        if (packed) HLQ_FRONT_ONE(true, false); else HLQ_FRONT_ONE(false, false);
+        HLQ_FRONT_CODES(HLQ_FRONT_ONE, false)
     }
 #undef HLQ_FRONT_ONE
     return hipGetLastError();
 }
 
 hipError_t launch_front_one(const FrontRows &jr, const FrontHla &jx, const FrontHla &jg, const FrontColsQ &jq,
-                            const ConvShape *conv, int B, int basis, bool is_f32, bool packed, hipStream_t st)
+                            const ConvShape *conv, int B, int basis, bool is_f32, int codes, hipStream_t st)
 {
     FrontConv jc{};
     if (conv) {
@@ -519,10 +568,10 @@ hipError_t launch_front_one(const FrontRows &jr, const FrontHla &jx, const Front
 #define HLQ_FRONT1_CASE(BB)                                                                     \
     case BB:                                                                                    \
         if (basis)                                                                              \
-            return is_f32 ? launch_front_one_t<float, BB, 1>(jr, jx, jg, jq, jc, packed, st)    \
-                          : launch_front_one_t<bf16_t, BB, 1>(jr, jx, jg, jq, jc, packed, st);  \
-        return is_f32 ? launch_front_one_t<float, BB, 0>(jr, jx, jg, jq, jc, packed, st)        \
-                      : launch_front_one_t<bf16_t, BB, 0>(jr, jx, jg, jq, jc, packed, st);
+            return is_f32 ? launch_front_one_t<float, BB, 1>(jr, jx, jg, jq, jc, codes, st)    \
+                          : launch_front_one_t<bf16_t, BB, 1>(jr, jx, jg, jq, jc, codes, st);  \
+        return is_f32 ? launch_front_one_t<float, BB, 0>(jr, jx, jg, jq, jc, codes, st)        \
+                      : launch_front_one_t<bf16_t, BB, 0>(jr, jx, jg, jq, jc, codes, st);
     switch (B) {
         HLQ_FRONT1_CASE(16)
         HLQ_FRONT1_CASE(32)
@@ -533,7 +582,7 @@ hipError_t launch_front_one(const FrontRows &jr, const FrontHla &jx, const Front
 }
 
 hipError_t launch_front(const FrontRows &jr, const FrontHla &jx, const FrontFill &jf, const FrontHla &jg,
-                        const FrontAbsmax &jw, const ConvShape *conv, int B, int basis, bool is_f32, bool packed,
+                        const FrontAbsmax &jw, const FrontRecode &jk, const ConvShape *conv, int B, int basis, bool is_f32, int codes,
                         hipStream_t st)
 {
     FrontConv jc{};
@@ -545,10 +594,10 @@ hipError_t launch_front(const FrontRows &jr, const FrontHla &jx, const FrontFill
 #define HLQ_FRONT_CASE(BB)                                                                      \
     case BB:                                                                                    \
         if (basis)                                                                              \
-            return is_f32 ? launch_front_t<float, BB, 1>(jr, jx, jf, jg, jw, jc, packed, st)        \
-                          : launch_front_t<bf16_t, BB, 1>(jr, jx, jf, jg, jw, jc, packed, st);      \
-        return is_f32 ? launch_front_t<float, BB, 0>(jr, jx, jf, jg, jw, jc, packed, st)            \
-                      : launch_front_t<bf16_t, BB, 0>(jr, jx, jf, jg, jw, jc, packed, st);
+            return is_f32 ? launch_front_t<float, BB, 1>(jr, jx, jf, jg, jw, jk, jc, codes, st)        \
+                          : launch_front_t<bf16_t, BB, 1>(jr, jx, jf, jg, jw, jk, jc, codes, st);      \
+        return is_f32 ? launch_front_t<float, BB, 0>(jr, jx, jf, jg, jw, jk, jc, codes, st)            \
+                      : launch_front_t<bf16_t, BB, 0>(jr, jx, jf, jg, jw, jk, jc, codes, st);
     switch (B) {
         HLQ_FRONT_CASE(16)
         HLQ_FRONT_CASE(32)

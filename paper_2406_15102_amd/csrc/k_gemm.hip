@@ -41,13 +41,19 @@ template <int KIND, int OUT>
 __global__ __launch_bounds__(256) void k_gemm_dl(GemmDev g, GemmDev gt, int n_main)
 {
     const int b = static_cast<int>(blockIdx.x);
-    if constexpr (KIND != 2 && OUT != 2 && OUT != 3) {
+    if constexpr (KIND < 2 && OUT != 2 && OUT != 3) {
         if (b >= n_main) {
             gemm_tile_dl<KIND, 6, OUT>(gt, b - n_main);
             return;
         }
     }
     gemm_tile_dl<KIND, 8, OUT>(g, b);
+}
+
+template <int OUT>
+__global__ __launch_bounds__(256) void k_gemm_f6_128(GemmDev g)
+{
+    gemm_tile_dl<3, 4, OUT, 4>(g, static_cast<int>(blockIdx.x));
 }
 
 template <int KIND, int WM, int WN, int KCH, bool TAIL, int OUT>
@@ -118,7 +124,7 @@ GemmPlan plan_for(int kind, int M, int N, int K, size_t ws_bytes, bool allow_spl
 {
     // a step of the packed product carries twice the MFMAs of a byte-operand step
     const int nk = (row_bytes(kind, K) + 127) / 128;
-    GemmPlan p = plan_gemm(M, N, nk, kind == 2 ? P4_STEP_SCALE : 1.0, ws_bytes, allow_split);
+    GemmPlan p = plan_gemm(M, N, nk, step_scale(kind), ws_bytes, allow_split);
     if (const int t = gemm_plan_forced_tile()) p.big = t == 256;
     if (const int S = gemm_plan_forced_splits(nk, static_cast<double>(M) * N, ws_bytes, allow_split)) p.splits = S;
     return p;
@@ -176,7 +182,7 @@ static hipError_t launch_dl(const GemmArgs &a, int splits, hipStream_t st)
     GemmDev g = gemm_dev(KIND, a, 256, 256, splits);
     GemmDev gt = g;
     gt.tiles_m = 0;
-    if (KIND != 2 && (OUT == 0 || OUT == 1) && splits == 1) {
+    if (KIND < 2 && (OUT == 0 || OUT == 1) && splits == 1) {
         const int tail_rows = gemm_tail_rows(a.M, a.N, 0);
         if (tail_rows > 0) gt = gemm_dev_cut_tail(g, tail_rows);
     }
@@ -217,12 +223,34 @@ static hipError_t launch_t(const GemmArgs &a, int splits, hipStream_t st)
     return a.c_is_f32 ? launch_o<KIND, WM, WN, KCH, 1>(a, 1, st) : launch_o<KIND, WM, WN, KCH, 0>(a, 1, st);
 }
 
+// f6 codes: always straight into LDS, rows being whole steps by construction
+template <int OUT>
+static hipError_t launch_f6(const GemmArgs &a, const GemmPlan &p, hipStream_t st)
+{
+    if (p.big) return launch_dl<3, OUT>(a, p.splits, st);
+    const GemmDev g = gemm_dev(3, a, 128, 128, p.splits);
+    static bool attr_set = false;     // idempotent; racing callers set the same value
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_f6_128<OUT>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kGemmDl128LdsBytes));
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((k_gemm_f6_128<OUT>), dim3(g.tiles_m * g.tiles_n * p.splits), dim3(256), kGemmDl128LdsBytes, st, g);
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm_nt(int kind, const GemmArgs &a, hipStream_t st)
 {
     const bool can_split = a.ws != nullptr && a.C != nullptr && (reinterpret_cast<uintptr_t>(a.ws) & 15) == 0;
     const GemmPlan p = plan_for(kind, a.M, a.N, a.K, a.ws_bytes, can_split);
     if (p.big && p.splits == 1 && gemm_stream_wanted(kind, a, 0, nullptr)) return launch_gemm_stream(kind, a, 0, nullptr, st);
     if (kind == 0) return p.big ? launch_t<0, 4, 4, 8>(a, p.splits, st) : launch_t<0, 2, 2, 8>(a, p.splits, st);
+    if (kind == 3) {
+        if (p.splits == 1) return a.c_is_f32 ? launch_f6<1>(a, p, st) : launch_f6<0>(a, p, st);
+        const hipError_t e = launch_f6<3>(a, p, st);      // partials as integers
+        return e == hipSuccess ? launch_splitk_reduce(0, a, p.splits, st) : e;
+    }
     if (kind == 2) return p.big ? launch_t<2, 4, 4, 8>(a, p.splits, st) : launch_t<2, 2, 2, 8>(a, p.splits, st);
     return p.big ? launch_t<1, 4, 4, 8>(a, p.splits, st) : launch_t<1, 2, 2, 8>(a, p.splits, st);
 }

@@ -8,6 +8,10 @@ namespace hlq {
 
 hipError_t launch_pair_21(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB, int outB,
                           bool b_first, hipStream_t st);
+hipError_t launch_pair_31(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB, int outB,
+                          bool b_first, hipStream_t st);
+hipError_t launch_pair_30(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB, int outB,
+                          bool b_first, hipStream_t st);
 hipError_t launch_pair_20(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB, int outB,
                           bool b_first, hipStream_t st);
 hipError_t launch_pair_01(const GemmDev &ga, const GemmDev &gb, const GemmDev &gbt, bool bigA, bool f32, bool bigB, int outB,
@@ -34,7 +38,7 @@ struct PairPlan {
 static PairPlan plan_pair(const GemmArgs &a, int kindA, const GemmArgs &b, int kindB, size_t ws_bytes)
 {
     const int nkA = (row_bytes(kindA, a.K) + 127) / 128, nkB = (row_bytes(kindB, b.K) + 127) / 128;
-    const double scaleA = kindA == 2 ? kPackedScale : 1.0, scaleB = kindB == 2 ? kPackedScale : 1.0;
+    const double scaleA = step_scale(kindA), scaleB = step_scale(kindB);
     const double mnB = static_cast<double>(b.M) * b.N;
     PairPlan best{true, true, 1, false};
     double best_t = 1e30;
@@ -91,7 +95,7 @@ bool gemm_pair_available(int kindA, const GemmArgs &a, int kindB, const GemmArgs
     // the grid of the launch (128-tiles of both products, the second split 16 ways) must fit 31 bits with room
     const int64_t blocks = static_cast<int64_t>((a.M + 127) / 128) * ((a.N + 127) / 128) +
                            16 * static_cast<int64_t>((b.M + 127) / 128) * ((b.N + 127) / 128);
-    return (kindA == 2 || kindA == 0) && (kindB == 1 || kindB == 0) && a.C && b.C && !a.acc && !b.acc &&
+    return (kindA == 3 || kindA == 2 || kindA == 0) && (kindB == 1 || kindB == 0) && a.C && b.C && !a.acc && !b.acc &&
            a.c_is_f32 == b.c_is_f32 && blocks < (int64_t(1) << 30);
 }
 
@@ -115,7 +119,10 @@ hipError_t launch_gemm_pair(int kindA, const GemmArgs &a, int kindB, const GemmA
         if (tail_rows > 0) gbt = gemm_dev_cut_tail(gb, tail_rows);
     }
     hipError_t e;
-    if (kindA == 2)
+    if (kindA == 3)
+        e = kindB == 1 ? launch_pair_31(ga, gb, gbt, p.bigA, a.c_is_f32, p.bigB, outB, p.b_first, st)
+                       : launch_pair_30(ga, gb, gbt, p.bigA, a.c_is_f32, p.bigB, outB, p.b_first, st);
+    else if (kindA == 2)
         e = kindB == 1 ? launch_pair_21(ga, gb, gbt, p.bigA, a.c_is_f32, p.bigB, outB, p.b_first, st)
                        : launch_pair_20(ga, gb, gbt, p.bigA, a.c_is_f32, p.bigB, outB, p.b_first, st);
     else

@@ -72,6 +72,7 @@ hipError_t launch_tt(const GemmDev &ga, const GemmDev &gb, int grid, hipStream_t
 }
 }  // namespace
 
+bool gemm_stream_enabled() { return g_stream_enabled.load() != 0; }
 void gemm_stream_enable(bool on) { g_stream_enabled.store(on ? 1 : 0); }
 
 // a: the g_x product or the only one; b: the g_w product or NULL

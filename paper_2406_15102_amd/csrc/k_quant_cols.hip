@@ -47,6 +47,16 @@ __global__ __launch_bounds__(256) void k_cols_quantize(const Tin *__restrict__ W
     cols_quantize_body<Tin, B, PACKED, MANT>(W, O, I, amax_bits, k0, k1, qmax, WqT, sW, coeffT, lin % gridDim.x, lin / gridDim.x);
 }
 
+template <typename Tin, int B, bool MANT>
+__global__ __launch_bounds__(256) void k_cols_quantize_f6(const Tin *__restrict__ W, int O, int I,
+                                                          const uint32_t *__restrict__ amax_bits, uint32_t k0, uint32_t k1,
+                                                          float qmax, uint8_t *__restrict__ WqT, float *__restrict__ sW)
+{
+    const int lin = reverse_same_xcd(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y,
+                                     static_cast<int64_t>(O) * I * static_cast<int64_t>(sizeof(Tin)));
+    cols_quantize_f6_body<Tin, B, MANT>(W, O, I, amax_bits, k0, k1, qmax, WqT, sW, lin % gridDim.x, lin / gridDim.x);
+}
+
 size_t quant_cols_ws_bytes(int64_t /*O*/, int64_t I)
 {
     // amax bit patterns, one uint32 per in-feature
@@ -65,7 +75,7 @@ static hipError_t launch_cols_pass1_t(const void *W, int O, int I, void *ws, hip
 }
 
 template <typename Tin, int B>
-static hipError_t launch_cols_pass2_t(const void *W, int O, int I, uint32_t k0, uint32_t k1, float qmax, bool packed,
+static hipError_t launch_cols_pass2_t(const void *W, int O, int I, uint32_t k0, uint32_t k1, float qmax, int codes,
                                       bool mant, int8_t *WqT, float *sW, float *coeffT, const void *ws, hipStream_t st)
 {
     constexpr int CPL = 128 / B;
@@ -74,7 +84,12 @@ static hipError_t launch_cols_pass2_t(const void *W, int O, int I, uint32_t k0, 
     dim3 grid(cols_grid_x(I, B), cols_grid_y(O, B));
 #define HLQ_COLS2_LAUNCH(P, M) \
     hipLaunchKernelGGL((k_cols_quantize<Tin, B, P, M>), grid, dim3(256), 0, st, w, O, I, amax, k0, k1, qmax, WqT, sW, coeffT)
-    if (packed) {
+    if (codes == kCodesF6) {
+        if (coeffT) return hipErrorInvalidValue;
+        uint8_t *q = reinterpret_cast<uint8_t *>(WqT);
+        if (mant) hipLaunchKernelGGL((k_cols_quantize_f6<Tin, B, true>), grid, dim3(256), 0, st, w, O, I, amax, k0, k1, qmax, q, sW);
+        else hipLaunchKernelGGL((k_cols_quantize_f6<Tin, B, false>), grid, dim3(256), 0, st, w, O, I, amax, k0, k1, qmax, q, sW);
+    } else if (codes == kCodesNibbles) {
         if (mant) HLQ_COLS2_LAUNCH(true, true); else HLQ_COLS2_LAUNCH(true, false);
     } else {
         if (mant) HLQ_COLS2_LAUNCH(false, true); else HLQ_COLS2_LAUNCH(false, false);
@@ -84,13 +99,13 @@ static hipError_t launch_cols_pass2_t(const void *W, int O, int I, uint32_t k0, 
 }
 
 hipError_t launch_quant_cols_pass2(const void *W, int O, int I, int B, bool is_f32, uint32_t k0, uint32_t k1,
-                                   float qmax, bool packed, bool mant, int8_t *WqT, float *sW, float *coeffT,
+                                   float qmax, int codes, bool mant, int8_t *WqT, float *sW, float *coeffT,
                                    const void *ws, hipStream_t st)
 {
 #define HLQ_COLS2_CASE(BB)                                                                                               \
     case BB:                                                                                                             \
-        return is_f32 ? launch_cols_pass2_t<float, BB>(W, O, I, k0, k1, qmax, packed, mant, WqT, sW, coeffT, ws, st)     \
-                      : launch_cols_pass2_t<bf16_t, BB>(W, O, I, k0, k1, qmax, packed, mant, WqT, sW, coeffT, ws, st);
+        return is_f32 ? launch_cols_pass2_t<float, BB>(W, O, I, k0, k1, qmax, codes, mant, WqT, sW, coeffT, ws, st)     \
+                      : launch_cols_pass2_t<bf16_t, BB>(W, O, I, k0, k1, qmax, codes, mant, WqT, sW, coeffT, ws, st);
     switch (B) {
         HLQ_COLS2_CASE(16)
         HLQ_COLS2_CASE(32)
@@ -101,7 +116,7 @@ hipError_t launch_quant_cols_pass2(const void *W, int O, int I, int B, bool is_f
 }
 
 hipError_t launch_quant_cols(const void *W, int O, int I, int B, bool is_f32, uint32_t k0, uint32_t k1,
-                             float qmax, bool packed, bool mant, int8_t *WqT, float *sW, float *coeffT, void *ws,
+                             float qmax, int codes, bool mant, int8_t *WqT, float *sW, float *coeffT, void *ws,
                              hipStream_t st)
 {
     hipError_t e = hipErrorInvalidValue;
@@ -116,7 +131,7 @@ hipError_t launch_quant_cols(const void *W, int O, int I, int B, bool is_f32, ui
     }
 #undef HLQ_COLS_CASE
     if (e != hipSuccess) return e;
-    return launch_quant_cols_pass2(W, O, I, B, is_f32, k0, k1, qmax, packed, mant, WqT, sW, coeffT, ws, st);
+    return launch_quant_cols_pass2(W, O, I, B, is_f32, k0, k1, qmax, codes, mant, WqT, sW, coeffT, ws, st);
 }
 
 // ---- scratch for callers that cannot allocate -------------------------------------------------

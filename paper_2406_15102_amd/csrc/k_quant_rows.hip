@@ -21,6 +21,29 @@ __global__ __launch_bounds__(BLOCK) void k_quant_rows(const Tin *__restrict__ G,
     quant_rows_body<Tin, B, BLOCK, PACKED, MANT>(G, N, O, T, k0, k1, qmax, Gq, sG, coeff, blockIdx.x);
 }
 
+template <typename Tin, int B, int BLOCK, bool MANT>
+__global__ __launch_bounds__(BLOCK) void k_quant_rows_f6(const Tin *__restrict__ G, int64_t N, int O, int T, uint32_t k0,
+                                                         uint32_t k1, float qmax, uint8_t *__restrict__ Gq, float *__restrict__ sG)
+{
+    quant_rows_f6_body<Tin, B, BLOCK, MANT>(G, N, O, T, k0, k1, qmax, Gq, sG, blockIdx.x);
+}
+
+template <typename Tin, int B, bool MANT>
+static hipError_t launch_rows_f6(const void *G, int64_t N, int O, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG,
+                                 hipStream_t st)
+{
+    const Tin *g = static_cast<const Tin *>(G);
+    uint8_t *q = reinterpret_cast<uint8_t *>(Gq);
+    const int T = quant_rows_f6_lanes(O);
+    if (T > 0) {
+        const int rows = 256 / T;
+        hipLaunchKernelGGL((k_quant_rows_f6<Tin, B, 256, MANT>), dim3(static_cast<unsigned>((N + rows - 1) / rows)), dim3(256), 0, st, g, N, O, T, k0, k1, qmax, q, sG);
+    } else {
+        hipLaunchKernelGGL((k_quant_rows_f6<Tin, B, 1024, MANT>), dim3(static_cast<unsigned>(N)), dim3(1024), 0, st, g, N, O, 1024, k0, k1, qmax, q, sG);
+    }
+    return hipGetLastError();
+}
+
 template <typename Tin, int B, bool PACKED, bool MANT>
 static hipError_t launch_rows_t(const void *G, int64_t N, int O, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq,
                                 float *sG, float *coeff, hipStream_t st)
@@ -40,22 +63,27 @@ static hipError_t launch_rows_t(const void *G, int64_t N, int O, uint32_t k0, ui
 }
 
 template <typename Tin, int B>
-static hipError_t launch_rows_v(const void *G, int64_t N, int O, uint32_t k0, uint32_t k1, float qmax, bool packed,
+static hipError_t launch_rows_v(const void *G, int64_t N, int O, uint32_t k0, uint32_t k1, float qmax, int codes,
                                 bool mant, int8_t *Gq, float *sG, float *coeff, hipStream_t st)
 {
-    if (packed) return mant ? launch_rows_t<Tin, B, true, true>(G, N, O, k0, k1, qmax, Gq, sG, coeff, st)
+    if (codes == kCodesF6) {
+        if (coeff) return hipErrorInvalidValue;
+        return mant ? launch_rows_f6<Tin, B, true>(G, N, O, k0, k1, qmax, Gq, sG, st)
+                    : launch_rows_f6<Tin, B, false>(G, N, O, k0, k1, qmax, Gq, sG, st);
+    }
+    if (codes == kCodesNibbles) return mant ? launch_rows_t<Tin, B, true, true>(G, N, O, k0, k1, qmax, Gq, sG, coeff, st)
                             : launch_rows_t<Tin, B, true, false>(G, N, O, k0, k1, qmax, Gq, sG, coeff, st);
     return mant ? launch_rows_t<Tin, B, false, true>(G, N, O, k0, k1, qmax, Gq, sG, coeff, st)
                 : launch_rows_t<Tin, B, false, false>(G, N, O, k0, k1, qmax, Gq, sG, coeff, st);
 }
 
 hipError_t launch_quant_rows(const void *G, int64_t N, int O, int B, bool is_f32, uint32_t k0, uint32_t k1,
-                             float qmax, bool packed, bool mant, int8_t *Gq, float *sG, float *coeff, hipStream_t st)
+                             float qmax, int codes, bool mant, int8_t *Gq, float *sG, float *coeff, hipStream_t st)
 {
 #define HLQ_ROWS_CASE(BB)                                                                                     \
     case BB:                                                                                                  \
-        return is_f32 ? launch_rows_v<float, BB>(G, N, O, k0, k1, qmax, packed, mant, Gq, sG, coeff, st)      \
-                      : launch_rows_v<bf16_t, BB>(G, N, O, k0, k1, qmax, packed, mant, Gq, sG, coeff, st);
+        return is_f32 ? launch_rows_v<float, BB>(G, N, O, k0, k1, qmax, codes, mant, Gq, sG, coeff, st)      \
+                      : launch_rows_v<bf16_t, BB>(G, N, O, k0, k1, qmax, codes, mant, Gq, sG, coeff, st);
     switch (B) {
         HLQ_ROWS_CASE(16)
         HLQ_ROWS_CASE(32)

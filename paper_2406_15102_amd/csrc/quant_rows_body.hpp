@@ -2,6 +2,7 @@
 // threads is to process the rows bx * (BLOCK / T) ... of G, and the host-side choice of T.
 #pragma once
 #include "hlq_device.hpp"
+#include "hlq_kernels.hpp"
 
 namespace hlq {
 
@@ -85,6 +86,109 @@ __device__ __forceinline__ void quant_rows_body(const Tin *__restrict__ G, int64
             }
         }
     }
+}
+
+// K1 with the codes in the f6 layout (hlq_device.hpp): rows of f6_row_bytes(O), 16 bytes for 32 codes, zeros behind the
+// row's end.  A lane owns up to kF6Rounds groups of 32 consecutive elements, g + m T, so that a group's codes are
+// packed without leaving the lane; the butterflies of B = 16 and 32 stay in it too, and at B = 64 one stage, stride 32,
+// pairs it with its neighbour.  (A lane's loads are then 64 bytes apart, and an instruction takes a quarter of
+// four times as many lines; the next three find them in the L1.)
+constexpr int kF6Rounds = 3;
+
+template <typename Tin, int B, int BLOCK, bool MANT = false>
+__device__ __forceinline__ void quant_rows_f6_body(const Tin *__restrict__ G, int64_t N, int O, int T, uint32_t k0, uint32_t k1,
+                                                   float qmax, uint8_t *__restrict__ Gq, float *__restrict__ sG, int bx)
+{
+    __shared__ float s_red[BLOCK / 64];
+    const int tid = threadIdx.x;
+    const int64_t row = static_cast<int64_t>(bx) * (BLOCK / T) + tid / T;
+    const bool row_ok = row < N;
+    // lane of the row; where a row takes the whole workgroup, whose last round is mostly empty, the wavefront that
+    // starts it changes from row to row, as the groups of one round do not fill the SIMDs evenly
+    const int g = T < BLOCK ? tid % T : (tid + 64 * static_cast<int>(row & (BLOCK / 64 - 1))) % BLOCK;
+    const int ng = (O + 31) >> 5;                     // groups of a row; O % 16 == 0: the last may be half of one
+
+    float v[kF6Rounds][32];
+    const Tin *grow = G + (row_ok ? row : 0) * static_cast<int64_t>(O);
+#pragma unroll
+    for (int m = 0; m < kF6Rounds; ++m) {
+        const int gi = g + m * T;
+        if (gi < ng) {
+            const Tin *p = grow + static_cast<int64_t>(gi) * 32;
+            Loader<Tin, 8>::load(p, v[m]);
+            Loader<Tin, 8>::load(p + 8, v[m] + 8);
+            if (B > 16 || gi * 32 + 16 < O) {
+                Loader<Tin, 8>::load(p + 16, v[m] + 16);
+                Loader<Tin, 8>::load(p + 24, v[m] + 24);
+            } else {
+#pragma unroll
+                for (int e = 16; e < 32; ++e) v[m][e] = 0.0f;
+            }
+        }
+    }
+
+    const float sign = (B == 64 && (tid & 1)) ? -1.0f : 1.0f;
+    float amax = 0.0f;
+#pragma unroll
+    for (int m = 0; m < kF6Rounds; ++m) {
+        if (g + m * T < ng) {      // at B = 64 a row's groups come in pairs: both lanes of one or neither
+            fwht_regs<(B < 32 ? B : 32), 1>(v[m]);
+            if (B == 16) fwht_regs<16, 1>(v[m] + 16);
+            if (B == 64) {
+#pragma unroll
+                for (int e = 0; e < 32; e += 8) butterfly_lanes_signed8<1>(v[m] + e, sign);
+            }
+#pragma unroll
+            for (int e = 0; e < 32; ++e) amax = fmaxf(amax, fabsf(v[m][e]));
+        }
+    }
+    if (T <= 64) {
+        for (int off = 1; off < T; off *= 2) amax = fmaxf(amax, __shfl_xor(amax, off));
+    } else {
+        for (int off = 1; off < 64; off *= 2) amax = fmaxf(amax, __shfl_xor(amax, off));
+        if ((tid & 63) == 0) s_red[tid >> 6] = amax;
+        __syncthreads();
+        amax = s_red[0];
+#pragma unroll
+        for (int w = 1; w < BLOCK / 64; ++w) amax = fmaxf(amax, s_red[w]);
+    }
+    if (!row_ok) return;
+    const float inv = absmax_to_inv(amax, qmax) * sign;   // exact: undoes the sign the lane exchange left
+    if (g == 0) sG[row] = absmax_to_scale(amax, qmax);
+
+    const uint32_t cbase = static_cast<uint32_t>(row) * static_cast<uint32_t>(O >> 2);
+    const int row_bytes = f6_row_bytes(O);
+    uint8_t *qrow = Gq + row * static_cast<int64_t>(row_bytes);
+#pragma unroll
+    for (int m = 0; m < kF6Rounds; ++m) {
+        const int gi = g + m * T;
+        if (gi < ng) {
+            float f[32];
+            quant_floats<MANT, 4>(v[m], 1, inv, cbase + 8u * gi, k0, k1, f);
+            quant_floats<MANT, 4>(v[m] + 16, 1, inv, cbase + 8u * gi + 4u, k0, k1, f + 16);
+            *reinterpret_cast<uint4 *>(qrow + static_cast<int64_t>(gi) * 16) = f6_pack32(f);
+        } else if (gi * 16 < row_bytes) {
+            *reinterpret_cast<uint4 *>(qrow + static_cast<int64_t>(gi) * 16) = make_uint4(0, 0, 0, 0);
+        }
+    }
+}
+
+// Lanes per row of the f6 variant, or 0 if the row needs 1024 threads: the split with the fewest lanes idle in its last
+// round, rows of whole wavefronts' lanes first.
+inline int quant_rows_f6_lanes(int O)
+{
+    const int ng = f6_row_bytes(O) / 16;
+    if (ng > kF6Rounds * 64) return ng <= kF6Rounds * 256 ? 256 : 0;
+    int best = 64, waste = 1 << 30;
+    for (int T = 64; T >= 4; T /= 2) {
+        const int rounds = (ng + T - 1) / T;
+        if (rounds > kF6Rounds) break;
+        if (rounds * T - ng < waste) {
+            waste = rounds * T - ng;
+            best = T;
+        }
+    }
+    return best;
 }
 
 // Lanes per row for the 256-thread variant, or 0 if the row needs the 1024-thread one.
