@@ -79,20 +79,48 @@ int check_backward_shape(int64_t N, int64_t d_in, int64_t d_out, int B, int r)
 // maxima (kAmaxTableRows) come last: `least` is the size without them.  A call that is given that much and not `total`
 // merges by atomics instead (same bits), so that scratch sized for a longer problem, whose maxima have no table,
 // holds a shorter one: 4096 x 96 x 768 at r = 16 with its tables takes 10.08 MB, 4112 x 96 x 768 10.05.
+// The rows of the projections are Kp elements apart: padded (pad_row) in the room that 4-bit codes leave beside one byte
+// each, which is what `least` counts; a call that is given less than that takes carves it without padding.
 struct Layout {
-    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, least, tabw, tabg, tabx, total;
+    int64_t Kp;
+    int codes;       // kCodesBytes, ...: how the codes of the g_x list are kept
+    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, least, tabw, tabg, tabx, padded, total;
 };
 
-Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags)
+// the launches that make both projections with padded rows, and fold tables of column maxima: the fused ones
+bool fused_front(int64_t d_out, int B, int flags)
+{
+    return !(flags & HLQ_FLAG_ROUND_MANTISSA) && hlq::front_fusable(static_cast<int>(d_out), B);
+}
+
+// How the codes of the g_x list are kept: 4-bit codes travel two to a byte, in the f6 layout unless more than a quarter of its
+// rows would be padding (f6_rows_ok), else, or where the persistent form of the products is asked for, which multiplies
+// bytes, as nibbles where the rows stay 16-byte aligned that way.  image: see backward_impl.
+int codes_kept(int64_t d_out, int flags, bool image)
+{
+    const bool four = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && !image;
+    if (four && hlq::f6_rows_ok(static_cast<int>(d_out)) && !hlq::gemm_stream_enabled()) return hlq::kCodesF6;
+    return four && d_out % 32 == 0 ? hlq::kCodesNibbles : hlq::kCodesBytes;
+}
+
+Layout carve_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags, bool image, size_t gws_bytes,
+                    bool pad)
 {
     Layout L;
-    const size_t Kc = static_cast<size_t>(N / B * r);
-    const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0;
+    L.codes = codes_kept(d_out, flags, image);
+    const int codes = pad ? L.codes : hlq::kCodesBytes;      // what there is room for
+    const size_t code_row = codes == hlq::kCodesF6 ? hlq::f6_row_bytes(static_cast<int>(d_out)) : static_cast<size_t>(codes == hlq::kCodesNibbles ? d_out / 2 : d_out);
+    const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0, fused = fused_front(d_out, B, flags);
     const size_t esz = gwi ? 1 : 2;
+    // X projected here, or the int8 codes unpacked from a 4-bit store that was handed over
+    const bool x_unpack = x_is_compressed && (flags & HLQ_FLAG_XC_INT4), x_here = !x_is_compressed || x_unpack;
+    L.Kp = N / B * r;
+    if (pad && fused && x_here) L.Kp = hlq::pad_row(L.Kp, static_cast<int>(esz));
+    const size_t Kp = static_cast<size_t>(L.Kp);
     size_t off = 0;
-    L.Gq = off;    off += up256(static_cast<size_t>(N) * d_out);
+    L.Gq = off;    off += up256(static_cast<size_t>(N) * code_row);
     L.sG = off;    off += up256(static_cast<size_t>(N) * 4);
-    L.Wq = off;    off += up256(static_cast<size_t>(d_in) * d_out);
+    L.Wq = off;    off += up256(static_cast<size_t>(d_in) * code_row);
     L.sW = off;    off += up256(static_cast<size_t>(d_in) * 4);
     L.wws = off;   off += up256(hlq::quant_cols_ws_bytes(d_out, d_in));
     // integer g_w list: column maxima of projected G (d_out words), then of projected X (d_in words),
@@ -100,16 +128,29 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
     L.hws = off;   off += gwi ? up256(hlq::hla_quant_ws_bytes(d_out)) : 0;
     L.hwsx = off;  off += gwi ? up256(hlq::hla_quant_ws_bytes(d_in)) : 0;
     L.amax_end = off;
-    L.GhatT = off; off += up256(static_cast<size_t>(d_out) * Kc * esz);
+    L.GhatT = off; off += up256(static_cast<size_t>(d_out) * Kp * esz);
     L.sGhat = off; off += gwi ? up256(static_cast<size_t>(d_out) * 4) : 0;
-    // X projected here, or the int8 codes unpacked from a 4-bit store that was handed over
-    const bool x_unpack = x_is_compressed && (flags & HLQ_FLAG_XC_INT4);
-    L.XhatT = off; off += (x_is_compressed && !x_unpack) ? 0 : up256(static_cast<size_t>(d_in) * Kc * esz);
+    L.XhatT = off; off += x_here ? up256(static_cast<size_t>(d_in) * Kp * esz) : 0;
     L.sXhat = off; off += (gwi && !x_is_compressed) ? up256(static_cast<size_t>(d_in) * 4) : 0;
+    L.gws_bytes = gws_bytes;
+    L.gws = off;   off += up256(L.gws_bytes);
+    L.least = off;
+    const bool tables = gwi && fused;
+    L.tabw = off;  off += tables ? up256(hlq::amax_table_bytes(d_out, d_in)) : 0;
+    L.tabg = off;  off += tables ? up256(hlq::amax_table_bytes(N, d_out)) : 0;
+    L.tabx = off;  off += tables && !x_is_compressed ? up256(hlq::amax_table_bytes(N, d_in)) : 0;
+    L.padded = L.total = off;
+    return L;
+}
+
+Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags, bool image = false)
+{
+    const int64_t Kc = N / B * r;
+    const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0;
     // split-K partial sums of whichever product wants them (the two products run one after the other)
     const size_t g1 = hlq::gemm_ws_bytes(0, static_cast<int>(N), static_cast<int>(d_in), static_cast<int>(d_out));
     const size_t g2 = hlq::gemm_ws_bytes(gwi ? 0 : 1, static_cast<int>(d_out), static_cast<int>(d_in), static_cast<int>(Kc));
-    L.gws_bytes = g1 > g2 ? g1 : g2;
+    size_t gws_bytes = g1 > g2 ? g1 : g2;
     if (!(flags & HLQ_FLAG_SEPARATE_PRODUCTS)) {
         // the two products in one launch plan the g_w product's k split for the pair
         const bool packed = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && d_out % 32 == 0;
@@ -117,16 +158,13 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
         ax.M = static_cast<int>(N), ax.N = static_cast<int>(d_in), ax.K = static_cast<int>(d_out);
         aw.M = static_cast<int>(d_out), aw.N = static_cast<int>(d_in), aw.K = static_cast<int>(Kc);
         const size_t gp = hlq::gemm_pair_ws_bytes(packed ? 2 : 0, ax, gwi ? 0 : 1, aw, size_t(256) << 20);
-        if (gp > L.gws_bytes) L.gws_bytes = gp;
+        if (gp > gws_bytes) gws_bytes = gp;
     }
-    L.gws = off;   off += up256(L.gws_bytes);
-    L.least = off;
-    // the passes that fold a table are those of the fused launches
-    const bool tables = gwi && !(flags & HLQ_FLAG_ROUND_MANTISSA) && hlq::front_fusable(static_cast<int>(d_out), B);
-    L.tabw = off;  off += tables ? up256(hlq::amax_table_bytes(d_out, d_in)) : 0;
-    L.tabg = off;  off += tables ? up256(hlq::amax_table_bytes(N, d_out)) : 0;
-    L.tabx = off;  off += tables && !x_is_compressed ? up256(hlq::amax_table_bytes(N, d_in)) : 0;
-    L.total = off;
+    Layout L = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, image, gws_bytes, true);
+    const Layout bytes = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, image, gws_bytes, false);
+    L.least = bytes.least;
+    L.padded = L.total;
+    if (L.total < bytes.total) L.total = bytes.total;
     return L;
 }
 
@@ -609,24 +647,21 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     if ((rc = backward_check(G, X, Xc, sXc, W, Wc, sWc, N, d_in, d_out, B, r, dtype, flags, dX, dW)) != HLQ_OK) return rc;
     const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0;
     const float qmax = (flags & HLQ_FLAG_GX_8BIT) ? 127.0f : 7.0f;
-    // 4-bit codes travel two to a byte: in the f6 layout unless more than a quarter of its rows would be padding (f6_rows_ok),
-    // else, or where the persistent form of the products is asked for, which multiplies bytes, as nibbles where the rows stay
-    // 16-byte aligned that way
-    const bool four = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && !image;
-    const int codes = four && hlq::f6_rows_ok(static_cast<int>(d_out)) && !hlq::gemm_stream_enabled() ? hlq::kCodesF6 : (four && d_out % 32 == 0 ? hlq::kCodesNibbles : hlq::kCodesBytes);
     const int basis = (flags & HLQ_FLAG_GW_SEQUENCY) ? HLQ_BASIS_SEQUENCY : HLQ_BASIS_NATURAL;
     const bool mant = (flags & HLQ_FLAG_ROUND_MANTISSA) != 0;
 
     const bool xc = (Xc != nullptr) || !dW;   // no projection of X is held here: it was handed over, or dW is not wanted
-    const Layout L = make_layout(N, d_in, d_out, B, r, xc, flags);
+    const Layout full = make_layout(N, d_in, d_out, B, r, xc, flags, image != nullptr);
     char *ws = static_cast<char *>(workspace);
     if (ws) {
-        if (!aligned(ws, 256) || workspace_bytes < L.least) return HLQ_ERR_WORKSPACE;
+        if (!aligned(ws, 256) || workspace_bytes < full.least) return HLQ_ERR_WORKSPACE;
     } else {
         void *p = nullptr;
-        if ((rc = own_workspace(L.least, L.total, &p, &workspace_bytes)) != HLQ_OK) return rc;
+        if ((rc = own_workspace(full.least, full.total, &p, &workspace_bytes)) != HLQ_OK) return rc;
         ws = static_cast<char *>(p);
     }
+    const Layout L = workspace_bytes >= full.padded ? full : carve_layout(N, d_in, d_out, B, r, xc, flags, image != nullptr, full.gws_bytes, false);
+    const int codes = full.codes;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool f32 = dtype == HLQ_F32;
     const int O = static_cast<int>(d_out), I = static_cast<int>(d_in);
@@ -650,7 +685,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     // and pass 2 over the weight for the default path (one in all when the weight has few rows or
     // is not transformed here), two or three for the integer g_w list.  Very long rows of G and the mantissa-bit rounding keep one
     // launch per stage.
-    const bool fusable = hlq::front_fusable(O, B) && !mant;   // the fused launches carry the seeded rounding only
+    const bool fusable = fused_front(d_out, B, flags);   // the fused launches carry the seeded rounding only
     const bool fused = !gwi && fusable;
     const bool fused_q = gwi && fusable;
     const uint64_t kg = stream_key(seed, 0);
@@ -661,14 +696,13 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         if ((rc = launch_rc(hlq::launch_f6_recode(jk, st))) != HLQ_OK) return rc;
         jk = no_recode;
     }
-    hlq::FrontUnpack ju = hlq::front_unpack(nullptr, nullptr, 0);
+    hlq::FrontUnpack ju = hlq::front_unpack(nullptr, nullptr, 0, Kc, Kc);
     if (dW && Xc && (flags & HLQ_FLAG_XC_INT4)) {
         // the activation was kept as 4-bit codes (Sec. 6.1): widened to the int8 operand of the product, beside the
         // passes that take the maxima where there is such a launch
         int8_t *xu = reinterpret_cast<int8_t *>(ws + L.XhatT);
-        const int64_t bytes = static_cast<int64_t>(d_in) * Kc / 2;
-        if (fused_q) ju = hlq::front_unpack(Xc, xu, bytes);
-        else if ((rc = launch_rc(hlq::launch_unpack_nibbles(Xc, xu, bytes, st))) != HLQ_OK) return rc;
+        if (fused_q) ju = hlq::front_unpack(Xc, xu, d_in, Kc, L.Kp);
+        else if ((rc = launch_rc(hlq::launch_unpack_nibbles(Xc, xu, static_cast<int64_t>(d_in) * Kc / 2, st))) != HLQ_OK) return rc;
         Xh = xu;
     }
     if (fused_q) {
@@ -680,7 +714,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         const int rows_w = wq ? hlq::amax_table_rows(O) : 1, rows_t = dW ? hlq::amax_table_rows(N) : 1;
         const int64_t reads = (wq ? hlq::amax_table_reads(O, I) : 0) + (dW ? hlq::amax_table_reads(N, xc ? O : O + I) : 0);
         const bool tables = rows_w && rows_t && reads <= hlq::kAmaxTableReads &&
-                            ((rows_w == 1 && rows_t == 1) || workspace_bytes >= L.total);
+                            ((rows_w == 1 && rows_t == 1) || workspace_bytes >= L.padded);
         const int tw = tables ? rows_w : 0, tt = tables ? rows_t : 0;
         uint32_t *amax_w = reinterpret_cast<uint32_t *>(ws + (tw > 1 ? L.tabw : L.wws));
         uint32_t *amax_g = reinterpret_cast<uint32_t *>(ws + (tt > 1 ? L.tabg : L.hws));
@@ -691,9 +725,9 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         int8_t *xq = xc ? nullptr : reinterpret_cast<int8_t *>(ws + L.XhatT);
         float *sx = xc ? nullptr : reinterpret_cast<float *>(ws + L.sXhat);
         const hlq::FrontHlaQ jg = hlq::front_hlaq(dW ? G : nullptr, N, O, B, r, amax_g, tt, static_cast<uint32_t>(k3),
-                                                  static_cast<uint32_t>(k3 >> 32), static_cast<int8_t *>(Gh), sGh);
+                                                  static_cast<uint32_t>(k3 >> 32), L.Kp, static_cast<int8_t *>(Gh), sGh);
         const hlq::FrontHlaQ jx = hlq::front_hlaq(dW && !xc ? X : nullptr, N, I, B, r, amax_x, tt, static_cast<uint32_t>(k2),
-                                                  static_cast<uint32_t>(k2 >> 32), xq, sx);
+                                                  static_cast<uint32_t>(k2 >> 32), L.Kp, xq, sx);
         const hlq::FrontColsQ jq = hlq::front_colsq(wq ? W : nullptr, O, I, B, amax_w, tw, static_cast<uint32_t>(kw),
                                                     static_cast<uint32_t>(kw >> 32), qmax, reinterpret_cast<int8_t *>(ws + L.Wq),
                                                     reinterpret_cast<float *>(ws + L.sW));
@@ -703,7 +737,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         const size_t zero_from = wq ? L.wws : L.hws;
         const size_t zero_to = jx.T ? L.amax_end : (jg.T ? L.hwsx : L.hws);
         const hlq::FrontFill jf{reinterpret_cast<uint32_t *>(ws + zero_from), tables ? 0 : static_cast<int>((zero_to - zero_from) / 4)};
-        const hlq::FrontHla none = hlq::front_hla(nullptr, N, O, B, r, nullptr);
+        const hlq::FrontHla none = hlq::front_hla(nullptr, N, O, B, r, L.Kp, nullptr);
         const hlq::FrontAbsmax none_w = hlq::front_absmax(nullptr, O, I, B, nullptr);
         const bool k1_later = front_mix;
         const hlq::FrontRows no_rows = hlq::front_rows(nullptr, N, O, B, codes, 0, 0, qmax, nullptr, nullptr);
@@ -725,8 +759,8 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         uint16_t *xh = xc ? nullptr : reinterpret_cast<uint16_t *>(ws + L.XhatT);
         const hlq::FrontRows jr = hlq::front_rows(dX ? G : nullptr, N, O, B, codes, static_cast<uint32_t>(kg),
                                                   static_cast<uint32_t>(kg >> 32), qmax, Gq, sG);
-        const hlq::FrontHla jx = hlq::front_hla(dW && !xc ? X : nullptr, N, I, B, r, xh);
-        const hlq::FrontHla jg = hlq::front_hla(dW ? G : nullptr, N, O, B, r, static_cast<uint16_t *>(Gh));
+        const hlq::FrontHla jx = hlq::front_hla(dW && !xc ? X : nullptr, N, I, B, r, L.Kp, xh);
+        const hlq::FrontHla jg = hlq::front_hla(dW ? G : nullptr, N, O, B, r, L.Kp, static_cast<uint16_t *>(Gh));
         if (w_done && !conv && front_mix) {
             // no pass over W here: the front launch alone (its second launch has nothing to do), with the
             // quantiser's and the projections' workgroups in turns
@@ -806,7 +840,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     // g_w stage 5 (and 6) over the compressed token axis.  Independent of each other: one launch
     // carries both when that combination of kernels is built (k_gemm_pair.hip).
     hlq::GemmArgs ax{Gq, Wq, static_cast<int>(N), I, O, sG, sW, invB, dX, f32, nullptr, ws + L.gws, L.gws_bytes};
-    hlq::GemmArgs aw{Gh, Xh, O, I, Kc, gwi ? sGh : nullptr, gwi ? sXh : nullptr, invB, dW, f32, nullptr, ws + L.gws,
+    hlq::GemmArgs aw{Gh, Xh, O, I, static_cast<int>(L.Kp), gwi ? sGh : nullptr, gwi ? sXh : nullptr, invB, dW, f32, nullptr, ws + L.gws,
                      L.gws_bytes};
     const int kind_x = codes == hlq::kCodesF6 ? 3 : (codes == hlq::kCodesNibbles ? 2 : 0), kind_w = gwi ? 0 : 1;
     if (dX && image) {
@@ -997,7 +1031,7 @@ static ConvLayout conv_layout(const hlq::ConvShape &c, const hlq_conv_geom *g, i
     L.inner = L.dcols + mat;
     L.least = L.total = 0;
     if (check_backward_shape(c.N, I, g->O, B, r) == HLQ_OK && check_flags(flags, r, c.N, B) == HLQ_OK) {
-        const Layout in = make_layout(c.N, I, g->O, B, r, false, flags);
+        const Layout in = make_layout(c.N, I, g->O, B, r, false, flags, !L.pointwise && hlq::conv_dx_ok(g->O, c, dtype == HLQ_F32));
         L.least = L.inner + in.least;
         L.total = L.inner + in.total;
     }

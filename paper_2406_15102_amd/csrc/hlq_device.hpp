@@ -387,9 +387,9 @@ __device__ __forceinline__ void fold_column_maxima(const uint32_t *__restrict__ 
 }
 
 // 4-bit codes two to a byte -> one int8 each: a lane turns 16 bytes into 32 (see k_unpack_nibbles)
-__device__ __forceinline__ void unpack_nibbles16(const uint4 *__restrict__ in, uint4 *__restrict__ out, int64_t i)
+__device__ __forceinline__ void unpack_nibbles16(const uint4 *__restrict__ in, uint4 *__restrict__ out)
 {
-    const uint4 x = in[i];
+    const uint4 x = *in;
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
     uint32_t o[8];
 #pragma unroll
@@ -404,8 +404,8 @@ __device__ __forceinline__ void unpack_nibbles16(const uint4 *__restrict__ in, u
         o[2 * d] = a;
         o[2 * d + 1] = b;
     }
-    out[2 * i] = make_uint4(o[0], o[1], o[2], o[3]);
-    out[2 * i + 1] = make_uint4(o[4], o[5], o[6], o[7]);
+    out[0] = make_uint4(o[0], o[1], o[2], o[3]);
+    out[1] = make_uint4(o[4], o[5], o[6], o[7]);
 }
 
 // qmax = 7 for 4-bit codes, 127 for 8-bit codes (int8 warm-up phase, integer g_w path).

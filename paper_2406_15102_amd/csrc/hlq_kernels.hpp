@@ -17,6 +17,13 @@ __host__ __device__ constexpr int f6_row_bytes(int K) { return (K + 255) / 256 *
 // int8 a code.)
 inline bool f6_rows_ok(int K) { return 2 * K >= 3 * f6_row_bytes(K); }
 
+// Rows of the projections that the whole path makes and multiplies itself, in elements of `esz` bytes: zeros up to whole
+// 128-byte steps of the dW product, so that none is ragged and operands can be loaded straight into LDS.  (The rows of a
+// store that is handed over have no padding.)  Not rows of at most four steps, which are multiplied through registers anyway.
+// Whole pass, ragged rows -> padded: 9200 x 1160 x 3120 126.9 -> 117.7 us, 12608 x 768 x 3072 117.0 -> 113.9, 12608 x 768 x 2304
+// in 8 bits 104.6 -> 99.6.
+inline int64_t pad_row(int64_t Kc, int esz) { return Kc * esz <= 512 ? Kc : (Kc * esz + 127) / 128 * 128 / esz; }
+
 // K1: rows of G -> codes + per-row scales (and optionally, not with kCodesF6, the fp32 coefficients).
 // `mant`: round by the low 11 mantissa bits of each value instead of the seeded stream (k0, k1 unused).
 hipError_t launch_quant_rows(const void *G, int64_t N, int O, int B, bool is_f32, uint32_t k0, uint32_t k1,
@@ -88,8 +95,9 @@ struct FrontHla {    // K3 on one tensor
     const void *T;
     int64_t N;
     int D, r;
+    int64_t Kp;      // values from one row of `out` to the next (pad_row)
     uint16_t *out;
-    int gx, gy;      // column strips of 128, groups of 256/B token blocks
+    int gx, gy;      // column strips of 128, groups of 256/B token blocks, with those that only clear the end of the rows
     int grp, nb;     // hla_job_map's grouping and the workgroups it needs (>= gx * gy)
 };
 // Shape of a K3 workgroup: B lanes side by side (each CPL = 128/B columns: 256 B of a row of bf16
@@ -158,15 +166,18 @@ struct FrontHlaQ {   // K3 + int8 quantisation of one tensor: pass 1 (amax) and 
     int D, r;
     uint32_t *amax;
     uint32_t k0, k1;
+    int64_t Kp;      // codes from one row of TqT to the next (pad_row)
     int8_t *TqT;
     float *sT;
-    int gx, gy;
+    int gx, gy;      // of pass 1
     int table;       // see kAmaxTableRows; 0: one maximum per column, merged by atomics
+    int gy2;         // of pass 2, with the workgroups that only clear the end of the rows
 };
-struct FrontUnpack { // 4-bit codes two to a byte -> one int8 each; n16 pieces of 16 bytes in
+struct FrontUnpack { // 4-bit codes two to a byte -> one int8 each; n pieces of 32 codes out, row_out a row, the first row_in of them from `in`
     const void *in;
     void *out;
-    int64_t n16;
+    int64_t n;       // below 2^31
+    int row_in, row_out;
     int blocks;
 };
 struct FrontRecode { // weight codes [rows][O], one int8 each or two to a byte -> the f6 layout; 256 groups of 32 codes a workgroup
@@ -211,10 +222,10 @@ inline size_t amax_table_bytes(int64_t rows, int64_t cols)
     return t > 1 && amax_table_reads(rows, cols) <= kAmaxTableReads ? static_cast<size_t>(t) * static_cast<size_t>(cols) * 4 : 0;
 }
 FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, int table, uint32_t k0, uint32_t k1,
-                     int8_t *TqT, float *sT);
+                     int64_t Kp, int8_t *TqT, float *sT);
 FrontColsQ front_colsq(const void *W, int O, int I, int B, const uint32_t *amax, int table, uint32_t k0, uint32_t k1,
                        float qmax, int8_t *WqT, float *sW);
-FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in);
+FrontUnpack front_unpack(const void *in, void *out, int64_t rows, int64_t Kc, int64_t Kp);   // in == NULL: empty
 FrontRecode front_recode(const void *in, int rows, int O, bool nibbles, void *out);   // in == NULL: empty
 hipError_t launch_f6_recode(const FrontRecode &jk, hipStream_t st);
 // The integer g_w list in two launches: every pass 1 (maxima of projected G, projected X, transformed W),
@@ -226,7 +237,7 @@ hipError_t launch_front_q(const FrontHlaQ &jg, const FrontHlaQ &jx, const FrontA
                           int codes, hipStream_t st);
 bool front_fusable(int O, int B);
 FrontRows front_rows(const void *G, int64_t N, int O, int B, int codes, uint32_t k0, uint32_t k1, float qmax, int8_t *Gq, float *sG);
-FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, uint16_t *out);
+FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, int64_t Kp, uint16_t *out);
 FrontAbsmax front_absmax(const void *W, int O, int I, int B, uint32_t *amax, int table = 0);
 // all of K1T for a weight that passes cols_full_ok: one workgroup per strip of columns (gy carries the
 // strip's width as a shift)

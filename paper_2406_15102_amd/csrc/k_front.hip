@@ -70,6 +70,21 @@ __device__ __forceinline__ void front_fill_or_recode(const FrontFill &jf, const 
     }
 }
 
+// The widening of a 4-bit store: a thread per 32 bytes out, those behind the end of a row zeros.
+__device__ __forceinline__ void front_unpack_body(const FrontUnpack &ju, int b)
+{
+    const int64_t i = static_cast<int64_t>(b) * 256 + threadIdx.x;
+    if (i >= ju.n) return;
+    uint4 *out = static_cast<uint4 *>(ju.out);
+    const uint32_t row = static_cast<uint32_t>(i) / static_cast<uint32_t>(ju.row_out), p = static_cast<uint32_t>(i) - row * static_cast<uint32_t>(ju.row_out);
+    if (p < static_cast<uint32_t>(ju.row_in)) {
+        unpack_nibbles16(static_cast<const uint4 *>(ju.in) + static_cast<int64_t>(row) * ju.row_in + p, out + 2 * i);
+    } else {
+        out[2 * i] = make_uint4(0, 0, 0, 0);
+        out[2 * i + 1] = make_uint4(0, 0, 0, 0);
+    }
+}
+
 // CONV: X is a channels-last image and K3 reads its column matrix through ConvRows.  A kernel of
 // its own: the extra address arithmetic would cost the matrix variant registers, and with them a
 // wavefront of occupancy at B = 32.
@@ -92,7 +107,7 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
                 if (blk < jr.blocks)
                     front_rows_body<Tin, B, CODES>(jr, blk);
             } else {
-                hla_body<Tin, B, BASIS, 2>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.out, nullptr, v - js.nk1, grp);
+                hla_body<Tin, B, BASIS, 2>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, v - js.nk1, grp);
             }
             return;
         }
@@ -107,11 +122,11 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
         } else if (k3 >= 0 && k3 < jx.nb) {
             int bx, by;
             hla_job_map(k3, jx.gx, jx.grp, bx, by);
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         } else if (k3 >= 0) {
             int bx, by;
             hla_job_map(k3 - jx.nb, jy.gx, jy.grp, bx, by);
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.Kp, jy.out, nullptr, bx, by);
         } else {
             front_fill_or_recode<CODES>(jf, jk, b);
         }
@@ -126,16 +141,16 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
         int bx, by;
         hla_job_map(b, jx.gx, jx.grp, bx, by);
         if (CONV)
-            hla_body_src<B, BASIS>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.out, nullptr, bx, by);
+            hla_body_src<B, BASIS>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         else
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         return;
     }
     b -= jx.nb;
     if (b < jy.nb) {
         int bx, by;
         hla_job_map(b, jy.gx, jy.grp, bx, by);
-        hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.out, nullptr, bx, by);
+        hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.Kp, jy.out, nullptr, bx, by);
         return;
     }
     front_fill_or_recode<CODES>(jf, jk, b - jy.nb);
@@ -171,15 +186,15 @@ __global__ __launch_bounds__(256, B == 64 ? 2 : 3) void k_front_one(FrontRows jr
         int bx, by;
         hla_job_map(b, jx.gx, jx.grp, bx, by);
         if (CONV)
-            hla_body_src<B, BASIS>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.out, nullptr, bx, by);
+            hla_body_src<B, BASIS>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         else
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         return;
     }
     b -= jx.nb;
     int bx, by;
     hla_job_map(b, jg.gx, jg.grp, bx, by);
-    hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.out, nullptr, bx, by);
+    hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.Kp, jg.out, nullptr, bx, by);
 }
 
 template <typename Tin, int B, int BASIS>
@@ -189,7 +204,7 @@ __global__ __launch_bounds__(256) void k_front_b(FrontHla jg, FrontAbsmax jw)
     if (b < jg.nb) {
         int bx, by;
         hla_job_map(b, jg.gx, jg.grp, bx, by);
-        hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.out, nullptr, bx, by);
+        hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.Kp, jg.out, nullptr, bx, by);
         return;
     }
     b -= jg.nb;
@@ -249,8 +264,7 @@ __global__ __launch_bounds__(256) void k_front_q1(FrontHlaQ jg, FrontHlaQ jx, Fr
             return;
         }
     }
-    const int64_t i = static_cast<int64_t>(b) * 256 + threadIdx.x;
-    if (i < ju.n16) unpack_nibbles16(static_cast<const uint4 *>(ju.in), static_cast<uint4 *>(ju.out), i);
+    front_unpack_body(ju, b);
 }
 
 // pass 2 of everything: int8 codes of projected G and X, codes of the weight
@@ -261,22 +275,22 @@ __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, Fr
     // read last is what the last-level cache still holds
     const int64_t bytes = (jg.T ? jg.N * jg.D : 0) + (jx.T ? jx.N * jx.D : 0) + (jq.W ? static_cast<int64_t>(jq.O) * jq.I : 0);
     int b = reverse_same_xcd(blockIdx.x, gridDim.x, bytes * static_cast<int64_t>(sizeof(Tin)));
-    if (b < jg.gx * jg.gy) {
-        hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, jg.k0, jg.k1, jg.TqT,
+    if (b < jg.gx * jg.gy2) {
+        hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, jg.k0, jg.k1, jg.Kp, jg.TqT,
                                          jg.sT, nullptr, b % jg.gx, b / jg.gx, jg.table);
         return;
     }
-    b -= jg.gx * jg.gy;
-    if (b < jx.gx * jx.gy) {
+    b -= jg.gx * jg.gy2;
+    if (b < jx.gx * jx.gy2) {
         if (CONV)
             hla_quantize_body_src<B, BASIS, false>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.amax,
-                                                   jx.k0, jx.k1, jx.TqT, jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
+                                                   jx.k0, jx.k1, jx.Kp, jx.TqT, jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
         else
-            hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, jx.k0, jx.k1, jx.TqT,
+            hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, jx.k0, jx.k1, jx.Kp, jx.TqT,
                                              jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
         return;
     }
-    b -= jx.gx * jx.gy;
+    b -= jx.gx * jx.gy2;
     if constexpr (CODES == kCodesF6)
         cols_quantize_f6_body<Tin, B>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.amax, jq.k0, jq.k1, jq.qmax,
                                       reinterpret_cast<uint8_t *>(jq.WqT), jq.sW, b % jq.gx, b / jq.gx, jq.table);
@@ -285,10 +299,10 @@ __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, Fr
                                                            jq.WqT, jq.sW, nullptr, b % jq.gx, b / jq.gx, jq.table);
 }
 
-FrontUnpack front_unpack(const void *in, void *out, int64_t bytes_in)
+FrontUnpack front_unpack(const void *in, void *out, int64_t rows, int64_t Kc, int64_t Kp)
 {
-    FrontUnpack j{in, out, in ? bytes_in / 16 : 0, 0};
-    j.blocks = static_cast<int>((j.n16 + 255) / 256);
+    FrontUnpack j{in, out, in ? rows * (Kp / 32) : 0, static_cast<int>(Kc / 32), static_cast<int>(Kp / 32), 0};
+    j.blocks = static_cast<int>((j.n + 255) / 256);
     return j;
 }
 
@@ -309,12 +323,13 @@ hipError_t launch_f6_recode(const FrontRecode &jk, hipStream_t st)
 }
 
 FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *amax, int table, uint32_t k0, uint32_t k1,
-                     int8_t *TqT, float *sT)
+                     int64_t Kp, int8_t *TqT, float *sT)
 {
-    FrontHlaQ j{T, N, D, r, amax, k0, k1, TqT, sT, 0, 0, table};
+    FrontHlaQ j{T, N, D, r, amax, k0, k1, Kp, TqT, sT, 0, 0, table};
     if (!T) return j;
     j.gx = hla_grid_x(D, B);
     j.gy = hla_grid_y(N, B);
+    j.gy2 = hla_grid_y(Kp / r * B, B);
     return j;
 }
 
@@ -336,7 +351,7 @@ static hipError_t launch_front_q_t(const FrontHlaQ &jg, const FrontHlaQ &jx, con
     const int n1 = n3 + jr.blocks + ju.blocks + jk.blocks;
     const FrontMix jm = jr.blocks > 0 ? front_mix_of(jr.blocks, n3) : FrontMix{0, 0, 0};
     if (n1 > 0) hipLaunchKernelGGL((k_front_q1<Tin, B, BASIS, CODES, CONV>), dim3(n1), dim3(256), 0, st, jg, jx, jw, jr, jm, ju, jc, jk);
-    const int n2 = jg.gx * jg.gy + jx.gx * jx.gy + jq.gx * jq.gy;
+    const int n2 = jg.gx * jg.gy2 + jx.gx * jx.gy2 + jq.gx * jq.gy;
     if (n2 > 0) hipLaunchKernelGGL((k_front_q2<Tin, B, BASIS, CODES, CONV>), dim3(n2), dim3(256), 0, st, jg, jx, jq, jc);
     return hipGetLastError();
 }
@@ -396,12 +411,12 @@ FrontRows front_rows(const void *G, int64_t N, int O, int B, int codes, uint32_t
     return j;
 }
 
-FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, uint16_t *out)
+FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, int64_t Kp, uint16_t *out)
 {
-    FrontHla j{T, N, D, r, out, 0, 0, 1, 0};
+    FrontHla j{T, N, D, r, Kp, out, 0, 0, 1, 0};
     if (!T) return j;
     j.gx = hla_grid_x(D, B);
-    j.gy = hla_grid_y(N, B);
+    j.gy = hla_grid_y(Kp / r * B, B);
     j.grp = hla_job_grp(B, r);
     j.nb = hla_job_blocks(j.gx, j.gy, j.grp);
     return j;
@@ -487,7 +502,7 @@ FrontShare front_share(const FrontRows &jr, const FrontHla &jx, int B, bool is_f
     // together (4 MB), and the tensor must be large enough for its second read to cost real time.
     const int64_t row_bytes = static_cast<int64_t>(jr.O) * (is_f32 ? 4 : 2);
     if (row_bytes * RG > (int64_t(3) << 20) || row_bytes * jr.N < (int64_t(16) << 20)) return s;
-    const int64_t groups = (jr.N + RG - 1) / RG;
+    const int64_t groups = (jx.Kp / jx.r * B + RG - 1) / RG;     // with those that only clear the end of K3's rows
     int pair = B / (2 * jx.r);                          // K3 writes 256 r / B bytes per column and group
     if (pair < 1) pair = 1;
     if (pair > 8) pair = 8;
@@ -517,7 +532,7 @@ static hipError_t launch_front_t(const FrontRows &jr, const FrontHla &jx, const 
     // Unless that is switched off, the first launch takes both projections (the second is left with the pass
     // over W, if there is one) and hands out its workgroups in turns: the row quantiser's arithmetic then has
     // all the memory-bound work there is to run beside.
-    const FrontHla none = front_hla(nullptr, 0, 0, B, 1, nullptr);
+    const FrontHla none = front_hla(nullptr, 0, 0, B, 1, 0, nullptr);
     const bool both = g_mix_enabled.load() && !jc.on && !js.on && jg.T;
     const FrontMix jm = (jc.on || js.on) ? FrontMix{0, 0, 0} : front_mix(jr, jx, both ? jg.nb : 0);
     const FrontHla &jy = both ? jg : none;        // second projection of the first launch
