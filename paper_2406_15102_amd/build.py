@@ -26,6 +26,9 @@ FLAGS = [
     # the k loops of the matrix products are written to be unrolled in full (a step of 256 MFMAs with
     # everything that issues between them); the default size limit for `#pragma unroll` is below that
     "-mllvm", "-pragma-unroll-threshold=1000000",
+    # every nested guard restores the lanes of the one around it: without that the register allocator's reloads at the end of
+    # a guarded store missed the lanes that only the inner guard had switched off (tests/test_gpu_edge_columns.py)
+    "-mllvm", "-amdgpu-remove-redundant-endcf=false",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 
