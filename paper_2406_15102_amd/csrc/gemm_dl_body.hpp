@@ -14,7 +14,7 @@
 //     steps every line is asked for twice and a load takes 1.7 x as long to land;
 //   * loads go out singly between the MFMAs, never in a burst from all four wavefronts (the address
 //     queues of the memory pipeline fill up and the wavefront stalls at issue);
-//   * LDS is a ring of five units, 32 KB each for a 256-tile -- all 160 KB.  Step kt keeps its A rows in unit 2 kt mod 5 and
+//   * LDS is a ring of five units (2 AHEAD + 1), 32 KB each for a 256-tile -- all 160 KB.  Step kt keeps its A rows in unit 2 kt mod 5 and
 //     its Bm rows in the next one, so while step kt is multiplied step kt + 1 is complete or landing
 //     in two more units and the fifth takes the A rows of step kt + 2 already: a load has between
 //     0.75 and 1.5 steps to land, about what the register-staged pipeline gives it.
@@ -42,6 +42,9 @@
 // than 128, hence the second workgroup.  The launch of both products, register-staged -> this, whole passes on changing
 // inputs: 4096 x 2048 x 5632 in fp32 92.1 -> 84.1 us; products called alone: 8192 x 2048 x 2048 72.4 -> 69.1, 4096 x 1024 x
 // 4096 29.4 -> 26.6, 2048 x 2048 x 2048 21.3 -> 20.0; gemm_dl128_ok says where it is taken.
+// Beside 256-tiles of the other product, whose LDS leaves it a compute unit to itself, its ring is nine units (AHEAD = 4): a load
+// has 2.75 to 3.5 steps to land instead of 0.75 to 1.5, which one wavefront a SIMD and 32 MFMAs a step do not cover.  Whole passes
+// with that pair of tiles, register-staged -> this: 9200 x 1160 x 3120 117.6 -> 113.2 us, 12608 x 768 x 3072 104.4 -> 102.6.
 // 4-bit codes in the f6 layout (KIND 3; hlq_device.hpp says how it widens) are 6-bit floats to the matrix cores, 128 of k
 // to an MFMA of the cycles that 64 bytes take.  Registers alone sustain 6.9 POP/s that way, 4.1 on the bytes that
 // nibbles widen to (Mma16<2>): 1.65 and 1.97 GHz, the power limit in either case.  A step is that of bytes: 16 rows x 64 B
@@ -61,6 +64,8 @@ typedef float v4f_t __attribute__((ext_vector_type(4)));
 
 constexpr size_t kGemmDlLdsBytes = 5u * 256u * 128u;   // the ring; the epilogue's slabs reuse its start
 constexpr size_t kGemmDl128LdsBytes = 5u * 128u * 128u;   // of a 128 x 128 tile: two to a compute unit
+constexpr int kGemmDlDeep = 4;                            // steps ahead of a 128 x 128 tile that has its compute unit to itself
+constexpr size_t kGemmDl128DeepLdsBytes = (2u * kGemmDlDeep + 1u) * 128u * 128u;
 
 // 16 x 16 MFMAs.  The MFMA's A operand is fed from Bm and its B operand from A, which leaves a lane with
 // C[m][n .. n + 3], m = 16 i + lane % 16, n = 16 j + 4 (lane / 16), of accumulator (i, j).
@@ -227,7 +232,7 @@ __device__ __forceinline__ void store_scaled16(typename Mma16<KIND>::acc_t (&acc
 // Requires tiles of 32 NBM rows x 32 NB columns, NBM = 8 or 6 with NB = 8, or both 4 (g.tiles_m, g.tiles_n counted
 // in such tiles; the 192-row tile is not written for packed codes), at least two whole steps a workgroup, and
 // g.Kb % 128 == 0 unless RAGGED (then g.Kb % 16 == 0).
-template <int KIND, int NBM, int OUT, int NB = 8, bool RAGGED = false>
+template <int KIND, int NBM, int OUT, int NB = 8, bool RAGGED = false, int AHEAD = 2>
 __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 {
     constexpr int BT = 32 * NB, BTM = 32 * NBM, GROUP = 4;
@@ -239,7 +244,9 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     constexpr int SLOTS = NBM * NB;               // MFMAs of a sub-step, one per accumulator
     constexpr int NR = NBM + NB;                  // fragments of a sub-step
     constexpr uint32_t UNIT = BT * 128u;          // one operand's rows of one step: 32 or 16 KB
-    constexpr uint32_t RING = 5u * UNIT;
+    static_assert(AHEAD == 2 || (NB == 4 && !RAGGED), "a longer ring: 128 x 128 tiles of whole steps");
+    constexpr int UNITS = 2 * AHEAD + 1;
+    constexpr uint32_t RING = UNITS * UNIT;
     extern __shared__ u32x4 lds[];
     char *const ldsb = reinterpret_cast<char *>(lds);
 
@@ -373,17 +380,17 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 #pragma unroll
         for (int j = 0; j < NB; ++j) acc[i][j] = Mma16<KIND>::zero();
 
-    // prologue: steps 0 and 1 in flight (units 0, 1 and 2, 3), wait for step 0
+    // prologue: AHEAD steps in flight (steps 0 and 1 in units 0, 1 and 2, 3), wait for step 0
 #pragma unroll
-    for (int j = 0; j < NBM; ++j) HLQD_LOAD_ONE(0, 0, j, 0)
+    for (int a = 0; a < AHEAD; ++a) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) HLQD_LOAD_ONE(0, 1, j, 1)
+        for (int j = 0; j < NBM; ++j) HLQD_LOAD_ONE(a, 0, j, 2 * a)
 #pragma unroll
-    for (int j = 0; j < NBM; ++j) HLQD_LOAD_ONE(1, 0, j, 2)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) HLQD_LOAD_ONE(1, 1, j, 3)
+        for (int j = 0; j < NB; ++j) HLQD_LOAD_ONE(a, 1, j, 2 * a + 1)
+    }
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0070 | (NR & 15) | ((NR >> 4) << 14));   // vmcnt(NR): step 0 has landed
+    constexpr int AFTER = (AHEAD - 1) * NR;
+    __builtin_amdgcn_s_waitcnt(0x0070 | (AFTER & 15) | ((AFTER >> 4) << 14));   // vmcnt(AFTER): step 0 has landed
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
@@ -415,7 +422,7 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
         asm volatile("s_nop 1");                // ... and two instructions ahead of the first MFMA
     }
 
-    // Step kt reads units u = 2 kt mod 5 (A) and u + 1 (Bm); step kt + 1 sits in the next two units.
+    // Step kt reads units u = 2 kt mod UNITS (A) and u + 1 (Bm); step kt + 1 sits in the next two units.  (Below, for AHEAD = 2.)
     // Every sub-step is SLOTS = NBM NB MFMAs -- accumulator (q / NB, q % NB) in slot q -- and reads the NR = NBM + NB
     // fragments of the next sub-step in its even slots, from the first on (packed codes: see below).  The loop is written
     // slot by slot, what is to issue around one MFMA, with a scheduling fence after each slot, so the issue
@@ -428,7 +435,7 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
     //                               go into unit u, one load every fourth slot from the first on
     int u = 0;
     for (int kt = 0; kt < nk; ++kt) {
-        const int ua = u == 0 ? 4 : u - 1;   // (2 kt + 4) mod 5
+        const int ua = u == 0 ? UNITS - 1 : u - 1;   // (2 kt + 2 AHEAD) mod UNITS
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int cur = s & 1;
@@ -445,8 +452,8 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
                     if (q >= 2 && q < 8) HLQD_WIDEN(0, NB + 7, q - 2)
                     if (q >= 8 && (q & 7) >= 2) HLQD_WIDEN(0, NB + (q >> 3) - 1, (q & 7) - 2)
                     if (q >= 10 && q < 58) HLQD_WIDEN(cur ^ 1, (q - 10) / 6, (q - 10) % 6)
-                    if (s == 0 && (q & 7) == 1) HLQD_LOAD_ONE(kt + 2, 0, q >> 3, ua)
-                    if (s == 1 && q < 32 && (q & 3) == 1) HLQD_LOAD_ONE(kt + 2, 1, q >> 2, u)
+                    if (s == 0 && (q & 7) == 1) HLQD_LOAD_ONE(kt + AHEAD, 0, q >> 3, ua)
+                    if (s == 1 && q < 32 && (q & 3) == 1) HLQD_LOAD_ONE(kt + AHEAD, 1, q >> 2, u)
                     if (s == 0 && q >= 58 && q < 62) HLQD_NEXT_UNIT((q - 58) >> 1, q & 1)
                     Mma16<KIND>::mma(wb[cur][q & 7], wa[0][q >> 3], acc[q >> 3][q & 7]);
                     __builtin_amdgcn_sched_barrier(0);
@@ -460,7 +467,7 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
                         HLQD_READ_ONE(cur ^ 1, ns, 2 * q)
                         HLQD_READ_ONE(cur ^ 1, ns, 2 * q + 1)
                     }
-                    if ((q & 3) == 1) HLQD_LOAD_ONE(kt + 2, s, q >> 2, s == 0 ? ua : u)
+                    if ((q & 3) == 1) HLQD_LOAD_ONE(kt + AHEAD, s, q >> 2, s == 0 ? ua : u)
                     if (q == 3 || q == 7) HLQD_NEXT_UNIT(s, q == 7)
                     if (q >= 4) {
 #pragma unroll
@@ -474,8 +481,8 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 #pragma unroll
                 for (int q = 0; q < SLOTS; ++q) {
                     if (q < 2 * NR && !(q & 1)) HLQD_READ_ONE(cur ^ 1, ns, q >> 1)
-                    if (s < NS - 1 && (s * SLOTS + q) % APER == APER - 3) HLQD_LOAD_ONE(kt + 2, 0, (s * SLOTS + q) / APER, ua)
-                    if (s == NS - 1 && q < 4 * NB && (q & 3) == 1) HLQD_LOAD_ONE(kt + 2, 1, q >> 2, u)
+                    if (s < NS - 1 && (s * SLOTS + q) % APER == APER - 3) HLQD_LOAD_ONE(kt + AHEAD, 0, (s * SLOTS + q) / APER, ua)
+                    if (s == NS - 1 && q < 4 * NB && (q & 3) == 1) HLQD_LOAD_ONE(kt + AHEAD, 1, q >> 2, u)
                     if constexpr (NB == 8) {
                         if (s == NS - 2 && q >= 4 * NB && q < 4 * NB + 2 * NS) HLQD_NEXT_UNIT((q - 4 * NB) >> 1, q & 1)
                     } else {
@@ -494,9 +501,9 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
                         HLQD_READ_ONE(cur ^ 1, ns, 2 * q)
                         HLQD_READ_ONE(cur ^ 1, ns, 2 * q + 1)
                     }
-                    if (s == 0 && (q == 4 || q == 11)) HLQD_LOAD_ONE(kt + 2, 0, q == 11, ua)
-                    if ((s == 1 || s == 2) && q == 4) HLQD_LOAD_ONE(kt + 2, 0, s + 1, ua)
-                    if (s == 3 && (q & 3) == 1) HLQD_LOAD_ONE(kt + 2, 1, q >> 2, u)
+                    if (s == 0 && (q == 4 || q == 11)) HLQD_LOAD_ONE(kt + AHEAD, 0, q == 11, ua)
+                    if ((s == 1 || s == 2) && q == 4) HLQD_LOAD_ONE(kt + AHEAD, 0, s + 1, ua)
+                    if (s == 3 && (q & 3) == 1) HLQD_LOAD_ONE(kt + AHEAD, 1, q >> 2, u)
                     if (s < 3 && (q == 5 || q == 12)) HLQD_NEXT_UNIT(ns, q == 12)
                     if (s == 0 && (q == 13 || q == 14)) HLQD_NEXT_UNIT(0, q == 14)
                     if (q >= 6) {
@@ -523,9 +530,9 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
                         HLQD_READ_ONE(cur ^ 1, ns, 2 * q + 1)
                     }
                     if (lslot) {
-                        if (s < 2 && li % 3 == 1) HLQD_LOAD_ONE(kt + 2, 0, 3 * s + li / 3, ua)
-                        if (s == 2 && (li == 1 || li == 4)) HLQD_LOAD_ONE(kt + 2, 0, 6 + li / 3, ua)
-                        if (s == 3) HLQD_LOAD_ONE(kt + 2, 1, li, u)
+                        if (s < 2 && li % 3 == 1) HLQD_LOAD_ONE(kt + AHEAD, 0, 3 * s + li / 3, ua)
+                        if (s == 2 && (li == 1 || li == 4)) HLQD_LOAD_ONE(kt + AHEAD, 0, 6 + li / 3, ua)
+                        if (s == 3) HLQD_LOAD_ONE(kt + AHEAD, 1, li, u)
                         if (s < 3 && (li == 3 || li == 6)) HLQD_NEXT_UNIT(ns, li == 6)
                         if (s == 0 && (li == 0 || li == 2)) HLQD_NEXT_UNIT(0, li == 2)
                     }
@@ -539,13 +546,15 @@ __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
             }
             if (s == NS - 2) {
                 asm volatile("" ::: "memory");   // no memory access of the program may cross the barrier
-                __builtin_amdgcn_s_waitcnt(0x0070 | NBM);   // vmcnt(NBM): all but the A rows of step kt + 2; lgkmcnt(0)
+                // vmcnt: all but the A rows of step kt + AHEAD and what is between (step kt + 2 up to it); lgkmcnt(0)
+                constexpr int YOUNG = (AHEAD - 2) * NR + NBM;
+                __builtin_amdgcn_s_waitcnt(0x0070 | (YOUNG & 15) | ((YOUNG >> 4) << 14));
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        u = u + 2 >= 5 ? u - 3 : u + 2;
+        u = u + 2 >= UNITS ? u + 2 - UNITS : u + 2;
     }
     if constexpr (RAGGED) {
         // the sub-steps of the ragged step, with what lies past the end of a row cleared in either operand (not in one

@@ -20,17 +20,18 @@
 namespace hlq {
 
 // MODE: 0 = rows of whole 128-byte steps, 1 = a ragged last step, 2 = whole steps loaded straight into
-// LDS (gemm_dl_body.hpp), 3 = the same with a ragged last step (128-tiles only)
+// LDS (gemm_dl_body.hpp), 3 = the same with a ragged last step (128-tiles only), 4 = as 2 with the ring of a 128-tile that has
+// its compute unit to itself
 template <int KIND_, int W_, int MODE_, int OUT_> struct TileCfg {
     static constexpr int KIND = KIND_, W = W_, OUT = OUT_, MODE = MODE_;
-    static constexpr size_t LDS = MODE_ >= 2 ? (W_ == 4 ? kGemmDlLdsBytes : kGemmDl128LdsBytes) : gemm_lds_bytes(W_, W_, 8);
+    static constexpr size_t LDS = MODE_ == 4 ? kGemmDl128DeepLdsBytes : MODE_ >= 2 ? (W_ == 4 ? kGemmDlLdsBytes : kGemmDl128LdsBytes) : gemm_lds_bytes(W_, W_, 8);
     static_assert(MODE_ < 3 || W_ == 2, "a ragged last step straight into LDS: 128 x 128 tiles");
 };
 
 template <class C>
 __device__ __forceinline__ void pair_tile(const GemmDev &g, int idx)
 {
-    if constexpr (C::MODE >= 2) gemm_tile_dl<C::KIND, 2 * C::W, C::OUT, 2 * C::W, C::MODE == 3>(g, idx);
+    if constexpr (C::MODE >= 2) gemm_tile_dl<C::KIND, 2 * C::W, C::OUT, 2 * C::W, C::MODE == 3, C::MODE == 4 ? kGemmDlDeep : 2>(g, idx);
     else gemm_tile<C::KIND, C::W, C::W, 8, C::MODE == 1, C::OUT>(g, idx);
 }
 // whether a product of this configuration may hand its last rows to 192-row tiles (gemm_dl_body.hpp)
@@ -105,6 +106,9 @@ static hipError_t launch_pair_a(const GemmDev &ga, const GemmDev &gb, const Gemm
             if (modeB == 2) return launch_pair_b<CA, KB, 4, 2>(ga, gb, gbt, outB, b_first, st);
             return modeB ? launch_pair_b<CA, KB, 4, 1>(ga, gb, gbt, outB, b_first, st) : launch_pair_b<CA, KB, 4, 0>(ga, gb, gbt, outB, b_first, st);
         }
+        if constexpr (CA::W == 4 && CA::MODE == 2) {
+            if (modeB == 4) return launch_pair_b<CA, KB, 2, 4>(ga, gb, gbt, outB, b_first, st);
+        }
         if constexpr (CA::KIND == 3 && CA::W == 2) {
             if (modeB == 2) return launch_pair_b<CA, KB, 2, 2>(ga, gb, gbt, outB, b_first, st);
             if (modeB == 3) return launch_pair_b<CA, KB, 2, 3>(ga, gb, gbt, outB, b_first, st);
@@ -149,7 +153,9 @@ static hipError_t launch_pair_kinds(const GemmDev &ga, const GemmDev &gb, const 
         if (dl128) return whole ? 2 : 3;
         return whole ? (big && gemm_dl_ok(g.Kb, g.splits) ? 2 : 0) : 1;
     };
-    const int modeB = mode(gb, bigB);
+    int modeB = mode(gb, bigB);
+    // 128-tiles beside 256-tiles straight into LDS, which leave them a compute unit each
+    if (bigA && !bigB && (KA == 3 || mode(ga, true) == 2) && gemm_dl_ok(gb.Kb, gb.splits)) modeB = 4;
     if constexpr (KA == 3)      // f6 codes: always straight into LDS
         return bigA ? launch_pair_o<KA, KB, 4, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st)
                     : launch_pair_o<KA, KB, 2, 2>(ga, gb, gbt, f32, bigB, modeB, outB, b_first, st);
