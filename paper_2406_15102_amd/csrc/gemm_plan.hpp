@@ -41,6 +41,7 @@ bool gemm_dl_ok(int Kb, int splits);
 void gemm_dl_enable(bool on);
 // the same for two products on 128-tiles in one launch; scale_a: cost of a step of `a` in steps of `b`
 bool gemm_dl128_ok(const GemmDev &a, double scale_a, const GemmDev &b);
+bool gemm_dl128_pays(int steps_a, double scale_a, double tiles_a, int steps_b, double tiles_b);   // whole steps a workgroup, workgroups
 
 // Rows at the end of a product of M x N in 256 x 256 tiles that are better served by 192-row tiles
 // (gemm_dl_body.hpp), 0 = none: when `before` tiles of the same launch are dispatched ahead of it and its
@@ -109,6 +110,24 @@ static inline GemmDev gemm_dev_cut_tail(GemmDev &g, int tail_rows)
 // ---- model of a launch that carries two products (k_gemm_pair.hip says how it is fitted), microseconds ----
 constexpr double kStepBig = 1.3, kStepSmallAlone = 0.6, kStepSmallShared = 0.9;
 constexpr double kFixedBig = 16.0, kFixedSmall = 6.5;
+// one product's tiles: a step, and what a tile costs beside its steps
+struct TileCost {
+    double step, fixed;
+};
+// 256-tiles, 128-tiles beside 256-tiles of the other product (a compute unit each), 128-tiles of both products that have one
+// each, and that share one in twos
+struct TileCosts {
+    TileCost big, beside, alone, shared;
+};
+constexpr TileCosts kTileCosts = {{kStepBig, kFixedBig}, {kStepSmallAlone, kFixedSmall}, {kStepSmallAlone, kFixedSmall}, {kStepSmallShared, kFixedSmall}};
+// The same where the g_x product is on codes in the f6 layout: its tiles, and the g_w product's with operands straight into LDS or
+// through registers.  Fitted to every plan of 653 layers of 2 to 800 GFLOP (whole passes, either dispatch order): the plan
+// taken is 1.2 % from the best one in the mean, 2.0 % with the constants above, and 12608 x 768 x 3072 takes 102.6 us where those
+// picked one of 114.9.
+constexpr TileCosts kTileCostsF6 = {{1.35, 16.4}, {0.58, 6.8}, {0.58, 7.3}, {1.02, 4.0}};
+constexpr TileCosts kTileCostsDirect = {{1.2, 17.0}, {0.55, 5.3}, {0.58, 4.7}, {1.0, 4.2}}, kTileCostsStaged = {{2.0, 17.3}, {0.77, 3.6}, {0.72, 3.6}, {1.32, 4.1}};
+constexpr double kPartialUs = 1.0e-6, kReduceUs = 3.0;     // a k split: of each partial value, and of the reduction's launch
+constexpr double kPartialUsF6 = 1.54e-6, kReduceUsF6 = 4.5;
 constexpr double kOneStepSaves = 2.0;    // a tile of one step skips the pipeline (gemm_body.hpp)
 constexpr int kSplitChoices[] = {1, 2, 3, 4, 6, 8, 12, 16};
 
@@ -116,11 +135,11 @@ struct TileClass {
     double step, fixed;
     int slots;   // tiles in flight on the chip
 };
-inline TileClass tile_class(bool big, bool mixed, double n)
+inline TileClass tile_class(const TileCosts &c, bool big, bool mixed, double n)
 {
-    if (big) return {kStepBig, kFixedBig, 256};
-    if (mixed || n <= 256.0) return {kStepSmallAlone, kFixedSmall, 256};
-    return {kStepSmallShared, kFixedSmall, 512};
+    const bool share = !big && !mixed && n > 256.0;
+    const TileCost &t = big ? c.big : (mixed ? c.beside : (share ? c.shared : c.alone));
+    return {t.step, t.fixed, share ? 512 : 256};
 }
 
 // nA tiles of tA on mA slots, then nB tiles of tB on mB slots (the same silicon, possibly cut finer)

@@ -84,7 +84,7 @@ int check_backward_shape(int64_t N, int64_t d_in, int64_t d_out, int B, int r)
 struct Layout {
     int64_t Kp;
     int codes;       // kCodesBytes, ...: how the codes of the g_x list are kept
-    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, least, tabw, tabg, tabx, padded, total;
+    size_t Gq, sG, Wq, sW, wws, GhatT, sGhat, XhatT, sXhat, hws, hwsx, amax_end, gws, gws_bytes, gws_least, least, tabw, tabg, tabx, padded, total;
 };
 
 // the launches that make both projections with padded rows, and fold tables of column maxima: the fused ones
@@ -103,6 +103,15 @@ int codes_kept(int64_t d_out, int flags, bool image)
     return four && d_out % 32 == 0 ? hlq::kCodesNibbles : hlq::kCodesBytes;
 }
 
+// elements from one row of the projections to the next, where they are padded
+int64_t padded_k(int64_t N, int64_t d_out, int B, int r, bool x_is_compressed, int flags)
+{
+    // X projected here, or the int8 codes unpacked from a 4-bit store that was handed over
+    const bool x_here = !x_is_compressed || (flags & HLQ_FLAG_XC_INT4);
+    const int64_t Kc = N / B * r;
+    return fused_front(d_out, B, flags) && x_here ? hlq::pad_row(Kc, (flags & HLQ_FLAG_GW_INT8) ? 1 : 2) : Kc;
+}
+
 Layout carve_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags, bool image, size_t gws_bytes,
                     bool pad)
 {
@@ -112,10 +121,8 @@ Layout carve_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x
     const size_t code_row = codes == hlq::kCodesF6 ? hlq::f6_row_bytes(static_cast<int>(d_out)) : static_cast<size_t>(codes == hlq::kCodesNibbles ? d_out / 2 : d_out);
     const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0, fused = fused_front(d_out, B, flags);
     const size_t esz = gwi ? 1 : 2;
-    // X projected here, or the int8 codes unpacked from a 4-bit store that was handed over
-    const bool x_unpack = x_is_compressed && (flags & HLQ_FLAG_XC_INT4), x_here = !x_is_compressed || x_unpack;
-    L.Kp = N / B * r;
-    if (pad && fused && x_here) L.Kp = hlq::pad_row(L.Kp, static_cast<int>(esz));
+    const bool x_here = !x_is_compressed || (flags & HLQ_FLAG_XC_INT4);
+    L.Kp = pad ? padded_k(N, d_out, B, r, x_is_compressed, flags) : N / B * r;
     const size_t Kp = static_cast<size_t>(L.Kp);
     size_t off = 0;
     L.Gq = off;    off += up256(static_cast<size_t>(N) * code_row);
@@ -132,7 +139,7 @@ Layout carve_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x
     L.sGhat = off; off += gwi ? up256(static_cast<size_t>(d_out) * 4) : 0;
     L.XhatT = off; off += x_here ? up256(static_cast<size_t>(d_in) * Kp * esz) : 0;
     L.sXhat = off; off += (gwi && !x_is_compressed) ? up256(static_cast<size_t>(d_in) * 4) : 0;
-    L.gws_bytes = gws_bytes;
+    L.gws_bytes = L.gws_least = gws_bytes;
     L.gws = off;   off += up256(L.gws_bytes);
     L.least = off;
     const bool tables = gwi && fused;
@@ -150,7 +157,7 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
     // split-K partial sums of whichever product wants them (the two products run one after the other)
     const size_t g1 = hlq::gemm_ws_bytes(0, static_cast<int>(N), static_cast<int>(d_in), static_cast<int>(d_out));
     const size_t g2 = hlq::gemm_ws_bytes(gwi ? 0 : 1, static_cast<int>(d_out), static_cast<int>(d_in), static_cast<int>(Kc));
-    size_t gws_bytes = g1 > g2 ? g1 : g2;
+    size_t gws_bytes = g1 > g2 ? g1 : g2, gws_f6 = 0;
     if (!(flags & HLQ_FLAG_SEPARATE_PRODUCTS)) {
         // the two products in one launch plan the g_w product's k split for the pair
         const bool packed = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && d_out % 32 == 0;
@@ -159,10 +166,14 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
         aw.M = static_cast<int>(d_out), aw.N = static_cast<int>(d_in), aw.K = static_cast<int>(Kc);
         const size_t gp = hlq::gemm_pair_ws_bytes(packed ? 2 : 0, ax, gwi ? 0 : 1, aw, size_t(256) << 20);
         if (gp > gws_bytes) gws_bytes = gp;
+        // the plan for codes in the f6 layout is another; what it asks for beyond that of nibbles is not part of `least`
+        aw.K = static_cast<int>(padded_k(N, d_out, B, r, x_is_compressed, flags));
+        if (codes_kept(d_out, flags, image) == hlq::kCodesF6) gws_f6 = hlq::gemm_pair_ws_bytes(3, ax, gwi ? 0 : 1, aw, size_t(256) << 20);
     }
-    Layout L = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, image, gws_bytes, true);
+    Layout L = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, image, gws_bytes > gws_f6 ? gws_bytes : gws_f6, true);
     const Layout bytes = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, image, gws_bytes, false);
     L.least = bytes.least;
+    L.gws_least = gws_bytes;
     L.padded = L.total;
     if (L.total < bytes.total) L.total = bytes.total;
     return L;
@@ -660,7 +671,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         if ((rc = own_workspace(full.least, full.total, &p, &workspace_bytes)) != HLQ_OK) return rc;
         ws = static_cast<char *>(p);
     }
-    const Layout L = workspace_bytes >= full.padded ? full : carve_layout(N, d_in, d_out, B, r, xc, flags, image != nullptr, full.gws_bytes, false);
+    const Layout L = workspace_bytes >= full.padded ? full : carve_layout(N, d_in, d_out, B, r, xc, flags, image != nullptr, full.gws_least, false);
     const int codes = full.codes;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool f32 = dtype == HLQ_F32;

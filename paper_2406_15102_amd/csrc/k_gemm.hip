@@ -25,14 +25,18 @@ bool gemm_dl_ok(int Kb, int splits)
 // one wavefront a SIMD waits out LDS.  Whole pass on changing inputs, register-staged -> this: 4096 x 2048 x 5632 in
 // fp32 (work 2.1 x the longest tile) 167.9 -> 158.3 us, 12608 x 768 x 3072 (0.53 x) 120.3 -> 125.6; products alone, 4 tiles
 // of 392 steps beside short ones (50176 x 432 x 96) 157 -> 180.
-bool gemm_dl128_ok(const GemmDev &a, double scale_a, const GemmDev &b)
+bool gemm_dl128_pays(int steps_a, double scale_a, double tiles_a, int steps_b, double tiles_b)
 {
     constexpr int kMinSteps = 2;
     constexpr double kSlots = 512.0, kLeastRounds = 0.9;
-    const double steps_a = scale_a * (a.Kb / 128 / a.splits), steps_b = b.Kb / 128 / b.splits;
-    const double work = steps_a * a.tiles_m * a.tiles_n * a.splits + steps_b * b.tiles_m * b.tiles_n * b.splits;
-    return g_dl_enabled.load() != 0 && a.Kb / 128 / a.splits >= kMinSteps && b.Kb / 128 / b.splits >= kMinSteps &&
-           work >= kLeastRounds * kSlots * (steps_a > steps_b ? steps_a : steps_b);
+    const double a = scale_a * steps_a, b = steps_b;
+    return steps_a >= kMinSteps && steps_b >= kMinSteps && a * tiles_a + b * tiles_b >= kLeastRounds * kSlots * (a > b ? a : b);
+}
+bool gemm_dl128_ok(const GemmDev &a, double scale_a, const GemmDev &b)
+{
+    return g_dl_enabled.load() != 0 &&
+           gemm_dl128_pays(a.Kb / 128 / a.splits, scale_a, static_cast<double>(a.tiles_m) * a.tiles_n * a.splits, b.Kb / 128 / b.splits,
+                           static_cast<double>(b.tiles_m) * b.tiles_n * b.splits);
 }
 
 // `gt`: the product's last rows in 192-row tiles (gt.tiles_m = 0: none), dispatched behind the n_main

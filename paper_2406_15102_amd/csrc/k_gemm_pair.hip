@@ -37,6 +37,10 @@ struct PairPlan {
 
 static PairPlan plan_pair(const GemmArgs &a, int kindA, const GemmArgs &b, int kindB, size_t ws_bytes)
 {
+    const bool f6 = kindA == 3;
+    const TileCosts &costsA = f6 ? kTileCostsF6 : kTileCosts;
+    const double saves = f6 ? 0.0 : kOneStepSaves;
+    const double partial = f6 ? kPartialUsF6 : kPartialUs, reduce = f6 ? kReduceUsF6 : kReduceUs;
     const int nkA = (row_bytes(kindA, a.K) + 127) / 128, nkB = (row_bytes(kindB, b.K) + 127) / 128;
     const double scaleA = step_scale(kindA), scaleB = step_scale(kindB);
     const double mnB = static_cast<double>(b.M) * b.N;
@@ -48,19 +52,25 @@ static PairPlan plan_pair(const GemmArgs &a, int kindA, const GemmArgs &b, int k
             const int ta = bigA ? 256 : 128, tb = bigB ? 256 : 128;
             const double nA = static_cast<double>((a.M + ta - 1) / ta) * ((a.N + ta - 1) / ta);
             const double nB1 = static_cast<double>((b.M + tb - 1) / tb) * ((b.N + tb - 1) / tb);
-            const TileClass ca = tile_class(bigA != 0, mixed, nA);
-            const double tA = nkA * scaleA * ca.step + ca.fixed - (nkA == 1 ? kOneStepSaves : 0.0);
+            const TileClass ca = tile_class(costsA, bigA != 0, mixed, nA);
+            const double tA = nkA * scaleA * ca.step + ca.fixed - (nkA == 1 ? saves : 0.0);
             for (int S : kSplitChoices) {
                 if (S > 1 && (S > nkB || S * mnB * 4.0 > static_cast<double>(ws_bytes))) break;
-                const TileClass cb = tile_class(bigB != 0, mixed, nB1 * S);
+                // by sizes alone: rows of a store, which may end inside a step, are split like the padded ones (same sums)
+                const bool direct = bigA || bigB ? nkB / S >= 4 : gemm_dl128_pays(nkA, scaleA, nA, nkB / S, nB1 * S);
+                const TileClass cb = tile_class(f6 ? (direct ? kTileCostsDirect : kTileCostsStaged) : kTileCosts, bigB != 0, mixed, nB1 * S);
                 const double stepsB = __builtin_ceil(static_cast<double>(nkB) / S);
-                const double tB = stepsB * scaleB * cb.step + cb.fixed - (stepsB == 1.0 ? kOneStepSaves : 0.0);
+                const double tB = stepsB * scaleB * cb.step + cb.fixed - (stepsB == 1.0 ? saves : 0.0);
+                const double extra = S > 1 ? partial * S * mnB + reduce : 0.0;     // partials out and back, one more launch
+                // no shorter than its longest tile, nor (but for rounding) than its work spread over the chip: most plans need
+                // no look at how they unfold
+                const double least = __builtin_fmax(__builtin_fmax(tA, tB), 0.99 * (nA * tA / ca.slots + nB1 * S * tB / cb.slots));
+                if (least + extra >= best_t) continue;
                 // either product may go first: usually the one with the longer tiles, which must not start late
                 const double tab = pair_makespan(nA, tA, ca.slots, nB1 * S, tB, cb.slots);
                 const double tba = pair_makespan(nB1 * S, tB, cb.slots, nA, tA, ca.slots);
                 const bool b_first = tba < tab;
-                double t = b_first ? tba : tab;
-                if (S > 1) t += 2.0 * S * mnB * 4.0 / 8.0e6 + 3.0;     // partials out and back, one more launch
+                const double t = (b_first ? tba : tab) + extra;
                 if (t < best_t) {
                     best_t = t;
                     best = PairPlan{bigA != 0, bigB != 0, S, b_first};
