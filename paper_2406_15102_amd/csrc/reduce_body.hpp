@@ -7,6 +7,29 @@
 
 namespace hlq {
 
+// The sum of a value's partials, 16 bytes a lane, in split order.  Up to eight loads go out before the first addition (past the
+// last split it is loaded again and not added): one after the other their latency is the kernel.  Whole pass of 50176 x 432 x 96,
+// twelve splits, one load at a time 54.2 us, four 52.6, eight 52.3; three splits even.
+template <typename V, int AT_ONCE>
+__device__ __forceinline__ V splitk_sum_by(const int32_t *__restrict__ p, int splits, int64_t total)
+{
+    V sum{};
+    for (int z = 0; z < splits; z += AT_ONCE) {
+        V v[AT_ONCE];
+#pragma unroll
+        for (int k = 0; k < AT_ONCE; ++k) v[k] = *reinterpret_cast<const V *>(p + (z + k < splits ? z + k : splits - 1) * total);
+#pragma unroll
+        for (int k = 0; k < AT_ONCE; ++k)
+            if (z + k < splits) sum += v[k];
+    }
+    return sum;
+}
+template <typename V>
+__device__ __forceinline__ V splitk_sum(const int32_t *__restrict__ p, int splits, int64_t total)
+{
+    return splits <= 4 ? splitk_sum_by<V, 4>(p, splits, total) : splitk_sum_by<V, 8>(p, splits, total);
+}
+
 // KIND 0: int32 partials (the two integer products), 1: fp32 partials.  `block`: 1024 outputs each.
 template <int KIND, bool F32>
 __device__ __forceinline__ void splitk_reduce_body(const int32_t *__restrict__ partial, int splits, int M, int N,
@@ -19,17 +42,14 @@ __device__ __forceinline__ void splitk_reduce_body(const int32_t *__restrict__ p
     const int m = static_cast<int>(e / N), n = static_cast<int>(e % N);
     f32x4 o;
     if (KIND == 0) {
-        v4i sum = {0, 0, 0, 0};
-        for (int z = 0; z < splits; ++z) sum += *reinterpret_cast<const v4i *>(partial + z * total + e);
+        const v4i sum = splitk_sum<v4i>(partial + e, splits, total);
         const float sa = sA ? sA[m] : 1.0f;
         f32x4 cs = {alpha, alpha, alpha, alpha};
         if (sB) cs = *reinterpret_cast<const f32x4 *>(sB + n) * alpha;
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[k] = static_cast<float>(sum[k]) * (sa * cs[k]);
     } else {
-        f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int z = 0; z < splits; ++z) sum += *reinterpret_cast<const f32x4 *>(partial + z * total + e);
-        o = sum * alpha;
+        o = splitk_sum<f32x4>(partial + e, splits, total) * alpha;
     }
     if (F32) {
         *reinterpret_cast<f32x4 *>(static_cast<float *>(C) + e) = o;
