@@ -9,7 +9,7 @@
 // the k split of the g_w product are planned for the pair, not for each product alone.
 //
 // One translation unit per pair of operand kinds (k_gemm_pair_*.hip instantiate launch_pair_kinds
-// below: 116 kernels each -- two tile sizes and whole or ragged k steps per product, the 256-tile of whole steps and
+// below: over a hundred kernels each -- two tile sizes and whole or ragged k steps per product, the 256-tile of whole steps and
 // two 128-tiles also with their operands loaded straight into LDS, bf16 or fp32
 // output, direct output or split-k partials for the g_w product); k_gemm_pair.hip plans and dispatches.
 #pragma once

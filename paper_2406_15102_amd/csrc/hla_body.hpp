@@ -133,8 +133,8 @@ __device__ __forceinline__ void hla_job_map(int l, int gx, int grp, int &bx, int
 // LM: lanes side by side as a multiple of hla_lanes(B) -- 1 for the stand-alone shape (B lanes x 256/B token
 // blocks), 2 for the workgroups that share their rows of G with K1 through one XCD's L2
 // (2 B lanes = 256 columns x 128/B token blocks = 128 rows).
-// Kp: values from one row of ThatT to the next, those behind the N / B * r coefficients zeros (pad_row; with coeffT there are none)
-template <int B, int BASIS, typename Src, int LM = 1>
+// PAD: rows of ThatT are Kp values apart, those behind the N / B * r coefficients zeros (pad_row; not with coeffT)
+template <int B, int BASIS, typename Src, int LM = 1, bool PAD = false>
 __device__ __forceinline__ void hla_body_src(const Src &src, int64_t N, int D, int r, int64_t Kp, bf16_t *__restrict__ ThatT,
                                              float *__restrict__ coeffT, int bx, int by)
 {
@@ -143,22 +143,27 @@ __device__ __forceinline__ void hla_body_src(const Src &src, int64_t N, int D, i
     static_assert(NB >= 1 && L * NB == 256, "a K3 workgroup is 256 lanes");
     const int tid = threadIdx.x;
     const int col0 = (bx * L + tid % L) * CPL;
+    const int64_t nblk = N / B;
+    const int64_t pitch = PAD ? Kp : nblk * r;
     const int64_t blk = static_cast<int64_t>(by) * NB + tid / L;
-    if (col0 >= D || blk * r >= Kp) return;
-    if (blk >= N / B) {
+    if constexpr (PAD) {
+        if (col0 >= D || blk * r >= Kp) return;
+        if (blk >= nblk) {
 #pragma unroll
-        for (int c = 0; c < CPL; ++c)
+            for (int c = 0; c < CPL; ++c)
 #pragma nounroll
-            for (int k = 0; k < r; ++k) ThatT[static_cast<int64_t>(col0 + c) * Kp + blk * r + k] = 0;
-        return;
+                for (int k = 0; k < r; ++k) ThatT[static_cast<int64_t>(col0 + c) * Kp + blk * r + k] = 0;
+            return;
+        }
     }
+    if (col0 >= D || blk >= nblk) return;
 
     float v[B * CPL];
     src.template load_block<B, CPL>(blk * B, col0, v);
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
         fwht_regs<B, CPL>(v + c);
-        const int64_t o = static_cast<int64_t>(col0 + c) * Kp + blk * r;
+        const int64_t o = static_cast<int64_t>(col0 + c) * pitch + blk * r;
         if (r >= 8) {
 #pragma unroll
             for (int k = 0; k < B; k += 8) {
@@ -189,11 +194,11 @@ __device__ __forceinline__ void hla_body_src(const Src &src, int64_t N, int D, i
     }
 }
 
-template <typename Tin, int B, int BASIS, int LM = 1>
+template <typename Tin, int B, int BASIS, int LM = 1, bool PAD = false>
 __device__ __forceinline__ void hla_body(const Tin *__restrict__ T, int64_t N, int D, int r, int64_t Kp, bf16_t *__restrict__ ThatT,
                                          float *__restrict__ coeffT, int bx, int by)
 {
-    hla_body_src<B, BASIS, DenseRows<Tin>, LM>(DenseRows<Tin>{T, D}, N, D, r, Kp, ThatT, coeffT, bx, by);
+    hla_body_src<B, BASIS, DenseRows<Tin>, LM, PAD>(DenseRows<Tin>{T, D}, N, D, r, Kp, ThatT, coeffT, bx, by);
 }
 
 template <int NW> struct Words { static constexpr int value = NW; };
@@ -248,8 +253,8 @@ __device__ __forceinline__ void hla_absmax_body(const Tin *__restrict__ T, int64
 
 // P4: codes in [-7, 7] stored two to a byte (TqT then has Kc/2 bytes per feature; needs r % 8 == 0) -- the
 // 4-bit form in which the compressed activation is kept between the passes (Sec. 6.1) -- instead of
-// codes in [-127, 127], one int8 each.  Same stream, same counters, same maxima either way.  Kp: as in hla_body_src.
-template <int B, int BASIS, bool MANT, typename Src, bool P4 = false>
+// codes in [-127, 127], one int8 each.  Same stream, same counters, same maxima either way.  PAD, Kp: as in hla_body_src.
+template <int B, int BASIS, bool MANT, typename Src, bool P4 = false, bool PAD = false>
 __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N, int D, int r,
                                                       const uint32_t *__restrict__ amax_bits, uint32_t k0, uint32_t k1,
                                                       int64_t Kp, int8_t *__restrict__ TqT, float *__restrict__ sT,
@@ -263,14 +268,19 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
     const int64_t blk = static_cast<int64_t>(by) * NB + tid / L;
     float amax[CPL];
     fold_column_maxima<CPL>(amax_bits, D, table, bx, tid % L, amax);
-    if (col0 >= D || blk * r >= Kp) return;
-    if (blk >= nblk) {      // not with P4, whose rows have no padding
+    const int64_t pitch = PAD ? Kp : Kc;
+    if constexpr (PAD) {
+        static_assert(!P4, "4-bit codes are stored without padding");
+        if (col0 >= D || blk * r >= Kp) return;
+        if (blk >= nblk) {
 #pragma unroll
-        for (int c = 0; c < CPL; ++c)
+            for (int c = 0; c < CPL; ++c)
 #pragma nounroll
-            for (int k = 0; k < r; k += 4) *reinterpret_cast<uint32_t *>(TqT + static_cast<int64_t>(col0 + c) * Kp + blk * r + k) = 0u;
-        return;
+                for (int k = 0; k < r; k += 4) *reinterpret_cast<uint32_t *>(TqT + static_cast<int64_t>(col0 + c) * Kp + blk * r + k) = 0u;
+            return;
+        }
     }
+    if (col0 >= D || blk >= nblk) return;
 
     float v[B * CPL];
     src.template load_block<B, CPL>(blk * B, col0, v);
@@ -281,7 +291,7 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
         const float a = amax[c];
         const float inv = absmax_to_inv(a, QMAX);
         if (blk == 0) sT[col0 + c] = absmax_to_scale(a, QMAX);
-        const int64_t o = static_cast<int64_t>(col0 + c) * Kp + blk * r;          // r % 4 == 0
+        const int64_t o = static_cast<int64_t>(col0 + c) * pitch + blk * r;          // r % 4 == 0
         const uint32_t cnt = static_cast<uint32_t>(col0 + c) * static_cast<uint32_t>(Kc >> 2) +
                              static_cast<uint32_t>((blk * r) >> 2);
         // the kept coefficients in order, a group of random words at a time
@@ -317,13 +327,13 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
     }
 }
 
-template <typename Tin, int B, int BASIS, bool MANT = false, bool P4 = false>
+template <typename Tin, int B, int BASIS, bool MANT = false, bool P4 = false, bool PAD = false>
 __device__ __forceinline__ void hla_quantize_body(const Tin *__restrict__ T, int64_t N, int D, int r,
                                                   const uint32_t *__restrict__ amax_bits, uint32_t k0, uint32_t k1,
                                                   int64_t Kp, int8_t *__restrict__ TqT, float *__restrict__ sT,
                                                   float *__restrict__ coeffT, int bx, int by, int table = 0)
 {
-    hla_quantize_body_src<B, BASIS, MANT, DenseRows<Tin>, P4>(DenseRows<Tin>{T, D}, N, D, r, amax_bits, k0, k1, Kp, TqT, sT, coeffT,
+    hla_quantize_body_src<B, BASIS, MANT, DenseRows<Tin>, P4, PAD>(DenseRows<Tin>{T, D}, N, D, r, amax_bits, k0, k1, Kp, TqT, sT, coeffT,
                                                              bx, by, table);
 }
 

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
                 if (blk < jr.blocks)
                     front_rows_body<Tin, B, CODES>(jr, blk);
             } else {
-                hla_body<Tin, B, BASIS, 2>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, v - js.nk1, grp);
+                hla_body<Tin, B, BASIS, 2, true>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, v - js.nk1, grp);
             }
             return;
         }
@@ -122,11 +122,11 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
         } else if (k3 >= 0 && k3 < jx.nb) {
             int bx, by;
             hla_job_map(k3, jx.gx, jx.grp, bx, by);
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS, 1, true>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         } else if (k3 >= 0) {
             int bx, by;
             hla_job_map(k3 - jx.nb, jy.gx, jy.grp, bx, by);
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.Kp, jy.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS, 1, true>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.Kp, jy.out, nullptr, bx, by);
         } else {
             front_fill_or_recode<CODES>(jf, jk, b);
         }
@@ -141,16 +141,16 @@ __global__ __launch_bounds__(256) void k_front_a(FrontRows jr, FrontHla jx, Fron
         int bx, by;
         hla_job_map(b, jx.gx, jx.grp, bx, by);
         if (CONV)
-            hla_body_src<B, BASIS>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
+            hla_body_src<B, BASIS, ConvRows<Tin>, 1, true>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         else
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS, 1, true>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         return;
     }
     b -= jx.nb;
     if (b < jy.nb) {
         int bx, by;
         hla_job_map(b, jy.gx, jy.grp, bx, by);
-        hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.Kp, jy.out, nullptr, bx, by);
+        hla_body<Tin, B, BASIS, 1, true>(static_cast<const Tin *>(jy.T), jy.N, jy.D, jy.r, jy.Kp, jy.out, nullptr, bx, by);
         return;
     }
     front_fill_or_recode<CODES>(jf, jk, b - jy.nb);
@@ -186,15 +186,15 @@ __global__ __launch_bounds__(256, B == 64 ? 2 : 3) void k_front_one(FrontRows jr
         int bx, by;
         hla_job_map(b, jx.gx, jx.grp, bx, by);
         if (CONV)
-            hla_body_src<B, BASIS>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
+            hla_body_src<B, BASIS, ConvRows<Tin>, 1, true>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         else
-            hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
+            hla_body<Tin, B, BASIS, 1, true>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.Kp, jx.out, nullptr, bx, by);
         return;
     }
     b -= jx.nb;
     int bx, by;
     hla_job_map(b, jg.gx, jg.grp, bx, by);
-    hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.Kp, jg.out, nullptr, bx, by);
+    hla_body<Tin, B, BASIS, 1, true>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.Kp, jg.out, nullptr, bx, by);
 }
 
 template <typename Tin, int B, int BASIS>
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void k_front_b(FrontHla jg, FrontAbsmax jw)
     if (b < jg.nb) {
         int bx, by;
         hla_job_map(b, jg.gx, jg.grp, bx, by);
-        hla_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.Kp, jg.out, nullptr, bx, by);
+        hla_body<Tin, B, BASIS, 1, true>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.Kp, jg.out, nullptr, bx, by);
         return;
     }
     b -= jg.nb;
@@ -276,17 +276,17 @@ __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, Fr
     const int64_t bytes = (jg.T ? jg.N * jg.D : 0) + (jx.T ? jx.N * jx.D : 0) + (jq.W ? static_cast<int64_t>(jq.O) * jq.I : 0);
     int b = reverse_same_xcd(blockIdx.x, gridDim.x, bytes * static_cast<int64_t>(sizeof(Tin)));
     if (b < jg.gx * jg.gy2) {
-        hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, jg.k0, jg.k1, jg.Kp, jg.TqT,
+        hla_quantize_body<Tin, B, BASIS, false, false, true>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, jg.k0, jg.k1, jg.Kp, jg.TqT,
                                          jg.sT, nullptr, b % jg.gx, b / jg.gx, jg.table);
         return;
     }
     b -= jg.gx * jg.gy2;
     if (b < jx.gx * jx.gy2) {
         if (CONV)
-            hla_quantize_body_src<B, BASIS, false>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.amax,
+            hla_quantize_body_src<B, BASIS, false, ConvRows<Tin>, false, true>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.amax,
                                                    jx.k0, jx.k1, jx.Kp, jx.TqT, jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
         else
-            hla_quantize_body<Tin, B, BASIS>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, jx.k0, jx.k1, jx.Kp, jx.TqT,
+            hla_quantize_body<Tin, B, BASIS, false, false, true>(static_cast<const Tin *>(jx.T), jx.N, jx.D, jx.r, jx.amax, jx.k0, jx.k1, jx.Kp, jx.TqT,
                                              jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
         return;
     }

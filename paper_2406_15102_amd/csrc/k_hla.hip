@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void k_hla(const Tin *__restrict__ T, int64_t 
 {
     int bx, by;
     hla_job_map(static_cast<int>(blockIdx.x), gx, grp, bx, by);
-    hla_body<Tin, B, BASIS>(T, N, D, r, N / B * r, ThatT, coeffT, bx, by);
+    hla_body<Tin, B, BASIS>(T, N, D, r, 0, ThatT, coeffT, bx, by);
 }
 
 template <typename Tin, int B>
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void k_hla_quantize(const Tin *__restrict__ T,
     // backwards (reverse_same_xcd): what the pass that took the maxima read last is what the last-level cache still holds
     const int lin = reverse_same_xcd(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y,
                                      N * D * static_cast<int64_t>(sizeof(Tin)));
-    hla_quantize_body<Tin, B, BASIS, MANT, P4>(T, N, D, r, amax_bits, k0, k1, N / B * r, TqT, sT, coeffT, lin % gridDim.x, lin / gridDim.x);
+    hla_quantize_body<Tin, B, BASIS, MANT, P4>(T, N, D, r, amax_bits, k0, k1, 0, TqT, sT, coeffT, lin % gridDim.x, lin / gridDim.x);
 }
 
 // 4-bit codes two to a byte (code 2b low nibble, code 2b+1 high nibble, two's complement) -> one int8
@@ -155,7 +155,7 @@ template <typename Tin, int B, int BASIS>
 __global__ __launch_bounds__(256) void k_hla_conv(const Tin *__restrict__ X, ConvShape g, int D, int r,
                                                   bf16_t *__restrict__ ThatT, float *__restrict__ coeffT)
 {
-    hla_body_src<B, BASIS>(ConvRows<Tin>{X, g}, g.N, D, r, g.N / B * r, ThatT, coeffT, blockIdx.x, blockIdx.y);
+    hla_body_src<B, BASIS>(ConvRows<Tin>{X, g}, g.N, D, r, 0, ThatT, coeffT, blockIdx.x, blockIdx.y);
 }
 
 template <typename Tin, int B, int BASIS>
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void k_hla_quantize_conv(const Tin *__restrict
 {
     const int lin = reverse_same_xcd(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y,   // backwards, as above
                                      g.N * D * static_cast<int64_t>(sizeof(Tin)));
-    hla_quantize_body_src<B, BASIS, MANT>(ConvRows<Tin>{X, g}, g.N, D, r, amax_bits, k0, k1, g.N / B * r, TqT, sT, coeffT, lin % gridDim.x,
+    hla_quantize_body_src<B, BASIS, MANT>(ConvRows<Tin>{X, g}, g.N, D, r, amax_bits, k0, k1, 0, TqT, sT, coeffT, lin % gridDim.x,
                                           lin / gridDim.x);
 }
 
