@@ -383,13 +383,14 @@ def main():
             traffic = json.load(open(tpath)).get(args.workload, {}).get(dom)
         except Exception:
             traffic = None
-    roofline = {"kernel": "products (k_gemm_pair: int8 dX product | bf16 dW product in one launch)", "bound": "mfma",
+    roofline = {"kernel": "products (stage entry point, k_gemm_pair: int8 dX product of nibbles | bf16 dW product in one launch)", "bound": "mfma",
                 "achieved": kernels[dom]["achieved"], "peak": PEAK_I8_TOPS, "unit": "TFLOP/s", "frac": kernels[dom]["frac"],
                 "traffic": traffic,
                 "note": "int8-equivalent ops per launch (2*N*d_in*d_out int8 ops + 2 x 2*d_out*d_in*Kc bf16 flops: a bf16 "
                         "flop counts as two, the ratio of the MFMA peaks, so frac = time at the two datasheet peaks / time "
                         "taken) over the HIP-event average of %s launches, each timed inside the stage sequence of the "
-                        "path; the products alone: kernels.int8_gemm, kernels.bf16_gemm" % iters}
+                        "path; the products alone: kernels.int8_gemm, kernels.bf16_gemm.  The whole path keeps its 4-bit codes as "
+                        "6-bit floats and multiplies those at twice the int8 rate" % iters}
 
     cpu = None
     if args.cpu_tokens > 0:
@@ -414,7 +415,7 @@ def main():
         "metric": "hlq_backward_dX_dW_latency", "value": round(hlq_us, 2), "unit": "us", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(hlq_us / 1e3, 5),
         "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
-        "dtype": "i8 MFMA (dX product, 4-bit codes) + bf16 (dW product), fp32 transforms", "data": "synthetic",
+        "dtype": "fp6 MFMA (dX product, 4-bit codes, exact sums) + bf16 (dW product), fp32 transforms", "data": "synthetic",
         "config": {"workload": "%s: %s" % (w.name, w.desc), "N": N, "d_in": I, "d_out": O, "B": B, "r": r,
                    "io_dtype": w.dtype, "includes": "W quantisation counted every step",
                    "code_storage": "4-bit, two per byte" if packed else "int8"},
