@@ -148,11 +148,12 @@ __device__ __forceinline__ void hla_body_src(const Src &src, int64_t N, int D, i
     const int64_t blk = static_cast<int64_t>(by) * NB + tid / L;
     if constexpr (PAD) {
         if (col0 >= D || blk * r >= Kp) return;
-        if (blk >= nblk) {
-#pragma unroll
-            for (int c = 0; c < CPL; ++c)
+        if (blk >= nblk) {      // few workgroups come here: short code, not fast code
+            bf16_t *p = ThatT + static_cast<int64_t>(col0) * Kp + blk * r;
 #pragma nounroll
-                for (int k = 0; k < r; ++k) ThatT[static_cast<int64_t>(col0 + c) * Kp + blk * r + k] = 0;
+            for (int c = 0; c < CPL; ++c, p += Kp)
+#pragma nounroll
+                for (int k = 0; k < r; ++k) p[k] = 0;
             return;
         }
     }
@@ -273,10 +274,11 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
         static_assert(!P4, "4-bit codes are stored without padding");
         if (col0 >= D || blk * r >= Kp) return;
         if (blk >= nblk) {
-#pragma unroll
-            for (int c = 0; c < CPL; ++c)
+            int8_t *p = TqT + static_cast<int64_t>(col0) * Kp + blk * r;
 #pragma nounroll
-                for (int k = 0; k < r; k += 4) *reinterpret_cast<uint32_t *>(TqT + static_cast<int64_t>(col0 + c) * Kp + blk * r + k) = 0u;
+            for (int c = 0; c < CPL; ++c, p += Kp)
+#pragma nounroll
+                for (int k = 0; k < r; k += 4) *reinterpret_cast<uint32_t *>(p + k) = 0u;
             return;
         }
     }
