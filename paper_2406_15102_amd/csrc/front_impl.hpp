@@ -257,13 +257,13 @@ __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, Fr
     // read last is what the last-level cache still holds
     const int64_t bytes = (jg.T ? jg.N * jg.D : 0) + (jx.T ? jx.N * jx.D : 0) + (jq.W ? static_cast<int64_t>(jq.O) * jq.I : 0);
     int b = reverse_same_xcd(blockIdx.x, gridDim.x, bytes * static_cast<int64_t>(sizeof(Tin)));
-    if (b < jg.gx * jg.gy2) {
+    if (b < jg.gx * jg.gy) {
         hla_quantize_body<Tin, B, BASIS, false, false, true>(static_cast<const Tin *>(jg.T), jg.N, jg.D, jg.r, jg.amax, jg.k0, jg.k1, jg.Kp, jg.TqT,
                                          jg.sT, nullptr, b % jg.gx, b / jg.gx, jg.table);
         return;
     }
-    b -= jg.gx * jg.gy2;
-    if (b < jx.gx * jx.gy2) {
+    b -= jg.gx * jg.gy;
+    if (b < jx.gx * jx.gy) {
         if (CONV)
             hla_quantize_body_src<B, BASIS, false, ConvRows<Tin>, false, true>(ConvRows<Tin>{static_cast<const Tin *>(jx.T), jc.g}, jx.N, jx.D, jx.r, jx.amax,
                                                    jx.k0, jx.k1, jx.Kp, jx.TqT, jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void k_front_q2(FrontHlaQ jg, FrontHlaQ jx, Fr
                                              jx.sT, nullptr, b % jx.gx, b / jx.gx, jx.table);
         return;
     }
-    b -= jx.gx * jx.gy2;
+    b -= jx.gx * jx.gy;
     if constexpr (CODES == kCodesF6)
         cols_quantize_f6_body<Tin, B>(static_cast<const Tin *>(jq.W), jq.O, jq.I, jq.amax, jq.k0, jq.k1, jq.qmax,
                                       reinterpret_cast<uint8_t *>(jq.WqT), jq.sW, b % jq.gx, b / jq.gx, jq.table);
@@ -289,7 +289,7 @@ static hipError_t launch_front_q_t(const FrontHlaQ &jg, const FrontHlaQ &jx, con
     const int n1 = n3 + jr.blocks + ju.blocks + jk.blocks;
     const FrontMix jm = jr.blocks > 0 ? front_mix_of(jr.blocks, n3) : FrontMix{0, 0, 0};
     if (n1 > 0) hipLaunchKernelGGL((k_front_q1<Tin, B, BASIS, CODES, CONV>), dim3(n1), dim3(256), 0, st, jg, jx, jw, jr, jm, ju, jc, jk);
-    const int n2 = jg.gx * jg.gy2 + jx.gx * jx.gy2 + jq.gx * jq.gy;
+    const int n2 = jg.gx * jg.gy + jx.gx * jx.gy + jq.gx * jq.gy;
     if (n2 > 0) hipLaunchKernelGGL((k_front_q2<Tin, B, BASIS, CODES, CONV>), dim3(n2), dim3(256), 0, st, jg, jx, jq, jc);
     return hipGetLastError();
 }

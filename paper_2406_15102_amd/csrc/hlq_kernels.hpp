@@ -97,7 +97,7 @@ struct FrontHla {    // K3 on one tensor
     int D, r;
     int64_t Kp;      // values from one row of `out` to the next (pad_row)
     uint16_t *out;
-    int gx, gy;      // column strips of 128, groups of 256/B token blocks, with those that only clear the end of the rows
+    int gx, gy;      // column strips of 128, groups of 256/B token blocks
     int grp, nb;     // hla_job_map's grouping and the workgroups it needs (>= gx * gy)
 };
 // Shape of a K3 workgroup: B lanes side by side (each CPL = 128/B columns: 256 B of a row of bf16
@@ -169,9 +169,8 @@ struct FrontHlaQ {   // K3 + int8 quantisation of one tensor: pass 1 (amax) and 
     int64_t Kp;      // codes from one row of TqT to the next (pad_row)
     int8_t *TqT;
     float *sT;
-    int gx, gy;      // of pass 1
+    int gx, gy;
     int table;       // see kAmaxTableRows; 0: one maximum per column, merged by atomics
-    int gy2;         // of pass 2, with the workgroups that only clear the end of the rows
 };
 struct FrontUnpack { // 4-bit codes two to a byte -> one int8 each; n pieces of 32 codes out, row_out a row, the first row_in of them from `in`
     const void *in;

@@ -55,7 +55,6 @@ FrontHlaQ front_hlaq(const void *T, int64_t N, int D, int B, int r, uint32_t *am
     if (!T) return j;
     j.gx = hla_grid_x(D, B);
     j.gy = hla_grid_y(N, B);
-    j.gy2 = hla_grid_y(Kp / r * B, B);
     return j;
 }
 
@@ -114,7 +113,7 @@ FrontHla front_hla(const void *T, int64_t N, int D, int B, int r, int64_t Kp, ui
     FrontHla j{T, N, D, r, Kp, out, 0, 0, 1, 0};
     if (!T) return j;
     j.gx = hla_grid_x(D, B);
-    j.gy = hla_grid_y(Kp / r * B, B);
+    j.gy = hla_grid_y(N, B);
     j.grp = hla_job_grp(B, r);
     j.nb = hla_job_blocks(j.gx, j.gy, j.grp);
     return j;
@@ -200,7 +199,7 @@ FrontShare front_share(const FrontRows &jr, const FrontHla &jx, int B, bool is_f
     // together (4 MB), and the tensor must be large enough for its second read to cost real time.
     const int64_t row_bytes = static_cast<int64_t>(jr.O) * (is_f32 ? 4 : 2);
     if (row_bytes * RG > (int64_t(3) << 20) || row_bytes * jr.N < (int64_t(16) << 20)) return s;
-    const int64_t groups = (jx.Kp / jx.r * B + RG - 1) / RG;     // with those that only clear the end of K3's rows
+    const int64_t groups = (jr.N + RG - 1) / RG;
     int pair = B / (2 * jx.r);                          // K3 writes 256 r / B bytes per column and group
     if (pair < 1) pair = 1;
     if (pair > 8) pair = 8;
