@@ -130,11 +130,19 @@ __device__ __forceinline__ void hla_job_map(int l, int gx, int grp, int &bx, int
     by = grp * (u / gx) + t % grp;
 }
 
-// values Kc .. Kp - 1 of CPL rows := 0 (either a multiple of 16 bytes, a row less than 128 bytes in all)
-template <int CPL, typename T> __device__ __forceinline__ void clear_row_ends(T *row, int64_t Kc, int64_t Kp)
+// The lanes of a column's last token block clear what lies behind its nblk * r values (either length a multiple of 16 bytes, a
+// row less than 128 bytes in all).  A lane's columns and its block are worked out again from its index, which is hidden from the
+// compiler for that: kept over the transform they were three registers more (k_front_one<float, 32, ...> spilled 8 for it).
+template <int L, int NB, int CPL, typename T>
+__device__ __forceinline__ void clear_row_ends(T *out, int64_t nblk, int r, int64_t Kp, int bx, int by)
 {
     constexpr int PIECE = 16 / sizeof(T);
+    const int64_t Kc = nblk * r;
     if (Kc == Kp) return;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    if (static_cast<int64_t>(by) * NB + tid / L != nblk - 1) return;
+    T *row = out + static_cast<int64_t>((bx * L + tid % L) * CPL) * Kp;
 #pragma nounroll
     for (int c = 0; c < CPL; ++c, row += Kp)
 #pragma nounroll
@@ -197,7 +205,7 @@ __device__ __forceinline__ void hla_body_src(const Src &src, int64_t N, int D, i
                 if (k < r) coeffT[o + k] = v[kept_row<B, BASIS>(k) * CPL + c];
         }
     }
-    if (PAD && blk == nblk - 1) clear_row_ends<CPL>(ThatT + static_cast<int64_t>(col0) * Kp, nblk * r, Kp);
+    if (PAD) clear_row_ends<L, NB, CPL>(ThatT, N / B, r, Kp, bx, by);
 }
 
 template <typename Tin, int B, int BASIS, int LM = 1, bool PAD = false>
@@ -321,7 +329,7 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
             codes(Words<1>{}, 0);      // r == 4
         }
     }
-    if (PAD && blk == nblk - 1) clear_row_ends<CPL>(TqT + static_cast<int64_t>(col0) * Kp, Kc, Kp);
+    if (PAD) clear_row_ends<L, NB, CPL>(TqT, N / B, r, Kp, bx, by);
 }
 
 template <typename Tin, int B, int BASIS, bool MANT = false, bool P4 = false, bool PAD = false>

@@ -273,16 +273,21 @@ __device__ __forceinline__ void cols_full_body(const Tin *__restrict__ W, int O,
         if (grp == 0) sW[col0 + c] = absmax_to_scale(cmax[c], qmax);
     }
     if constexpr (F6) {
-        // two columns of a group of rows at a time, for the same short chain (at B = 16 a lane's four are two units)
+        // Two columns of a group of rows at a time, for the same short chain (at B = 16 a lane's four are two units).  The rows past O
+        // are cleared in a loop of their own: as the other side of a test in this one they had the compiler keep every row's address
+        // over it, 111 registers spilled at B = 64 (k_front_one; none now).  Whole passes at B = 64, that form -> this: 4096 x 1024
+        // x 1024 46.2 -> 31.2 us, 2048 x 512 x 512 in fp32 29.6 -> 19.8, 12608 x 768 x 768 60.0 -> 49.4.
         constexpr int RB = ColsF6<B>::RB, UNITS = CW / 2;
-        const int nrb6 = f6_row_bytes(O) * 2 / RB;
+        const int nrb6 = (O + RB - 1) / RB;
 #pragma nounroll
         for (int i = grp; i < nrb6 * UNITS; i += groups) {
             const int o0 = i / UNITS * RB, second = UNITS == 2 ? i & 1 : 0;
             const float inv2[2] = {second ? inv[CW - 2] : inv[0], second ? inv[CW - 1] : inv[1]};
-            if (o0 < O) cols_quantize_block_f6<Tin, B, false, 2>(W, O, I, inv2, k0, k1, reinterpret_cast<uint8_t *>(WqT), col0 + 2 * second, o0);
-            else cols_clear_f6<B, 2>(reinterpret_cast<uint8_t *>(WqT), O, col0 + 2 * second, o0);
+            cols_quantize_block_f6<Tin, B, false, 2>(W, O, I, inv2, k0, k1, reinterpret_cast<uint8_t *>(WqT), col0 + 2 * second, o0);
         }
+#pragma nounroll
+        for (int i = nrb6 + grp; i < f6_row_bytes(O) * 2 / RB; i += groups)
+            cols_clear_f6<B, CW>(reinterpret_cast<uint8_t *>(WqT), O, col0, i * RB);
     } else {
 #pragma nounroll
         for (int rb = grp; rb < nrb; rb += groups)
