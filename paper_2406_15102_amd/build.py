@@ -27,7 +27,10 @@ FLAGS = [
     # everything that issues between them); the default size limit for `#pragma unroll` is below that
     "-mllvm", "-pragma-unroll-threshold=1000000",
     # every nested guard restores the lanes of the one around it: without that the register allocator's reloads at the end of
-    # a guarded store missed the lanes that only the inner guard had switched off (tests/test_gpu_edge_columns.py)
+    # a guarded store missed the lanes that only the inner guard had switched off.  The epilogues that showed it have no guard inside
+    # another any more and pass tests/test_gpu_edge_columns.py without this option too; it stays for the other kernels.  It costs
+    # scalar spills in the convolution's products (40 and 47 -> 49), which do not show: whole passes of convolutions without / with
+    # it 48.2 / 47.7 us (12544 x 256 over 256, 3 x 3), 68.9 / 69.4 (50176 x 128 over 128), 54.7 / 54.9 (fp32).
     "-mllvm", "-amdgpu-remove-redundant-endcf=false",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]

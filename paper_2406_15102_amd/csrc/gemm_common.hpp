@@ -137,7 +137,7 @@ __device__ __forceinline__ void store_raw(typename Mma<KIND>::acc_t (&acc)[WM][W
 #pragma unroll
             for (int vg = 0; vg < 4; ++vg) {
                 const int nl = j * 32 + vg * 8;
-                if (!GUARD || (m < g.M && wn0 + nl + fh * 4 < g.N)) {
+                if (!GUARD || ((m < g.M) & (wn0 + nl + fh * 4 < g.N))) {
                     // element reads into scalars first: a bit_cast applied to a vector element
                     // expression reads element 0
                     const auto e0 = acc[i][j][vg * 4 + 0], e1 = acc[i][j][vg * 4 + 1];
@@ -226,15 +226,14 @@ __device__ __forceinline__ void store_scaled(typename Mma<KIND>::acc_t (&acc)[WM
             if (!GUARD) {
                 *reinterpret_cast<u32x4 *>(dst + p * step) = v[p];
             } else {
+                // one guard a store, row and column in one test: see -amdgpu-remove-redundant-endcf in build.py
                 const int m = mbase + p * RPI, n = wn0 + cc;
-                if (m < g.M) {
-                    if (F32 || (g.N & 7) == 0) {
-                        if (n < g.N) *reinterpret_cast<u32x4 *>(dst + p * step) = v[p];
-                    } else {   // bf16 rows that are only 8-byte aligned: two halves, the last may be missing
-                        const u32x2 lo = {v[p][0], v[p][1]}, hi = {v[p][2], v[p][3]};
-                        if (n < g.N) *reinterpret_cast<u32x2 *>(dst + p * step) = lo;
-                        if (n + 4 < g.N) *reinterpret_cast<u32x2 *>(dst + p * step + 8) = hi;
-                    }
+                if (F32 || (g.N & 7) == 0) {
+                    if ((m < g.M) & (n < g.N)) *reinterpret_cast<u32x4 *>(dst + p * step) = v[p];
+                } else {   // bf16 rows that are only 8-byte aligned: two halves, the last may be missing
+                    const u32x2 lo = {v[p][0], v[p][1]}, hi = {v[p][2], v[p][3]};
+                    if ((m < g.M) & (n < g.N)) *reinterpret_cast<u32x2 *>(dst + p * step) = lo;
+                    if ((m < g.M) & (n + 4 < g.N)) *reinterpret_cast<u32x2 *>(dst + p * step + 8) = hi;
                 }
             }
         }

@@ -138,7 +138,7 @@ __device__ __forceinline__ void store_raw16(typename Mma16<KIND>::acc_t (&acc)[N
         int32_t *row = out + static_cast<int64_t>(m) * N + wn0 + fq * 4;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            if (!GUARD || (m < M && wn0 + j * 16 + fq * 4 < N)) {
+            if (!GUARD || ((m < M) & (wn0 + j * 16 + fq * 4 < N))) {
                 const auto e0 = acc[i][j][0], e1 = acc[i][j][1], e2 = acc[i][j][2], e3 = acc[i][j][3];
                 v4i raw = {Mma<KIND>::raw(e0), Mma<KIND>::raw(e1), Mma<KIND>::raw(e2), Mma<KIND>::raw(e3)};
                 *reinterpret_cast<v4i *>(row + j * 16) = raw;
@@ -212,15 +212,14 @@ __device__ __forceinline__ void store_scaled16(typename Mma16<KIND>::acc_t (&acc
             if (!GUARD) {
                 *reinterpret_cast<u32x4 *>(dst + p * step) = v[p];
             } else {
+                // one guard a store, row and column in one test: see -amdgpu-remove-redundant-endcf in build.py
                 const int m = mbase + p * RPI, n = wn0 + cc;
-                if (m < M) {
-                    if (F32 || (N & 7) == 0) {
-                        if (n < N) *reinterpret_cast<u32x4 *>(dst + p * step) = v[p];
-                    } else {   // bf16 rows that are only 8-byte aligned: two halves, the last may be missing
-                        const u32x2 lo = {v[p][0], v[p][1]}, hi = {v[p][2], v[p][3]};
-                        if (n < N) *reinterpret_cast<u32x2 *>(dst + p * step) = lo;
-                        if (n + 4 < N) *reinterpret_cast<u32x2 *>(dst + p * step + 8) = hi;
-                    }
+                if (F32 || (N & 7) == 0) {
+                    if ((m < M) & (n < N)) *reinterpret_cast<u32x4 *>(dst + p * step) = v[p];
+                } else {   // bf16 rows that are only 8-byte aligned: two halves, the last may be missing
+                    const u32x2 lo = {v[p][0], v[p][1]}, hi = {v[p][2], v[p][3]};
+                    if ((m < M) & (n < N)) *reinterpret_cast<u32x2 *>(dst + p * step) = lo;
+                    if ((m < M) & (n + 4 < N)) *reinterpret_cast<u32x2 *>(dst + p * step + 8) = hi;
                 }
             }
         }

@@ -119,11 +119,11 @@ __device__ __forceinline__ void stream_epilogue(typename Mma<KIND>::acc_t (&acc)
                 const int soff = (row * g.N + ch * 64) * 2;         // wave-uniform part of the offset
                 const int mm = wm0 + row + rr0, n = wn0 + ch * 64 + cc;
                 if ((g.N & 7) == 0) {
-                    if (interior || (mm < g.M && n < g.N)) __builtin_amdgcn_raw_buffer_store_b128(v[p], rsC, voff, soff, 0);
-                } else if (mm < g.M) {   // rows that are only 8-byte aligned: two halves, the last may be missing
+                    if (interior | ((mm < g.M) & (n < g.N))) __builtin_amdgcn_raw_buffer_store_b128(v[p], rsC, voff, soff, 0);
+                } else {   // rows that are only 8-byte aligned: two halves, the last may be missing
                     const u32x2 lo = {v[p][0], v[p][1]}, hi = {v[p][2], v[p][3]};
-                    if (n < g.N) __builtin_amdgcn_raw_buffer_store_b64(lo, rsC, voff, soff, 0);
-                    if (n + 4 < g.N) __builtin_amdgcn_raw_buffer_store_b64(hi, rsC, voff + 8, soff, 0);
+                    if ((mm < g.M) & (n < g.N)) __builtin_amdgcn_raw_buffer_store_b64(lo, rsC, voff, soff, 0);
+                    if ((mm < g.M) & (n + 4 < g.N)) __builtin_amdgcn_raw_buffer_store_b64(hi, rsC, voff + 8, soff, 0);
                 }
             }
             lds_wave_fence();
