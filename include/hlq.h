@@ -371,6 +371,7 @@ int hlq_linear_backward_mode(const void *G, const void *X, const void *Xc, const
  * step, its codes can serve every micro-batch in between (same seed => the codes the path itself
  * would compute, so the results are those of hlq_linear_backward_mode bit for bit).
  *   WqT, sW   as written by hlq_quantize_w(W, ..., seed, ..., bits = hlq_weight_code_bits(d_out, flags)):
+ *             codes in [-7, 7] (8 bits: [-127, 127]), no others;
  *             that helper returns the HLQ_BITS_* value (storage included) this path expects for
  *             the given flags.  Ignored (may be NULL) when dX is NULL.
  *   Other arguments, workspace and errors as for hlq_linear_backward_mode.
@@ -422,6 +423,17 @@ size_t hlq_backward_products_workspace_bytes(int64_t N, int64_t d_in, int64_t d_
  */
 int hlq_backward_products_plan(int64_t N, int64_t d_in, int64_t d_out, int64_t Kc, int gx_bits, int gw_int8,
                                size_t workspace_bytes, int *plan);
+/*
+ * How the whole pass would keep its operands and lay its two products out (without HLQ_FLAG_SEPARATE_PRODUCTS), given
+ * `workspace_bytes` of scratch; host arithmetic only.  x_is_compressed as for hlq_workspace_bytes_mode; w_is_codes != 0: a call
+ * of hlq_linear_backward_cached.
+ *   plan[0] .. plan[4]  as for hlq_backward_products_plan
+ *   plan[5]             the g_x product's codes: 0 one int8 each, 1 two to a byte, 2 in the layout that widens to 6-bit floats
+ *   plan[6]             elements from one row of the projections to the next
+ * Status codes as for hlq_linear_backward_mode's shapes, flags and workspace; plan NULL: HLQ_ERR_NULL.
+ */
+int hlq_linear_backward_plan(int64_t N, int64_t d_in, int64_t d_out, int B, int r, int x_is_compressed, int w_is_codes,
+                             int flags, size_t workspace_bytes, int *plan);
 int hlq_backward_products(const void *Gq, const float *sG, const void *WqT, const float *sW, int gx_bits,
                           const void *GhatT, const float *sGhat, const void *XhatT, const float *sXhat, int64_t N,
                           int64_t d_in, int64_t d_out, int64_t Kc, int B, int dtype, void *dX, void *dW, void *workspace,

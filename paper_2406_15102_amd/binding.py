@@ -85,6 +85,7 @@ _EXPORTS = {
     "hlq_mfma_probe": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p]),
     "hlq_backward_products_workspace_bytes": (C.c_size_t, [C.c_int64] * 4 + [C.c_int, C.c_int]),
     "hlq_backward_products_plan": (C.c_int, [C.c_int64] * 4 + [C.c_int, C.c_int, C.c_size_t, C.POINTER(C.c_int)]),
+    "hlq_linear_backward_plan": (C.c_int, [C.c_int64] * 3 + [C.c_int] * 5 + [C.c_size_t, C.POINTER(C.c_int)]),
     "hlq_backward_products": (C.c_int, [C.c_void_p] * 4 + [C.c_int] + [C.c_void_p] * 4 + [C.c_int64] * 4
                               + [C.c_int, C.c_int] + [C.c_void_p] * 3 + [C.c_size_t, C.c_void_p]),
     "hlq_conv_sizes": (C.c_int, [_GEOM_P] + [C.POINTER(C.c_int64)] * 4),
@@ -452,6 +453,17 @@ def hlq_backward_products_plan(N, d_in, d_out, Kc, gx_bits, gw_int8=False, works
     plan = (C.c_int * 5)()
     _check(lib().hlq_backward_products_plan(N, d_in, d_out, Kc, gx_bits, int(bool(gw_int8)), workspace_bytes, plan),
            "hlq_backward_products_plan")
+    return tuple(int(v) for v in plan)
+
+
+def hlq_linear_backward_plan(N, d_in, d_out, B, r, x_is_compressed=False, w_is_codes=False, flags=0, workspace_bytes=None):
+    """-> (tile_x, tile_w, splits_w, w_first, persistent, codes, row elements of the projections) of a whole pass; without
+    workspace_bytes, of one that is given what hlq_workspace_bytes_mode asks for."""
+    plan = (C.c_int * 7)()
+    if workspace_bytes is None:
+        workspace_bytes = hlq_workspace_bytes_mode(N, d_in, d_out, B, r, x_is_compressed, flags)
+    _check(lib().hlq_linear_backward_plan(N, d_in, d_out, B, r, int(bool(x_is_compressed)), int(bool(w_is_codes)), flags,
+                                          workspace_bytes, plan), "hlq_linear_backward_plan")
     return tuple(int(v) for v in plan)
 
 

@@ -95,13 +95,20 @@ bool fused_front(int64_t d_out, int B, int flags)
 
 // How the codes of the g_x list are kept: 4-bit codes travel two to a byte, in the f6 layout unless more than a quarter of its
 // rows would be padding (f6_rows_ok), else, or where the persistent form of the products is asked for, which multiplies
-// bytes, as nibbles where the rows stay 16-byte aligned that way.  image: see backward_impl.
-int codes_kept(int64_t d_out, int flags, bool image)
+// bytes, as nibbles where the rows stay 16-byte aligned that way.  image: see backward_impl.  Weight codes that are handed over, as
+// nibbles or bytes, are kept so where bringing them into the f6 layout does not pay (f6_recode_pays).
+enum Handed { kNotHanded, kHanded, kHandedDxAlone };
+int codes_kept(int64_t N, int64_t d_in, int64_t d_out, int flags, bool image, Handed w)
 {
     const bool four = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && !image;
-    if (four && hlq::f6_rows_ok(static_cast<int>(d_out)) && !hlq::gemm_stream_enabled()) return hlq::kCodesF6;
+    if (four && hlq::f6_rows_ok(static_cast<int>(d_out)) && !hlq::gemm_stream_enabled() &&
+        (w == kNotHanded || hlq::f6_recode_pays(N, d_in, d_out, w == kHandedDxAlone)))
+        return hlq::kCodesF6;
     return four && d_out % 32 == 0 ? hlq::kCodesNibbles : hlq::kCodesBytes;
 }
+
+// kind of the g_x product (launch_gemm_nt) on codes that are kept so
+int kind_of_codes(int codes) { return codes == hlq::kCodesF6 ? 3 : (codes == hlq::kCodesNibbles ? 2 : 0); }
 
 // elements from one row of the projections to the next, where they are padded
 int64_t padded_k(int64_t N, int64_t d_out, int B, int r, bool x_is_compressed, int flags)
@@ -112,11 +119,11 @@ int64_t padded_k(int64_t N, int64_t d_out, int B, int r, bool x_is_compressed, i
     return fused_front(d_out, B, flags) && x_here ? hlq::pad_row(Kc, (flags & HLQ_FLAG_GW_INT8) ? 1 : 2) : Kc;
 }
 
-Layout carve_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags, bool image, size_t gws_bytes,
+Layout carve_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags, int codes_wanted, size_t gws_bytes,
                     bool pad)
 {
     Layout L;
-    L.codes = codes_kept(d_out, flags, image);
+    L.codes = codes_wanted;
     const int codes = pad ? L.codes : hlq::kCodesBytes;      // what there is room for
     const size_t code_row = codes == hlq::kCodesF6 ? hlq::f6_row_bytes(static_cast<int>(d_out)) : static_cast<size_t>(codes == hlq::kCodesNibbles ? d_out / 2 : d_out);
     const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0, fused = fused_front(d_out, B, flags);
@@ -150,8 +157,9 @@ Layout carve_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x
     return L;
 }
 
-Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags, bool image = false)
+Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_is_compressed, int flags, bool image = false, Handed w = kNotHanded)
 {
+    const int codes = codes_kept(N, d_in, d_out, flags, image, w);
     const int64_t Kc = N / B * r;
     const bool gwi = (flags & HLQ_FLAG_GW_INT8) != 0;
     // split-K partial sums of whichever product wants them (the two products run one after the other)
@@ -168,10 +176,10 @@ Layout make_layout(int64_t N, int64_t d_in, int64_t d_out, int B, int r, bool x_
         if (gp > gws_bytes) gws_bytes = gp;
         // the plan for codes in the f6 layout is another; what it asks for beyond that of nibbles is not part of `least`
         aw.K = static_cast<int>(padded_k(N, d_out, B, r, x_is_compressed, flags));
-        if (codes_kept(d_out, flags, image) == hlq::kCodesF6) gws_f6 = hlq::gemm_pair_ws_bytes(3, ax, gwi ? 0 : 1, aw, size_t(256) << 20);
+        if (codes == hlq::kCodesF6) gws_f6 = hlq::gemm_pair_ws_bytes(3, ax, gwi ? 0 : 1, aw, size_t(256) << 20);
     }
-    Layout L = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, image, gws_bytes > gws_f6 ? gws_bytes : gws_f6, true);
-    const Layout bytes = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, image, gws_bytes, false);
+    Layout L = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, codes, gws_bytes > gws_f6 ? gws_bytes : gws_f6, true);
+    const Layout bytes = carve_layout(N, d_in, d_out, B, r, x_is_compressed, flags, codes, gws_bytes, false);
     L.least = bytes.least;
     L.gws_least = gws_bytes;
     L.padded = L.total;
@@ -320,6 +328,26 @@ size_t hlq_workspace_bytes_mode(int64_t N, int64_t d_in, int64_t d_out, int B, i
 {
     if (check_backward_shape(N, d_in, d_out, B, r) != HLQ_OK || check_flags(flags, r, N, B) != HLQ_OK) return 0;
     return make_layout(N, d_in, d_out, B, r, x_is_compressed != 0, flags).total;
+}
+
+int hlq_linear_backward_plan(int64_t N, int64_t d_in, int64_t d_out, int B, int r, int x_is_compressed, int w_is_codes, int flags,
+                             size_t workspace_bytes, int *plan)
+{
+    int rc;
+    if (!plan) return HLQ_ERR_NULL;
+    if ((rc = check_backward_shape(N, d_in, d_out, B, r)) != HLQ_OK || (rc = check_flags(flags, r, N, B)) != HLQ_OK) return rc;
+    const bool xc = x_is_compressed != 0;
+    const Layout full = make_layout(N, d_in, d_out, B, r, xc, flags, false, w_is_codes ? kHanded : kNotHanded);
+    if (workspace_bytes < full.least) return HLQ_ERR_WORKSPACE;
+    const Layout L = workspace_bytes >= full.padded ? full : carve_layout(N, d_in, d_out, B, r, xc, flags, full.codes, full.gws_least, false);
+    hlq::GemmArgs ax{}, aw{};
+    ax.M = static_cast<int>(N), ax.N = static_cast<int>(d_in), ax.K = static_cast<int>(d_out);
+    aw.M = static_cast<int>(d_out), aw.N = static_cast<int>(d_in), aw.K = static_cast<int>(L.Kp);
+    ax.C = aw.C = plan;      // as in hlq_backward_products_plan
+    hlq::gemm_pair_describe(kind_of_codes(full.codes), ax, (flags & HLQ_FLAG_GW_INT8) ? 0 : 1, aw, L.gws_bytes, plan);
+    plan[5] = full.codes;
+    plan[6] = static_cast<int>(L.Kp);
+    return HLQ_OK;
 }
 
 int hlq_quantize_g(const void *G, int64_t N, int64_t d_out, int B, uint64_t seed, int dtype, int bits, int8_t *Gq,
@@ -662,7 +690,8 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     const bool mant = (flags & HLQ_FLAG_ROUND_MANTISSA) != 0;
 
     const bool xc = (Xc != nullptr) || !dW;   // no projection of X is held here: it was handed over, or dW is not wanted
-    const Layout full = make_layout(N, d_in, d_out, B, r, xc, flags, image != nullptr);
+    const bool wc = (Wc != nullptr);
+    const Layout full = make_layout(N, d_in, d_out, B, r, xc, flags, image != nullptr, !wc || !dX ? kNotHanded : (dW ? kHanded : kHandedDxAlone));
     char *ws = static_cast<char *>(workspace);
     if (ws) {
         if (!aligned(ws, 256) || workspace_bytes < full.least) return HLQ_ERR_WORKSPACE;
@@ -671,7 +700,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
         if ((rc = own_workspace(full.least, full.total, &p, &workspace_bytes)) != HLQ_OK) return rc;
         ws = static_cast<char *>(p);
     }
-    const Layout L = workspace_bytes >= full.padded ? full : carve_layout(N, d_in, d_out, B, r, xc, flags, image != nullptr, full.gws_least, false);
+    const Layout L = workspace_bytes >= full.padded ? full : carve_layout(N, d_in, d_out, B, r, xc, flags, full.codes, full.gws_least, false);
     const int codes = full.codes;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool f32 = dtype == HLQ_F32;
@@ -683,8 +712,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     // cache), the two passes over W back to back, then the two products.
     int8_t *Gq = reinterpret_cast<int8_t *>(ws + L.Gq);
     float *sG = reinterpret_cast<float *>(ws + L.sG);
-    const bool wc = (Wc != nullptr);
-    // codes that were handed over are nibbles or bytes: they are brought into the f6 layout first
+    // codes that were handed over are nibbles or bytes: they are brought into the f6 layout first, where that pays
     const bool recode = wc && dX && codes == hlq::kCodesF6;
     const int8_t *Wq = wc && !recode ? static_cast<const int8_t *>(Wc) : reinterpret_cast<const int8_t *>(ws + L.Wq);
     const float *sW = wc ? sWc : reinterpret_cast<const float *>(ws + L.sW);
@@ -853,7 +881,7 @@ static int backward_impl(const void *G, const void *X, const void *Xc, const flo
     hlq::GemmArgs ax{Gq, Wq, static_cast<int>(N), I, O, sG, sW, invB, dX, f32, nullptr, ws + L.gws, L.gws_bytes};
     hlq::GemmArgs aw{Gh, Xh, O, I, static_cast<int>(L.Kp), gwi ? sGh : nullptr, gwi ? sXh : nullptr, invB, dW, f32, nullptr, ws + L.gws,
                      L.gws_bytes};
-    const int kind_x = codes == hlq::kCodesF6 ? 3 : (codes == hlq::kCodesNibbles ? 2 : 0), kind_w = gwi ? 0 : 1;
+    const int kind_x = kind_of_codes(codes), kind_w = gwi ? 0 : 1;
     if (dX && image) {
         if (dW && !(flags & HLQ_FLAG_SEPARATE_PRODUCTS) && hlq::conv_pair_available())
             return launch_rc(hlq::launch_conv_pair(ax, *image, kind_w, aw, st));

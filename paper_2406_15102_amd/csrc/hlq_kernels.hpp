@@ -16,6 +16,19 @@ __host__ __device__ constexpr int f6_row_bytes(int K) { return (K + 255) / 256 *
 // row padding (44416 x 176 over 128) a pass took 31.2 us against 30.5 with nibbles.  (Rows that pass fit the scratch of one
 // int8 a code.)
 inline bool f6_rows_ok(int K) { return 2 * K >= 3 * f6_row_bytes(K); }
+// Weight codes that are handed over, nibbles or bytes, are read and written once more to come into that layout, which the g_x product
+// pays back with its tokens.  A weight that the last-level cache keeps in both forms (2^26 codes) pays from the first token on in a pass for
+// both gradients (with them as bytes or nibbles / in the layout: 256 x 4096 x 11008 72 / 56 us, 256 x 8192 x 8192 73 / 74, 512 x 8192 x 8192
+// 104 / 98); in a call for dX alone one of more than 2^25 does from 512 on (256 x 4096 x 11008 31.4 / 34.0, 256 x 8192 x 8192 34 / 40,
+// 512 x 8192 x 8192 42.9 / 42.8, 256 x 4096 x 4096 27.7 / 19.2).  A larger one goes through memory each time: 512 x 28672 x 8192 283 / 340,
+// 1024 tokens 452 / 464 and with the integer g_w list 414 / 452, 1536 tokens 623 / 616, 2048 785 / 738; dX alone 90 / 114 at 512
+// tokens, 168 / 164 at 1024, 254 / 222 at 1536.
+inline bool f6_recode_pays(int64_t N, int64_t d_in, int64_t d_out, bool dx_alone)
+{
+    const int64_t codes = d_in * d_out;
+    if (codes > (int64_t(1) << 26)) return N > 1024;
+    return !dx_alone || codes <= (int64_t(1) << 25) || N >= 512;
+}
 
 // Rows of the projections that the whole path makes and multiplies itself, in elements of `esz` bytes: zeros up to whole
 // 128-byte steps of the dW product, so that none is ragged and operands can be loaded straight into LDS.  (The rows of a

@@ -37,3 +37,41 @@ def test_plan_properties():
         assert s * w.d_out * w.d_in * 4 <= 1 << 28
     with pytest.raises(hlq.HlqError):
         hlq.hlq_backward_products_plan(4096, 4096, 11000, 2048, hlq.HLQ_BITS_4_PACKED)   # d_out % 32 for packed codes
+
+
+F6, NIBBLES, BYTES = 2, 1, 0
+
+
+def test_how_codes_are_kept():
+    """The route of the g_x codes: the 6-bit layout unless its rows are mostly padding, and for weight codes that are handed over
+    where the tokens pay for bringing them into it."""
+    def kept(N, I, O, codes=False, flags=0):
+        return hlq.hlq_linear_backward_plan(N, I, O, 16, 8, w_is_codes=codes, flags=flags)[5]
+
+    assert kept(4096, 4096, 11008) == F6 and kept(4096, 4096, 11008, True) == F6
+    assert kept(1024, 432, 96) == NIBBLES and kept(1024, 432, 80) == BYTES
+    for flag in (hlq.HLQ_FLAG_GX_8BIT, hlq.HLQ_FLAG_GX_UNPACKED):
+        assert kept(4096, 4096, 11008, flags=flag) == BYTES
+    # 235 million codes: read, written and read again by every call
+    assert kept(256, 28672, 8192) == F6
+    for N in (256, 512, 1024):
+        assert kept(N, 28672, 8192, True) == NIBBLES
+        assert kept(N, 28672, 8208, True) == BYTES
+    assert kept(1040, 28672, 8192, True) == F6
+    # a weight that the cache holds
+    assert kept(256, 8192, 8192, True) == F6
+    assert kept(256, 8200, 8192, True) == NIBBLES
+
+
+def test_pass_plan_checks_like_the_pass():
+    N, I, O = 4096, 512, 768
+    need = hlq.hlq_workspace_bytes_mode(N, I, O, 16, 8, False, 0)
+    assert hlq.hlq_linear_backward_plan(N, I, O, 16, 8, workspace_bytes=need)[6] == N // 2
+    assert hlq.hlq_linear_backward_plan(N + 16, I, O, 16, 8)[6] == (N + 16) // 2 + 56      # whole steps of 64 values
+    for bad in ((N + 8, I, O, 16, 8), (N, I, O, 24, 8), (N, I, O, 16, 17)):
+        with pytest.raises(hlq.HlqError):
+            hlq.hlq_linear_backward_plan(*bad, workspace_bytes=need)
+    with pytest.raises(hlq.HlqError):
+        hlq.hlq_linear_backward_plan(N, I, O, 16, 8, workspace_bytes=1 << 20)
+    with pytest.raises(hlq.HlqError):
+        hlq.hlq_linear_backward_plan(N, I, O, 16, 8, flags=1 << 20, workspace_bytes=need)
