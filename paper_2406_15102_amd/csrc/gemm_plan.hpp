@@ -126,6 +126,13 @@ constexpr TileCosts kTileCosts = {{kStepBig, kFixedBig}, {kStepSmallAlone, kFixe
 // picked one of 114.9.
 constexpr TileCosts kTileCostsF6 = {{1.35, 16.4}, {0.58, 6.8}, {0.58, 7.3}, {1.02, 4.0}};
 constexpr TileCosts kTileCostsDirect = {{1.2, 17.0}, {0.55, 5.3}, {0.58, 4.7}, {1.0, 4.2}}, kTileCostsStaged = {{2.0, 17.3}, {0.77, 3.6}, {0.72, 3.6}, {1.32, 4.1}};
+// 128-tiles of both products in many rounds fetch each operand twice as often as 256-tiles, which the costs above, fitted to layers of
+// more tokens, do not have: wide layers of few tokens went to them and lost to the nibbles' 256-tiles.  So much more for launches of at
+// least four rounds whose g_w tiles have 7 to 16 steps; of 861 layers whose every plan was timed (profiles/pair_plans_f6.txt) 13 are
+// faster by more than 2 %, none slower.  Whole passes, before -> this, with nibbles: 1024 x 28672 x 8192 723 -> 653 us, 697; 1024 x 8192 x 28672
+// 654 -> 613, 641; 1024 x 8192 x 8192 214 -> 194, 207; 2048 x 11008 x 4096 227 -> 220, 228.
+constexpr double kManyRoundsMore = 1.06, kManyRounds = 4.0;
+constexpr int kManyRoundsSteps[2] = {7, 16};
 constexpr double kPartialUs = 1.0e-6, kReduceUs = 3.0;     // a k split: of each partial value, and of the reduction's launch
 constexpr double kPartialUsF6 = 1.54e-6, kReduceUsF6 = 4.5;
 constexpr double kOneStepSaves = 2.0;    // a tile of one step skips the pipeline (gemm_body.hpp)

@@ -70,7 +70,8 @@ static PairPlan plan_pair(const GemmArgs &a, int kindA, const GemmArgs &b, int k
                 const double tab = pair_makespan(nA, tA, ca.slots, nB1 * S, tB, cb.slots);
                 const double tba = pair_makespan(nB1 * S, tB, cb.slots, nA, tA, ca.slots);
                 const bool b_first = tba < tab;
-                const double t = (b_first ? tba : tab) + extra;
+                const bool many = f6 && !bigA && !bigB && nA + nB1 * S >= kManyRounds * 512.0 && stepsB >= kManyRoundsSteps[0] && stepsB <= kManyRoundsSteps[1];
+                const double t = (b_first ? tba : tab) * (many ? kManyRoundsMore : 1.0) + extra;
                 if (t < best_t) {
                     best_t = t;
                     best = PairPlan{bigA != 0, bigB != 0, S, b_first};

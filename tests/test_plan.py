@@ -75,3 +75,18 @@ def test_pass_plan_checks_like_the_pass():
         hlq.hlq_linear_backward_plan(N, I, O, 16, 8, workspace_bytes=1 << 20)
     with pytest.raises(hlq.HlqError):
         hlq.hlq_linear_backward_plan(N, I, O, 16, 8, flags=1 << 20, workspace_bytes=need)
+
+
+# (N, d_in, d_out, B, r) -> tile edges, k splits, g_w first, of passes whose codes are kept in the 6-bit layout: the pick is the best plan that
+# was timed, or within 2 % of it; the last three are wide layers of few tokens (kManyRoundsMore), before them one that is not
+MEASURED_PICKS_OF_PASSES = {
+    (12608, 768, 3072, 16, 8): (256, 128, 1, 1), (9200, 1160, 3120, 16, 8): (256, 128, 1, 0), (4096, 4096, 11008, 16, 8): (256, 256, 1, 0),
+    (512, 28672, 8192, 16, 8): (128, 128, 1, 0), (1024, 28672, 8192, 16, 8): (256, 256, 1, 0), (1024, 8192, 8192, 16, 8): (256, 256, 1, 0),
+    (2048, 11008, 4096, 16, 8): (256, 256, 1, 0),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(MEASURED_PICKS_OF_PASSES))
+def test_pass_plan_picks_the_measured_plan(shape):
+    plan = hlq.hlq_linear_backward_plan(*shape)
+    assert plan[:4] == MEASURED_PICKS_OF_PASSES[shape] and plan[5] == F6, plan
