@@ -102,7 +102,7 @@ int codes_kept(int64_t N, int64_t d_in, int64_t d_out, int flags, bool image, Ha
 {
     const bool four = !(flags & (HLQ_FLAG_GX_8BIT | HLQ_FLAG_GX_UNPACKED)) && !image;
     if (four && hlq::f6_rows_ok(static_cast<int>(d_out)) && !hlq::gemm_stream_enabled() &&
-        (w == kNotHanded || hlq::f6_recode_pays(N, d_in, d_out, w == kHandedDxAlone)))
+        (w == kNotHanded || hlq::f6_recode_pays(N, d_in, d_out, w == kHandedDxAlone, (flags & HLQ_FLAG_GW_INT8) != 0)))
         return hlq::kCodesF6;
     return four && d_out % 32 == 0 ? hlq::kCodesNibbles : hlq::kCodesBytes;
 }

@@ -17,17 +17,21 @@ __host__ __device__ constexpr int f6_row_bytes(int K) { return (K + 255) / 256 *
 // int8 a code.)
 inline bool f6_rows_ok(int K) { return 2 * K >= 3 * f6_row_bytes(K); }
 // Weight codes that are handed over, nibbles or bytes, are read and written once more to come into that layout, which the g_x product
-// pays back with its tokens.  A weight that the last-level cache keeps in both forms (2^26 codes) pays from the first token on in a pass for
-// both gradients (with them as bytes or nibbles / in the layout: 256 x 4096 x 11008 72 / 56 us, 256 x 8192 x 8192 73 / 74, 512 x 8192 x 8192
-// 104 / 98); in a call for dX alone one of more than 2^25 does from 512 on (256 x 4096 x 11008 31.4 / 34.0, 256 x 8192 x 8192 34 / 40,
-// 512 x 8192 x 8192 42.9 / 42.8, 256 x 4096 x 4096 27.7 / 19.2).  A larger one goes through memory each time: 512 x 28672 x 8192 283 / 340,
-// 1024 tokens 452 / 464 and with the integer g_w list 414 / 452, 1536 tokens 623 / 616, 2048 785 / 738; dX alone 90 / 114 at 512
-// tokens, 168 / 164 at 1024, 254 / 222 at 1536.
-inline bool f6_recode_pays(int64_t N, int64_t d_in, int64_t d_out, bool dx_alone)
+// pays back with its tokens, the sooner the fewer tiles it has beside long reductions: d_out of 1.5 d_in on is told apart.  Passes for both
+// gradients with the codes as they come / in the layout, us: 256 x 4096 x 11008 72 / 56, 256 x 3936 x 17280 121 / 94, 256 x 8192 x 14336 158 / 125,
+// above 2^27 codes 512 x 8192 x 28672 324 / 366 and 1024 tokens 452 / 447; the others 512 x 28672 x 8192 273 / 341, 1024 tokens 444 / 452,
+// 1536 tokens 623 / 608, 256 x 16384 x 8192 118 / 132, 1024 x 16384 x 8192 256 / 258, 1536 tokens 360 / 345.  Beside the integer g_w list, whose
+// int8 product is the shorter one, from 2048 on: 1536 x 28672 x 8192 544 / 592, 2048 tokens 646 / 634.  Calls for dX alone: 256 x 4096 x 11008 31.4 / 34,
+// 512 tokens 43.7 / 43.7, 512 x 3936 x 17280 57 / 54; 512 x 28672 x 8192 88 / 114, 768 tokens 170 / 160, 768 x 8192 x 8192 60 / 55; above 2^27
+// codes and long 768 x 8192 x 28672 162 / 175, 1024 tokens 228 / 195.  Up to 2^25 codes the layout is ahead or even throughout (256 x
+// 4096 x 4096 34 / 27, dX alone 27.7 / 19.2).
+inline bool f6_recode_pays(int64_t N, int64_t d_in, int64_t d_out, bool dx_alone, bool gw_int8)
 {
     const int64_t codes = d_in * d_out;
-    if (codes > (int64_t(1) << 26)) return N > 1024;
-    return !dx_alone || codes <= (int64_t(1) << 25) || N >= 512;
+    if (codes <= (int64_t(1) << 25)) return true;
+    if (2 * d_out < 3 * d_in) return dx_alone ? N >= 768 : (N >= 2048 || (N > 1024 && !gw_int8));
+    if (codes > (int64_t(1) << 27)) return N >= 1024;
+    return !dx_alone || N >= 512;
 }
 
 // Rows of the projections that the whole path makes and multiplies itself, in elements of `esz` bytes: zeros up to whole

@@ -58,9 +58,10 @@ def test_how_codes_are_kept():
         assert kept(N, 28672, 8192, True) == NIBBLES
         assert kept(N, 28672, 8208, True) == BYTES
     assert kept(1040, 28672, 8192, True) == F6
-    # a weight that the cache holds
-    assert kept(256, 8192, 8192, True) == F6
-    assert kept(256, 8200, 8192, True) == NIBBLES
+    assert kept(1056, 28672, 8192, True, hlq.HLQ_FLAG_GW_INT8) == NIBBLES and kept(2048, 28672, 8192, True, hlq.HLQ_FLAG_GW_INT8) == F6
+    assert kept(512, 8192, 28672, True) == NIBBLES and kept(1024, 8192, 28672, True) == F6
+    # long reductions, and few codes
+    assert kept(256, 4096, 11008, True) == F6 and kept(256, 8192, 8192, True) == NIBBLES and kept(256, 4096, 8192, True) == F6
 
 
 def test_pass_plan_checks_like_the_pass():
