@@ -19,25 +19,40 @@ def _backward(G, X, W, B, r, flags):
     return dX, dW
 
 
-# plans of a 256-tile dX product and an unsplit 128-tile dW product of 23 to 64 steps (every position of the ring's nine units a
-# last step can end in), edges of rows and columns that fill no tile; with int8 projections half the steps
-@pytest.mark.parametrize("N,I,O", [(2848, 2040, 2304), (3104, 1216, 1920), (3840, 1856, 1152), (4352, 2240, 3072), (4640, 1512, 1280), (4896, 1616, 896),
-                                   (5376, 1304, 1024), (8192, 2144, 512), (6144, 736, 2944)])
+# layers whose plan is a 256-tile dX product beside 128-tiles of dW, for each pair of kinds nine reductions of consecutive step counts: every
+# position of the ring's nine units that a last step can end in; edges of rows and columns that fill no tile
+FIRST_STEPS = {X8: 25, 0: 22, X8 | GWI: 10, GWI: 15}
+LAYERS = {
+    X8: [(3168, 936, 512), (3232, 2152, 512), (3392, 784, 640), (3520, 1072, 640), (3616, 784, 768), (3776, 1024, 768), (3968, 904, 896), (4096, 1224, 640),
+         (4192, 1168, 640)],
+    0: [(2784, 1248, 512), (2944, 1256, 512), (3040, 928, 768), (3136, 776, 688), (3296, 1000, 512), (3392, 800, 640), (3552, 1032, 512), (3648, 792, 512),
+        (3744, 856, 640)],
+    X8 | GWI: [(2336, 2080, 768), (2784, 1800, 896), (2848, 1872, 768), (3232, 1712, 768), (3360, 1648, 896), (3712, 1664, 768), (3936, 1448, 896),
+               (4256, 1448, 768), (4448, 1360, 768)],
+    GWI: [(3840, 2368, 3072), (3936, 1344, 3088), (4224, 1168, 2352), (4576, 1032, 2560), (4768, 912, 2832), (4960, 928, 2992), (5184, 656, 2944),
+          (5440, 1672, 512), (5792, 640, 512)],
+}
+
+
+@pytest.mark.parametrize("flags", sorted(LAYERS))
+@pytest.mark.parametrize("i", range(9))
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-def test_same_bits_as_through_registers(N, I, O, dtype):
+def test_same_bits_as_through_registers(flags, i, dtype):
     B, r = 16, 8
-    assert tuple(hlq.hlq_backward_products_plan(N, I, O, N // B * r, hlq.HLQ_BITS_8, False, 1 << 28)[:3]) == (256, 128, 1)
+    N, I, O = LAYERS[flags][i]
+    steps = FIRST_STEPS[flags] + i
     g = torch.Generator(device=DEV).manual_seed(N)
     G, X, W = (torch.randn(s, generator=g, device=DEV).to(dtype) for s in ((N, O), (N, I), (O, I)))
-    for flags in (X8, 0, X8 | GWI):
-        if flags & GWI and N // B * r % 16:
-            continue
-        hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, 1)
+    # whole reductions, and k splits whose partials come from this body: down to four steps a workgroup, the fewest that take it
+    for splits in sorted({1, 2, steps // 5, steps // 4}):
+        hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, splits)
         try:
+            plan = hlq.hlq_linear_backward_plan(N, I, O, B, r, flags=flags)
+            assert plan[:3] == (256, 128, splits) and plan[5] == (0 if flags & X8 else 2) and plan[6] * (1 if flags & GWI else 2) == 128 * steps
             got = _backward(G, X, W, B, r, flags)
             hlq.hlq_set_option(hlq.HLQ_OPT_DIRECT_TO_LDS, 0)
             want = _backward(G, X, W, B, r, flags)
         finally:
             hlq.hlq_set_option(hlq.HLQ_OPT_DIRECT_TO_LDS, 1)
             hlq.hlq_set_option(hlq.HLQ_OPT_PLAN_SPLITS, 0)
-        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), splits
