@@ -13,6 +13,7 @@
 namespace hlq {
 
 template <typename Tin> struct DenseRows {
+    using elem = Tin;
     const Tin *T;
     int64_t D;
     template <int B, int CPL> __device__ __forceinline__ void load_block(int64_t row0, int col0, float *v) const
@@ -53,6 +54,7 @@ template <typename T, int CPL> __device__ __forceinline__ void load_buffer(__amd
 
 // needs C % CPL == 0 (a lane's columns stay inside one tap) and N < 2^31
 template <typename Tin> struct ConvRows {
+    using elem = Tin;
     const Tin *X;
     ConvShape g;
     template <int B, int CPL> __device__ __forceinline__ void load_block(int64_t row0, int col0, float *v) const
@@ -130,23 +132,33 @@ __device__ __forceinline__ void hla_job_map(int l, int gx, int grp, int &bx, int
     by = grp * (u / gx) + t % grp;
 }
 
-// The lanes of a column's last token block clear what lies behind its nblk * r values (either length a multiple of 16 bytes, a
-// row less than 128 bytes in all).  A lane's columns and its block are worked out again from its index, which is hidden from the
-// compiler for that: kept over the transform they were three registers more (k_front_one<float, 32, ...> spilled 8 for it).
-template <int L, int NB, int CPL, typename T>
-__device__ __forceinline__ void clear_row_ends(T *out, int64_t nblk, int r, int64_t Kp, int bx, int by)
+// values Kc .. Kp - 1 of CPL rows := 0 (either a multiple of 16 bytes, a row less than 128 bytes in all)
+template <int CPL, typename T> __device__ __forceinline__ void clear_row_ends(T *row, int64_t Kc, int64_t Kp)
 {
     constexpr int PIECE = 16 / sizeof(T);
-    const int64_t Kc = nblk * r;
     if (Kc == Kp) return;
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    if (static_cast<int64_t>(by) * NB + tid / L != nblk - 1) return;
-    T *row = out + static_cast<int64_t>((bx * L + tid % L) * CPL) * Kp;
 #pragma nounroll
     for (int c = 0; c < CPL; ++c, row += Kp)
 #pragma nounroll
         for (int64_t k = Kc; k < Kp; k += PIECE) *reinterpret_cast<uint4 *>(row + k) = make_uint4(0, 0, 0, 0);
+}
+
+// The same by the lanes of a column's last token block, behind their coefficients.  At B = 32 in fp32 a lane's columns and its block
+// are worked out again from its index, hidden from the compiler for that: kept over the transform they were three registers too
+// many (k_front_one<float, 32, ...> spilled 8, on the sequency basis 60; 0 and 20 so).  Only there: a convolution of 65536 x 864 over 256
+// in fp32 at B = 16 takes 126.0 us and 132.9 that way, on as many wavefronts.
+template <int B, typename Src, int L, int NB, int CPL, typename T>
+__device__ __forceinline__ void clear_ends_of_last_block(T *out, int64_t nblk, int r, int64_t Kp, int bx, int by, int col0, int64_t blk)
+{
+    if constexpr (B == 32 && sizeof(typename Src::elem) == 4) {
+        if (nblk * r == Kp) return;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        if (static_cast<int64_t>(by) * NB + tid / L == nblk - 1)
+            clear_row_ends<CPL>(out + static_cast<int64_t>((bx * L + tid % L) * CPL) * Kp, nblk * r, Kp);
+    } else {
+        if (blk == nblk - 1) clear_row_ends<CPL>(out + static_cast<int64_t>(col0) * Kp, nblk * r, Kp);
+    }
 }
 
 // LM: lanes side by side as a multiple of hla_lanes(B) -- 1 for the stand-alone shape (B lanes x 256/B token
@@ -205,7 +217,7 @@ __device__ __forceinline__ void hla_body_src(const Src &src, int64_t N, int D, i
                 if (k < r) coeffT[o + k] = v[kept_row<B, BASIS>(k) * CPL + c];
         }
     }
-    if (PAD) clear_row_ends<L, NB, CPL>(ThatT, N / B, r, Kp, bx, by);
+    if constexpr (PAD) clear_ends_of_last_block<B, Src, L, NB, CPL>(ThatT, nblk, r, Kp, bx, by, col0, blk);
 }
 
 template <typename Tin, int B, int BASIS, int LM = 1, bool PAD = false>
@@ -329,7 +341,7 @@ __device__ __forceinline__ void hla_quantize_body_src(const Src &src, int64_t N,
             codes(Words<1>{}, 0);      // r == 4
         }
     }
-    if (PAD) clear_row_ends<L, NB, CPL>(TqT, N / B, r, Kp, bx, by);
+    if constexpr (PAD) clear_ends_of_last_block<B, Src, L, NB, CPL>(TqT, nblk, r, Kp, bx, by, col0, blk);
 }
 
 template <typename Tin, int B, int BASIS, bool MANT = false, bool P4 = false, bool PAD = false>
