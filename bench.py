@@ -185,7 +185,7 @@ def main():
 
     # ---- the same path with the weight codes taken as cached (W quantised once per optimiser step) ----
     # ---- and kernel by kernel through the stage entry points, HIP events on the launch stream ----------
-    packed = O % 32 == 0          # the whole path stores the 4-bit codes two to a byte then
+    packed = O % 32 == 0          # the stage entry points take the 4-bit codes two to a byte then
     cb = O // 2 if packed else O
     qbits = hlq.HLQ_BITS_4_PACKED if packed else hlq.HLQ_BITS_4
     Gq = torch.empty((N, cb), dtype=torch.uint8 if packed else torch.int8, device=dev)
@@ -375,6 +375,7 @@ def main():
     copy_us = _event_time_us(lambda: calib_dst.copy_(calib_src), 20, torch, warm=10)
     del calib_src, calib_dst
 
+    kept = hlq.hlq_linear_backward_plan(N, I, O, B, r)[5]      # how the timed path keeps its 4-bit codes
     dom = "products"
     traffic = None
     tpath = os.path.join(ROOT, "profiles", "traffic.json")
@@ -415,10 +416,11 @@ def main():
         "metric": "hlq_backward_dX_dW_latency", "value": round(hlq_us, 2), "unit": "us", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(hlq_us / 1e3, 5),
         "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
-        "dtype": "fp6 MFMA (dX product, 4-bit codes, exact sums) + bf16 (dW product), fp32 transforms", "data": "synthetic",
+        "dtype": "%s MFMA (dX product, 4-bit codes, exact sums) + bf16 (dW product), fp32 transforms" % ("fp6" if kept == 2 else "int8"),
+        "data": "synthetic",
         "config": {"workload": "%s: %s" % (w.name, w.desc), "N": N, "d_in": I, "d_out": O, "B": B, "r": r,
                    "io_dtype": w.dtype, "includes": "W quantisation counted every step",
-                   "code_storage": "4-bit, two per byte" if packed else "int8"},
+                   "code_storage": ("int8", "4-bit, two per byte", "4-bit, widened to 6-bit floats")[kept]},
         "wall_us_per_step": round(wall_us, 2),
         "single_step": step_stats,
         "dense_bf16_backward_us": round(dense_us, 2),

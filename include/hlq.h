@@ -90,7 +90,8 @@ size_t hlq_workspace_bytes(int64_t N, int64_t d_in, int64_t d_out, int B, int r,
  *       whole 128-byte steps (at least four per workgroup) load their operands from global memory
  *       straight into LDS, and so do the 128 x 128 tiles of two products in one launch where each has at
  *       least two whole steps a workgroup and their work, spread over two tiles a compute unit, takes at
- *       least 0.9 of the time of the longest tile;  0: every tile of these stages them through registers.
+ *       least 0.9 of the time of the longest tile, and those of the g_w product (four steps at least) beside 256 x 256
+ *       tiles of the g_x product that do;  0: every tile of these stages them through registers.
  *       (The image gradient that hlq_conv2d_backward takes from the codes is no matrix product of this
  *       kind, and the whole path's product of 4-bit codes is kept in a layout of its own: both always load
  *       straight into LDS.)
@@ -132,7 +133,9 @@ int hlq_set_option(int option, int value);
  *   bytes    its size; size it with hlq_workspace_bytes / hlq_workspace_bytes_mode /
  *            hlq_conv_workspace_bytes for the largest problem that will be run.  (The integer g_w list takes
  *            a little more, for a launch less, where N or d_out is at most 4096: a problem of that kind whose
- *            size comes out above what a longer one needed runs in the longer one's scratch, without that.)
+ *            size comes out above what a longer one needed runs in the longer one's scratch, without that.  Likewise
+ *            a problem whose padded rows of the projections find no room there runs without the padding, and with it
+ *            without loads straight into LDS where its token count leaves a ragged row; same results.)
  * HLQ_ERR_WORKSPACE for a misaligned pointer or bytes == 0 with a non-NULL pointer (the previous
  * registration stays).  The memory is not touched by this call.  Host-side only: no GPU work.
  */
@@ -307,8 +310,11 @@ int hlq_bf16_gemm_nt(const void *A, const void *Bm, int64_t M, int64_t Nn, int64
                                         the chip for most layers); dX is the same bit for bit either way, dW
                                         up to the summation order of its k splits. */
 #define HLQ_FLAG_GX_UNPACKED 4 /* keep the 4-bit g_x codes one per int8 between the stages.  By default
-                                  they are stored two to a byte (same codes, same
-                                  dX bit for bit; half the traffic). */
+                                  they take four bits: in a layout that widens to 6-bit floats unless more than a
+                                  quarter of its rows of whole 256 codes would be padding, else two to a byte where
+                                  d_out % 32 == 0 (hlq_linear_backward_plan tells); one int8 each otherwise, and for an
+                                  image gradient that hlq_conv2d_backward takes from the codes.  Same codes, same dX bit for
+                                  bit either way. */
 
 /*
  * Stages 1-2 (T = X, tensor 2) or 3-4 (T = G, tensor 3) of the g_w list: the projection described
@@ -371,9 +377,9 @@ int hlq_linear_backward_mode(const void *G, const void *X, const void *Xc, const
  * step, its codes can serve every micro-batch in between (same seed => the codes the path itself
  * would compute, so the results are those of hlq_linear_backward_mode bit for bit).
  *   WqT, sW   as written by hlq_quantize_w(W, ..., seed, ..., bits = hlq_weight_code_bits(d_out, flags)):
- *             codes in [-7, 7] (8 bits: [-127, 127]), no others;
  *             that helper returns the HLQ_BITS_* value (storage included) this path expects for
- *             the given flags.  Ignored (may be NULL) when dX is NULL.
+ *             the given flags.  Codes in [-7, 7] (8 bits: [-127, 127]) and no others: another, which that call never
+ *             writes, is multiplied as something else.  Ignored (may be NULL) when dX is NULL.
  *   Other arguments, workspace and errors as for hlq_linear_backward_mode.
  */
 int hlq_weight_code_bits(int64_t d_out, int flags);

@@ -46,12 +46,12 @@
 // has 2.75 to 3.5 steps to land instead of 0.75 to 1.5, which one wavefront a SIMD and 32 MFMAs a step do not cover.  Whole passes
 // with that pair of tiles, register-staged -> this: 9200 x 1160 x 3120 117.6 -> 113.2 us, 12608 x 768 x 3072 104.4 -> 102.6.
 // 4-bit codes in the f6 layout (KIND 3; hlq_device.hpp says how it widens) are 6-bit floats to the matrix cores, 128 of k
-// to an MFMA of the cycles that 64 bytes take.  Registers alone sustain 6.9 POP/s that way, 4.1 on the bytes that
-// nibbles widen to (Mma16<2>): 1.65 and 1.97 GHz, the power limit in either case.  A step is that of bytes: 16 rows x 64 B
+// to an MFMA of the cycles that 64 bytes take.  Registers alone sustain 5.9 POP/s on such floats (hlq_mfma_probe, kind 3) and 4.5 on
+// the bytes that nibbles widen to (kind 9), at the power limit in either case.  A step is that of bytes: 16 rows x 64 B
 // and one ds_read_b128 a fragment, where nibbles are read 8 bytes a lane with two-way conflicts.  The product alone,
-// nibbles -> f6: 4096 x 4096 x 11008 112.5 -> 80.8 us (4.6 POP/s), 8192 x 28672 x 8192 1168 -> 828: MFMAs busy 61 % of its
-// cycles at 1.82 GHz, vector instructions issued for 12 %, so it is power here too, and an MFMA's share of the
-// widening (1.5 instructions) and of LDS reads weighs double beside half the MFMAs.
+// nibbles -> f6: 4096 x 4096 x 11008 112.5 -> 80.8 us (4.6 POP/s), 8192 x 28672 x 8192 1168 -> 828.  The launch of both products
+// at 4096 x 4096 x 11008: MFMAs busy 61 % of its cycles at 1.96 GHz (nibbles 68 % at 2.10; profiles/hlq_c4_products_f6_pmc.txt), so
+// it is power here too, and an MFMA's share of the widening (1.5 instructions) and of LDS reads weighs double beside half the MFMAs.
 // RAGGED (128 x 128 only): the last step of a row need not be whole.  It is multiplied behind the loop, chunks past
 // the end of a row cleared in registers, so the loop of whole steps carries one subtraction a load for it.
 #pragma once
@@ -229,8 +229,12 @@ __device__ __forceinline__ void store_scaled16(typename Mma16<KIND>::acc_t (&acc
 
 // OUT as in gemm_tile; `bid`: index of the workgroup among those of this product.
 // Requires tiles of 32 NBM rows x 32 NB columns, NBM = 8 or 6 with NB = 8, or both 4 (g.tiles_m, g.tiles_n counted
-// in such tiles; the 192-row tile is not written for packed codes), at least two whole steps a workgroup, and
-// g.Kb % 128 == 0 unless RAGGED (then g.Kb % 16 == 0).
+// in such tiles; the 192-row tile is not written for packed codes), at least one whole step a workgroup, and
+// g.Kb % 128 == 0 unless RAGGED (then g.Kb % 16 == 0, and at least two whole steps).  The dispatch hands over reductions of two steps and
+// more (gemm_dl_ok, gemm_dl128_pays), but f6 codes any: with one step the prologue and the loop load it again where later ones would be,
+// and what they read of it is never multiplied.  Such layers are no slower for it than through registers, where one step skips the
+// pipeline (whole passes, nibbles / bytes there -> this: 50176 x 256 over 192 46.2 -> 42.5 us, over 240 52.0 -> 45.1, over 256 49.7 -> 44.7;
+// 12544 x 1152 over 224 37.9 -> 37.0, over 256 38.6 -> 38.5; 3136 x 512 over 256 19.7 -> 16.8).
 template <int KIND, int NBM, int OUT, int NB = 8, bool RAGGED = false, int AHEAD = 2>
 __device__ __forceinline__ void gemm_tile_dl(const GemmDev &g, const int bid)
 {

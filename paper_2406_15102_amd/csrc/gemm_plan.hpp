@@ -122,8 +122,9 @@ struct TileCosts {
 constexpr TileCosts kTileCosts = {{kStepBig, kFixedBig}, {kStepSmallAlone, kFixedSmall}, {kStepSmallAlone, kFixedSmall}, {kStepSmallShared, kFixedSmall}};
 // The same where the g_x product is on codes in the f6 layout: its tiles, and the g_w product's with operands straight into LDS or
 // through registers.  Fitted to every plan of 653 layers of 2 to 800 GFLOP (whole passes, either dispatch order): the plan
-// taken is 1.2 % from the best one in the mean, 2.0 % with the constants above, and 12608 x 768 x 3072 takes 102.6 us where those
-// picked one of 114.9.
+// taken was 1.2 % from the best one in the mean, 2.0 % with the constants above, and 12608 x 768 x 3072 took 102.6 us where those
+// picked one of 114.9 (one session).  Over the 861 other layers of profiles/pair_plans_f6.txt it is 1.3 %.  All of these fitted anew to those
+// come to 1.0 % of them, but the next box's best plans are others by as much, and 13 layers lose more than 2 %: left as they are.
 constexpr TileCosts kTileCostsF6 = {{1.35, 16.4}, {0.58, 6.8}, {0.58, 7.3}, {1.02, 4.0}};
 constexpr TileCosts kTileCostsDirect = {{1.2, 17.0}, {0.55, 5.3}, {0.58, 4.7}, {1.0, 4.2}}, kTileCostsStaged = {{2.0, 17.3}, {0.77, 3.6}, {0.72, 3.6}, {1.32, 4.1}};
 // 128-tiles of both products in many rounds fetch each operand twice as often as 256-tiles, which the costs above, fitted to layers of

@@ -334,7 +334,8 @@ static_assert((~F6M0 & ~F6M1) == 0 && (~F6M0 | ~F6M1) == F6M2, "the third dword 
 // lie in the order 0, 16, 1, 17, ...: every row of both operands of a product is packed by this function.
 // Codes that are none (a reciprocal scale that is infinite, sums that are not numbers) set one of the bits 3 and 4; they
 // are then taken as the low four bits, two's complement, of what the conversion to an integer gives, as pack_nibbles8
-// and pack_bytes4 take them (0 and -1 where the scale's reciprocal is infinite).
+// takes them (0 and -1 where the scale's reciprocal is infinite).  The layout has no place for -8, which no quantiser here
+// makes: handed over as a weight's code, which hlq.h excludes, it comes out as 0.
 typedef float v16f_t __attribute__((ext_vector_type(16)));
 typedef unsigned int v6u_t __attribute__((ext_vector_type(6)));
 __device__ __forceinline__ v6u_t f6_convert(const float *f)

@@ -1,7 +1,8 @@
 // K2 | K4 in one launch: the plan and the dispatch over the operand kinds.  The kernels live in
 // gemm_pair_impl.hpp, instantiated by k_gemm_pair_KK.hip for KK = (kind of the g_x product, kind of
-// the g_w product): 21 the default lists (packed 4-bit codes, bf16 projections), 20 with the integer
-// g_w list, 01 / 00 the same with one int8 per g_x code (8-bit warm-up, unpacked storage).
+// the g_w product): 31 the default lists (4-bit codes in the f6 layout, bf16 projections), 30 with the integer
+// g_w list, 21 / 20 the same with codes two to a byte (rows that f6 would mostly pad, weight codes handed over beside few
+// tokens, the stage entry point), 01 / 00 with one int8 per g_x code (8-bit warm-up, unpacked storage).
 #include "gemm_plan.hpp"
 
 namespace hlq {
