@@ -14,6 +14,7 @@ namespace hlq {
 
 template <typename Tin> struct DenseRows {
     using elem = Tin;
+    static constexpr bool image = false;
     const Tin *T;
     int64_t D;
     template <int B, int CPL> __device__ __forceinline__ void load_block(int64_t row0, int col0, float *v) const
@@ -55,6 +56,7 @@ template <typename T, int CPL> __device__ __forceinline__ void load_buffer(__amd
 // needs C % CPL == 0 (a lane's columns stay inside one tap) and N < 2^31
 template <typename Tin> struct ConvRows {
     using elem = Tin;
+    static constexpr bool image = true;
     const Tin *X;
     ConvShape g;
     template <int B, int CPL> __device__ __forceinline__ void load_block(int64_t row0, int col0, float *v) const
@@ -143,14 +145,16 @@ template <int CPL, typename T> __device__ __forceinline__ void clear_row_ends(T 
         for (int64_t k = Kc; k < Kp; k += PIECE) *reinterpret_cast<uint4 *>(row + k) = make_uint4(0, 0, 0, 0);
 }
 
-// The same by the lanes of a column's last token block, behind their coefficients.  At B = 32 in fp32 a lane's columns and its block
-// are worked out again from its index, hidden from the compiler for that: kept over the transform they were three registers too
-// many (k_front_one<float, 32, ...> spilled 8, on the sequency basis 60; 0 and 20 so).  Only there: a convolution of 65536 x 864 over 256
-// in fp32 at B = 16 takes 126.0 us and 132.9 that way, on as many wavefronts.
+// The same by the lanes of a column's last token block, behind their coefficients.  At B = 32 in fp32, and for bf16 projections of
+// a bf16 image, a lane's columns and its block are worked out again from its index, hidden from the compiler for that: kept over the
+// transform they were three registers too many (k_front_one<float, 32, ...> spilled 8, on the sequency basis 60; 0 and 20 so;
+// the one of bf16 images 6, 0 so: 9408 x 2304 over 256 40.4 -> 40.0 us, 50176 x 576 over 64 36.6 -> 36.2).  Only there: a
+// convolution of 65536 x 864 over 256 in fp32 at B = 16 takes 126.0 us and 132.9 that way, on as many wavefronts, one of
+// 50176 x 576 over 64 in bf16 at B = 32 beside the integer list 65.0 and 66.5.
 template <int B, typename Src, int L, int NB, int CPL, typename T>
 __device__ __forceinline__ void clear_ends_of_last_block(T *out, int64_t nblk, int r, int64_t Kp, int bx, int by, int col0, int64_t blk)
 {
-    if constexpr (B == 32 && sizeof(typename Src::elem) == 4) {
+    if constexpr (B == 32 && (sizeof(typename Src::elem) == 4 || (Src::image && sizeof(T) == 2))) {
         if (nblk * r == Kp) return;
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
